@@ -17,10 +17,9 @@ cmoe_ws_layout cmoe_layout(const cmoe_dims& dm, int T) {
     return at;
   };
   size_t Tz = (size_t)(T > 0 ? T : 0);
-  size_t n_blocks = (Tz + PERMUTE_BLOCK - 1) / PERMUTE_BLOCK;
   size_t n_tiles = (T <= SKINNY_T) ? ((size_t)dm.d_ff + SKINNY_SN - 1) / SKINNY_SN
                                    : ((size_t)dm.d_ff + G1_BN - 1) / G1_BN;
-  L.blk_counts = take(sizeof(int32_t) * (n_blocks + 1) * (dm.G > 64 ? dm.G : 64));
+  L.blk_counts = take(sizeof(int32_t) * sort_counts(Tz, 64 * (size_t)dm.G));
   L.sort_i32 = take(sizeof(int32_t) * 2 * Tz);
   L.v1cat = take(sizeof(half_t) * dm.G * dm.KRp * dm.d);
   L.u1t = take(sizeof(half_t) * dm.G * dm.d_ff * dm.KRp);
@@ -251,24 +250,25 @@ extern "C" int cmoe_permute_static(cmoe_handle* h, const int32_t* cluster_id, in
 
 // y_fused != NULL: when the shapes allow it, the down-projection also applies the residual of
 // the second matrix and writes y in token order (y_base_sorted is then not produced);
-// *fused tells the caller whether that happened.
+// *fused tells the caller whether that happened.  sorted: the rows' expert-pair order is
+// already in the workspace (permute_step).
 static int ffn_impl(cmoe_handle* h, const cmoe_weights* w, const cmoe_f16* x, int32_t T, const int32_t* perm,
                     const int32_t* offsets, const int32_t* expert_idx, const float* gate, cmoe_f16* y_base_sorted,
-                    float* s_down, cmoe_f16* y_fused, bool* fused, int x_div, void* workspace, size_t workspace_bytes,
-                    void* stream);
+                    float* s_down, cmoe_f16* y_fused, bool* fused, int x_div, bool sorted, void* workspace,
+                    size_t workspace_bytes, void* stream);
 
 extern "C" int cmoe_ffn_forward(cmoe_handle* h, const cmoe_weights* w, const cmoe_f16* x, int32_t T,
                                 const int32_t* perm, const int32_t* offsets, const int32_t* expert_idx,
                                 const float* gate, cmoe_f16* y_base_sorted, float* s_down, void* workspace,
                                 size_t workspace_bytes, void* stream) {
-  return ffn_impl(h, w, x, T, perm, offsets, expert_idx, gate, y_base_sorted, s_down, nullptr, nullptr, 1, workspace,
-                  workspace_bytes, stream);
+  return ffn_impl(h, w, x, T, perm, offsets, expert_idx, gate, y_base_sorted, s_down, nullptr, nullptr, 1, false,
+                  workspace, workspace_bytes, stream);
 }
 
 static int ffn_impl(cmoe_handle* h, const cmoe_weights* w, const cmoe_f16* x, int32_t T, const int32_t* perm,
                     const int32_t* offsets, const int32_t* expert_idx, const float* gate, cmoe_f16* y_base_sorted,
-                    float* s_down, cmoe_f16* y_fused, bool* fused, int x_div, void* workspace, size_t workspace_bytes,
-                    void* stream) {
+                    float* s_down, cmoe_f16* y_fused, bool* fused, int x_div, bool sorted, void* workspace,
+                    size_t workspace_bytes, void* stream) {
   if (fused) *fused = false;
   if (!handle_ok(h) || T < 0) return CMOE_ERR_INVALID_ARG;
   if (!weights_ffn_ok(w)) return CMOE_ERR_INVALID_ARG;
@@ -317,7 +317,7 @@ static int ffn_impl(cmoe_handle* h, const cmoe_weights* w, const cmoe_f16* x, in
   // cluster-sorted (or token) order
   int* rm = (int*)(ws + L.sort_i32);
   int* p2 = rm + (size_t)T;
-  CMOE_LAUNCH(TS_PERMUTE, launch_pair_sort(dm, perm, offsets, expert_idx, T, rm, p2, st));
+  if (!sorted) CMOE_LAUNCH(TS_PERMUTE, launch_pair_sort(dm, perm, offsets, expert_idx, rm, p2, st));
   const int* rperm = p2;
   const int* rowmap = rm;
   // when the combine is fused into the down-projection its U2 panel joins the same launch
@@ -335,6 +335,22 @@ static int ffn_impl(cmoe_handle* h, const cmoe_weights* w, const cmoe_f16* x, in
     return CMOE_OK;
   }
   CMOE_LAUNCH(TS_GEMM2, launch_gemm2(dm, *w, a, T, offsets, rowmap, (half_t*)y_base_sorted, st));
+  return CMOE_OK;
+}
+
+// The permutation of a whole step: above SKINNY_T tokens together with the expert-pair order
+// that ffn_impl needs, else the plain permutation.
+static int permute_step(cmoe_handle* h, const int32_t* cluster_id, const int32_t* expert_idx, int32_t T, int32_t* perm,
+                        int32_t* inv_perm, int32_t* offsets, void* workspace, hipStream_t st) {
+  const cmoe_ws_layout L = cmoe_layout(h->dm, T);
+  int* blk = (int*)((char*)workspace + L.blk_counts);
+  if (T <= SKINNY_T) {
+    CMOE_LAUNCH(TS_PERMUTE, launch_permute(h->dm, cluster_id, T, perm, inv_perm, offsets, blk, st));
+  } else {
+    int* rm = (int*)((char*)workspace + L.sort_i32);
+    CMOE_LAUNCH(TS_PERMUTE, launch_sort_pairs(h->dm, cluster_id, expert_idx, T, perm, inv_perm, offsets, blk, rm,
+                                              rm + (size_t)T, st));
+  }
   return CMOE_OK;
 }
 
@@ -418,15 +434,15 @@ extern "C" int cmoe_forward_multi(cmoe_handle* h, const cmoe_weights* w, const c
   int rc = cmoe_route_multi(h, w, opt, x, T, cluster_id, expert_idx, gate, stream);
   if (rc != CMOE_OK) return rc;
   // from here on the virtual tokens are ordinary tokens of the single-cluster path
-  rc = cmoe_permute(h, cluster_id, Tv, perm, inv_perm, offsets, workspace, base_bytes, stream);
+  rc = permute_step(h, cluster_id, expert_idx, Tv, perm, inv_perm, offsets, workspace, st);
   if (rc != CMOE_OK || T == 0) return rc;
   cmoe_ws_layout L = cmoe_layout(dm, Tv);
   cmoe_f16* yb = (cmoe_f16*)(ws + L.yb);
   float* s_down = (float*)(ws + L.sdown);
   bool fused = false;
   // virtual token vt reads row vt / top_g of x
-  rc = ffn_impl(h, w, x, Tv, perm, offsets, expert_idx, gate, yb, s_down, (cmoe_f16*)yrep, &fused, g1, workspace,
-                base_bytes, stream);
+  rc = ffn_impl(h, w, x, Tv, perm, offsets, expert_idx, gate, yb, s_down, (cmoe_f16*)yrep, &fused, g1, true,
+                workspace, base_bytes, stream);
   if (rc != CMOE_OK) return rc;
   if (!fused) {
     rc = cmoe_combine(h, w, yb, s_down, perm, inv_perm, offsets, expert_idx, gate, Tv, (cmoe_f16*)yrep, workspace,
@@ -525,11 +541,11 @@ extern "C" int cmoe_forward(cmoe_handle* h, const cmoe_weights* w, const cmoe_f1
   float* s_down = (float*)(ws + L.sdown);
   rc = cmoe_route(h, w, x, T, cluster_id, expert_idx, gate, stream);
   if (rc != CMOE_OK) return rc;
-  rc = cmoe_permute(h, cluster_id, T, perm, inv_perm, offsets, workspace, workspace_bytes, stream);
+  rc = permute_step(h, cluster_id, expert_idx, T, perm, inv_perm, offsets, workspace, (hipStream_t)stream);
   if (rc != CMOE_OK || T == 0) return rc;
   bool fused = false;
-  rc = ffn_impl(h, w, x, T, perm, offsets, expert_idx, gate, yb, s_down, y, &fused, 1, workspace, workspace_bytes,
-                stream);
+  rc = ffn_impl(h, w, x, T, perm, offsets, expert_idx, gate, yb, s_down, y, &fused, 1, true, workspace,
+                workspace_bytes, stream);
   if (rc != CMOE_OK || fused) return rc;
   return cmoe_combine(h, w, yb, s_down, perm, inv_perm, offsets, expert_idx, gate, T, y, workspace, workspace_bytes,
                       stream);

@@ -49,44 +49,6 @@ __global__ __launch_bounds__(256) void bw_panel_kernel(const uint8_t* __restrict
   }
 }
 
-// cluster of a token = cluster of its first selected expert
-__global__ __launch_bounds__(256) void bw_cluster_kernel(const int* __restrict__ expert_idx, int T, int k, int K,
-                                                         int* __restrict__ cid) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t < T) cid[t] = expert_idx[(size_t)t * k] / K;
-}
-
-// More than 64 experts: the pairs are sorted by expert in two stable counting sorts, by the
-// expert's index inside its cluster and then by cluster.
-// mode 0: key[i] = expert_idx[i] % K;  mode 1: key[i] = expert_idx[perm_a[i]] / K.
-__global__ __launch_bounds__(256) void bw_key_kernel(const int* __restrict__ expert_idx,
-                                                     const int* __restrict__ perm_a, int M, int K, int E, int mode,
-                                                     int* __restrict__ key) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= M) return;
-  const int e = min(max(expert_idx[mode ? perm_a[i] : i], 0), E - 1);
-  key[i] = mode ? e / K : e % K;
-}
-
-// permm[i] = perm_a[perm_b[i]], invm[permm[i]] = i, and the expert offsets from the sorted
-// keys: offe[e] = first sorted row whose expert is >= e, offe[E] = M.
-__global__ __launch_bounds__(256) void bw_compose_kernel(const int* __restrict__ expert_idx,
-                                                         const int* __restrict__ perm_a,
-                                                         const int* __restrict__ perm_b, int M, int E,
-                                                         int* __restrict__ permm, int* __restrict__ invm,
-                                                         int* __restrict__ offe) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= M) return;
-  const int m = perm_a[perm_b[i]];
-  permm[i] = m;
-  invm[m] = i;
-  const int e = min(max(expert_idx[m], 0), E - 1);
-  const int prev = i > 0 ? min(max(expert_idx[perm_a[perm_b[i - 1]]], 0), E - 1) : -1;
-  for (int x = prev + 1; x <= e; ++x) offe[x] = i;
-  if (i == M - 1)
-    for (int x = e + 1; x <= E; ++x) offe[x] = M;
-}
-
 // Column ranges of the group-padded transposed copies and, for every padded column qc, the
 // sorted row it holds (-1: padding), the source row perm[row] / div and its gate.
 // krange[2g] = first column of group g, krange[2g+1] = its rows rounded up to 32.
@@ -525,17 +487,13 @@ cmoe_bw_layout cmoe_backward_layout(const cmoe_dims& dm, int T) {
     off = up256(off + bytes);
     return at;
   };
-  const size_t n_blocks = (M + PERMUTE_BLOCK - 1) / PERMUTE_BLOCK;
-  L.blk_counts = take(sizeof(int) * (n_blocks + 1) * 64);
-  L.cid = take(sizeof(int) * Tz);
+  L.counts = take(sizeof(int) * sort_counts(M, E));
   L.permc = take(sizeof(int) * Tz);
   L.invc = take(sizeof(int) * Tz);
   L.offc = take(sizeof(int) * (G + 1));
   L.permm = take(sizeof(int) * M);
   L.invm = take(sizeof(int) * M);
   L.offe = take(sizeof(int) * (E + 1));
-  L.sort_tmp = take(E > 64 ? sizeof(int) * 4 * M : 0);   // key, perm_a, perm_b, scratch inverse
-  L.off_tmp = take(sizeof(int) * 65);
   L.krange_c = take(sizeof(int) * 2 * G);
   L.srow_c = take(sizeof(int) * Tp);
   L.ssrc_c = take(sizeof(int) * Tp);
@@ -610,22 +568,12 @@ hipError_t launch_backward(const cmoe_dims& dm, const cmoe_weights& w, const hal
     return hipSuccess;
   };
 
-  // tokens sorted by cluster, pairs sorted by expert (both stable)
-  if (T > 0)
-    hipLaunchKernelGGL(bw_cluster_kernel, dim3((T + 255) / 256), dim3(256), 0, st, expert_idx, T, k, dm.K, I(L.cid));
-  BW_CHECK(launch_permute_bins(G, I(L.cid), T, permc, I(L.invc), offc, I(L.blk_counts), st));
-  if (E <= 64) {
-    BW_CHECK(launch_permute_bins(E, expert_idx, M, permm, invm, offe, I(L.blk_counts), st));
-  } else if (M > 0) {
-    int *key = I(L.sort_tmp), *perm_a = key + M, *perm_b = key + 2 * (size_t)M, *scratch = key + 3 * (size_t)M;
-    const dim3 gm((M + 255) / 256), blk(256);
-    hipLaunchKernelGGL(bw_key_kernel, gm, blk, 0, st, expert_idx, (const int*)nullptr, M, dm.K, E, 0, key);
-    BW_CHECK(launch_permute_bins(dm.K, key, M, perm_a, scratch, I(L.off_tmp), I(L.blk_counts), st));
-    hipLaunchKernelGGL(bw_key_kernel, gm, blk, 0, st, expert_idx, (const int*)perm_a, M, dm.K, E, 1, key);
-    BW_CHECK(launch_permute_bins(G, key, M, perm_b, scratch, I(L.off_tmp), I(L.blk_counts), st));
-    hipLaunchKernelGGL(bw_compose_kernel, gm, blk, 0, st, expert_idx, (const int*)perm_a, (const int*)perm_b, M, E,
-                       permm, invm, offe);
+  // tokens sorted by cluster (of their first selected expert), pairs sorted by expert (both stable)
+  if (T > 0) {
+    BW_CHECK(launch_sort_ids(expert_idx, k, dm.K, T, G, permc, I(L.invc), offc, I(L.counts), st));
+    BW_CHECK(launch_sort_ids(expert_idx, 1, 1, M, E, permm, invm, offe, I(L.counts), st));
   } else {
+    hipLaunchKernelGGL(bw_zero_kernel, dim3(1), dim3(256), 0, st, offc, G + 1);
     hipLaunchKernelGGL(bw_zero_kernel, dim3((E + 256) / 256), dim3(256), 0, st, offe, E + 1);
   }
   hipLaunchKernelGGL(bw_map_kernel, dim3((Tpad + 255) / 256), dim3(256), 0, st, offc, permc, (const float*)nullptr, G,

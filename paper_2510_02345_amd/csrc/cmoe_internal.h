@@ -54,7 +54,7 @@ struct cmoe_handle {
 
 // Workspace layout for T tokens (byte offsets, all 256-byte aligned).
 struct cmoe_ws_layout {
-  size_t blk_counts;  // int32 [n_blocks][max(G,64)] permute: per-block histogram -> bases
+  size_t blk_counts;  // int32 [n_blocks + 1][64 G] permute: per-block counts of (cluster, pair key)
   size_t sort_i32;    // int32 [2][T]          expert-pair order inside clusters: rowmap, perm2
   size_t v1cat;       // f16 [G][KRp][d]       dequantised V1, rows kk = j*r + rho
   size_t u1t;         // f16 [G][d_ff][KRp]    dequantised U1, transposed
@@ -99,7 +99,9 @@ inline cmoe_packed_layout cmoe_packed(const cmoe_dims& dm) {
   return L;
 }
 
-static const int PERMUTE_BLOCK = 1024;  // tokens per workgroup in the permutation kernels
+static const int PERMUTE_BLOCK = 1024;  // items per workgroup in the sorting kernels
+// ints of a sort's per-block counts: one row per block and a row of totals
+inline size_t sort_counts(size_t n, size_t bins) { return ((n + PERMUTE_BLOCK - 1) / PERMUTE_BLOCK + 1) * bins; }
 static const int G1_BN = 256;           // rows of d_ff per workgroup tile (= per s partial) in the fused up-projection
 static const int SKINNY_T = 256;        // at most this many tokens: weight-streaming kernels
 static const int SKINNY_SN = 2048;      // columns of d_ff per s partial in the weight-streaming path
@@ -112,13 +114,15 @@ hipError_t launch_route(const cmoe_dims& dm, const cmoe_weights& w, const half_t
 hipError_t launch_route_mfma(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int* cluster_id,
                              int* expert_idx, float* gate, hipStream_t st);
 hipError_t launch_permute(const cmoe_dims& dm, const int* cluster_id, int T, int* perm, int* inv_perm, int* offsets,
-                          int* blk_counts, hipStream_t st);
+                          int* counts, hipStream_t st);
 hipError_t launch_permute_static(const cmoe_dims& dm, const int* cluster_id, int T, int* perm, int* inv_perm,
                                  int* offsets, hipStream_t st);
-hipError_t launch_permute_bins(int bins, const int* keys, int T, int* perm, int* inv_perm, int* offsets,
-                               int* blk_counts, hipStream_t st);
-hipError_t launch_pair_sort(const cmoe_dims& dm, const int* perm, const int* offsets, const int* expert_idx, int T,
-                            int* rowmap, int* perm2, hipStream_t st);
+hipError_t launch_pair_sort(const cmoe_dims& dm, const int* perm, const int* offsets, const int* expert_idx, int* rowmap,
+                            int* perm2, hipStream_t st);
+hipError_t launch_sort_pairs(const cmoe_dims& dm, const int* cluster_id, const int* expert_idx, int T, int* perm,
+                             int* inv_perm, int* offsets, int* counts, int* rowmap, int* perm2, hipStream_t st);
+hipError_t launch_sort_ids(const int* ids, int stride, int div, int n, int bins, int* perm, int* inv_perm, int* offsets,
+                           int* counts, hipStream_t st);
 hipError_t launch_dequant_ffn(const cmoe_dims& dm, const cmoe_weights& w, const int* offsets, half_t* v1cat,
                               half_t* u1t, half_t* v2p, half_t* u2t, hipStream_t st);
 hipError_t launch_dequant_u2(const cmoe_dims& dm, const cmoe_weights& w, const int* offsets, half_t* u2t,
@@ -170,7 +174,7 @@ hipError_t launch_combine(const cmoe_dims& dm, const half_t* u2t, const half_t* 
 // the transposed copies whose groups (clusters) are padded to 32.
 struct cmoe_bw_layout {
   int M, Tpad;
-  size_t blk_counts, cid, permc, invc, offc, permm, invm, offe, sort_tmp, off_tmp, krange_c;
+  size_t counts, permc, invc, offc, permm, invm, offe, krange_c;
   size_t srow_c, ssrc_c;
   size_t offx_f, gidx_f, offx_d, gidx_d, dl;
   size_t v1p, u2p, u1p, v2p;                  // f16 rank panels [E][32][L]

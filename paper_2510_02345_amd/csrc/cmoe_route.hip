@@ -246,95 +246,6 @@ __global__ __launch_bounds__(256) void sum_groups_kernel(const half_t* __restric
   *(half8*)(y + (size_t)t * d + col) = o;
 }
 
-// ---------------------------------------------------------------- permutation
-// Pass 1: per-block histogram of cluster ids (LDS integer atomics: order-independent).
-__global__ __launch_bounds__(PERMUTE_BLOCK) void permute_hist_kernel(const int* __restrict__ cluster_id, int T, int G,
-                                                                     int* __restrict__ blk_counts) {
-  __shared__ int hist[64];
-  if (threadIdx.x < 64) hist[threadIdx.x] = 0;
-  __syncthreads();
-  int t = blockIdx.x * PERMUTE_BLOCK + threadIdx.x;
-  if (t < T) atomicAdd(&hist[min(max(cluster_id[t], 0), G - 1)], 1);
-  __syncthreads();
-  if (threadIdx.x < G) blk_counts[(size_t)blockIdx.x * G + threadIdx.x] = hist[threadIdx.x];
-}
-
-// Pass 2: one workgroup.  offsets = exclusive scan of the cluster totals; each block's
-// count is replaced by the first sorted row that block may write for that cluster.  The
-// blocks are cut into SCAN_SEG segments, one wavefront per segment and one lane per cluster:
-// segment totals first (independent loads), then the walk inside each segment.
-constexpr int SCAN_SEG = 16;
-__global__ __launch_bounds__(SCAN_SEG * 64) void permute_scan_kernel(int n_blocks, int G,
-                                                                     int* __restrict__ blk_counts,
-                                                                     int* __restrict__ offsets) {
-  __shared__ int segsum[SCAN_SEG][64];
-  __shared__ int total[64];
-  const int g = threadIdx.x & 63, seg = threadIdx.x >> 6;
-  const int per = (n_blocks + SCAN_SEG - 1) / SCAN_SEG;
-  const int b0 = min(seg * per, n_blocks), b1 = min(b0 + per, n_blocks);
-  int sum = 0;
-  if (g < G)
-    for (int b = b0; b < b1; ++b) sum += blk_counts[(size_t)b * G + g];
-  segsum[seg][g] = sum;
-  __syncthreads();
-  if (seg == 0) {
-    int run = 0;
-    for (int s2 = 0; s2 < SCAN_SEG; ++s2) {   // exclusive over the segments of cluster g
-      const int v = segsum[s2][g];
-      segsum[s2][g] = run;
-      run += v;
-    }
-    total[g] = g < G ? run : 0;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int c = 0; c < G; ++c) {
-      offsets[c] = run;
-      const int v = total[c];
-      total[c] = run;
-      run += v;
-    }
-    offsets[G] = run;
-  }
-  __syncthreads();
-  if (g < G) {
-    int run = total[g] + segsum[seg][g];
-    for (int b = b0; b < b1; ++b) {
-      const int v = blk_counts[(size_t)b * G + g];
-      blk_counts[(size_t)b * G + g] = run;
-      run += v;
-    }
-  }
-}
-
-// Pass 3: stable ranks.  Inside a block, a token's rank among equal clusters is the count
-// in earlier wavefronts plus the number of lower lanes with the same cluster (ballot).
-__global__ __launch_bounds__(PERMUTE_BLOCK) void permute_rank_kernel(const int* __restrict__ cluster_id, int T, int G,
-                                                                     const int* __restrict__ blk_base,
-                                                                     int* __restrict__ perm,
-                                                                     int* __restrict__ inv_perm) {
-  constexpr int NW = PERMUTE_BLOCK / 64;
-  __shared__ int wcount[NW][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int t = blockIdx.x * PERMUTE_BLOCK + threadIdx.x;
-  const int c = (t < T) ? min(max(cluster_id[t], 0), G - 1) : -1;
-  int my_rank = 0;
-  for (int g = 0; g < G; ++g) {
-    unsigned long long m = __ballot(c == g);
-    if (lane == 0) wcount[wave][g] = __popcll(m);
-    if (c == g) my_rank = __popcll(m & ((1ull << lane) - 1ull));
-  }
-  __syncthreads();
-  if (t < T) {
-    int before = 0;
-    for (int w = 0; w < wave; ++w) before += wcount[w][c];
-    int pos = blk_base[(size_t)blockIdx.x * G + c] + before + my_rank;
-    perm[pos] = t;
-    inv_perm[t] = pos;
-  }
-}
-
 // Few tokens: one workgroup (eight wavefronts) per token, the logits of a stage spread over
 // the wavefronts so that their dot products run side by side instead of one after another.
 constexpr int RS_WAVES = 8;
@@ -424,43 +335,6 @@ __global__ __launch_bounds__(RS_WAVES * 64) void route_small_kernel(
   }
 }
 
-// T <= 1024: histogram, scan and stable ranks in one workgroup.
-__global__ __launch_bounds__(PERMUTE_BLOCK) void permute_small_kernel(const int* __restrict__ cluster_id, int T, int G,
-                                                                      int* __restrict__ perm,
-                                                                      int* __restrict__ inv_perm,
-                                                                      int* __restrict__ offsets) {
-  constexpr int NW = PERMUTE_BLOCK / 64;
-  __shared__ int wcount[NW][64];
-  __shared__ int base[64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int t = threadIdx.x;
-  const int c = (t < T) ? min(max(cluster_id[t], 0), G - 1) : -1;
-  int my_rank = 0;
-  for (int g = 0; g < G; ++g) {
-    unsigned long long m = __ballot(c == g);
-    if (lane == 0) wcount[wave][g] = __popcll(m);
-    if (c == g) my_rank = __popcll(m & ((1ull << lane) - 1ull));
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int g = 0; g < G; ++g) {
-      offsets[g] = run;
-      base[g] = run;
-      for (int w = 0; w < NW; ++w) run += wcount[w][g];
-    }
-    offsets[G] = run;
-  }
-  __syncthreads();
-  if (t < T) {
-    int before = 0;
-    for (int w = 0; w < wave; ++w) before += wcount[w][c];
-    int pos = base[c] + before + my_rank;
-    perm[pos] = t;
-    inv_perm[t] = pos;
-  }
-}
-
 __global__ void zero_offsets_kernel(int G, int* offsets) {
   if ((int)threadIdx.x <= G) offsets[threadIdx.x] = 0;
 }
@@ -468,63 +342,251 @@ __global__ void zero_offsets_kernel(int G, int* offsets) {
 }  // namespace
 
 namespace {
-// One workgroup per cluster: a stable counting sort of the cluster's rows by the key
-// (first selected expert, second selected expert) taken inside the cluster, or by the
-// first expert alone when K * K keys do not fit the 64 bins.
-//   rowmap[i] = cluster-sorted row of refined row i,  perm2[i] = its token.
-constexpr int PS_THREADS = 1024;
-constexpr int PS_KEEP = 8;   // rows per thread whose token and key stay in registers
-__global__ __launch_bounds__(PS_THREADS) void pair_sort_kernel(const int* __restrict__ perm,
+// ---------------------------------------------------------------- permutation
+// Stable counting sort by blocks of SORT_BLOCK items, one thread per item.
+//   item i -> bin.  Plain: bin = id, id(i) = ids[i * stride] / div clamped to the bins.  PAIR: id is
+//   the token's cluster c and bin = c NK + (pair key of the token inside its cluster): the
+//   refined order of the fused up-projection, ranked together with the plain order by cluster.
+// sort_rank_kernel ranks a block; what it needs of the other blocks are the counts per bin over
+// all blocks and over the earlier ones.  It makes them itself
+//   - from the ids, up to SORT_SELF items (one launch),
+//   - from the per-block histograms of sort_hist_kernel, up to SORT_SUM_BLOCKS blocks (two),
+//   - else from those histograms after sort_scan_kernel has summed them over the blocks (three).
+// Everything here is latency, not bandwidth: a launch costs about as much as a block's ranks.
+// Histogram, scan, ranks and a one-workgroup-per-cluster pair sort were four launches: 21 -> 8 us
+// of kernel time at 4096 tokens and 2 clusters (now one launch), 31 -> 11 us at 16384 tokens
+// with Zipf loads and 27 -> 14 us at 32768 tokens and 8 clusters (two launches).
+constexpr int SORT_BLOCK = PERMUTE_BLOCK, SORT_WAVES = SORT_BLOCK / 64;
+constexpr int SORT_SELF = 4 * SORT_BLOCK;
+constexpr int SORT_SUM_BLOCKS = 128;
+constexpr int SORT_BINS = 4096;   // bins of a sort: 64 clusters x 64 pair keys, 64 x 32 experts
+
+// Exclusive sum over the workgroup's 1024 threads, in thread order; contains one barrier, and
+// the caller separates two uses of ws by another.
+__device__ __forceinline__ int block_exclusive(int v, int* ws) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int incl = v;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int u = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += u;
+  }
+  if (lane == 63) ws[wave] = incl;
+  __syncthreads();
+  int before = 0;
+#pragma unroll
+  for (int w = 0; w < SORT_WAVES; ++w) before += w < wave ? ws[w] : 0;
+  return before + incl - v;
+}
+
+// Sort key of a token inside its cluster c: its (first, second) selected expert, or the first
+// alone when K * K keys do not fit 64.  Expert slots outside the cluster (inconsistent caller
+// input) are clamped into it.
+__device__ __forceinline__ int pair_key(const int* expert_idx, int tok, int c, int K, int k, int two_keys) {
+  const int* e = expert_idx + (size_t)tok * k;
+  const int j0 = min(max(e[0] - c * K, 0), K - 1);
+  return two_keys ? j0 * K + min(max(e[1] - c * K, 0), K - 1) : j0;
+}
+
+struct SortArgs {
+  const int* ids;
+  int stride, div, n, n_ids;     // items and ids' bins
+  const int* expert_idx;         // PAIR
+  int K, k, two_keys, nk;        // PAIR: nk keys per cluster
+  int n_blocks, bins;            // bins = n_ids (plain) or n_ids * nk
+};
+// (id, bin) of item i < n
+template <bool PAIR>
+__device__ __forceinline__ void sort_bin(const SortArgs& a, int i, int& id, int& bin) {
+  const int raw = a.ids[(size_t)i * a.stride];
+  id = min(max(a.div == 1 ? raw : raw / a.div, 0), a.n_ids - 1);
+  bin = PAIR ? id * a.nk + pair_key(a.expert_idx, i, id, a.K, a.k, a.two_keys) : id;
+}
+
+// counts[block][bin]
+template <bool PAIR>
+__global__ __launch_bounds__(SORT_BLOCK) void sort_hist_kernel(SortArgs a, int* __restrict__ counts) {
+  __shared__ int hist[SORT_BINS];
+  const int i = blockIdx.x * SORT_BLOCK + threadIdx.x;
+  int id = 0, bin = 0;
+  if (i < a.n) sort_bin<PAIR>(a, i, id, bin);
+  for (int b = threadIdx.x; b < a.bins; b += SORT_BLOCK) hist[b] = 0;
+  __syncthreads();
+  if (i < a.n) atomicAdd(&hist[bin], 1);   // integer counts: order-independent
+  __syncthreads();
+  for (int b = threadIdx.x; b < a.bins; b += SORT_BLOCK) counts[(size_t)blockIdx.x * a.bins + b] = hist[b];
+}
+
+// counts[block][bin] -> the bin's count in earlier blocks, totals in counts[n_blocks][bin].
+__global__ __launch_bounds__(64) void sort_scan_kernel(SortArgs a, int* __restrict__ counts) {
+  const int b = blockIdx.x * 64 + threadIdx.x;
+  if (b >= a.bins) return;
+  int run = 0;
+  for (int blk0 = 0; blk0 < a.n_blocks; blk0 += 16) {
+    int v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = blk0 + u < a.n_blocks ? counts[(size_t)(blk0 + u) * a.bins + b] : 0;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      if (blk0 + u < a.n_blocks) counts[(size_t)(blk0 + u) * a.bins + b] = run;
+      run += v[u];
+    }
+  }
+  counts[(size_t)a.n_blocks * a.bins + b] = run;
+}
+
+enum { SORT_FROM_IDS = 0, SORT_FROM_HIST = 1, SORT_FROM_SCAN = 2 };
+// perm[row] = item, inv_perm[item] = row in the order by id; offsets[id] = first row of an id.
+// PAIR: rowmap[refined row] = row, perm2[refined row] = item in the order by bin.
+template <bool PAIR>
+__global__ __launch_bounds__(SORT_BLOCK) void sort_rank_kernel(SortArgs a, int mode, const int* __restrict__ counts,
+                                                              int* __restrict__ perm, int* __restrict__ inv_perm,
+                                                              int* __restrict__ offsets, int* __restrict__ rowmap,
+                                                              int* __restrict__ perm2) {
+  extern __shared__ int dyn[];
+  __shared__ int ws[SORT_WAVES];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, me = blockIdx.x, bins = a.bins;
+  int* tot = dyn;                 // [bins] count over all blocks, then first row of the bin
+  int* bef = tot + bins;          // [bins] count in earlier blocks
+  int* idb = bef + bins;          // [n_ids] PAIR: count of an id in earlier blocks
+  unsigned char* wc = (unsigned char*)(idb + (PAIR ? a.n_ids : 0));          // [SORT_WAVES][bins] items of a wavefront
+  unsigned char* wid = wc + SORT_WAVES * ((bins + 3) & ~3);                  // [SORT_WAVES][n_ids], PAIR
+  const int ldw = (bins + 3) & ~3, ldi = (a.n_ids + 3) & ~3;
+  const int i = me * SORT_BLOCK + tid;
+  const bool in = i < a.n;
+  int id = 0, bin = 0;
+  if (in) sort_bin<PAIR>(a, i, id, bin);
+  const int words = 2 * bins + (PAIR ? a.n_ids : 0) + SORT_WAVES * (ldw + (PAIR ? ldi : 0)) / 4;
+  for (int w = tid; w < words; w += SORT_BLOCK) dyn[w] = 0;
+  __syncthreads();
+  // ranks inside the wavefront: lanes with the same bin (and the same id)
+  auto match = [&](int val, int bits) {
+    unsigned long long same = __ballot(in);
+    for (int b = 0; b < bits; ++b) {
+      const unsigned long long m = __ballot((val >> b) & 1);
+      same &= ((val >> b) & 1) ? m : ~m;
+    }
+    return same;
+  };
+  const unsigned long long lower = (1ull << lane) - 1ull;
+  const unsigned long long sb = match(bin, 32 - __builtin_clz(bins));
+  const int rank_b = __popcll(sb & lower);
+  if (in && rank_b == 0) wc[wave * ldw + bin] = (unsigned char)__popcll(sb);
+  int rank_i = rank_b;
+  if (PAIR) {
+    const unsigned long long si = match(id, 32 - __builtin_clz(a.n_ids));
+    rank_i = __popcll(si & lower);
+    if (in && rank_i == 0) wid[wave * ldi + id] = (unsigned char)__popcll(si);
+  }
+  // counts over all blocks and over the earlier ones
+  if (mode == SORT_FROM_IDS) {
+    for (int b0 = 0; b0 < a.n_blocks; ++b0) {
+      const int i2 = b0 * SORT_BLOCK + tid;
+      int id2 = id, bin2 = bin;
+      if (b0 != me && i2 < a.n) sort_bin<PAIR>(a, i2, id2, bin2);
+      if (i2 < a.n) {
+        atomicAdd(&tot[bin2], 1);
+        if (b0 < me) {
+          atomicAdd(&bef[bin2], 1);
+          if (PAIR) atomicAdd(&idb[id2], 1);
+        }
+      }
+    }
+  } else if (mode == SORT_FROM_HIST) {
+    // threads beyond the bins share the blocks
+    int width = 1;
+    while (width < bins && width < SORT_BLOCK) width <<= 1;
+    const int parts = SORT_BLOCK / width, part = tid / width;
+    const int per = (a.n_blocks + parts - 1) / parts, b0 = part * per, b1 = min(a.n_blocks, b0 + per);
+    for (int b = tid % width; b < bins; b += width) {
+      int t = 0, f = 0;
+#pragma unroll 8
+      for (int blk = b0; blk < b1; ++blk) {
+        const int v = counts[(size_t)blk * bins + b];
+        t += v;
+        f += blk < me ? v : 0;
+      }
+      if (t) atomicAdd(&tot[b], t);
+      if (f) {
+        atomicAdd(&bef[b], f);
+        if (PAIR) atomicAdd(&idb[b / a.nk], f);
+      }
+    }
+  } else {
+    for (int b = tid; b < bins; b += SORT_BLOCK) {
+      const int f = counts[(size_t)me * bins + b];
+      tot[b] = counts[(size_t)a.n_blocks * bins + b];
+      bef[b] = f;
+      if (PAIR && f) atomicAdd(&idb[b / a.nk], f);
+    }
+  }
+  __syncthreads();
+  {   // first row of every bin: exclusive sum over the bins, four consecutive bins per thread
+    int n4[4], sum = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      n4[u] = 4 * tid + u < bins ? tot[4 * tid + u] : 0;
+      sum += n4[u];
+    }
+    int at = block_exclusive(sum, ws);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (4 * tid + u < bins) tot[4 * tid + u] = at;
+      at += n4[u];
+    }
+  }
+  __syncthreads();
+  const int nk = PAIR ? a.nk : 1;
+  if (me == 0)
+    for (int g = tid; g <= a.n_ids; g += SORT_BLOCK) offsets[g] = g < a.n_ids ? tot[g * nk] : a.n;
+  if (!in) return;
+  int row = tot[id * nk] + rank_i + (PAIR ? idb[id] : bef[id]);
+  const unsigned char* col = PAIR ? wid + id : wc + id;
+  const int ldc = PAIR ? ldi : ldw;
+#pragma unroll
+  for (int w = 0; w < SORT_WAVES; ++w) row += w < wave ? col[w * ldc] : 0;
+  perm[row] = i;
+  inv_perm[i] = row;
+  if (PAIR) {
+    int fine = tot[bin] + bef[bin] + rank_b;
+#pragma unroll
+    for (int w = 0; w < SORT_WAVES; ++w) fine += w < wave ? wc[w * ldw + bin] : 0;
+    rowmap[fine] = row;
+    perm2[fine] = i;
+  }
+}
+
+// The pair sort alone, for a permutation the caller already has: one workgroup per cluster, the
+// rows of the cluster in chunks of SORT_BLOCK.
+__global__ __launch_bounds__(SORT_BLOCK) void pair_sort_kernel(const int* __restrict__ perm,
                                                               const int* __restrict__ offsets,
                                                               const int* __restrict__ expert_idx, int K, int k,
                                                               int two_keys, int* __restrict__ rowmap,
                                                               int* __restrict__ perm2) {
-  constexpr int NW = PS_THREADS / 64;
-  __shared__ int binbase[64];
-  __shared__ int wcount[NW][64];
+  __shared__ int next[64];   // next refined row of every key
+  __shared__ int wcount[SORT_WAVES][64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int c = blockIdx.x;
-  const int lo = offsets[c], n = offsets[c + 1] - lo;
+  const int c = blockIdx.x, lo = offsets[c], n = offsets[c + 1] - lo;
   if (n <= 0) return;
-  auto key_of_tok = [&](int tok) {
-    const int* e = expert_idx + (size_t)tok * k;
-    // expert slots outside the cluster (inconsistent caller input) are clamped into it
-    const int j0 = min(max(e[0] - c * K, 0), K - 1);
-    return two_keys ? j0 * K + min(max(e[1] - c * K, 0), K - 1) : j0;
-  };
-  // The first PS_KEEP rows of a thread (row tid + j * PS_THREADS) are read once, all loads in
-  // flight together, and kept in registers for both passes; clusters with more rows take
-  // the rest from memory in each pass.
-  int tokr[PS_KEEP], keyr[PS_KEEP];
-#pragma unroll
-  for (int j = 0; j < PS_KEEP; ++j) {
-    const int i = tid + j * PS_THREADS;
-    tokr[j] = i < n ? perm[lo + i] : 0;
-  }
-#pragma unroll
-  for (int j = 0; j < PS_KEEP; ++j) keyr[j] = tid + j * PS_THREADS < n ? key_of_tok(tokr[j]) : 0;
-  if (tid < 64) binbase[tid] = 0;
+  if (tid < 64) next[tid] = 0;
   __syncthreads();
-#pragma unroll
-  for (int j = 0; j < PS_KEEP; ++j)
-    if (tid + j * PS_THREADS < n) atomicAdd(&binbase[keyr[j]], 1);
-  for (int i = tid + PS_KEEP * PS_THREADS; i < n; i += PS_THREADS) atomicAdd(&binbase[key_of_tok(perm[lo + i])], 1);
+  for (int i = tid; i < n; i += SORT_BLOCK) atomicAdd(&next[pair_key(expert_idx, perm[lo + i], c, K, k, two_keys)], 1);
   __syncthreads();
-  if (wave == 0) {   // exclusive scan of the 64 bin counts
-    const int cnt = binbase[lane];
+  if (wave == 0) {
+    const int cnt = next[lane];
     int incl = cnt;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
       const int v = __shfl_up(incl, off, 64);
       if (lane >= off) incl += v;
     }
-    binbase[lane] = incl - cnt;
+    next[lane] = lo + incl - cnt;
   }
-  __syncthreads();
-  // one chunk of PS_THREADS rows; chunks in order keep the sort stable
-  auto chunk = [&](int i, bool in, int key, int tok) {
-    // lanes of this wavefront holding the same key
-    unsigned long long same = __ballot(in);
+  for (int i0 = 0; i0 < n; i0 += SORT_BLOCK) {   // chunks in order keep the sort stable
+    const int i = i0 + tid;
+    const bool in = i < n;
+    const int tok = in ? perm[lo + i] : 0, key = in ? pair_key(expert_idx, tok, c, K, k, two_keys) : 0;
+    unsigned long long same = __ballot(in);   // lanes of this wavefront holding the same key
 #pragma unroll
     for (int b = 0; b < 6; ++b) {
       const unsigned long long m = __ballot((key >> b) & 1);
@@ -536,9 +598,8 @@ __global__ __launch_bounds__(PS_THREADS) void pair_sort_kernel(const int* __rest
     if (in && below == 0) wcount[wave][key] = __popcll(same);
     __syncthreads();
     if (in) {
-      int before = 0;
-      for (int w = 0; w < wave; ++w) before += wcount[w][key];
-      const int pos = lo + binbase[key] + before + below;
+      int pos = next[key] + below;
+      for (int w = 0; w < wave; ++w) pos += wcount[w][key];
       rowmap[pos] = lo + i;
       perm2[pos] = tok;
     }
@@ -546,23 +607,34 @@ __global__ __launch_bounds__(PS_THREADS) void pair_sort_kernel(const int* __rest
     if (tid < 64) {
       int add = 0;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) add += wcount[w][tid];
-      binbase[tid] += add;
+      for (int w = 0; w < SORT_WAVES; ++w) add += wcount[w][tid];
+      next[tid] += add;
     }
     __syncthreads();
-  };
-#pragma unroll
-  for (int j = 0; j < PS_KEEP; ++j) {
-    if (j * PS_THREADS >= n) break;   // uniform over the workgroup
-    const int i = tid + j * PS_THREADS;
-    chunk(i, i < n, keyr[j], tokr[j]);
   }
-  for (int i0 = PS_KEEP * PS_THREADS; i0 < n; i0 += PS_THREADS) {
-    const int i = i0 + tid;
-    const bool in = i < n;
-    const int tok = in ? perm[lo + i] : 0;
-    chunk(i, in, in ? key_of_tok(tok) : 0, tok);
+}
+
+inline int two_keys_of(const cmoe_dims& dm) { return (dm.k >= 2 && dm.K * dm.K <= 64) ? 1 : 0; }
+
+template <bool PAIR>
+hipError_t go_sort(SortArgs a, int* perm, int* inv_perm, int* offsets, int* rowmap, int* perm2, int* counts,
+                   hipStream_t st) {
+  a.n_blocks = (a.n + SORT_BLOCK - 1) / SORT_BLOCK;
+  a.bins = PAIR ? a.n_ids * a.nk : a.n_ids;
+  const int mode = a.n <= SORT_SELF ? SORT_FROM_IDS : a.n_blocks <= SORT_SUM_BLOCKS ? SORT_FROM_HIST : SORT_FROM_SCAN;
+  const dim3 grid(a.n_blocks), block(SORT_BLOCK);
+  if (mode != SORT_FROM_IDS) hipLaunchKernelGGL((sort_hist_kernel<PAIR>), grid, block, 0, st, a, counts);
+  if (mode == SORT_FROM_SCAN) hipLaunchKernelGGL(sort_scan_kernel, dim3((a.bins + 63) / 64), dim3(64), 0, st, a, counts);
+  const size_t lds = 4 * (2 * (size_t)a.bins + (PAIR ? a.n_ids : 0)) +
+                     SORT_WAVES * (size_t)(((a.bins + 3) & ~3) + (PAIR ? ((a.n_ids + 3) & ~3) : 0));
+  if (lds > 65536) {   // 64 clusters with 64 pair keys each
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sort_rank_kernel<PAIR>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
   }
+  hipLaunchKernelGGL((sort_rank_kernel<PAIR>), grid, block, lds, st, a, mode, (const int*)counts, perm, inv_perm, offsets,
+                     rowmap, perm2);
+  return hipGetLastError();
 }
 }  // namespace
 
@@ -570,13 +642,27 @@ __global__ __launch_bounds__(PS_THREADS) void pair_sort_kernel(const int* __rest
 // selected expert, second selected expert, original order).  Cluster boundaries (offsets)
 // do not move.  Rows of a 16-token block then mostly share their experts, so the fused
 // up-projection skips most rank chunks.
-hipError_t launch_pair_sort(const cmoe_dims& dm, const int* perm, const int* offsets, const int* expert_idx, int T,
-                            int* rowmap, int* perm2, hipStream_t st) {
-  (void)T;
-  const int two = (dm.k >= 2 && dm.K * dm.K <= 64) ? 1 : 0;
-  hipLaunchKernelGGL(pair_sort_kernel, dim3(dm.G), dim3(PS_THREADS), 0, st, perm, offsets, expert_idx, dm.K, dm.k, two,
-                     rowmap, perm2);
+hipError_t launch_pair_sort(const cmoe_dims& dm, const int* perm, const int* offsets, const int* expert_idx, int* rowmap,
+                            int* perm2, hipStream_t st) {
+  hipLaunchKernelGGL(pair_sort_kernel, dim3(dm.G), dim3(SORT_BLOCK), 0, st, perm, offsets, expert_idx, dm.K, dm.k,
+                     two_keys_of(dm), rowmap, perm2);
   return hipGetLastError();
+}
+
+// The permutation and the pair order of a step together.  counts: sort_counts(T, G * 64) ints.
+hipError_t launch_sort_pairs(const cmoe_dims& dm, const int* cluster_id, const int* expert_idx, int T, int* perm,
+                             int* inv_perm, int* offsets, int* counts, int* rowmap, int* perm2, hipStream_t st) {
+  const int two = two_keys_of(dm);
+  SortArgs a{cluster_id, 1, 1, T, dm.G, expert_idx, dm.K, dm.k, two, two ? dm.K * dm.K : dm.K, 0, 0};
+  return go_sort<true>(a, perm, inv_perm, offsets, rowmap, perm2, counts, st);
+}
+
+// Stable sort of n > 0 items by id(i) = ids[i * stride] / div into at most SORT_BINS bins.
+// counts: sort_counts(n, bins) ints.
+hipError_t launch_sort_ids(const int* ids, int stride, int div, int n, int bins, int* perm, int* inv_perm, int* offsets,
+                           int* counts, hipStream_t st) {
+  SortArgs a{ids, stride, div, n, bins, nullptr, 1, 1, 0, 1, 0, 0};
+  return go_sort<false>(a, perm, inv_perm, offsets, nullptr, nullptr, counts, st);
 }
 
 hipError_t launch_route(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int* cluster_id,
@@ -619,29 +705,12 @@ hipError_t launch_route(const cmoe_dims& dm, const cmoe_weights& w, const half_t
 }
 
 hipError_t launch_permute(const cmoe_dims& dm, const int* cluster_id, int T, int* perm, int* inv_perm, int* offsets,
-                          int* blk_counts, hipStream_t st) {
-  return launch_permute_bins(dm.G, cluster_id, T, perm, inv_perm, offsets, blk_counts, st);
-}
-
-hipError_t launch_permute_bins(int bins, const int* cluster_id, int T, int* perm, int* inv_perm, int* offsets,
-                               int* blk_counts, hipStream_t st) {
-  struct { int G; } dm{bins};
+                          int* counts, hipStream_t st) {
   if (T == 0) {
     hipLaunchKernelGGL(zero_offsets_kernel, dim3(1), dim3(128), 0, st, dm.G, offsets);
     return hipGetLastError();
   }
-  if (T <= PERMUTE_BLOCK) {
-    hipLaunchKernelGGL(permute_small_kernel, dim3(1), dim3(PERMUTE_BLOCK), 0, st, cluster_id, T, dm.G, perm,
-                       inv_perm, offsets);
-    return hipGetLastError();
-  }
-  int n_blocks = (T + PERMUTE_BLOCK - 1) / PERMUTE_BLOCK;
-  hipLaunchKernelGGL(permute_hist_kernel, dim3(n_blocks), dim3(PERMUTE_BLOCK), 0, st, cluster_id, T, dm.G,
-                     blk_counts);
-  hipLaunchKernelGGL(permute_scan_kernel, dim3(1), dim3(SCAN_SEG * 64), 0, st, n_blocks, dm.G, blk_counts, offsets);
-  hipLaunchKernelGGL(permute_rank_kernel, dim3(n_blocks), dim3(PERMUTE_BLOCK), 0, st, cluster_id, T, dm.G,
-                     blk_counts, perm, inv_perm);
-  return hipGetLastError();
+  return launch_sort_ids(cluster_id, 1, 1, T, dm.G, perm, inv_perm, offsets, counts, st);
 }
 
 // ---------------------------------------------------------------- permutation without a workspace argument
@@ -649,7 +718,7 @@ hipError_t launch_permute_bins(int bins, const int* cluster_id, int T, int* perm
 // instead of the caller's workspace, for callers that cannot allocate device memory.  Every
 // GPU holds its own copy of the array at its own address; the host resolves that address
 // once per device and passes it to the kernels like any other buffer.
-static const int kStaticBlocks = CMOE_PERMUTE_STATIC_MAX_TOKENS / PERMUTE_BLOCK;
+static const int kStaticBlocks = CMOE_PERMUTE_STATIC_MAX_TOKENS / PERMUTE_BLOCK + 1;   // and a row of totals
 static __device__ __align__(256) int scratch[(size_t)kStaticBlocks * 64];
 static const int kMaxDevices = 64;
 static int* g_scratch_ptr[kMaxDevices];
@@ -676,14 +745,14 @@ static hipError_t scratch_address(int** out) {
 hipError_t launch_permute_static(const cmoe_dims& dm, const int* cluster_id, int T, int* perm, int* inv_perm,
                                  int* offsets, hipStream_t st) {
   int* blk_counts = nullptr;
-  // up to PERMUTE_BLOCK tokens run in one workgroup and need no histogram buffer
-  if (T > PERMUTE_BLOCK) {
+  // up to SORT_SELF tokens are sorted in one launch without a histogram buffer
+  if (T > SORT_SELF) {
     hipError_t e = scratch_address(&blk_counts);
     if (e != hipSuccess) return e;
   }
   // every entry the later passes read is written by the first pass of the same call: nothing
   // has to start at zero, whatever an earlier call left behind
-  return launch_permute_bins(dm.G, cluster_id, T, perm, inv_perm, offsets, blk_counts, st);
+  return launch_permute(dm, cluster_id, T, perm, inv_perm, offsets, blk_counts, st);
 }
 
 hipError_t launch_route_multi(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int top_g,
