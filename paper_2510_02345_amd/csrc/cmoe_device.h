@@ -73,6 +73,35 @@ __device__ __forceinline__ int pi_row(int rho) {
 // read without conflicts but gives two-way conflicts on every 16-row read.
 __device__ __forceinline__ int swz(int row) { return ((row >> 2) & 3) ^ ((row >> 1) & 2); }
 
+// Inclusive sum over the lanes of a wavefront by data-parallel-primitive moves (no LDS round
+// trips): rows of 16 lanes by shifts, then the row totals broadcast upwards.
+__device__ __forceinline__ int wave_inclusive_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+// Row tiles of bm rows that never straddle a group, dealt group after group: the group of tile
+// `slot` and its rows [m0, m_end) up to the group's end (m0 the tile's first row).  false: past the
+// last tile.  offsets [n_groups + 1], n_groups <= 64: lane g looks at group g, so the search costs
+// one round trip to memory instead of one per group.
+__device__ __forceinline__ bool find_tile(const int* offsets, int n_groups, int bm, int slot, int& c, int& m0, int& m_end) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, hi = 0;
+  if (lane < n_groups) lo = offsets[lane], hi = offsets[lane + 1];
+  const int tiles = (hi - lo + bm - 1) / bm, incl = wave_inclusive_sum(tiles);
+  const unsigned long long past = __ballot(incl > slot);
+  if (past == 0ull) return false;
+  c = __builtin_ctzll(past);
+  m0 = __builtin_amdgcn_readlane(lo, c) + (slot - __builtin_amdgcn_readlane(incl - tiles, c)) * bm;
+  m_end = __builtin_amdgcn_readlane(hi, c);
+  return true;
+}
+
 __device__ __forceinline__ half8 pack_half8(const float4v& lo, const float4v& hi) {
   half8 o;
   o[0] = (half_t)lo[0]; o[1] = (half_t)lo[1]; o[2] = (half_t)lo[2]; o[3] = (half_t)lo[3];

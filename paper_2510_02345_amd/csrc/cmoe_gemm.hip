@@ -1,5 +1,4 @@
 // Grouped matrix-core kernels of the expert computation (Sec. 3.2):
-//   t1   = V1 x                       (all experts of the token's cluster, selected rows kept)
 //   Hb   = W1_base(c) x  -> fused: + U1 t1, GELU, gated sum A, s = V2 a
 //   Yb   = W2_base(c) A
 //   y    = Yb + sum_j g_j U2 s_j, back in token order
@@ -51,9 +50,6 @@ struct GemmArgs {
   int Kc;            // contraction length, multiple of 32
   const int* offsets;
   int G, n_tiles, m_slots, spx;
-  const half_t* W2;  // optional: rows >= w_split of the weight operand come from W2 (same ldw)
-  int w_split;
-  int T_all;         // offsets == NULL: one group holding rows [0, T_all)
   // A launch covers the slots rel_lo <= rel < rel_hi of every XCD's range.  Slots are
   // slot_bm rows of one cluster; a tail launch (tail != 0) cuts each of its slots into
   // slot_bm / BM row tiles of a smaller tile shape.
@@ -123,24 +119,10 @@ __global__ __launch_bounds__(TL::NT, TL::OCC) void gemm_nt_kernel(GemmArgs g, Ep
   }
   // which cluster and row tile the slot is: derived on the device from the cluster
   // offsets, so no host round trip sits between routing and the GEMMs
-  int c = 0, m0 = 0, m_end = 0;
-  if (g.offsets == nullptr) {
-    m0 = slot * TL::BM;
-    m_end = g.T_all;
-    if (m0 >= m_end) return;
-  } else {
-    for (; c < g.G; ++c) {
-      int lo = g.offsets[c], hi = g.offsets[c + 1];
-      int tiles = (hi - lo + g.slot_bm - 1) / g.slot_bm;
-      if (slot < tiles) {
-        m0 = lo + slot * g.slot_bm + sub * TL::BM;
-        m_end = hi;
-        break;
-      }
-      slot -= tiles;
-    }
-    if (c == g.G || m0 >= m_end) return;
-  }
+  int c, m0, m_end;
+  if (!find_tile(g.offsets, g.G, g.slot_bm, slot, c, m0, m_end)) return;
+  m0 += sub * TL::BM;
+  if (m0 >= m_end) return;
   const int n0 = n_tile * TL::BN;
   const half_t* Wc = g.W + (size_t)c * g.w_cstride;
   const int k_lo = g.krange ? g.krange[2 * c] : 0;
@@ -158,7 +140,7 @@ __global__ __launch_bounds__(TL::NT, TL::OCC) void gemm_nt_kernel(GemmArgs g, Ep
     const half_t* base;
     if (row < TL::BN) {
       const int n = min(n0 + pi_row(row), g.N - 1);
-      base = (g.W2 != nullptr && n >= g.w_split) ? g.W2 + (size_t)(n - g.w_split) * g.ldw : Wc + (size_t)n * g.ldw;
+      base = Wc + (size_t)n * g.ldw;
     } else {
       const int p = min(m0 + row - TL::BN, m_end - 1);
       base = g.X + (size_t)(g.gather ? (g.x_div > 1 ? g.gather[p] / g.x_div : g.gather[p]) : p) * g.ldx;
@@ -396,219 +378,6 @@ struct EpiDownCombine {
           acc[2 * P + 1][b] = mfma32(fa1, fb, acc[2 * P + 1][b]);
         }
         if (valid) *(half8*)(y + (size_t)tok * d + t.n0 + nl + 8 * q) = pack_half8(acc[2 * P][b], acc[2 * P + 1][b]);
-      }
-    }
-  }
-};
-
-// ---------------------------------------------------------------- epilogue: two-stage routing
-// acc rows are the logits of all G prototypes (rows 0..G-1) and all G*K expert vectors
-// (rows G..G+E-1) for the tile's tokens.  The decision is the paper's (Sec. 3.3): the
-// cluster with the largest z_g (+ bias) first, then the k largest l_i among that cluster's K
-// experts only, lowest index on ties, gates = softmax over the selected logits.  (All E
-// expert logits are computed because one matrix-core product over the routers is cheaper
-// here than K dot products per token on the vector units; the unselected clusters' logits
-// are discarded.)
-template <class TL>
-__device__ __forceinline__ void stage_logits(const TileCtx& t, float4v (&acc)[TL::NA][TL::MT], float* lg, int LD) {
-  const int t16 = t.lane & 15, q = t.lane >> 4;
-#pragma unroll
-  for (int b = 0; b < TL::MT; ++b) {
-    const int m = t.wm * TL::WM + b * 16 + t16;
-#pragma unroll
-    for (int P = 0; P < TL::NP; ++P)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int n = t.wn * TL::WN + 32 * P + 8 * q;
-        lg[m * LD + n + v] = acc[2 * P][b][v];
-        lg[m * LD + n + 4 + v] = acc[2 * P + 1][b][v];
-      }
-  }
-}
-
-struct EpiRoute {
-  const float* bias;
-  int* cluster_id;
-  int* expert_idx;
-  float* gate;
-  int G, K, k;
-  template <class TL>
-  static constexpr int smem_bytes() {
-    return TL::BM * (TL::BN + 1) * 4 > TL::SMEM_BYTES ? TL::BM * (TL::BN + 1) * 4 : TL::SMEM_BYTES;
-  }
-  template <class TL>
-  __device__ void run(const TileCtx& t, float4v (&acc)[TL::NA][TL::MT]) const {
-    constexpr int LD = TL::BN + 1;
-    float* lg = (float*)t.smem;  // [BM tokens][BN + 1 logits]
-    __syncthreads();  // the stage buffers are free
-    stage_logits<TL>(t, acc, lg, LD);
-    __syncthreads();
-    for (int m = t.tid; m < TL::BM; m += TL::NT) {
-      const int tok = t.m0 + m;
-      if (tok >= t.m_end) continue;
-      const float* row = lg + m * LD;
-      float best = -INFINITY;
-      int c = 0;
-      for (int g = 0; g < G; ++g) {
-        float z = row[g] + (bias ? bias[g] : 0.f);
-        if (z > best) {
-          best = z;
-          c = g;
-        }
-      }
-      const float* l = row + G + c * K;
-      unsigned long long taken = 0ull;  // K <= 32
-      float sel[8];
-      int selj[8];
-      float den = 0.f;
-      for (int a = 0; a < k; ++a) {
-        // lowest slot not taken yet, replaced by any later slot with a larger logit: a NaN
-        // never wins a comparison, so it ranks below every number and the k slots are distinct
-        int bj = __ffsll((long long)~taken) - 1;
-        float bl = l[bj] == l[bj] ? l[bj] : -INFINITY;
-        for (int j = bj + 1; j < K; ++j)
-          if (!((taken >> j) & 1ull) && l[j] > bl) {
-            bl = l[j];
-            bj = j;
-          }
-        taken |= 1ull << bj;
-        sel[a] = l[bj];
-        selj[a] = bj;
-      }
-      const float lmax = sel[0];
-      for (int a = 0; a < k; ++a) {
-        sel[a] = expf(sel[a] - lmax);
-        den += sel[a];
-      }
-      cluster_id[tok] = c;
-      for (int a = 0; a < k; ++a) {
-        expert_idx[(size_t)tok * k + a] = c * K + selj[a];
-        gate[(size_t)tok * k + a] = sel[a] / den;
-      }
-    }
-  }
-};
-
-// The routing variants on the same accumulators: top_g clusters per token (descending
-// logit, lowest index on ties), each with its own top-k experts; both softmaxes take
-// logits * inv_tau; gate = w_a * softmax(l_sel * inv_tau) with w_a = p_g (scale) or p_g
-// renormalised over the selected clusters.  Outputs per virtual token tok * top_g + a.
-struct EpiRouteMulti {
-  const float* bias;
-  int* cluster_id;
-  int* expert_idx;
-  float* gate;
-  int G, K, k, top_g;
-  float inv_tau;
-  int scale;
-  template <class TL>
-  static constexpr int smem_bytes() {
-    return EpiRoute::smem_bytes<TL>();
-  }
-  template <class TL>
-  __device__ void run(const TileCtx& t, float4v (&acc)[TL::NA][TL::MT]) const {
-    constexpr int LD = TL::BN + 1;
-    float* lg = (float*)t.smem;  // [BM tokens][BN + 1 logits]
-    __syncthreads();  // the stage buffers are free
-    stage_logits<TL>(t, acc, lg, LD);
-    __syncthreads();
-    for (int m = t.tid; m < TL::BM; m += TL::NT) {
-      const int tok = t.m0 + m;
-      if (tok >= t.m_end) continue;
-      float* row = lg + m * LD;
-      float zmax = -INFINITY;
-      for (int g = 0; g < G; ++g) {
-        row[g] += bias ? bias[g] : 0.f;
-        zmax = fmaxf(zmax, row[g]);
-      }
-      float zden = 0.f;
-      for (int g = 0; g < G; ++g) zden += expf((row[g] - zmax) * inv_tau);
-      unsigned long long ctaken = 0ull;  // G <= 64
-      int selc[8];
-      float selp[8];
-      float psum = 0.f;
-      for (int a = 0; a < top_g; ++a) {
-        int bg = __ffsll((long long)~ctaken) - 1;
-        float bz = row[bg] == row[bg] ? row[bg] : -INFINITY;
-        for (int g = bg + 1; g < G; ++g)
-          if (!((ctaken >> g) & 1ull) && row[g] > bz) {
-            bz = row[g];
-            bg = g;
-          }
-        ctaken |= 1ull << bg;
-        selc[a] = bg;
-        selp[a] = expf((row[bg] - zmax) * inv_tau) / zden;
-        psum += selp[a];
-      }
-      for (int a = 0; a < top_g; ++a) {
-        const int c = selc[a];
-        const float wa = scale ? selp[a] : selp[a] / psum;
-        const float* l = row + G + c * K;
-        unsigned long long taken = 0ull;  // K <= 32
-        float sel[8];
-        int selj[8];
-        for (int b = 0; b < k; ++b) {
-          int bj = __ffsll((long long)~taken) - 1;
-          float bl = l[bj] == l[bj] ? l[bj] : -INFINITY;
-          for (int j = bj + 1; j < K; ++j)
-            if (!((taken >> j) & 1ull) && l[j] > bl) {
-              bl = l[j];
-              bj = j;
-            }
-          taken |= 1ull << bj;
-          sel[b] = l[bj];
-          selj[b] = bj;
-        }
-        const float lmax = sel[0];
-        float den = 0.f;
-        for (int b = 0; b < k; ++b) {
-          sel[b] = expf((sel[b] - lmax) * inv_tau);
-          den += sel[b];
-        }
-        const size_t vt = (size_t)tok * top_g + a;
-        cluster_id[vt] = c;
-        for (int b = 0; b < k; ++b) {
-          expert_idx[vt * k + b] = c * K + selj[b];
-          gate[vt * k + b] = wa * (sel[b] / den);
-        }
-      }
-    }
-  }
-};
-
-// ---------------------------------------------------------------- epilogue: t1 = V1_{e_j} x
-// acc rows are kk = j_local * r + rho over ALL experts of the cluster; for the token's
-// j-th selected expert only its r rows are kept:  t1[p][j][rho] = acc[(e_j - c*K)*r + rho].
-struct EpiT1 {
-  half_t* t1;  // [T][k][r], sorted rows
-  const int* perm;
-  const int* expert_idx;
-  int k, K, r, KRp;
-  template <class TL>
-  static constexpr int smem_bytes() { return TL::SMEM_BYTES; }
-  template <class TL>
-  __device__ void run(const TileCtx& t, float4v (&acc)[TL::NA][TL::MT]) const {
-    const int t16 = t.lane & 15, q = t.lane >> 4;
-#pragma unroll
-    for (int b = 0; b < TL::MT; ++b) {
-      const int p = t.m0 + t.wm * TL::WM + b * 16 + t16;
-      if (p >= t.m_end) continue;
-      const int tok = perm[p];
-      for (int j = 0; j < k; ++j) {
-        const int e = min(max(expert_idx[(size_t)tok * k + j] - t.c * K, 0), K - 1);
-        half_t* row = t1 + ((size_t)p * k + j) * r;
-#pragma unroll
-        for (int P = 0; P < TL::NP; ++P) {
-          const int kk = t.n0 + t.wn * TL::WN + 32 * P + 8 * q;   // 8 consecutive rank rows
-          if (kk >= KRp) continue;
-          if (r >= 8) {           // all of one expert
-            if (kk / r == e) *(half8*)(row + (kk - e * r)) = pack_half8(acc[2 * P][b], acc[2 * P + 1][b]);
-          } else {                // r == 4: two experts
-            const half8 v8 = pack_half8(acc[2 * P][b], acc[2 * P + 1][b]);
-            if (kk / 4 == e) *(half4*)row = half4{v8[0], v8[1], v8[2], v8[3]};
-            if (kk / 4 + 1 == e) *(half4*)row = half4{v8[4], v8[5], v8[6], v8[7]};
-          }
-        }
       }
     }
   }
@@ -917,13 +686,6 @@ __global__ __launch_bounds__(CB_WAVES * 64) void combine_kernel(
   }
 }
 
-// Products with at most 128 weight rows (t1 = V1 x over the cluster's rank rows): 128 x 256
-// per workgroup, four wavefronts side by side along the tokens (each 128 x 64), two
-// workgroups per CU.
-using TileMain = Tile<128, 256, 1, 4, 3, 2, false, 8, 8>;
-// The router's product (all router rows in one 128-row tile): 128-token tiles, twice the
-// workgroups of TileMain for this short, x-streaming launch (64-token tiles measured slower).
-using TileRoute = Tile<128, 128, 1, 4, 3, 2, false, 8, 8>;
 // The two big products: 256 x 256 per workgroup, eight wavefronts (2 x 4, each 128 x 64) in
 // ping-pong, one workgroup per CU: half the operand bytes per flop of the tile above.
 using TileBig = Tile<256, 256, 2, 4, 4, 1, true, 4, 8>;
@@ -1018,16 +780,6 @@ hipError_t launch_gemm1_r(const cmoe_dims& dm, const GemmArgs& g, int T, const i
 
 }  // namespace
 
-hipError_t launch_t1(const cmoe_dims& dm, const half_t* x, int x_div, int T, const int* perm, const int* offsets,
-                     const int* expert_idx, const half_t* v1cat, half_t* t1, hipStream_t st) {
-  using TL = TileMain;
-  GemmArgs g{v1cat, (long)dm.KRp * dm.d, dm.d, dm.KRp, x, dm.d, perm, dm.d, offsets, dm.G,
-             (dm.KRp + TL::BN - 1) / TL::BN, 0, 0, nullptr, 0, 0};
-  g.x_div = x_div;
-  EpiT1 epi{t1, perm, expert_idx, dm.k, dm.K, dm.r, dm.KRp};
-  return launch_gemm<TL>(g, T, epi, st);
-}
-
 // With a packed copy of the bases (per cluster W1 as [d/32][d_ff][32], then all of W2 as
 // [d_ff/32][d][32]) the weight operand is read from it: row stride 32, block stride rows * 32.
 static void use_packed_base(GemmArgs& g, const cmoe_dims& dm, const cmoe_weights& w, bool second) {
@@ -1044,7 +796,7 @@ hipError_t launch_gemm1(const cmoe_dims& dm, const cmoe_weights& w, const half_t
                         const half_t* v2p, const half_t* t1, half_t* a, float* spart, hipStream_t st) {
   using TL = TileUp;
   GemmArgs g{(const half_t*)w.w1_base, (long)dm.d_ff * dm.d, dm.d, dm.d_ff, x, dm.d, perm, dm.d, offsets, dm.G,
-             (dm.d_ff + TL::BN - 1) / TL::BN, 0, 0, nullptr, 0, 0};
+             (dm.d_ff + TL::BN - 1) / TL::BN, 0, 0};
   g.x_div = x_div;
   use_packed_base(g, dm, w, false);
   switch (dm.r) {
@@ -1072,7 +824,7 @@ hipError_t launch_gemm2(const cmoe_dims& dm, const cmoe_weights& w, const half_t
   using TL = TileBig;
   // a is [d_ff / 32][T][32]
   GemmArgs g{(const half_t*)w.w2_base, (long)dm.d * dm.d_ff, dm.d_ff, dm.d, a, 32, nullptr, dm.d_ff, offsets,
-             dm.G, (dm.d + TL::BN - 1) / TL::BN, 0, 0, nullptr, 0, 0};
+             dm.G, (dm.d + TL::BN - 1) / TL::BN, 0, 0};
   g.kstep_x = (long)T * 32;
   use_packed_base(g, dm, w, true);
   EpiStore epi{y_base_sorted, rowmap, dm.d, dm.d};
@@ -1092,38 +844,6 @@ hipError_t launch_combine(const cmoe_dims& dm, const half_t* u2t, const half_t* 
   return hipGetLastError();
 }
 
-// Matrix-core router for large T (G + G*K logits per token fit one 128-row tile).
-hipError_t launch_route_mfma(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int* cluster_id,
-                             int* expert_idx, float* gate, hipStream_t st) {
-  using TL = TileRoute;
-  const int rows = dm.G + dm.G * dm.K;
-  GemmArgs g{(const half_t*)w.router_cluster, 0, dm.d, rows, x, dm.d, nullptr, dm.d, nullptr, 1, 1, 0, 0,
-             (const half_t*)w.router_expert, dm.G, T};
-  EpiRoute epi{w.cluster_bias, cluster_id, expert_idx, gate, dm.G, dm.K, dm.k};
-  GemmArgs ga = g;
-  ga.m_slots = (T + TL::BM - 1) / TL::BM;
-  ga.spx = 0;
-  dim3 grid((unsigned)ga.m_slots), block(TL::NT);
-  hipLaunchKernelGGL((gemm_nt_kernel<TL, EpiRoute>), grid, block, 0, st, ga, epi);
-  return hipGetLastError();
-}
-
-// The same product with the routing variants decided in the epilogue.
-hipError_t launch_route_multi_mfma(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int top_g,
-                                   float temperature, int scale, int* cluster_id, int* expert_idx, float* gate,
-                                   hipStream_t st) {
-  using TL = TileRoute;
-  const int rows = dm.G + dm.G * dm.K;
-  GemmArgs ga{(const half_t*)w.router_cluster, 0, dm.d, rows, x, dm.d, nullptr, dm.d, nullptr, 1, 1, 0, 0,
-              (const half_t*)w.router_expert, dm.G, T};
-  EpiRouteMulti epi{w.cluster_bias, cluster_id, expert_idx, gate, dm.G, dm.K, dm.k, top_g, 1.f / temperature, scale};
-  ga.m_slots = (T + TL::BM - 1) / TL::BM;
-  ga.spx = 0;
-  dim3 grid((unsigned)ga.m_slots), block(TL::NT);
-  hipLaunchKernelGGL((gemm_nt_kernel<TL, EpiRouteMulti>), grid, block, 0, st, ga, epi);
-  return hipGetLastError();
-}
-
 // Down-projection with the residual of the second matrix and the return to token order
 // fused into its epilogue (K*r <= 128).  rperm: token of each row of A.
 hipError_t launch_gemm2_combine(const cmoe_dims& dm, const cmoe_weights& w, const half_t* a, int T,
@@ -1131,7 +851,7 @@ hipError_t launch_gemm2_combine(const cmoe_dims& dm, const cmoe_weights& w, cons
                                 const int* expert_idx, const float* gate, half_t* y, hipStream_t st) {
   using TL = TileBig;
   GemmArgs g{(const half_t*)w.w2_base, (long)dm.d * dm.d_ff, dm.d_ff, dm.d, a, 32, nullptr, dm.d_ff, offsets,
-             dm.G, (dm.d + TL::BN - 1) / TL::BN, 0, 0, nullptr, 0, 0};
+             dm.G, (dm.d + TL::BN - 1) / TL::BN, 0, 0};
   g.kstep_x = (long)T * 32;
   use_packed_base(g, dm, w, true);
   EpiDownCombine epi{u2t, s_down, rperm, expert_idx, gate, y, dm.k, dm.K, dm.r, dm.KRp, dm.d};
@@ -1147,8 +867,7 @@ hipError_t launch_gemm_plain(const half_t* W, long w_gstride, int ldw, int N, co
                              const int* krange, const int* rowmap, void* out, int ldo, bool out_f32,
                              hipStream_t st, long kstep_w, long kstep_x) {
   using TL = TileBig;
-  GemmArgs g{W, w_gstride, ldw, N, X, ldx, gather, Kc, offsets, n_groups, (N + TL::BN - 1) / TL::BN, 0, 0, nullptr,
-             0, 0};
+  GemmArgs g{W, w_gstride, ldw, N, X, ldx, gather, Kc, offsets, n_groups, (N + TL::BN - 1) / TL::BN, 0, 0};
   g.x_div = x_div;
   g.krange = krange;
   g.kstep_w = kstep_w;

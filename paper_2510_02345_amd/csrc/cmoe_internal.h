@@ -111,7 +111,7 @@ cmoe_ws_layout cmoe_layout(const cmoe_dims& dm, int T);
 // Kernel launchers (each returns the hipError_t of its launch).
 hipError_t launch_route(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int* cluster_id,
                         int* expert_idx, float* gate, hipStream_t st);
-hipError_t launch_route_mfma(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int* cluster_id,
+hipError_t launch_route_rows(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int* cluster_id,
                              int* expert_idx, float* gate, hipStream_t st);
 hipError_t launch_permute(const cmoe_dims& dm, const int* cluster_id, int T, int* perm, int* inv_perm, int* offsets,
                           int* counts, hipStream_t st);
@@ -139,7 +139,7 @@ hipError_t launch_skinny_hb(const cmoe_dims& dm, const cmoe_weights& w, const ha
 hipError_t launch_route_multi(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int top_g,
                               float temperature, int scale, int* cluster_id, int* expert_idx, float* gate,
                               hipStream_t st);
-hipError_t launch_route_multi_mfma(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int top_g,
+hipError_t launch_route_multi_rows(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int top_g,
                                    float temperature, int scale, int* cluster_id, int* expert_idx, float* gate,
                                    hipStream_t st);
 hipError_t launch_sum_groups(const half_t* yrep, int T, int top_g, int d, half_t* y, hipStream_t st);

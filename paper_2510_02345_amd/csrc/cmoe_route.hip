@@ -672,7 +672,7 @@ hipError_t launch_route(const cmoe_dims& dm, const cmoe_weights& w, const half_t
   const half_t* re = (const half_t*)w.router_expert;
   int chunks_per_lane = (dm.d / 8 + 63) / 64;
   if (T > SKINNY_T && dm.G + dm.G * dm.K <= 128)
-    return launch_route_mfma(dm, w, x, T, cluster_id, expert_idx, gate, st);
+    return launch_route_rows(dm, w, x, T, cluster_id, expert_idx, gate, st);
   if (T <= SKINNY_T) {
     dim3 g1(T), b1(RS_WAVES * 64);
     if (chunks_per_lane <= 2)
@@ -758,10 +758,10 @@ hipError_t launch_permute_static(const cmoe_dims& dm, const int* cluster_id, int
 hipError_t launch_route_multi(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int top_g,
                               float temperature, int scale, int* cluster_id, int* expert_idx, float* gate,
                               hipStream_t st) {
-  // many tokens and all router rows in one 128-row tile: matrix-core product, decision in
-  // its epilogue (as for the single-cluster router)
+  // many tokens and few router rows: matrix-core product, decision in its epilogue (as for the
+  // single-cluster router)
   if (T > SKINNY_T && dm.G + dm.G * dm.K <= 128)
-    return launch_route_multi_mfma(dm, w, x, T, top_g, temperature, scale, cluster_id, expert_idx, gate, st);
+    return launch_route_multi_rows(dm, w, x, T, top_g, temperature, scale, cluster_id, expert_idx, gate, st);
   dim3 grid((T + ROUTE_WAVES - 1) / ROUTE_WAVES), block(ROUTE_WAVES * 64);
   const half_t* rc = (const half_t*)w.router_cluster;
   const half_t* re = (const half_t*)w.router_expert;

@@ -1,0 +1,440 @@
+// Products of every token with few weight rows, above SKINNY_T tokens: the router (Sec. 3.3, all
+// G prototypes and G*K expert vectors, with the two-stage decision) and t1 = V1 x (Sec. 3.2,
+// the rank rows of the experts a token selected).  Both read x once and are short.
+#include <type_traits>
+
+#include "cmoe_device.h"
+
+namespace {
+
+// ---------------------------------------------------------------- few tokens
+// With less than a workgroup per CU a launch takes as long as its chain of loads: a workgroup takes
+// only 32 tokens, its four wavefronts split the contraction, and the matrix-core fragments are
+// loaded straight from memory into registers (no LDS staging, no barrier in the loop).  A
+// 64-element step of a row is one whole 128-byte line: lane (t, q) takes its elements 8 q .. 8 q + 7
+// and 32 + 8 q .. 32 + 8 q + 7, two instructions that each read 64 contiguous bytes of 16 rows.
+constexpr int RW_M = 32, RW_MT = RW_M / 16;   // tokens of a workgroup
+constexpr int RW_WAVES = 4, RW_THREADS = 64 * RW_WAVES;
+
+// acc[a][b] += rows wr[a] (16 per block) x tokens xr[b] over the 64-element steps [it0, it1); the
+// pointers are those of the lane's row and include its 8 q.  The tokens come from memory and
+// are requested RW_AHEAD steps early, the weight rows (shared by every workgroup, so in L2) one.
+constexpr int RW_AHEAD = 4;
+template <int NA>
+__device__ __forceinline__ void rows_product(const half_t* const (&wr)[NA], const half_t* const (&xr)[RW_MT], int it0,
+                                             int it1, float4v (&acc)[NA][RW_MT]) {
+  half8 fx[RW_AHEAD][RW_MT][2], fw[2][NA][2];
+  auto load_x = [&](half8 (&f)[RW_MT][2], int it) {
+#pragma unroll
+    for (int b = 0; b < RW_MT; ++b) {
+      f[b][0] = *(const half8*)(xr[b] + it * 64);
+      f[b][1] = *(const half8*)(xr[b] + it * 64 + 32);
+    }
+  };
+  auto load_w = [&](half8 (&f)[NA][2], int it) {
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+      f[a][0] = *(const half8*)(wr[a] + it * 64);
+      f[a][1] = *(const half8*)(wr[a] + it * 64 + 32);
+    }
+  };
+  if (it0 >= it1) return;
+#pragma unroll
+  for (int u = 0; u < RW_AHEAD; ++u)
+    if (it0 + u < it1) load_x(fx[u], it0 + u);
+  load_w(fw[0], it0);
+  for (int it = it0; it < it1; it += RW_AHEAD) {
+#pragma unroll
+    for (int u = 0; u < RW_AHEAD; ++u) {
+      if (it + u >= it1) break;
+      if (it + u + 1 < it1) load_w(fw[(u + 1) & 1], it + u + 1);
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+          for (int b = 0; b < RW_MT; ++b) acc[a][b] = mfma32(fw[u & 1][a][s], fx[u][b][s], acc[a][b]);
+      if (it + u + RW_AHEAD < it1) load_x(fx[u], it + u + RW_AHEAD);
+    }
+  }
+}
+
+// Sum of the four wavefronts' accumulators, added in wavefront order: block i = a RW_MT + b is summed
+// by wavefront i % 4, which hands it to out(a, b, sum).  red: NA * RW_MT * 4 KiB of LDS.
+template <int NA, class OutF>
+__device__ __forceinline__ void rows_reduce(float4v* red, int wave, int lane, const float4v (&acc)[NA][RW_MT], OutF out) {
+  constexpr int NB = NA * RW_MT;
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int b = 0; b < RW_MT; ++b) red[(wave * NB + a * RW_MT + b) * 64 + lane] = acc[a][b];
+  __syncthreads();
+#pragma unroll
+  for (int i0 = 0; i0 < NB; i0 += RW_WAVES) {
+    const int i = i0 + wave;
+    if (i >= NB) break;
+    float4v s = red[i * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < RW_WAVES; ++w) s += red[(w * NB + i) * 64 + lane];
+    out(i / RW_MT, i % RW_MT, s);
+  }
+}
+
+// ---------------------------------------------------------------- many tokens
+// The same product for launches that are bound by their loads: 64 tokens per workgroup (a weight
+// row is loaded half as often), a wavefront takes 16 of them over the whole contraction, and
+// both operands go global -> LDS by direct loads, two or three 64-element steps ahead.
+// A tile row is one 128-byte line, its 16-byte chunks at position chunk ^ ((row >> 1) & 7), which
+// serves the fragment reads without bank conflicts.
+constexpr int RL_M = 64;
+template <int NA>
+struct RowsLds {
+  static constexpr int NS = NA <= 5 ? 4 : 3;   // stages: two workgroups per CU
+  static constexpr int ROWS = NA * 16 + RL_M, STAGE = ROWS * 128, SMEM = NS * STAGE;
+  static constexpr int PER_WAVE = (ROWS / 8 + RW_WAVES - 1) / RW_WAVES;   // 1-KiB loads (8 rows) per wavefront and step
+};
+__device__ __forceinline__ void dma16(const void* g, unsigned lds_byte) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_byte) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// acc[a] = rows of block a x the wavefront's 16 tokens.  row_of(i): source row i of the tile (NA * 16
+// weight rows, then the 64 tokens).  Ends with every load consumed; the caller's next use of
+// smem needs a barrier first.
+template <int NA, class RowF>
+__device__ __forceinline__ void rows_product_lds(char* smem, int steps, int wave, int lane, RowF row_of,
+                                                 float4v (&acc)[NA]) {
+  using RL = RowsLds<NA>;
+  const unsigned base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
+  const int t16 = lane & 15, q = lane >> 4;
+  const half_t* src[RL::PER_WAVE];
+  unsigned dst[RL::PER_WAVE];
+#pragma unroll
+  for (int i = 0; i < RL::PER_WAVE; ++i) {
+    const int g = min(i * RW_WAVES + wave, RL::ROWS / 8 - 1);   // past the last group: that group once more
+    const int row = g * 8 + (lane >> 3);
+    src[i] = row_of(row) + (((lane & 7) ^ ((row >> 1) & 7)) << 3);
+    dst[i] = base + g * 1024;
+  }
+  auto issue = [&](int it, int stage) {
+#pragma unroll
+    for (int i = 0; i < RL::PER_WAVE; ++i) dma16(src[i] + (size_t)it * 64, dst[i] + stage * RL::STAGE);
+  };
+#pragma unroll
+  for (int a = 0; a < NA; ++a) acc[a] = float4v{0.f, 0.f, 0.f, 0.f};
+  const int sw = (t16 >> 1) & 7;   // tile rows of a fragment start at multiples of 16
+#pragma unroll
+  for (int s = 0; s < RL::NS - 1; ++s)
+    if (s < steps) issue(s, s);
+  int stage = 0, nstage = RL::NS - 1;
+  for (int it = 0; it < steps; ++it) {
+    // step it has landed (own loads), then everyone's; the stage refilled below was read in
+    // step it - 1, which every wavefront has left
+    if (it + RL::NS - 2 < steps) wait_vm<(RL::NS - 2) * RL::PER_WAVE>(); else wait_vm<0>();
+    __builtin_amdgcn_s_barrier();
+    if (it + RL::NS - 1 < steps) issue(it + RL::NS - 1, nstage);
+    const char* sb = smem + stage * RL::STAGE + t16 * 128;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int ch = ((4 * s + q) ^ sw) << 4;
+      const half8 fb = *(const half8*)(sb + (NA * 16 + wave * 16) * 128 + ch);
+#pragma unroll
+      for (int a = 0; a < NA; ++a) acc[a] = mfma32(*(const half8*)(sb + a * 16 * 128 + ch), fb, acc[a]);
+    }
+    stage = stage + 1 == RL::NS ? 0 : stage + 1;
+    nstage = nstage + 1 == RL::NS ? 0 : nstage + 1;
+  }
+}
+
+// ---------------------------------------------------------------- router
+struct RouteRowsArgs {
+  const half_t *x, *rc, *re;
+  const float* bias;
+  int T, d, G, K, k;
+  int top_g, scale;      // MULTI
+  float inv_tau;         // MULTI
+  int *cluster_id, *expert_idx;
+  float* gate;
+};
+
+// A candidate of a selection: larger key first, lowest index among equals.  A NaN logit ranks
+// as -inf, so that a selection always returns distinct, valid slots.
+__device__ __forceinline__ float rank_key(float v) { return v == v ? v : -INFINITY; }
+// The best candidate of a group of 8 lanes.
+__device__ __forceinline__ int best_of_8(float key, int idx) {
+#pragma unroll
+  for (int off = 1; off < 8; off <<= 1) {
+    const float k2 = __shfl_xor(key, off, 64);
+    const int i2 = __shfl_xor(idx, off, 64);
+    if (k2 > key || (k2 == key && i2 < idx)) key = k2, idx = i2;
+  }
+  return idx;
+}
+// Best of val(0) .. val(n - 1) whose bit in `taken` is clear, by the 8 lanes `sub` of a group.
+template <class ValF>
+__device__ __forceinline__ int pick(int n, unsigned long long taken, int sub, ValF val) {
+  float key = -INFINITY;
+  int idx = 1 << 20;
+  for (int i = sub; i < n; i += 8) {
+    const float v = rank_key(val(i));
+    if (!((taken >> i) & 1ull) && (idx == 1 << 20 || v > key)) key = v, idx = i;
+  }
+  return best_of_8(key, idx);
+}
+
+// The k largest logits among the K experts of cluster c, softmax over them (times wa).
+__device__ __forceinline__ void pick_experts(const RouteRowsArgs& a, const float* row, int c, int sub, float inv_tau,
+                                             float wa, size_t vt) {
+  const float* l = row + a.G + c * a.K;
+  unsigned long long taken = 0ull;
+  float lmax = 0.f, den = 0.f, mine = 0.f;
+  int mine_j = 0;
+  for (int b = 0; b < a.k; ++b) {
+    const int j = pick(a.K, taken, sub, [&](int i) { return l[i]; });
+    taken |= 1ull << j;
+    const float v = l[j];
+    if (b == 0) lmax = v;
+    const float e = expf((v - lmax) * inv_tau);
+    den += e;
+    if (b == sub) mine = e, mine_j = j;   // k <= 8: lane b of the group writes expert b
+  }
+  if (sub < a.k) {
+    a.expert_idx[vt * a.k + sub] = c * a.K + mine_j;
+    a.gate[vt * a.k + sub] = wa * (mine / den);
+  }
+}
+
+// A token's decision from its logits `row` (prototypes, then expert vectors), by the 8 lanes `sub` of
+// a group: the cluster with the largest z_g (+ bias), then the k largest l_i among that
+// cluster's K experts only, lowest index on ties, gates = softmax over the selected logits.
+// MULTI: the top_g clusters by descending logit, each with its own top-k; both softmaxes take
+// logits * inv_tau; gate = w_a * softmax, w_a = p_g (scale) or p_g renormalised over the selected
+// clusters, per virtual token tok * top_g + a.
+template <bool MULTI>
+__device__ __forceinline__ void route_decide(const RouteRowsArgs& a, const float* row, int tok, int lane) {
+  const int sub = lane & 7;
+  auto z = [&](int g) { return row[g] + (a.bias ? a.bias[g] : 0.f); };
+  if (!MULTI) {
+    const int c = pick(a.G, 0ull, sub, z);
+    if (sub == 0) a.cluster_id[tok] = c;
+    pick_experts(a, row, c, sub, 1.f, 1.f, tok);
+    return;
+  }
+  float zmax = -INFINITY, zden = 0.f;
+  for (int g = sub; g < a.G; g += 8) zmax = fmaxf(zmax, z(g));
+#pragma unroll
+  for (int off = 1; off < 8; off <<= 1) zmax = fmaxf(zmax, __shfl_xor(zmax, off, 64));
+  for (int g = sub; g < a.G; g += 8) zden += expf((z(g) - zmax) * a.inv_tau);
+#pragma unroll
+  for (int off = 1; off < 8; off <<= 1) zden += __shfl_xor(zden, off, 64);
+  unsigned long long taken = 0ull;
+  float psum = 0.f, my_p = 0.f;
+  int my_c = 0;
+  for (int i = 0; i < a.top_g; ++i) {
+    const int c = pick(a.G, taken, sub, z);
+    taken |= 1ull << c;
+    const float p = expf((z(c) - zmax) * a.inv_tau) / zden;
+    psum += p;
+    if (i == sub) my_c = c, my_p = p;   // top_g <= 8
+  }
+  for (int i = 0; i < a.top_g; ++i) {
+    const int c = __shfl(my_c, (lane & ~7) | i, 64);
+    const float p = __shfl(my_p, (lane & ~7) | i, 64);
+    const size_t vt = (size_t)tok * a.top_g + i;
+    if (sub == 0) a.cluster_id[vt] = c;
+    pick_experts(a, row, c, sub, a.inv_tau, a.scale ? p : p / psum, vt);
+  }
+}
+__device__ __forceinline__ const half_t* router_row(const RouteRowsArgs& a, int n) {
+  n = min(n, a.G + a.G * a.K - 1);
+  return n < a.G ? a.rc + (size_t)n * a.d : a.re + (size_t)(n - a.G) * a.d;
+}
+
+// One workgroup per 32 tokens; NA blocks of 16 router rows.  Every token's logits end up in LDS, and
+// 8 lanes take the token's decision.
+template <int NA, bool MULTI>
+__global__ __launch_bounds__(RW_THREADS) void route_rows_kernel(RouteRowsArgs a) {
+  __shared__ float4v red[RW_WAVES * NA * RW_MT * 64];
+  constexpr int LD = NA * 16 + 4;
+  __shared__ float lg[RW_M][LD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t16 = lane & 15, q = lane >> 4;
+  const int m0 = blockIdx.x * RW_M;
+  const half_t *wr[NA], *xr[RW_MT];
+#pragma unroll
+  for (int i = 0; i < NA; ++i) wr[i] = router_row(a, i * 16 + t16) + 8 * q;
+#pragma unroll
+  for (int b = 0; b < RW_MT; ++b) xr[b] = a.x + (size_t)min(m0 + b * 16 + t16, a.T - 1) * a.d + 8 * q;
+  float4v acc[NA][RW_MT];
+#pragma unroll
+  for (int i = 0; i < NA; ++i)
+#pragma unroll
+    for (int b = 0; b < RW_MT; ++b) acc[i][b] = float4v{0.f, 0.f, 0.f, 0.f};
+  const int steps = a.d / 64;
+  rows_product<NA>(wr, xr, wave * steps / RW_WAVES, (wave + 1) * steps / RW_WAVES, acc);
+  rows_reduce<NA>(red, wave, lane, acc,
+                  [&](int i, int b, const float4v& s) { *(float4v*)&lg[b * 16 + t16][i * 16 + 4 * q] = s; });
+  __syncthreads();
+  const int m = tid >> 3, tok = m0 + m;
+  if (tok < a.T) route_decide<MULTI>(a, lg[m], tok, lane);
+}
+
+// The same for many tokens: 64 per workgroup, a wavefront decides for its own 16.
+template <int NA, bool MULTI>
+__global__ __launch_bounds__(RW_THREADS, 2) void route_rows_lds_kernel(RouteRowsArgs a) {
+  constexpr int LD = NA * 16 + 4;
+  static_assert(RL_M * LD * 4 <= RowsLds<NA>::SMEM, "the logits take the stages' place");
+  __shared__ __attribute__((aligned(1024))) char smem[RowsLds<NA>::SMEM];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t16 = lane & 15, q = lane >> 4, m0 = blockIdx.x * RL_M;
+  float4v acc[NA];
+  rows_product_lds<NA>(smem, a.d / 64, wave, lane,
+                       [&](int row) {
+                         return row < NA * 16 ? router_row(a, row) : a.x + (size_t)min(m0 + row - NA * 16, a.T - 1) * a.d;
+                       },
+                       acc);
+  __syncthreads();
+  float* lg = (float*)smem + wave * 16 * LD;
+#pragma unroll
+  for (int i = 0; i < NA; ++i) *(float4v*)&lg[t16 * LD + i * 16 + 4 * q] = acc[i];
+  __syncthreads();
+  for (int m = lane >> 3; m < 16; m += 8) {
+    const int tok = m0 + wave * 16 + m;
+    if (tok < a.T) route_decide<MULTI>(a, lg + m * LD, tok, lane);
+  }
+}
+
+// Up to this many tokens the 32-token workgroups with their split contraction are faster (fewer
+// than one workgroup per CU: what counts is the chain of steps): 5.6 against 7.7 us at 4096
+// tokens of width 768 and 10 router rows, 7.9 against 9.2 us at 8000 of 1024 and 20 rows.  Above it
+// the loads count: 12 against 12 us at 16384 of 1024, 65 against 36 us at 32768 of 2048 and 72
+// rows (one 128-row matrix-core tile against 128 tokens took 41).
+constexpr int ROUTE_SPLIT_T = 8192;
+template <int NA, bool MULTI>
+hipError_t go_route_na(const RouteRowsArgs& a, hipStream_t st) {
+  if (a.T > ROUTE_SPLIT_T)
+    hipLaunchKernelGGL((route_rows_lds_kernel<NA, MULTI>), dim3((a.T + RL_M - 1) / RL_M), dim3(RW_THREADS), 0, st, a);
+  else
+    hipLaunchKernelGGL((route_rows_kernel<NA, MULTI>), dim3((a.T + RW_M - 1) / RW_M), dim3(RW_THREADS), 0, st, a);
+  return hipGetLastError();
+}
+template <bool MULTI>
+hipError_t go_route(const RouteRowsArgs& a, hipStream_t st) {
+  const int rows = a.G + a.G * a.K;
+  if (rows <= 16) return go_route_na<1, MULTI>(a, st);
+  if (rows <= 32) return go_route_na<2, MULTI>(a, st);
+  if (rows <= 48) return go_route_na<3, MULTI>(a, st);
+  if (rows <= 80) return go_route_na<5, MULTI>(a, st);
+  return go_route_na<8, MULTI>(a, st);
+}
+
+// ---------------------------------------------------------------- t1 = V1_{e_j} x
+// t1[p][j][rho] for the 64 sorted rows p of a tile (one cluster).  Only the blocks of 16 rank rows
+// that at least one of the tile's tokens selected are multiplied, up to T1_NA at a time (rows
+// sorted by expert pair need two to four of them where a cluster has many tokens), and each is
+// kept only for the tokens whose expert it belongs to.  A matrix-core tile of all 128 rank rows
+// took 21 us at 4096 tokens of width 768, 28 us at 16384 of 1024 and 51 us at 32768 of 2048;
+// this kernel 7, 12 and 37 us.
+constexpr int T1_NA = 8;
+// 16-row blocks that hold the r rank rows from e0 on (K*r <= 512)
+__device__ __forceinline__ unsigned block_mask(int e0, int r) {
+  return (0xffffffffu >> (31 - ((e0 + r - 1) >> 4))) & (0xffffffffu << (e0 >> 4));
+}
+__device__ __forceinline__ unsigned wave_or(unsigned v) {
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) v |= (unsigned)__shfl_xor((int)v, off, 64);
+  return __builtin_amdgcn_readfirstlane(v);
+}
+// Takes up to T1_NA blocks out of `need`; entries past their number repeat the first.
+__device__ __forceinline__ int take_blocks(unsigned& need, int (&blk)[T1_NA]) {
+  int n = 0;
+#pragma unroll
+  for (int i = 0; i < T1_NA; ++i) {
+    blk[i] = need ? __builtin_ctz(need) : blk[0];
+    if (need) ++n, need &= need - 1u;
+  }
+  return n;
+}
+// rank rows rr .. rr + 3 of row p, kept by the experts they belong to
+__device__ __forceinline__ void t1_store(half_t* t1, int p, int rr, const int* es, int k, int r, const float4v& s) {
+  for (int j = 0; j < k; ++j) {
+    const int e0 = es[j];
+    if (rr >= e0 && rr < e0 + r)
+      *(half4*)(t1 + ((size_t)p * k + j) * r + (rr - e0)) = half4{(half_t)s[0], (half_t)s[1], (half_t)s[2], (half_t)s[3]};
+  }
+}
+__global__ __launch_bounds__(RW_THREADS, 2) void t1_rows_kernel(const half_t* __restrict__ x, int x_div,
+                                                                    const int* __restrict__ perm,
+                                                                    const int* __restrict__ offsets,
+                                                                    const int* __restrict__ expert_idx,
+                                                                    const half_t* __restrict__ v1cat, int d, int G, int K,
+                                                                    int k, int r, int KRp, half_t* __restrict__ t1) {
+  __shared__ __attribute__((aligned(1024))) char smem[RowsLds<T1_NA>::SMEM];
+  __shared__ int es[RL_M][8];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t16 = lane & 15, q = lane >> 4;
+  int c, m0, m_end;
+  if (!find_tile(offsets, G, RL_M, blockIdx.x, c, m0, m_end)) return;
+  const int tok = perm[min(m0 + lane, m_end - 1)];
+  unsigned need = 0u;
+  for (int j = 0; j < k; ++j) {
+    const int e0 = min(max(expert_idx[(size_t)tok * k + j] - c * K, 0), K - 1) * r;
+    if (wave == 0) es[lane][j] = e0;
+    need |= block_mask(e0, r);
+  }
+  need = wave_or(need);
+  const half_t* vc = v1cat + (size_t)c * KRp * d;
+  while (need != 0u) {
+    int blk[T1_NA];
+    const int n = take_blocks(need, blk);
+    unsigned long long order = 0ull;   // the blocks' numbers, eight bits each
+#pragma unroll
+    for (int i = 0; i < T1_NA; ++i) order |= (unsigned long long)blk[i] << (8 * i);
+    auto pass = [&](auto na) {
+      constexpr int NA = decltype(na)::value;
+      float4v acc[NA];
+      rows_product_lds<NA>(smem, d / 64, wave, lane,
+                           [&](int row) {
+                             const int src = __shfl(tok, (row - NA * 16) & 63, 64) / x_div;
+                             return row < NA * 16 ? vc + ((size_t)((order >> (8 * (row >> 4))) & 255) * 16 + (row & 15)) * d
+                                                  : x + (size_t)src * d;
+                           },
+                           acc);
+      const int m = wave * 16 + t16, p = m0 + m;
+#pragma unroll
+      for (int i = 0; i < NA; ++i)
+        if (i < n && p < m_end) t1_store(t1, p, blk[i] * 16 + 4 * q, es[m], k, r, acc[i]);
+    };
+    if (n <= 2) pass(std::integral_constant<int, 2>{});
+    else if (n <= 4) pass(std::integral_constant<int, 4>{});
+    else pass(std::integral_constant<int, T1_NA>{});
+    __syncthreads();   // the stages have been read
+  }
+}
+
+}  // namespace
+
+// Router for more than SKINNY_T tokens and at most 128 router rows (G + G*K).
+hipError_t launch_route_rows(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int* cluster_id,
+                             int* expert_idx, float* gate, hipStream_t st) {
+  RouteRowsArgs a{x, (const half_t*)w.router_cluster, (const half_t*)w.router_expert, w.cluster_bias, T, dm.d, dm.G, dm.K,
+                  dm.k, 1, 0, 1.f, cluster_id, expert_idx, gate};
+  return go_route<false>(a, st);
+}
+
+hipError_t launch_route_multi_rows(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int top_g,
+                                   float temperature, int scale, int* cluster_id, int* expert_idx, float* gate,
+                                   hipStream_t st) {
+  RouteRowsArgs a{x, (const half_t*)w.router_cluster, (const half_t*)w.router_expert, w.cluster_bias, T, dm.d, dm.G, dm.K,
+                  dm.k, top_g, scale, 1.f / temperature, cluster_id, expert_idx, gate};
+  return go_route<true>(a, st);
+}
+
+hipError_t launch_t1(const cmoe_dims& dm, const half_t* x, int x_div, int T, const int* perm, const int* offsets,
+                     const int* expert_idx, const half_t* v1cat, half_t* t1, hipStream_t st) {
+  hipLaunchKernelGGL(t1_rows_kernel, dim3((T + RL_M - 1) / RL_M + dm.G), dim3(RW_THREADS), 0, st, x, x_div > 1 ? x_div : 1,
+                     perm, offsets, expert_idx, v1cat, dm.d, dm.G, dm.K, dm.k, dm.r, dm.KRp, t1);
+  return hipGetLastError();
+}

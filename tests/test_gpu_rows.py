@@ -1,0 +1,52 @@
+"""The router's matrix-core kernels (few and many tokens, every number of 16-row blocks, ragged last
+workgroup) and the t1 kernel's passes over the rank rows, against the oracle."""
+import numpy as np
+import pytest
+
+import cmoe_inputs as ci
+from oracle import cmoe_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T", [257, 8192, 8193, 8250])
+@pytest.mark.parametrize("G,K,k,d", [(2, 4, 1, 64), (4, 7, 2, 192), (5, 8, 3, 320), (8, 8, 2, 128), (8, 15, 8, 64)])
+def test_router_rows(T, G, K, k, d):
+    import torch
+
+    import paper_2510_02345_amd as cm
+    cfg = ci.small_config("rows", T=T, d=d, d_ff=64, G=G, K=K, r=4, k=k, q=8, seed=T + G)
+    print(f"case {cfg}", flush=True)
+    w = ci.generate(cfg)
+    cid, eidx, gate, _, _ = orc.route(w["x"], w["router_cluster"], w["router_expert"], K, k, w["cluster_bias"])
+    layer = cm.Layer(d, cfg.d_ff, G, K, cfg.r, k, cfg.q, w, T)
+    c, e, g = layer.route(torch.from_numpy(w["x"]).to("cuda:0"))
+    torch.cuda.synchronize()
+    assert np.array_equal(c.cpu().numpy(), cid) and np.array_equal(e.cpu().numpy(), eidx)
+    assert np.allclose(g.cpu().numpy(), gate, rtol=1e-5, atol=1e-6)
+    # the variant of one cluster and temperature 1 is the same decision
+    c2, e2, g2 = layer.route_multi(torch.from_numpy(w["x"]).to("cuda:0"))
+    torch.cuda.synchronize()
+    assert np.array_equal(c2.cpu().numpy()[:, 0], cid) and np.array_equal(e2.cpu().numpy()[:, 0], eidx)
+    assert np.allclose(g2.cpu().numpy()[:, 0], gate, rtol=1e-5, atol=1e-6)
+    layer.close()
+
+
+# rank rows per cluster: 2, 4, 8 and more than 8 blocks of 16, one or two passes; tiles of 64 rows
+# that hold one to 64 tokens
+@pytest.mark.parametrize("T,K,r,k", [(257, 2, 16, 2), (600, 8, 8, 1), (900, 8, 16, 4), (1300, 16, 32, 3), (321, 32, 16, 8)])
+def test_rank_rows_of_selected_experts(T, K, r, k):
+    import torch
+
+    import paper_2510_02345_amd as cm
+    cfg = ci.small_config("t1", T=T, d=128, d_ff=64, G=3, K=K, r=r, k=k, q=8, factor_std=0.2, seed=T)
+    print(f"case {cfg}", flush=True)
+    w = ci.generate(cfg)
+    ref = orc.forward_naive(w, w["x"], K, k, cfg.q)
+    layer = cm.Layer(cfg.d, cfg.d_ff, cfg.G, K, r, k, cfg.q, w, T)
+    out = layer.forward(torch.from_numpy(w["x"]).to("cuda:0"))
+    torch.cuda.synchronize()
+    # factors ten times the usual size: the rank part is a large share of y (the layer's bars)
+    m = orc.error_metrics(out["y"].cpu().numpy(), ref["y"])
+    assert m["max_over_rms"] <= 1e-2 and m["mean_rel"] <= 2e-3, m
+    layer.close()
