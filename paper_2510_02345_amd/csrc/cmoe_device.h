@@ -85,21 +85,30 @@ __device__ __forceinline__ int wave_inclusive_sum(int v) {
   return v;
 }
 
-// Row tiles of bm rows that never straddle a group, dealt group after group: the group of tile
-// `slot` and its rows [m0, m_end) up to the group's end (m0 the tile's first row).  false: past the
-// last tile.  offsets [n_groups + 1], n_groups <= 64: lane g looks at group g, so the search costs
+// Row tiles of bm rows that never straddle a group, dealt group after group.  offsets
+// [n_groups + 1], n_groups <= 64: lane g looks at group g, so that the search for a tile costs
 // one round trip to memory instead of one per group.
+struct RowTiles {
+  int lo, hi, tiles, incl;   // per lane: rows and tiles of group `lane`, tiles up to and including it
+  __device__ __forceinline__ RowTiles(const int* offsets, int n_groups, int bm) : lo(0), hi(0) {
+    const int lane = threadIdx.x & 63;
+    if (lane < n_groups) lo = offsets[lane], hi = offsets[lane + 1];
+    tiles = (hi - lo + bm - 1) / bm;
+    incl = wave_inclusive_sum(tiles);
+  }
+  __device__ __forceinline__ int total() const { return __builtin_amdgcn_readlane(incl, 63); }
+  // group c of tile `slot`, its first row m0 and the end m_end of the group's rows; false: past the last tile
+  __device__ __forceinline__ bool find(int slot, int bm, int& c, int& m0, int& m_end) const {
+    const unsigned long long past = __ballot(incl > slot);
+    if (past == 0ull) return false;
+    c = __builtin_ctzll(past);
+    m0 = __builtin_amdgcn_readlane(lo, c) + (slot - __builtin_amdgcn_readlane(incl - tiles, c)) * bm;
+    m_end = __builtin_amdgcn_readlane(hi, c);
+    return true;
+  }
+};
 __device__ __forceinline__ bool find_tile(const int* offsets, int n_groups, int bm, int slot, int& c, int& m0, int& m_end) {
-  const int lane = threadIdx.x & 63;
-  int lo = 0, hi = 0;
-  if (lane < n_groups) lo = offsets[lane], hi = offsets[lane + 1];
-  const int tiles = (hi - lo + bm - 1) / bm, incl = wave_inclusive_sum(tiles);
-  const unsigned long long past = __ballot(incl > slot);
-  if (past == 0ull) return false;
-  c = __builtin_ctzll(past);
-  m0 = __builtin_amdgcn_readlane(lo, c) + (slot - __builtin_amdgcn_readlane(incl - tiles, c)) * bm;
-  m_end = __builtin_amdgcn_readlane(hi, c);
-  return true;
+  return RowTiles(offsets, n_groups, bm).find(slot, bm, c, m0, m_end);
 }
 
 __device__ __forceinline__ half8 pack_half8(const float4v& lo, const float4v& hi) {
@@ -165,6 +174,8 @@ struct FusedUp {
 
   // chunk of 32 rank rows that holds expert e
   __device__ static __forceinline__ int chunk_of(int e) { return (e * R) >> 5; }
+  // group of passes that holds expert e
+  __device__ static __forceinline__ int pass_group(int e) { return (e * R) / (16 * NSP); }
   // B operand of chunk c for a lane (contraction elements 32 c + 8 q ..) whose token selected
   // expert e and keeps the slice f of its t1
   __device__ static __forceinline__ half8 t1_frag(int e, int c, int q, const half8& f) {
@@ -181,9 +192,9 @@ struct FusedUp {
     return o;
   }
 
-  // Chunks of 32 rank rows and passes of 16 rank rows that at least one valid token of the
-  // 16-token block needs for its j-th expert (wavefront-uniform bit masks, taken once per
-  // token block).
+  // Chunks of 32 rank rows and groups of NSP passes of 16 rank rows that at least one valid token
+  // of the 16-token block needs for its j-th expert (wavefront-uniform bit masks, taken once
+  // per token block).
   struct Need {
     unsigned chunks[KMAX], passes[KMAX];
   };
@@ -195,8 +206,8 @@ struct FusedUp {
       if (j >= k) continue;
       for (int c = 0; c < n_chunks; ++c)
         if (__ballot(t.valid && chunk_of(t.e[j]) == c) != 0ull) nd.chunks[j] |= 1u << c;
-      for (int pp = 0; pp < n_pass; ++pp)
-        if (__ballot(t.valid && (pp & ~(NSP - 1)) == ((t.e[j] * R) >> 4)) != 0ull) nd.passes[j] |= 1u << pp;
+      for (int pg = 0; pg < n_pass / NSP; ++pg)
+        if (__ballot(t.valid && pg == pass_group(t.e[j])) != 0ull) nd.passes[j] |= 1u << pg;
     }
   }
 
@@ -236,12 +247,12 @@ struct FusedUp {
         o[i] = j == 0 ? t.g[0] * a[i] : fmaf(t.g[j], a[i], o[i]);
         ab[i] = (half_t)a[i];
       }
-      const int p0 = (ej * R) >> 4;   // first pass of the expert's rank rows
       for (unsigned m = nd.passes[j]; m != 0u; m &= m - 1u) {
-        const int pp = __builtin_ctz(m);
-        const bool on = t.valid && (pp & ~(NSP - 1)) == p0;
+        const int pg = __builtin_ctz(m);
         const half8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-        sacc[j][pp & (NSP - 1)] = mfma32(vf(pp), on ? ab : z, sacc[j][pp & (NSP - 1)]);
+        const half8 fb = t.valid && pg == pass_group(ej) ? ab : z;
+#pragma unroll
+        for (int s = 0; s < NSP; ++s) sacc[j][s] = mfma32(vf(pg * NSP + s), fb, sacc[j][s]);
       }
     }
   }

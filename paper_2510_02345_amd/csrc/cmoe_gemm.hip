@@ -12,21 +12,17 @@
 // product without leaving registers (its rows become the contraction index).
 #include "cmoe_device.h"
 
-#include <type_traits>
-
 namespace {
 
 // Tile of one workgroup: BN weight rows x BM tokens, WAVES_N x WAVES_M wavefronts, each
-// owning (BN/WAVES_N) x (BM/WAVES_M) outputs as 16x16 accumulator blocks.  Operand tiles
-// move global -> LDS with direct-to-LDS loads (no register staging) into NS stages of 32
-// contraction elements; rows are 64 B, their four 16-B chunks XOR-swizzled with swz(row)
-// so that the 16 lanes the LDS serves per cycle hit 64 distinct banks.  The
-// weight rows of a tile are stored in MFMA order: tile row rho holds weight row pi_row(rho).
-template <int BN_, int BM_, int WAVES_N_, int WAVES_M_, int NS_, int OCC_, bool PINGPONG_, int XSM_, int XSN_>
+// owning (BN/WAVES_N) x (BM/WAVES_M) outputs as 16x16 accumulator blocks (as the epilogue sees
+// it).  Operand tiles move global -> LDS with direct-to-LDS loads (no register staging) into NS
+// stages; tile rows are 64 B (32 contraction elements), their four 16-B chunks XOR-swizzled with
+// swz(row) so that the 16 lanes the LDS serves per cycle hit 64 distinct banks.  The weight rows
+// of a tile are stored in MFMA order: tile row rho holds weight row pi_row(rho).
+template <int BN_, int BM_, int WAVES_N_, int WAVES_M_, int NS_>
 struct Tile {
-  static constexpr int BN = BN_, BM = BM_, WAVES_N = WAVES_N_, WAVES_M = WAVES_M_, NS = NS_, OCC = OCC_;
-  static constexpr bool PINGPONG = PINGPONG_;
-  static constexpr int XSM = XSM_, XSN = XSN_;  // per-XCD super-tile: XSM row tiles x XSN column tiles
+  static constexpr int BN = BN_, BM = BM_, WAVES_N = WAVES_N_, WAVES_M = WAVES_M_, NS = NS_;
   static constexpr int NWAVES = WAVES_N * WAVES_M, NT = NWAVES * 64;
   static constexpr int WN = BN / WAVES_N, WM = BM / WAVES_M;
   static constexpr int NA = WN / 16, MT = WM / 16;   // 16-row blocks and 16-token blocks of a wavefront
@@ -34,11 +30,17 @@ struct Tile {
   static constexpr int BK = 32, ROWB = BK * 2;
   static constexpr int STAGE_BYTES = (BN + BM) * ROWB;
   static constexpr int SMEM_BYTES = NS * STAGE_BYTES;
-  static constexpr int PER_WAVE = (BN + BM) / 16 / NWAVES;  // 1-KiB load instructions per wavefront and stage
+  static constexpr int PER_WAVE = (BN + BM) / 16 / NWAVES;  // 1-KiB load instructions per wavefront and 32 elements
   static_assert(BN % (32 * WAVES_N) == 0 && BM % (16 * WAVES_M) == 0, "wave tile");
-  static_assert(((BN + BM) / 16) % NWAVES == 0, "load split");
-  static_assert(!PINGPONG || (NWAVES == 8 && NS >= 3), "ping-pong pairs wavefront w with w + 4");
 };
+// 256 x 256: half the operand bytes per flop of 128 x 128; eight wavefronts in ping-pong.
+using TileBig = Tile<256, 256, 2, 4, 4>;
+// Half and a quarter of it, for what does not fill a round of the CUs (tile_small).  The quarter is
+// 128 x 128, or 256 x 64 where the epilogue wants all 256 rows of the big tile in one workgroup.
+// A stage is 64 contraction elements, hence NS = 8 blocks of 32 are four stages.
+using TileHalf = Tile<256, 128, 2, 4, 6>;
+using TileQuad = Tile<128, 128, 2, 4, 8>;
+using TileSlab = Tile<256, 64, 4, 2, 6>;
 
 struct GemmArgs {
   const half_t* W;   // weights of cluster c: W + c * w_cstride, [N][ldw] row-major
@@ -49,11 +51,7 @@ struct GemmArgs {
   const int* gather;
   int Kc;            // contraction length, multiple of 32
   const int* offsets;
-  int G, n_tiles, m_slots, spx;
-  // A launch covers the slots rel_lo <= rel < rel_hi of every XCD's range.  Slots are
-  // slot_bm rows of one cluster; a tail launch (tail != 0) cuts each of its slots into
-  // slot_bm / BM row tiles of a smaller tile shape.
-  int slot_bm, rel_lo, rel_hi, tail;
+  int G, n_tiles;    // groups (at most 64); column tiles of TileBig::BN weight rows
   int x_div;         // row of X = gather[p] / x_div (several sorted rows may share one row of X); 0 = 1
   // optional per-group contraction range: group c contracts columns krange[2c] ..
   // krange[2c] + krange[2c+1] (both multiples of 32) of W and X instead of 0 .. Kc
@@ -78,80 +76,57 @@ __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-template <class TL, class Epi>
-__global__ __launch_bounds__(TL::NT, TL::OCC) void gemm_nt_kernel(GemmArgs g, Epi epi) {
-  constexpr int SMEM = Epi::template smem_bytes<TL>();
-  __shared__ __attribute__((aligned(1024))) char smem[SMEM];
+// Where a tile of a group comes from.
+struct TileSrc {
+  const GemmArgs& g;
+  int c, n0, m0, m_end;
+  int k_lo, KT;           // first 32-element block and number of blocks
+  long kstep_w, kstep_x;
+  __device__ __forceinline__ TileSrc(const GemmArgs& g_, int c_, int n0_, int m0_, int m_end_)
+      : g(g_), c(c_), n0(n0_), m0(m0_), m_end(m_end_) {
+    k_lo = g.krange ? g.krange[2 * c] / 32 : 0;
+    KT = (g.krange ? g.krange[2 * c + 1] : g.Kc) / 32;
+    kstep_w = g.kstep_w ? g.kstep_w : 32;
+    kstep_x = g.kstep_x ? g.kstep_x : 32;
+  }
+  // source of the 16-byte chunk at position `pos` of tile row `row` (BN weight rows, then the
+  // tokens) in the tile's first block; rows past the end of the matrix / group repeat the last one
+  __device__ __forceinline__ const half_t* chunk(int row, int pos, int bn) const {
+    const half_t* base;
+    if (row < bn) {
+      base = g.W + (size_t)c * g.w_cstride + (size_t)min(n0 + pi_row(row), g.N - 1) * g.ldw + (size_t)k_lo * kstep_w;
+    } else {
+      const int p = min(m0 + row - bn, m_end - 1);
+      base = g.X + (size_t)(g.gather ? (g.x_div > 1 ? g.gather[p] / g.x_div : g.gather[p]) : p) * g.ldx +
+             (size_t)k_lo * kstep_x;
+    }
+    return base + ((pos ^ swz(row)) << 3);
+  }
+};
+
+// ---------------------------------------------------------------- 256 x 256 tile
+// Ping-pong: the two wavefronts of a SIMD (w, w + 4) run one barrier interval apart, so in every
+// interval one of them issues its MFMAs while the other reads fragments from LDS and issues the
+// next loads.  (Issuing the loads from inside the MFMA phase instead, between the 16-cycle
+// MFMAs, measured 5 % slower on the whole layer.)
+template <class Epi>
+__device__ __forceinline__ void tile_big(const GemmArgs& g, const Epi& epi, char* smem, int c, int n_tile, int m0,
+                                         int m_end) {
+  using TL = TileBig;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // ping-pong pairs the two wavefronts of a SIMD (w, w + 4); both sets cover the tile
   const int wn = wave % TL::WAVES_N, wm = wave / TL::WAVES_N;
-
-  // Workgroups are dealt round-robin to the 8 XCDs.  XCD x takes the contiguous range of
-  // g.spx row-tile slots [x * spx, (x + 1) * spx); inside it, groups of XSM row tiles are
-  // walked over the column tiles in blocks of XSN, so the workgroups resident on one XCD
-  // share both operands through that XCD's L2.  With few row tiles (spx == 0) the column
-  // tiles are simply dealt across the XCDs.
-  int n_tile, slot, sub = 0;
-  if (g.tail) {
-    const int subs = g.slot_bm / TL::BM;
-    const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-    n_tile = local % g.n_tiles;
-    const int rest = local / g.n_tiles;
-    sub = rest % subs;
-    const int rel = g.rel_lo + rest / subs;
-    slot = xcd * g.spx + rel;
-    if (rel >= g.rel_hi || slot >= g.m_slots) return;
-  } else if (g.spx == 0) {
-    n_tile = blockIdx.x % g.n_tiles;
-    slot = blockIdx.x / g.n_tiles;
-    if (slot >= g.m_slots) return;
-  } else {
-    const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-    const int per_group = TL::XSM * g.n_tiles;
-    const int vg = local / per_group, rem = local % per_group;
-    const int nblk = rem / (TL::XSM * TL::XSN), r2 = rem % (TL::XSM * TL::XSN);
-    const int sn = min(TL::XSN, g.n_tiles - nblk * TL::XSN);
-    const int rel = vg * TL::XSM + r2 / sn;
-    slot = xcd * g.spx + rel;
-    n_tile = nblk * TL::XSN + r2 % sn;
-    if (r2 / sn >= TL::XSM || rel >= g.rel_hi || slot >= g.m_slots) return;
-  }
-  // which cluster and row tile the slot is: derived on the device from the cluster
-  // offsets, so no host round trip sits between routing and the GEMMs
-  int c, m0, m_end;
-  if (!find_tile(g.offsets, g.G, g.slot_bm, slot, c, m0, m_end)) return;
-  m0 += sub * TL::BM;
-  if (m0 >= m_end) return;
   const int n0 = n_tile * TL::BN;
-  const half_t* Wc = g.W + (size_t)c * g.w_cstride;
-  const int k_lo = g.krange ? g.krange[2 * c] : 0;
-  const long kstep_w = g.kstep_w ? g.kstep_w : TL::BK, kstep_x = g.kstep_x ? g.kstep_x : TL::BK;
+  const TileSrc src(g, c, n0, m0, m_end);
   const unsigned smem_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
-
-  // global source of each of this wavefront's load instructions (16 tile rows x 64 B);
-  // rows past the end of the matrix / cluster are clamped to the last valid row
   const half_t* gsrc[TL::PER_WAVE];
 #pragma unroll
-  for (int i = 0; i < TL::PER_WAVE; ++i) {
-    const int ii = wave * TL::PER_WAVE + i;
-    const int row = ii * 16 + (lane >> 2), pos = lane & 3;
-    const int chunk = pos ^ swz(row);
-    const half_t* base;
-    if (row < TL::BN) {
-      const int n = min(n0 + pi_row(row), g.N - 1);
-      base = Wc + (size_t)n * g.ldw;
-    } else {
-      const int p = min(m0 + row - TL::BN, m_end - 1);
-      base = g.X + (size_t)(g.gather ? (g.x_div > 1 ? g.gather[p] / g.x_div : g.gather[p]) : p) * g.ldx;
-    }
-    const long step = row < TL::BN ? kstep_w : kstep_x;
-    gsrc[i] = base + chunk * 8 + (size_t)(k_lo / TL::BK) * step;
-  }
+  for (int i = 0; i < TL::PER_WAVE; ++i)
+    gsrc[i] = src.chunk((wave * TL::PER_WAVE + i) * 16 + (lane >> 2), lane & 3, TL::BN);
   auto issue = [&](int kt, int stage) {
 #pragma unroll
     for (int i = 0; i < TL::PER_WAVE; ++i)
-      dma16(gsrc[i] + (size_t)kt * (((wave * TL::PER_WAVE + i) * 16 < TL::BN) ? kstep_w : kstep_x),
+      dma16(gsrc[i] + (size_t)kt * (((wave * TL::PER_WAVE + i) * 16 < TL::BN) ? src.kstep_w : src.kstep_x),
             smem_base + stage * TL::STAGE_BYTES + (wave * TL::PER_WAVE + i) * 1024);
   };
 
@@ -174,89 +149,283 @@ __global__ __launch_bounds__(TL::NT, TL::OCC) void gemm_nt_kernel(GemmArgs g, Ep
     const int row = TL::BN + wm * TL::WM + b * 16 + t16;
     offb[b] = row * TL::ROWB + ((q ^ swz(row)) << 4);
   }
-
   // 16-token blocks of this wavefront that hold at least one real token (a ragged last
   // row tile of a cluster skips the matrix-core work of the others)
   bool bv[TL::MT];
 #pragma unroll
   for (int b = 0; b < TL::MT; ++b) bv[b] = m0 + wm * TL::WM + b * 16 < m_end;
 
-  const int KT = (g.krange ? g.krange[2 * c + 1] : g.Kc) / TL::BK;
+  const int KT = src.KT;
 #pragma unroll
   for (int s = 0; s < TL::NS - 1; ++s)
     if (s < KT) issue(s, s);
   int stage = 0, nstage = TL::NS - 1;
-  if (!TL::PINGPONG) {
-    for (int kt = 0; kt < KT; ++kt) {
-      // tile kt has landed (own loads), then everyone's; the stage refilled below was
-      // read during iteration kt - 1, which every wavefront has left
-      if (kt + TL::NS - 2 < KT) wait_vm<(TL::NS - 2) * TL::PER_WAVE>(); else wait_vm<0>();
-      __builtin_amdgcn_s_barrier();
-      if (kt + TL::NS - 1 < KT) issue(kt + TL::NS - 1, nstage);
-      const char* sb = smem + stage * TL::STAGE_BYTES;
-      half8 fa[TL::NA], fb[TL::MT];
+  const bool set_b = wave >= 4;
+  if (KT > 1) wait_vm<(TL::NS - 2) * TL::PER_WAVE>(); else wait_vm<0>();
+  if (KT <= TL::NS - 2) wait_vm<0>();
+  __builtin_amdgcn_s_barrier();
+  if (set_b) __builtin_amdgcn_s_barrier();
+  for (int kt = 0; kt < KT; ++kt) {
+    const char* sb = smem + stage * TL::STAGE_BYTES;
+    half8 fa[TL::NA], fb[TL::MT];
 #pragma unroll
-      for (int a = 0; a < TL::NA; ++a) fa[a] = *(const half8*)(sb + offa[a]);
+    for (int a = 0; a < TL::NA; ++a) fa[a] = *(const half8*)(sb + offa[a]);
 #pragma unroll
-      for (int b = 0; b < TL::MT; ++b)
-        if (bv[b]) fb[b] = *(const half8*)(sb + offb[b]);
-#pragma unroll
-      for (int b = 0; b < TL::MT; ++b)
-        if (bv[b]) {
-#pragma unroll
-          for (int a = 0; a < TL::NA; ++a) acc[a][b] = mfma32(fa[a], fb[b], acc[a][b]);
-        }
-      stage = (stage + 1 == TL::NS) ? 0 : stage + 1;
-      nstage = (nstage + 1 == TL::NS) ? 0 : nstage + 1;
+    for (int b = 0; b < TL::MT; ++b)
+      if (bv[b]) fb[b] = *(const half8*)(sb + offb[b]);
+    // the stage refilled here held block kt - 1, which both sets read before the
+    // barrier that opened this interval
+    if (kt + TL::NS - 1 < KT) {
+      issue(kt + TL::NS - 1, nstage);
+      wait_vm<(TL::NS - 2) * TL::PER_WAVE>();   // block kt + 1 (own loads) has landed
+    } else {
+      wait_vm<0>();
     }
-  } else {
-    // Ping-pong: wavefronts 4..7 run one barrier interval behind wavefronts 0..3, so in
-    // every interval one wavefront of each SIMD issues its MFMAs while the other reads
-    // fragments from LDS and issues the next loads.  (Issuing the loads from inside the MFMA
-    // phase instead, between the 16-cycle MFMAs, measured 5 % slower on the whole layer.)
-    const bool set_b = wave >= 4;
-    if (KT > 1) wait_vm<(TL::NS - 2) * TL::PER_WAVE>(); else wait_vm<0>();
-    if (KT <= TL::NS - 2) wait_vm<0>();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
-    if (set_b) __builtin_amdgcn_s_barrier();
-    for (int kt = 0; kt < KT; ++kt) {
-      const char* sb = smem + stage * TL::STAGE_BYTES;
-      half8 fa[TL::NA], fb[TL::MT];
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-      for (int a = 0; a < TL::NA; ++a) fa[a] = *(const half8*)(sb + offa[a]);
+    for (int b = 0; b < TL::MT; ++b)
+      if (bv[b]) {
 #pragma unroll
-      for (int b = 0; b < TL::MT; ++b)
-        if (bv[b]) fb[b] = *(const half8*)(sb + offb[b]);
-      // the stage refilled here held tile kt - 1, which both sets read before the
-      // barrier that opened this interval
-      if (kt + TL::NS - 1 < KT) {
-        issue(kt + TL::NS - 1, nstage);
-        wait_vm<(TL::NS - 2) * TL::PER_WAVE>();   // tile kt + 1 (own loads) has landed
-      } else {
-        wait_vm<0>();
+        for (int a = 0; a < TL::NA; ++a) acc[a][b] = mfma32(fa[a], fb[b], acc[a][b]);
       }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-      for (int b = 0; b < TL::MT; ++b)
-        if (bv[b]) {
-#pragma unroll
-          for (int a = 0; a < TL::NA; ++a) acc[a][b] = mfma32(fa[a], fb[b], acc[a][b]);
-        }
-      __builtin_amdgcn_s_setprio(0);
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-      stage = (stage + 1 == TL::NS) ? 0 : stage + 1;
-      nstage = (nstage + 1 == TL::NS) ? 0 : nstage + 1;
-    }
-    if (!set_b) __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    stage = (stage + 1 == TL::NS) ? 0 : stage + 1;
+    nstage = (nstage + 1 == TL::NS) ? 0 : nstage + 1;
   }
-
+  if (!set_b) __builtin_amdgcn_s_barrier();
   TileCtx ctx{c, n_tile, n0, m0, m_end, wn, wm, lane, tid, (half_t*)smem};
+  epi.template run<TL>(ctx, acc);
+}
+
+// ---------------------------------------------------------------- half or a quarter of it
+// What bounds a small tile is the LDS: 64 x 64 outputs per wavefront need 8 KiB of fragments per
+// 32 contraction elements, half of what 64 x 32 need per flop.  So that eight wavefronts fit the
+// tile at that size (128 x 64 for the half), it is computed by TWO sets of four, one on the even
+// and one on the odd 32-element blocks, whose accumulators are added at the end (set 1 hands
+// token blocks 0, 1 of a wavefront to set 0 and gets 2, 3 in return), which leaves every
+// wavefront with 32 tokens for the epilogue.  A stage holds a block for each set; the fragments
+// of the next stage are read while the matrix cores work on the current one.  Measured on
+// 128 x 128 (204 workgroups, contraction 3072): 32 us, of which 0.42 us per 64 elements; with one
+// set of eight wavefronts of 64 x 32 in ping-pong 40 us.
+template <class TL, class Epi>
+__device__ __forceinline__ void tile_small(const GemmArgs& g, const Epi& epi, char* smem, int c, int n_tile, int n0, int m0,
+                                           int m_end) {
+  constexpr int NSTG = TL::NS / 2, HALF = TL::STAGE_BYTES, STAGE = 2 * HALF;
+  constexpr int PIECES = (TL::BN + TL::BM) / 16, PER = PIECES / 4;   // 16-row pieces of a block, per wavefront of a set
+  constexpr int NA = TL::NA, NB = 4;   // 16-row and 16-token blocks of a wavefront in the main loop
+  static_assert(TL::WM == 32 && TL::NWAVES == 8 && PIECES % 4 == 0, "two sets of four wavefronts");
+  static_assert(8 * NA * 2 * 1024 <= TL::SMEM_BYTES, "exchange area");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int set = wave >> 2, w4 = wave & 3, wn = w4 % TL::WAVES_N, wmh = w4 / TL::WAVES_N;
+  const TileSrc src(g, c, n0, m0, m_end);
+  const unsigned smem_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
+  const int KT = src.KT, steps = (KT + 1) / 2;   // an odd last block is set 0's; set 1 loads it too and ignores it
+  const half_t* gsrc[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) gsrc[i] = src.chunk((w4 * PER + i) * 16 + (lane >> 2), lane & 3, TL::BN);
+  auto issue = [&](int st, int stage) {
+    const int blk = min(2 * st + set, KT - 1);
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      dma16(gsrc[i] + (size_t)blk * (((w4 * PER + i) * 16 < TL::BN) ? src.kstep_w : src.kstep_x),
+            smem_base + stage * STAGE + set * HALF + (w4 * PER + i) * 1024);
+  };
+  float4v acc[NA][NB];
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[a][b] = float4v{0.f, 0.f, 0.f, 0.f};
+  const int t16 = lane & 15, q = lane >> 4;
+  const int frag = set * HALF + t16 * 64 + ((q ^ swz(t16)) << 4);   // tile rows of a fragment start at multiples of 16
+  const int offa = frag + wn * TL::WN * 64, offb = frag + (TL::BN + wmh * 64) * 64;
+  const int nb = min(NB, (m_end - m0 - wmh * 64 + 15) / 16);   // token blocks that hold a token
+  struct Frag {
+    half8 a[NA], b[NB];
+  };
+  auto read = [&](Frag& f, int stage) {
+    const char* sb = smem + stage * STAGE;
+#pragma unroll
+    for (int a = 0; a < NA; ++a) f.a[a] = *(const half8*)(sb + offa + a * 1024);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) f.b[b] = *(const half8*)(sb + offb + b * 1024);
+  };
+  auto use = [&](const Frag& f) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      if (b < nb) {
+#pragma unroll
+        for (int a = 0; a < NA; ++a) acc[a][b] = mfma32(f.a[a], f.b[b], acc[a][b]);
+      }
+  };
+  if (steps > 0) {
+#pragma unroll
+    for (int s = 0; s < NSTG - 1; ++s)
+      if (s < steps) issue(s, s);
+    if (NSTG - 2 < steps) wait_vm<(NSTG - 2) * PER>(); else wait_vm<0>();   // stage 0, for the first fragments
+    __builtin_amdgcn_s_barrier();
+    Frag f0, f1;
+    read(f0, 0);
+    int rd = 1, wr = NSTG - 1;   // stage of step st + 1; stage refilled in step st (it held step st - 1)
+    auto step = [&](int st, const Frag& cur, Frag& nxt) {
+      if (st + 1 < steps) {
+        // step st + 1 has landed (own loads), then everyone's; every wavefront has left step st - 1
+        if (st + NSTG - 2 < steps) wait_vm<(NSTG - 3) * PER>(); else wait_vm<0>();
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        read(nxt, rd);
+        if (st + NSTG - 1 < steps) issue(st + NSTG - 1, wr);
+      }
+      if (2 * st + set < KT) use(cur);
+      rd = rd + 1 == NSTG ? 0 : rd + 1;
+      wr = wr + 1 == NSTG ? 0 : wr + 1;
+    };
+    for (int st = 0; st < steps; st += 2) {
+      step(st, f0, f1);
+      if (st + 1 < steps) step(st + 1, f1, f0);
+    }
+  }
+  float4v out[NA][2];
+  __syncthreads();   // the stages have been read
+  {
+    float4v* xs = (float4v*)smem + (size_t)w4 * NA * 2 * 64 + lane;
+    float4v* send = xs + (set ? 0 : 4 * NA * 2 * 64);
+    const float4v* recv = xs + (set ? 4 * NA * 2 * 64 : 0);
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        send[(a * 2 + b) * 64] = set ? acc[a][b] : acc[a][b + 2];
+        out[a][b] = set ? acc[a][b + 2] : acc[a][b];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) out[a][b] += recv[(a * 2 + b) * 64];
+  }
+  __syncthreads();   // the epilogue may use the space
+  TileCtx ctx{c, n_tile, n0, m0, m_end, wn, wmh * 2 + set, lane, tid, (half_t*)smem};
+  epi.template run<TL>(ctx, out);
+}
+
+// ---------------------------------------------------------------- grouped product
+// Workgroups are dealt round-robin to the 8 XCDs.  Each XCD takes an equal run of the 256 x 256
+// tiles, walked in super-tiles of 4 row tiles x 8 column tiles, so that the workgroups resident on
+// one XCD share both operands through its L2.  Which tiles there are follows from the group
+// offsets on the device, so no host round trip sits between routing and the products.  An XCD's
+// 32 CUs take its tiles in rounds of 32; what is left after the full rounds is cut into halves or
+// quarters when these fit one round (a half takes about 0.4 and a quarter 0.25 of a big
+// tile's time), which is also how a launch with few tiles fills the machine.  Up-projection of
+// 777 tokens (64 tiles, contraction 1024): 50 -> 29 us in 220 quarters; 16384 tokens with Zipf
+// loads (132 tiles per XCD): 282 -> 250 us, its down-projection (33 tiles) 190 -> 168 us.
+constexpr int XSM = 4, XSN = 8, XCD_CUS = 32;
+template <class Epi>
+__global__ __launch_bounds__(512, 1) void gemm_kernel(GemmArgs g, Epi epi) {
+  using Quarter = typename Epi::Quarter;
+  constexpr int SB = Epi::template smem_bytes<TileBig>(), SH = Epi::template smem_bytes<TileHalf>(),
+                SQ = Epi::template smem_bytes<Quarter>();
+  constexpr int SMEM = SB > SH ? (SB > SQ ? SB : SQ) : (SH > SQ ? SH : SQ);
+  __shared__ __attribute__((aligned(1024))) char smem[SMEM];
+  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+  const RowTiles rt(g.offsets, g.G, TileBig::BM);
+  const int slots = rt.total(), tiles = slots * g.n_tiles;
+  const int lo = (int)((long)tiles * xcd >> 3), mine = (int)((long)tiles * (xcd + 1) >> 3) - lo;
+  int full = mine / XCD_CUS * XCD_CUS, cut = 0;   // log2 of the parts a leftover tile is cut into
+  if (mine - full > XCD_CUS / 2) full = mine; else cut = mine - full > XCD_CUS / 4 ? 1 : 2;
+  const bool big = local < full;
+  const int t = big ? lo + local : lo + full + ((local - full) >> cut), part = (local - full) & ((1 << cut) - 1);
+  if (t >= lo + mine) return;
+  const int per_group = XSM * g.n_tiles, vg = t / per_group, rem = t % per_group;
+  const int sm = min(XSM, slots - vg * XSM);                      // row tiles of the super-tile
+  const int nblk = rem / (sm * XSN), r2 = rem % (sm * XSN);
+  const int sn = min(XSN, g.n_tiles - nblk * XSN);                // column tiles of the super-tile
+  const int slot = vg * XSM + r2 / sn, n_tile = nblk * XSN + r2 % sn;
+  int c, m0, m_end;
+  if (!rt.find(slot, TileBig::BM, c, m0, m_end)) return;
+  int n0 = n_tile * TileBig::BN;
+  if (big) {
+    tile_big<Epi>(g, epi, smem, c, n_tile, m0, m_end);
+  } else if (cut == 1) {
+    m0 += part * TileHalf::BM;
+    if (m0 < m_end) tile_small<TileHalf, Epi>(g, epi, smem, c, n_tile, n0, m0, m_end);
+  } else {
+    constexpr int ACROSS = TileBig::BN / Quarter::BN;
+    n0 += part % ACROSS * Quarter::BN;
+    m0 += part / ACROSS * Quarter::BM;
+    if (n0 < g.N && m0 < m_end) tile_small<Quarter, Epi>(g, epi, smem, c, n_tile, n0, m0, m_end);
+  }
+}
+
+template <class Epi>
+hipError_t launch_gemm(const GemmArgs& g, int T, const Epi& epi, hipStream_t st) {
+  const int tiles = ((T + TileBig::BM - 1) / TileBig::BM + g.G) * g.n_tiles;   // at most
+  // a leftover of up to XCD_CUS / 4 tiles per XCD becomes 4 workgroups each, up to XCD_CUS / 2 two
+  hipLaunchKernelGGL((gemm_kernel<Epi>), dim3((unsigned)(8 * ((tiles + 7) / 8 + 3 * XCD_CUS / 4))), dim3(512), 0, st, g, epi);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- few weight rows
+// At most 64 weight rows (products into rank space): one 64-row weight tile against 128 tokens,
+// four wavefronts side by side along the tokens; bound by the stream of X rows.
+template <class Epi>
+__global__ __launch_bounds__(256, 3) void gemm_thin_kernel(GemmArgs g, Epi epi) {
+  using TL = Tile<64, 128, 1, 4, 4>;
+  __shared__ __attribute__((aligned(1024))) char smem[TL::SMEM_BYTES];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int c, m0, m_end;
+  if (!find_tile(g.offsets, g.G, TL::BM, blockIdx.x, c, m0, m_end)) return;
+  const TileSrc src(g, c, 0, m0, m_end);
+  const unsigned smem_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
+  const half_t* gsrc[TL::PER_WAVE];
+#pragma unroll
+  for (int i = 0; i < TL::PER_WAVE; ++i)
+    gsrc[i] = src.chunk((wave * TL::PER_WAVE + i) * 16 + (lane >> 2), lane & 3, TL::BN);
+  auto issue = [&](int kt, int stage) {
+#pragma unroll
+    for (int i = 0; i < TL::PER_WAVE; ++i)
+      dma16(gsrc[i] + (size_t)kt * (((wave * TL::PER_WAVE + i) * 16 < TL::BN) ? src.kstep_w : src.kstep_x),
+            smem_base + stage * TL::STAGE_BYTES + (wave * TL::PER_WAVE + i) * 1024);
+  };
+  float4v acc[TL::NA][TL::MT];
+#pragma unroll
+  for (int a = 0; a < TL::NA; ++a)
+#pragma unroll
+    for (int b = 0; b < TL::MT; ++b) acc[a][b] = float4v{0.f, 0.f, 0.f, 0.f};
+  const int t16 = lane & 15, q = lane >> 4, frag = t16 * 64 + ((q ^ swz(t16)) << 4);
+  const int KT = src.KT;
+#pragma unroll
+  for (int s = 0; s < TL::NS - 1; ++s)
+    if (s < KT) issue(s, s);
+  int stage = 0, nstage = TL::NS - 1;
+  for (int kt = 0; kt < KT; ++kt) {
+    // block kt has landed (own loads), then everyone's; the stage refilled below was
+    // read during iteration kt - 1, which every wavefront has left
+    if (kt + TL::NS - 2 < KT) wait_vm<(TL::NS - 2) * TL::PER_WAVE>(); else wait_vm<0>();
+    __builtin_amdgcn_s_barrier();
+    if (kt + TL::NS - 1 < KT) issue(kt + TL::NS - 1, nstage);
+    const char* sb = smem + stage * TL::STAGE_BYTES + frag;
+    half8 fa[TL::NA], fb[TL::MT];
+#pragma unroll
+    for (int a = 0; a < TL::NA; ++a) fa[a] = *(const half8*)(sb + a * 1024);
+#pragma unroll
+    for (int b = 0; b < TL::MT; ++b) fb[b] = *(const half8*)(sb + (TL::BN + wave * TL::WM + b * 16) * 64);
+#pragma unroll
+    for (int b = 0; b < TL::MT; ++b)
+#pragma unroll
+      for (int a = 0; a < TL::NA; ++a) acc[a][b] = mfma32(fa[a], fb[b], acc[a][b]);
+    stage = (stage + 1 == TL::NS) ? 0 : stage + 1;
+    nstage = (nstage + 1 == TL::NS) ? 0 : nstage + 1;
+  }
+  TileCtx ctx{c, 0, 0, m0, m_end, 0, wave, lane, tid, (half_t*)smem};
   epi.template run<TL>(ctx, acc);
 }
 
@@ -265,6 +434,7 @@ __global__ __launch_bounds__(TL::NT, TL::OCC) void gemm_nt_kernel(GemmArgs g, Ep
 // consecutive outputs of a pair block for its token in one piece.
 template <class OutT>
 struct EpiStoreT {
+  using Quarter = TileQuad;
   OutT* out;
   const int* rowmap;  // row p of the tile order is written to out[rowmap[p]] (NULL: identity)
   int ldo, N;
@@ -301,6 +471,7 @@ using EpiStore = EpiStoreT<half_t>;
 // of a 16-token block needs are skipped), and writes the rows straight to token order, 16
 // bytes per lane.  K*r <= 128.
 struct EpiDownCombine {
+  using Quarter = TileQuad;
   const half_t* u2t;     // [G][d][KRp]
   const float* s_down;   // [T][k][r], token order
   const int* rperm;      // token of tile row p
@@ -395,6 +566,7 @@ struct EpiDownCombine {
 // otherwise they are read from global memory.
 template <int R, int KMAX, bool STAGE>
 struct EpiFusedUp {
+  using Quarter = TileSlab;   // one s partial per 256 rows of d_ff whatever the tile
   const half_t* u1t;  // [G][d_ff][KRp]
   const half_t* v2p;  // [G][KRp][d_ff]
   const half_t* t1;   // [T][k][r], sorted rows
@@ -402,7 +574,7 @@ struct EpiFusedUp {
   const int* expert_idx;
   const float* gate;
   half_t* A;          // [d_ff / 32][T][32]
-  float* spart;       // [n_tiles][T][k][r] partials of V2 a over the tile's 256 rows of d_ff, FP32
+  float* spart;       // [n_tiles][T][k][r] partials of V2 a over the tile's rows of d_ff, FP32
   int T, k, K, KRp, d_ff;
   using FU = FusedUp<R, KMAX>;
 
@@ -412,21 +584,24 @@ struct EpiFusedUp {
                ? 2 * (TL::BN * (128 + 8) + 128 * (TL::BN + 8))
                : TL::SMEM_BYTES;
   }
-  // The two wavefronts that share a token block add their s partials through LDS.  With up
+  // The WAVES_N wavefronts that share a token block add their s partials through LDS.  With up
   // to two experts per token the partials of all token blocks are exchanged at the end, in
   // the space of the panels (no longer needed then); otherwise block by block through an
   // area of its own behind the panels.
   static constexpr bool BATCH = KMAX <= 2;
-  static constexpr int XS_FLOATS = (BATCH ? 4 * KMAX * FusedUp<R, KMAX>::NSP : 1) * 4 * 64;   // per wavefront column
+  template <class TL>
+  static constexpr int xs_floats() { return (BATCH ? TL::MT * KMAX * FU::NSP : 1) * 4 * 64; }   // per wavefront
+  template <class TL>
+  static constexpr int xs_bytes() { return TL::WAVES_M * (TL::WAVES_N - 1) * xs_floats<TL>() * 4; }
   template <class TL>
   static constexpr int smem_bytes() {
-    static_assert(!BATCH || (TL::MT == 4 && TL::WAVES_M * XS_FLOATS * 4 <= TL::SMEM_BYTES), "exchange area");
-    return panel_bytes<TL>() + (BATCH ? 0 : TL::WAVES_M * XS_FLOATS * 4);
+    static_assert(!BATCH || xs_bytes<TL>() <= TL::SMEM_BYTES, "exchange area");
+    return panel_bytes<TL>() + (BATCH ? 0 : xs_bytes<TL>());
   }
 
   template <class TL>
   __device__ void run(const TileCtx& t, float4v (&acc)[TL::NA][TL::MT]) const {
-    static_assert(TL::BN == G1_BN && TL::WAVES_N == 2, "one s partial per tile of G1_BN rows, summed over its two wavefront columns");
+    static_assert(TL::BN == TileBig::BN, "one s partial per tile, summed over its wavefront columns");
     const int t16 = t.lane & 15, q = t.lane >> 4;
     const half_t* u1c = u1t + (size_t)t.c * d_ff * KRp;
     const half_t* v2c = v2p + (size_t)t.c * KRp * d_ff;
@@ -489,7 +664,11 @@ struct EpiFusedUp {
     // at the end in one go; otherwise block by block
     constexpr int NSB = BATCH ? TL::MT : 1;
     float4v sacc[NSB][KMAX][FU::NSP];
-    float* xs = (BATCH ? (float*)t.smem : (float*)((char*)t.smem + panel_bytes<TL>())) + t.wm * XS_FLOATS;
+    // partials of wavefront column wn >= 1 of token column wm
+    auto xs = [&](int wn) {
+      return (BATCH ? (float*)t.smem : (float*)((char*)t.smem + panel_bytes<TL>())) +
+             ((wn - 1) * TL::WAVES_M + t.wm) * xs_floats<TL>() + t.lane;
+    };
 #pragma unroll
     for (int b = 0; b < TL::MT; ++b) {
       const int sb = BATCH ? b : 0;
@@ -528,22 +707,27 @@ struct EpiFusedUp {
         }
       }
       if (!BATCH) {
-        // the two wavefronts that share these tokens (wn = 0, 1) add their partial s through
-        // LDS, one accumulator at a time; wn = 0 stores the tile's partial
+        // the wavefronts that share these tokens add their partial s through LDS, one
+        // accumulator at a time; wn = 0 stores the tile's partial
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < KMAX; ++j) {
           if (j >= k) continue;
 #pragma unroll
           for (int s2 = 0; s2 < FU::NSP; ++s2) {
-            if (t.wn == 1) {
+            if (t.wn != 0) {
+              float* x = xs(t.wn);
 #pragma unroll
-              for (int v = 0; v < 4; ++v) xs[v * 64 + t.lane] = sacc[0][j][s2][v];
+              for (int v = 0; v < 4; ++v) x[v * 64] = sacc[0][j][s2][v];
             }
             __syncthreads();
             if (t.wn == 0) {
 #pragma unroll
-              for (int v = 0; v < 4; ++v) sacc[0][j][s2][v] += xs[v * 64 + t.lane];
+              for (int w = 1; w < TL::WAVES_N; ++w) {
+                const float* x = xs(w);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) sacc[0][j][s2][v] += x[v * 64];
+              }
             }
             __syncthreads();
           }
@@ -552,9 +736,10 @@ struct EpiFusedUp {
       }
     }
     if (BATCH) {
-      // all token blocks at once: wn = 1 writes its partials, wn = 0 adds them and stores
+      // all token blocks at once: wn > 0 write their partials, wn = 0 adds them in order and stores
       __syncthreads();
-      if (t.wn == 1) {
+      if (t.wn != 0) {
+        float* x = xs(t.wn);
 #pragma unroll
         for (int b = 0; b < NSB; ++b)
 #pragma unroll
@@ -562,18 +747,22 @@ struct EpiFusedUp {
 #pragma unroll
             for (int s2 = 0; s2 < FU::NSP; ++s2)
 #pragma unroll
-              for (int v = 0; v < 4; ++v) xs[(((b * KMAX + j) * FU::NSP + s2) * 4 + v) * 64 + t.lane] = sacc[b][j][s2][v];
+              for (int v = 0; v < 4; ++v) x[(((b * KMAX + j) * FU::NSP + s2) * 4 + v) * 64] = sacc[b][j][s2][v];
       }
       __syncthreads();
       if (t.wn == 0) {
 #pragma unroll
         for (int b = 0; b < NSB; ++b) {
 #pragma unroll
-          for (int j = 0; j < KMAX; ++j)
+          for (int w = 1; w < TL::WAVES_N; ++w) {
+            const float* x = xs(w);
 #pragma unroll
-            for (int s2 = 0; s2 < FU::NSP; ++s2)
+            for (int j = 0; j < KMAX; ++j)
 #pragma unroll
-              for (int v = 0; v < 4; ++v) sacc[b][j][s2][v] += xs[(((b * KMAX + j) * FU::NSP + s2) * 4 + v) * 64 + t.lane];
+              for (int s2 = 0; s2 < FU::NSP; ++s2)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) sacc[b][j][s2][v] += x[(((b * KMAX + j) * FU::NSP + s2) * 4 + v) * 64];
+          }
           FU::store_s(tk[PRELOAD ? b : 0], sacc[b], spart + (size_t)t.n_tile * T * k * R, k, q);
         }
       }
@@ -686,86 +875,16 @@ __global__ __launch_bounds__(CB_WAVES * 64) void combine_kernel(
   }
 }
 
-// The two big products: 256 x 256 per workgroup, eight wavefronts (2 x 4, each 128 x 64) in
-// ping-pong, one workgroup per CU: half the operand bytes per flop of the tile above.
-using TileBig = Tile<256, 256, 2, 4, 4, 1, true, 4, 8>;
-using TileUp = TileBig;  // tile of the fused up-projection
-static_assert(TileUp::BN == G1_BN, "workspace sizing assumes one s partial per G1_BN rows");
-
-// Leftover row tiles of the 256 x 256 schedule: 128 x 128, eight wavefronts (2 x 4, each
-// 64 x 32).  Four of them replace one big tile, so a last round that would occupy a
-// quarter of the CUs fills all of them.
-using TileTail = Tile<128, 128, 2, 4, 4, 1, true, 1, 1>;
-
-// TLT = void: one launch.  Otherwise, when the slots of an XCD do not fill whole rounds of
-// XSM slots and the leftover would leave at least half of the CUs idle, the leftover slots
-// go to a second launch with the smaller tile TLT.
-template <class TL, class Epi, class TLT = void>
-hipError_t launch_gemm(const GemmArgs& g, int T, const Epi& epi, hipStream_t st) {
-  GemmArgs ga = g;
-  ga.m_slots = (T + TL::BM - 1) / TL::BM + g.G;
-  ga.slot_bm = TL::BM;
-  ga.rel_lo = 0;
-  ga.tail = 0;
-  dim3 block(TL::NT);
-  if (ga.m_slots < 32) {
-    ga.spx = 0;
-    ga.rel_hi = ga.m_slots;
-    if constexpr (!std::is_void<TLT>::value) {
-      // fewer big tiles than half the CUs: the small tile shape fills the machine better
-      if (ga.m_slots * g.n_tiles <= 128) {
-        ga.m_slots = (T + TLT::BM - 1) / TLT::BM + g.G;
-        ga.slot_bm = TLT::BM;
-        ga.rel_hi = ga.m_slots;
-        ga.n_tiles = (g.N + TLT::BN - 1) / TLT::BN;
-        hipLaunchKernelGGL((gemm_nt_kernel<TLT, Epi>), dim3((unsigned)(ga.m_slots * ga.n_tiles)), dim3(TLT::NT), 0, st,
-                           ga, epi);
-        return hipGetLastError();
-      }
-    }
-    hipLaunchKernelGGL((gemm_nt_kernel<TL, Epi>), dim3((unsigned)(ga.m_slots * g.n_tiles)), block, 0, st, ga, epi);
-    return hipGetLastError();
-  }
-  ga.spx = (ga.m_slots + 7) / 8;
-  ga.rel_hi = ga.spx;
-  int tail_slots = 0;
-  if constexpr (!std::is_void<TLT>::value) {
-    tail_slots = ga.spx % TL::XSM;
-    // CUs of an XCD the leftover slots would occupy with the big tile: 32 per XCD
-    if (tail_slots * g.n_tiles > 16 || ga.spx < TL::XSM) tail_slots = 0;
-  }
-  ga.rel_hi = ga.spx - tail_slots;
-  const int groups = (ga.rel_hi + TL::XSM - 1) / TL::XSM;
-  hipLaunchKernelGGL((gemm_nt_kernel<TL, Epi>), dim3((unsigned)(8 * groups * TL::XSM * g.n_tiles)), block, 0, st, ga,
-                     epi);
-  hipError_t e = hipGetLastError();
-  if constexpr (!std::is_void<TLT>::value) {
-    if (e == hipSuccess && tail_slots > 0) {
-      GemmArgs gt = ga;
-      gt.tail = 1;
-      gt.rel_lo = ga.rel_hi;
-      gt.rel_hi = ga.spx;
-      gt.n_tiles = (g.N + TLT::BN - 1) / TLT::BN;
-      const int subs = TL::BM / TLT::BM;
-      hipLaunchKernelGGL((gemm_nt_kernel<TLT, Epi>), dim3((unsigned)(8 * tail_slots * subs * gt.n_tiles)),
-                         dim3(TLT::NT), 0, st, gt, epi);
-      e = hipGetLastError();
-    }
-  }
-  return e;
-}
-
 template <int R, int KMAX>
 hipError_t launch_gemm1_rk(const cmoe_dims& dm, const GemmArgs& g, int T, const int* perm, const int* expert_idx,
                            const float* gate, const half_t* u1t, const half_t* v2p, const half_t* t1, half_t* a,
                            float* spart, hipStream_t st) {
-  using TL = TileUp;
   if (dm.KRp <= 128) {
     EpiFusedUp<R, KMAX, true> epi{u1t, v2p, t1, perm, expert_idx, gate, a, spart, T, dm.k, dm.K, dm.KRp, dm.d_ff};
-    return launch_gemm<TL>(g, T, epi, st);
+    return launch_gemm(g, T, epi, st);
   }
   EpiFusedUp<R, KMAX, false> epi{u1t, v2p, t1, perm, expert_idx, gate, a, spart, T, dm.k, dm.K, dm.KRp, dm.d_ff};
-  return launch_gemm<TL>(g, T, epi, st);
+  return launch_gemm(g, T, epi, st);
 }
 
 template <int R>
@@ -794,9 +913,8 @@ hipError_t launch_gemm1(const cmoe_dims& dm, const cmoe_weights& w, const half_t
                         const int* perm,
                         const int* offsets, const int* expert_idx, const float* gate, const half_t* u1t,
                         const half_t* v2p, const half_t* t1, half_t* a, float* spart, hipStream_t st) {
-  using TL = TileUp;
   GemmArgs g{(const half_t*)w.w1_base, (long)dm.d_ff * dm.d, dm.d, dm.d_ff, x, dm.d, perm, dm.d, offsets, dm.G,
-             (dm.d_ff + TL::BN - 1) / TL::BN, 0, 0};
+             (dm.d_ff + TileBig::BN - 1) / TileBig::BN};
   g.x_div = x_div;
   use_packed_base(g, dm, w, false);
   switch (dm.r) {
@@ -821,14 +939,13 @@ hipError_t launch_sreduce(const cmoe_dims& dm, int T, const int* perm, const flo
 
 hipError_t launch_gemm2(const cmoe_dims& dm, const cmoe_weights& w, const half_t* a, int T, const int* offsets,
                         const int* rowmap, half_t* y_base_sorted, hipStream_t st) {
-  using TL = TileBig;
   // a is [d_ff / 32][T][32]
   GemmArgs g{(const half_t*)w.w2_base, (long)dm.d * dm.d_ff, dm.d_ff, dm.d, a, 32, nullptr, dm.d_ff, offsets,
-             dm.G, (dm.d + TL::BN - 1) / TL::BN, 0, 0};
+             dm.G, (dm.d + TileBig::BN - 1) / TileBig::BN};
   g.kstep_x = (long)T * 32;
   use_packed_base(g, dm, w, true);
   EpiStore epi{y_base_sorted, rowmap, dm.d, dm.d};
-  return launch_gemm<TL, EpiStore, TileTail>(g, T, epi, st);
+  return launch_gemm(g, T, epi, st);
 }
 
 hipError_t launch_combine(const cmoe_dims& dm, const half_t* u2t, const half_t* y_base_sorted, const float* s_down,
@@ -849,13 +966,12 @@ hipError_t launch_combine(const cmoe_dims& dm, const half_t* u2t, const half_t* 
 hipError_t launch_gemm2_combine(const cmoe_dims& dm, const cmoe_weights& w, const half_t* a, int T,
                                 const int* offsets, const int* rperm, const half_t* u2t, const float* s_down,
                                 const int* expert_idx, const float* gate, half_t* y, hipStream_t st) {
-  using TL = TileBig;
   GemmArgs g{(const half_t*)w.w2_base, (long)dm.d * dm.d_ff, dm.d_ff, dm.d, a, 32, nullptr, dm.d_ff, offsets,
-             dm.G, (dm.d + TL::BN - 1) / TL::BN, 0, 0};
+             dm.G, (dm.d + TileBig::BN - 1) / TileBig::BN};
   g.kstep_x = (long)T * 32;
   use_packed_base(g, dm, w, true);
   EpiDownCombine epi{u2t, s_down, rperm, expert_idx, gate, y, dm.k, dm.K, dm.r, dm.KRp, dm.d};
-  return launch_gemm<TL, EpiDownCombine, TileTail>(g, T, epi, st);
+  return launch_gemm(g, T, epi, st);
 }
 
 // Grouped product with a plain store, for callers outside the forward path:
@@ -866,26 +982,24 @@ hipError_t launch_gemm_plain(const half_t* W, long w_gstride, int ldw, int N, co
                              const int* gather, int x_div, int Kc, const int* offsets, int n_groups, int rows,
                              const int* krange, const int* rowmap, void* out, int ldo, bool out_f32,
                              hipStream_t st, long kstep_w, long kstep_x) {
-  using TL = TileBig;
-  GemmArgs g{W, w_gstride, ldw, N, X, ldx, gather, Kc, offsets, n_groups, (N + TL::BN - 1) / TL::BN, 0, 0};
+  GemmArgs g{W, w_gstride, ldw, N, X, ldx, gather, Kc, offsets, n_groups, (N + TileBig::BN - 1) / TileBig::BN};
   g.x_div = x_div;
   g.krange = krange;
   g.kstep_w = kstep_w;
   g.kstep_x = kstep_x;
   if (N <= 64 && !out_f32) {
-    // a few output columns per row (products into rank space): one 64-row weight tile, the
-    // launch is bound by the stream of X rows
-    using TN = Tile<64, 128, 1, 4, 4, 3, false, 8, 1>;
-    g.n_tiles = 1;
+    // a few output columns per row (products into rank space)
     EpiStore epi{(half_t*)out, rowmap, ldo, N};
-    return launch_gemm<TN, EpiStore>(g, rows, epi, st);
+    hipLaunchKernelGGL((gemm_thin_kernel<EpiStore>), dim3((unsigned)((rows + 127) / 128 + n_groups)), dim3(256), 0, st, g,
+                       epi);
+    return hipGetLastError();
   }
   if (out_f32) {
     EpiStoreT<float> epi{(float*)out, rowmap, ldo, N};
-    return launch_gemm<TL, EpiStoreT<float>, TileTail>(g, rows, epi, st);
+    return launch_gemm(g, rows, epi, st);
   }
   EpiStore epi{(half_t*)out, rowmap, ldo, N};
-  return launch_gemm<TL, EpiStore, TileTail>(g, rows, epi, st);
+  return launch_gemm(g, rows, epi, st);
 }
 
 // packed[c][(k / 32) * N + n][k % 32] = base[c][n][k].  A workgroup takes 64 rows n (four

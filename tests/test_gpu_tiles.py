@@ -1,0 +1,38 @@
+"""The grouped products' tile shapes: launches whose tiles per XCD (32 CUs) are below half a round,
+between, and above, or full rounds plus each kind of leftover, with ragged row tiles; one and
+several experts per token, rank panels in LDS and in memory."""
+import numpy as np
+import pytest
+
+import cmoe_inputs as ci
+from oracle import cmoe_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+# With d_ff = 2048 (8 column tiles) an XCD gets about T / 256 + G / 2 tiles of the up-projection.
+@pytest.mark.parametrize("T", [1500, 3300, 5800, 8300, 10900, 13300])
+@pytest.mark.parametrize("K,r,k", [(4, 8, 2), (2, 16, 1), (8, 32, 3)])
+def test_up_projection_tiles(T, K, r, k):
+    _check(ci.small_config("tiles", T=T, d=64, d_ff=2048, G=3, K=K, r=r, k=k, q=32, seed=T + K))
+
+
+# the same for the down-projection: d = 1088 is four column tiles and a quarter of one
+@pytest.mark.parametrize("T", [700, 2000, 4700, 9000, 14000])
+def test_down_projection_tiles(T):
+    _check(ci.small_config("tiles2", T=T, d=1088, d_ff=192, G=2, K=4, r=8, k=2, q=32, seed=T))
+
+
+def _check(cfg):
+    import torch
+
+    import paper_2510_02345_amd as cm
+    print(f"case {cfg}", flush=True)
+    w = ci.generate(cfg)
+    ref = orc.forward_naive(w, w["x"], cfg.K, cfg.k, cfg.q)
+    layer = cm.Layer(cfg.d, cfg.d_ff, cfg.G, cfg.K, cfg.r, cfg.k, cfg.q, w, cfg.T)
+    out = layer.forward(torch.from_numpy(w["x"]).to("cuda:0"))
+    torch.cuda.synchronize()
+    m = orc.error_metrics(out["y"].cpu().numpy(), ref["y"])   # the layer's bars (FP16 operands and results)
+    assert m["max_over_rms"] <= 1e-2 and m["mean_rel"] <= 2e-3, m
+    layer.close()
