@@ -2,7 +2,7 @@
 // token-to-cluster permutation (the single-device part of group-level dispatch).
 #include <mutex>
 
-#include "cmoe_internal.h"
+#include "cmoe_device.h"
 
 namespace {
 
@@ -556,6 +556,46 @@ __global__ __launch_bounds__(SORT_BLOCK) void sort_rank_kernel(SortArgs a, int m
   }
 }
 
+// Up to 256 items in up to 64 bins: one workgroup with a thread per item and no counters to clear.
+// Lane g counts bin g of its wavefront from the same ballots that rank the items, the sum over the
+// bins is a wavefront scan, and one barrier joins the wavefronts (none for up to 64 items).
+constexpr int SORT_FEW = 256;
+__global__ __launch_bounds__(SORT_FEW) void sort_few_kernel(SortArgs a, int* __restrict__ perm, int* __restrict__ inv_perm,
+                                                            int* __restrict__ offsets) {
+  __shared__ int wc[SORT_FEW / 64][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
+  const bool in = tid < a.n;
+  int id = 0, bin = 0;
+  if (in) sort_bin<false>(a, tid, id, bin);
+  unsigned long long same = __ballot(in), of_lane = same;   // lanes with this lane's bin; with bin `lane`
+  for (int b = 0; b < 32 - __builtin_clz(a.bins); ++b) {
+    const unsigned long long m = __ballot((id >> b) & 1);
+    same &= ((id >> b) & 1) ? m : ~m;
+    of_lane &= ((lane >> b) & 1) ? m : ~m;
+  }
+  const int cnt = lane < a.bins ? __popcll(of_lane) : 0;
+  int total = cnt, before = 0;
+  if (nw > 1) {
+    wc[wave][lane] = cnt;
+    __syncthreads();
+    total = 0;
+    for (int w = 0; w < nw; ++w) {
+      const int v = wc[w][lane];
+      total += v;
+      before += w < wave ? v : 0;
+    }
+  }
+  const int first = wave_inclusive_sum(total) - total;
+  const int row = __shfl(first + before, id, 64) + __popcll(same & ((1ull << lane) - 1ull));
+  if (wave == 0) {
+    if (lane < a.bins) offsets[lane] = first;
+    if (lane == 0) offsets[a.bins] = a.n;
+  }
+  if (!in) return;
+  perm[row] = tid;
+  inv_perm[tid] = row;
+}
+
 // The pair sort alone, for a permutation the caller already has: one workgroup per cluster, the
 // rows of the cluster in chunks of SORT_BLOCK.
 __global__ __launch_bounds__(SORT_BLOCK) void pair_sort_kernel(const int* __restrict__ perm,
@@ -661,7 +701,11 @@ hipError_t launch_sort_pairs(const cmoe_dims& dm, const int* cluster_id, const i
 // counts: sort_counts(n, bins) ints.
 hipError_t launch_sort_ids(const int* ids, int stride, int div, int n, int bins, int* perm, int* inv_perm, int* offsets,
                            int* counts, hipStream_t st) {
-  SortArgs a{ids, stride, div, n, bins, nullptr, 1, 1, 0, 1, 0, 0};
+  SortArgs a{ids, stride, div, n, bins, nullptr, 1, 1, 0, 1, 1, bins};
+  if (n <= SORT_FEW && bins <= 64) {
+    hipLaunchKernelGGL(sort_few_kernel, dim3(1), dim3((n + 63) / 64 * 64), 0, st, a, perm, inv_perm, offsets);
+    return hipGetLastError();
+  }
   return go_sort<false>(a, perm, inv_perm, offsets, nullptr, nullptr, counts, st);
 }
 
