@@ -19,7 +19,7 @@
 // 32-column blocks.  The ways back from rank space (U1 t, V2^T u, V1^T q) and the factor
 // gradients (r output rows per expert) are vector-ALU kernels that stream the pair rows of
 // an expert once.
-#include "cmoe_internal.h"
+#include "cmoe_device.h"
 
 namespace {
 
@@ -198,18 +198,17 @@ __global__ __launch_bounds__(256) void bw_dx_kernel(const half_t* __restrict__ d
 }
 
 // d v_e = sum over the pair rows of expert e of dl_m x_t: part[run][e][col], the rows of the
-// expert cut into DR_SPLIT runs added in row order (bw_rankgrad_finish_kernel adds the runs).
-// Block (E, ceil(d / 1024), DR_SPLIT).
-constexpr int DR_SPLIT = 4;
+// expert cut into gridDim.z runs added in row order (bw_rankgrad_finish_kernel adds the runs).
+// Block (E, ceil(d / 1024), runs).
 __global__ __launch_bounds__(256) void bw_drouter_kernel(const half_t* __restrict__ x, const int* __restrict__ permm,
                                                          const int* __restrict__ offe, const float* __restrict__ dl,
                                                          int k, int d, int E, float* __restrict__ part) {
-  const int e = blockIdx.x, sp = blockIdx.z;
+  const int e = blockIdx.x, sp = blockIdx.z, split = gridDim.z;
   const int col = (blockIdx.y * 256 + threadIdx.x) * 4;
   if (col >= d) return;
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
   const int lo = offe[e], n = offe[e + 1] - lo;
-  const int per = (n + DR_SPLIT - 1) / DR_SPLIT;
+  const int per = (n + split - 1) / split;
   const int p_lo = lo + sp * per, p_hi = min(lo + n, p_lo + per);
   for (int p0 = p_lo; p0 < p_hi; p0 += 8) {
     half4 v[8];
@@ -354,80 +353,111 @@ void rankexpand(int r, const half_t* t, const half_t* P, int L, const int* offe,
 }
 
 // Factor gradients: part[sp][e][rho][n] = sum over the sorted pair rows p of expert e in
-// split sp of t[p][rho] * D[row(p)][n], rho < R; row(p) = p (D in sorted pair order) or
+// run sp of t[p][rho] * D[row(p)][n], rho < R; row(p) = p (D in sorted pair order) or
 // permm[p] / k (D = x or dy); a gate factor is folded into t beforehand (bw_scale_kernel).
-// Products are exact (FP16 x FP16), sums FP32.  The rows of an expert are cut
-// into RG_SPLIT equal runs, added in row order; bw_rankgrad_finish_kernel adds the runs in
-// order.  One thread owns C consecutive columns n.  Block (ceil(L / (256 C)), E, RG_SPLIT).
-constexpr int RG_SPLIT = 4;
-template <int R, int C>
+// Products are exact (FP16 x FP16), sums FP32.  The rows of an expert are cut into `split`
+// equal runs, added in row order; bw_rankgrad_finish_kernel adds the runs in order.
+// Bound by the stream of D rows.  A wavefront takes 128 columns and 32 rows at a time: lane
+// (c, q) loads rows 8q .. 8q + 7 of the eight columns 8c .. 8c + 7, so that transposing its own
+// 8 x 8 values in registers gives the B operands of the matrix cores (eight rows of one
+// column), and the accumulators leave room for the next 32 rows in flight.  The t rows
+// are transposed through LDS, wavefront by wavefront.
+// Block (ceil(L / 512), E, split).
+template <int R>
 __global__ __launch_bounds__(256) void bw_rankgrad_kernel(const half_t* __restrict__ t, const half_t* __restrict__ D,
                                                           int L, const int* __restrict__ offe,
                                                           const int* __restrict__ permm, int k, int gather,
                                                           int E, float* __restrict__ part) {
-  typedef _Float16 halfC __attribute__((ext_vector_type(C)));
-  const int e = blockIdx.y, sp = blockIdx.z;
-  const int col = (blockIdx.x * 256 + threadIdx.x) * C;
-  if (col >= L) return;
+  constexpr int RB = R == 32 ? 2 : 1;   // 16-row blocks of rank rows
+  __shared__ __attribute__((aligned(16))) half_t st[4][RB * 16][40];
+  const int e = blockIdx.y, sp = blockIdx.z, split = gridDim.z;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 15, q = lane >> 4;
+  const int col = (blockIdx.x * 4 + wave) * 128 + 8 * c, colc = min(col, L - 8);
+  if (col - 8 * c >= L) return;
   const int lo = offe[e], n = offe[e + 1] - lo;
-  const int per = (n + RG_SPLIT - 1) / RG_SPLIT;
-  const int p0 = lo + sp * per, p1 = min(lo + n, p0 + per);
-  float acc[R][C];
+  const int per = ((n + split - 1) / split + 31) / 32 * 32;
+  const int p0 = min(lo + n, lo + sp * per), p1 = min(lo + n, p0 + per);
+  float4v acc[RB][8];
 #pragma unroll
-  for (int rho = 0; rho < R; ++rho)
+  for (int b = 0; b < RB; ++b)
 #pragma unroll
-    for (int i = 0; i < C; ++i) acc[rho][i] = 0.f;
-  // Four rows per batch, multiplied in pairs of rows: acc += t[p][rho] D[p][n] +
-  // t[p+1][rho] D[p+1][n] is one v_dot2_f32_f16.  The loads of the next batch are issued
-  // before the current one is used, so that a wavefront keeps eight rows in flight.
-  auto load = [&](int pb, halfC (&v)[4]) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int p = min(pb + u, p1 - 1);
-      const size_t row = gather ? (size_t)(permm[p] / k) : (size_t)p;
-      v[u] = *(const halfC*)(D + row * L + col);
-    }
+    for (int i = 0; i < 8; ++i) acc[b][i] = float4v{0.f, 0.f, 0.f, 0.f};
+  // source row of sorted row pb + lane % 32; rows past the run repeat its last one
+  auto index = [&](int pb) {
+    const int p = min(pb + (lane & 31), p1 - 1);
+    return gather ? permm[p] / k : p;
   };
-  halfC cur[4], nxt[4];
-  if (p0 < p1) load(p0, cur);
-  for (int pb = p0; pb < p1; pb += 4) {
-    if (pb + 4 < p1) load(pb + 4, nxt);
-    const half_t* tp[4];
+  auto load = [&](int pb, int my, half8 (&v)[8], half8 (&tv)[RB]) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (pb + u >= p1) cur[u] = halfC{};          // rows past the run contribute nothing
-      tp[u] = t + (size_t)min(pb + u, p1 - 1) * RP;
+    for (int i = 0; i < 8; ++i) v[i] = *(const half8*)(D + (size_t)__shfl(my, 8 * q + i, 64) * L + colc);
+    const int p = min(pb + (lane >> 1), p1 - 1);
+#pragma unroll
+    for (int b = 0; b < RB; ++b) tv[b] = *(const half8*)(t + (size_t)p * RP + 16 * b + 8 * (lane & 1));
+  };
+  const half8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+  half8 cur[8], nxt[8], tc[RB], tn[RB];
+  int ahead = 0;   // row indices of the batch after the one in flight
+  if (p0 < p1) {
+    load(p0, index(p0), cur, tc);
+    ahead = index(p0 + 32);
+  }
+  for (int pb = p0; pb < p1; pb += 32) {
+    if (pb + 32 < p1) {
+      load(pb + 32, ahead, nxt, tn);
+      ahead = index(pb + 64);
+    }
+    if (pb + 32 > p1) {   // rows past the run contribute nothing
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (pb + 8 * q + i >= p1) cur[i] = zero;
+      if (pb + (lane >> 1) >= p1)
+#pragma unroll
+        for (int b = 0; b < RB; ++b) tc[b] = zero;
     }
 #pragma unroll
-    for (int u = 0; u < 4; u += 2) {
-      half2v dv[C];
+    for (int b = 0; b < RB; ++b)
 #pragma unroll
-      for (int i = 0; i < C; ++i) dv[i] = half2v{cur[u][i], cur[u + 1][i]};
+      for (int u = 0; u < 8; ++u) st[wave][16 * b + 8 * (lane & 1) + u][lane >> 1] = tc[b][u];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    half8 fa[RB];
 #pragma unroll
-      for (int rho = 0; rho < R; ++rho) {
-        const half2v tv = half2v{tp[u][rho], tp[u + 1][rho]};
+    for (int b = 0; b < RB; ++b) fa[b] = *(const half8*)&st[wave][16 * b + c][8 * q];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int i = 0; i < C; ++i) acc[rho][i] = __builtin_amdgcn_fdot2(tv, dv[i], acc[rho][i], false);
-      }
+    for (int i = 0; i < 8; ++i) {
+      half8 fb;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) fb[u] = cur[u][i];
+#pragma unroll
+      for (int b = 0; b < RB; ++b) acc[b][i] = mfma32(fa[b], fb, acc[b][i]);
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) cur[u] = nxt[u];
-  }
+    for (int i = 0; i < 8; ++i) cur[i] = nxt[i];
 #pragma unroll
-  for (int rho = 0; rho < R; ++rho) {
-    float* dst = part + (((size_t)sp * E + e) * R + rho) * L + col;
-#pragma unroll
-    for (int i = 0; i < C; i += 4) *(float4v*)(dst + i) = float4v{acc[rho][i], acc[rho][i + 1], acc[rho][i + 2], acc[rho][i + 3]};
+    for (int b = 0; b < RB; ++b) tc[b] = tn[b];
   }
+  if (col >= L) return;
+#pragma unroll
+  for (int b = 0; b < RB; ++b)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int rho = 16 * b + 4 * q + v;
+      if (rho >= R) continue;
+      float* dst = part + (((size_t)sp * E + e) * R + rho) * L + col;
+      *(float4v*)dst = float4v{acc[b][0][v], acc[b][1][v], acc[b][2][v], acc[b][3][v]};
+      *(float4v*)(dst + 4) = float4v{acc[b][4][v], acc[b][5][v], acc[b][6][v], acc[b][7][v]};
+    }
 }
 
 // out[i] = part[0][i] + part[1][i] + ... in split order, i < n (a multiple of 4)
-__global__ __launch_bounds__(256) void bw_rankgrad_finish_kernel(const float* __restrict__ part, size_t n,
+__global__ __launch_bounds__(256) void bw_rankgrad_finish_kernel(const float* __restrict__ part, size_t n, int split,
                                                                  float* __restrict__ out) {
   const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i >= n) return;
   float4v acc = *(const float4v*)(part + i);
-  for (int sp = 1; sp < RG_SPLIT; ++sp) acc += *(const float4v*)(part + sp * n + i);
+  for (int sp = 1; sp < split; ++sp) acc += *(const float4v*)(part + sp * n + i);
   *(float4v*)(out + i) = acc;
 }
 
@@ -444,14 +474,27 @@ __global__ __launch_bounds__(256) void bw_scale_kernel(half_t* __restrict__ t, c
   *v = x;
 }
 
+// Runs an expert's rows are cut into (a power of two): 4, and more while the launch has fewer than
+// 1024 workgroups.  Above 16 the partial sums cost more than the shorter runs save.
+inline int row_runs(int E, int L, int cols) {
+  int s = 4;
+  while (s < 16 && (size_t)s * E * ((L + cols - 1) / cols) < 1024) s *= 2;
+  return s;
+}
+constexpr int RG_COLS = 512, DR_COLS = 1024;   // columns of a workgroup
+
+void finish(const float* part, size_t n, int split, float* out, hipStream_t st) {
+  hipLaunchKernelGGL(bw_rankgrad_finish_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, st, part, n, split,
+                     out);
+}
+
 template <int R>
 void rankgrad_r(const half_t* t, const half_t* D, int L, const int* offe, const int* permm, int k, int gather,
                 int E, float* part, float* out, hipStream_t st) {
-  constexpr int C = R >= 32 ? 4 : 8;
-  hipLaunchKernelGGL((bw_rankgrad_kernel<R, C>), dim3((L + 256 * C - 1) / (256 * C), E, RG_SPLIT), dim3(256), 0, st, t,
-                     D, L, offe, permm, k, gather, E, part);
-  const size_t n = (size_t)E * R * L;
-  hipLaunchKernelGGL(bw_rankgrad_finish_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, st, part, n, out);
+  const int split = row_runs(E, L, RG_COLS);
+  hipLaunchKernelGGL(bw_rankgrad_kernel<R>, dim3((L + RG_COLS - 1) / RG_COLS, E, split), dim3(256), 0, st, t, D, L, offe,
+                     permm, k, gather, E, part);
+  finish(part, (size_t)E * R * L, split, out, st);
 }
 
 void rankgrad(int r, const half_t* t, const half_t* D, int L, const int* offe, const int* permm, int k, int gather,
@@ -526,7 +569,10 @@ cmoe_bw_layout cmoe_backward_layout(const cmoe_dims& dm, int T) {
   L.dyct = take(sizeof(half_t) * d * Tp);
   L.dhst = take(sizeof(half_t) * f * Tp);
   L.agt = take(sizeof(half_t) * f * Tp);
-  L.rgpart = take(sizeof(float) * RG_SPLIT * E * r * (f > d ? f : d));
+  const size_t runs_f = row_runs((int)E, dm.d_ff, RG_COLS) * f, runs_d = row_runs((int)E, dm.d, RG_COLS) * d;
+  const size_t runs_r = row_runs((int)E, dm.d, DR_COLS) * d;
+  const size_t runs = r * (runs_f > runs_d ? runs_f : runs_d);
+  L.rgpart = take(sizeof(float) * E * (runs > runs_r ? runs : runs_r));
   L.total = off;
   return L;
 }
@@ -638,11 +684,10 @@ hipError_t launch_backward(const cmoe_dims& dm, const cmoe_weights& w, const hal
     transpose(H(L.ag16), f, f, ssrc_c, nullptr, Tpad, H(L.agt), st);
     BW_CHECK(hipGetLastError());
   }
-  static_assert(DR_SPLIT == RG_SPLIT, "the finish kernel adds RG_SPLIT runs");
-  hipLaunchKernelGGL(bw_drouter_kernel, dim3(E, (d / 4 + 255) / 256, DR_SPLIT), dim3(256), 0, st, x, permm, offe, dl,
+  const int runs = row_runs(E, d, DR_COLS);
+  hipLaunchKernelGGL(bw_drouter_kernel, dim3(E, (d + DR_COLS - 1) / DR_COLS, runs), dim3(256), 0, st, x, permm, offe, dl,
                      k, d, E, F(L.rgpart));
-  hipLaunchKernelGGL(bw_rankgrad_finish_kernel, dim3((unsigned)(((size_t)E * d / 4 + 255) / 256)), dim3(256), 0, st,
-                     (const float*)F(L.rgpart), (size_t)E * d, out.d_router_expert);
+  finish(F(L.rgpart), (size_t)E * d, runs, out.d_router_expert, st);
   // base gradients: contraction over the tokens of a cluster
   // (operands in the blocked layout [Tpad / 32][rows][32]: row stride 32, block stride rows * 32)
   BW_CHECK(launch_gemm_plain(H(L.xct), 0, 32, d, H(L.dhst), 32, I(L.gidx_f), 1, Tpad, I(L.offx_f), G, G * f, krc,
