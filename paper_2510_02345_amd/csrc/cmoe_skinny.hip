@@ -39,7 +39,6 @@ __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-constexpr int SK_COLS = 16;                         // tokens per pass over a cluster (layer path)
 constexpr int SK_A_BYTES = SK_ROWS * 128;           // weight rows x 64 elements
 // Ring geometry of one wavefront for COLS token rows per pass (16, or 32 when the caller
 // has more than 16 rows per group: all 32 accumulator columns are then distinct).
@@ -157,13 +156,13 @@ __device__ __forceinline__ void skinny_reduce(float* red, int wave, int lane, co
 struct SkinnyTile {
   int c, n0, m0, m_end;
 };
-// Stream workgroup `id` of a launch of nx row blocks x G clusters x passes (row block
-// fastest); a pass covers `cols` tokens of the cluster, m_end is the end of the pass.
+// Stream workgroup `id` of a launch of nx row blocks x slots (row block fastest).  A slot is a
+// pass over `cols` tokens of a cluster, m_end the end of the pass.  COMPACT (G <= 64): the slots
+// are the passes that exist, found from the offsets; else slot = pass * G + cluster.
+template <bool COMPACT>
 __device__ __forceinline__ bool skinny_tile(const int* offsets, int id, int nx, int G, int cols, SkinnyTile& t) {
   int xb = id % nx;
-  const int yz = id / nx;
-  t.c = yz % G;
-  const int pass = yz / G;
+  const int slot = id / nx;
   // Workgroups are dealt round-robin to the 8 XCDs.  The INT4 factor rows are 128-byte
   // lines shared by 8 neighbouring row blocks, so inside every run of 64 blocks the 8
   // workgroups that land on one XCD take 8 neighbouring row blocks: each line is then
@@ -171,8 +170,14 @@ __device__ __forceinline__ bool skinny_tile(const int* offsets, int id, int nx, 
   // index modulo 8.)
   if ((nx & 7) == 0 && xb < (nx & ~63)) xb = (xb & ~63) + ((xb & 7) << 3) + ((xb >> 3) & 7);
   t.n0 = xb * SK_ROWS;
-  const int lo = offsets[t.c], hi = offsets[t.c + 1];
-  t.m0 = lo + pass * cols;
+  int hi;
+  if (COMPACT) {
+    if (!find_tile(offsets, G, cols, slot, t.c, t.m0, hi)) return false;
+  } else {
+    t.c = slot % G;
+    hi = offsets[t.c + 1];
+    t.m0 = offsets[t.c] + slot / G * cols;
+  }
   t.m_end = min(hi, t.m0 + cols);
   return t.m0 < hi;
 }
@@ -320,7 +325,7 @@ struct SideArgs {
 // or NULL for the identity.  w_blk = 0: W[c] is row-major [N][Kc]; otherwise W[c] is stored
 // as [Kc / 32][N][32] and w_blk = N * 32 (the re-tiled copy of the bases): an 8-row load is
 // then two contiguous 256-byte pieces instead of eight 128-byte pieces a row apart.
-template <int SIDE, int COLS, bool NT>
+template <int SIDE, int COLS, bool NT, bool COMPACT>
 __global__ __launch_bounds__(256, SkRing<COLS>::OCC) void skinny_base_kernel(const half_t* __restrict__ X,
                                                                   const int* __restrict__ gather,
                                                                   const half_t* __restrict__ W,
@@ -346,7 +351,7 @@ __global__ __launch_bounds__(256, SkRing<COLS>::OCC) void skinny_base_kernel(con
   __shared__ __attribute__((aligned(1024))) char smem[RED_BYTES > RINGS ? RED_BYTES : RINGS];
   float* red = (float*)smem;
   SkinnyTile t;
-  if (!skinny_tile(offsets, (int)blockIdx.x - (SIDE != SIDE_NONE ? sa.n_side : 0), nx, G, COLS, t)) return;
+  if (!skinny_tile<COMPACT>(offsets, (int)blockIdx.x - (SIDE != SIDE_NONE ? sa.n_side : 0), nx, G, COLS, t)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, fr = lane & 31, h = lane >> 5;
   const int wv = __builtin_amdgcn_readfirstlane(wave);
   const unsigned smem_lds = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
@@ -621,28 +626,37 @@ static bool stream_once(const cmoe_dims& dm) {
   return (size_t)dm.G * dm.d * dm.d_ff * sizeof(half_t) > ((size_t)96 << 20);
 }
 
+// One weight stream of the layer.  A workgroup takes 16 tokens of a cluster, or 32 where the
+// expected load of a cluster is above 12: then many clusters would be read twice (203 tokens on 8
+// clusters of 2048 x 8192: 93 -> 65 us per stream), below it the wider ring costs more than the
+// few second reads (two workgroups per CU instead of three).
+template <int SIDE>
+hipError_t launch_stream(const cmoe_dims& dm, const half_t* X, const int* gather, const half_t* W, const int* offsets, int N,
+                         int Kc, half_t* out, int T, long w_blk, const SideArgs& sa, hipStream_t st) {
+  const int nx = N / SK_ROWS, cols = T > 12 * dm.G ? 32 : 16;
+  const int slots = T < dm.G + T / cols ? T : dm.G + T / cols;   // at most: a slot holds a token, all but G of them `cols`
+  const dim3 grid((unsigned)nx * slots + sa.n_side), block(256);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, grid, block, 0, st, X, gather, W, offsets, N, Kc, out, nx, dm.G, w_blk, sa);
+  };
+  if (cols == 32) {
+    if (stream_once(dm)) go(skinny_base_kernel<SIDE, 32, true, true>); else go(skinny_base_kernel<SIDE, 32, false, true>);
+  } else {
+    if (stream_once(dm)) go(skinny_base_kernel<SIDE, 16, true, true>); else go(skinny_base_kernel<SIDE, 16, false, true>);
+  }
+  return hipGetLastError();
+}
+
 // Hb = W1_base(c) x for every sorted row; with t1 != NULL the t1 = V1 x jobs ride along.
 hipError_t launch_skinny_hb(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int x_div, int T,
                             const int* perm, const int* offsets, const int* expert_idx, half_t* t1, half_t* hb,
                             hipStream_t st) {
-  const int passes = (T + SK_COLS - 1) / SK_COLS, nx = dm.d_ff / SK_ROWS;
-  const unsigned n_stream = (unsigned)nx * dm.G * passes;
-  dim3 block(256);
   SideArgs sa{};
   sa.x_div = x_div > 1 ? x_div : 1;
   // the re-tiled copy of W1 when the caller keeps one, else the canonical array
   const half_t* w1 = w.packed ? (const half_t*)((const char*)w.packed + cmoe_packed(dm).w1) : (const half_t*)w.w1_base;
   const long w_blk = w.packed ? (long)dm.d_ff * 32 : 0;
-  const bool nt = stream_once(dm);
-  if (t1 == nullptr) {
-    if (nt)
-      hipLaunchKernelGGL((skinny_base_kernel<SIDE_NONE, SK_COLS, true>), dim3(n_stream), block, 0, st, x, perm, w1,
-                         offsets, dm.d_ff, dm.d, hb, nx, dm.G, w_blk, sa);
-    else
-      hipLaunchKernelGGL((skinny_base_kernel<SIDE_NONE, SK_COLS, false>), dim3(n_stream), block, 0, st, x, perm, w1,
-                         offsets, dm.d_ff, dm.d, hb, nx, dm.G, w_blk, sa);
-    return hipGetLastError();
-  }
+  if (t1 == nullptr) return launch_stream<SIDE_NONE>(dm, x, perm, w1, offsets, dm.d_ff, dm.d, hb, T, w_blk, sa, st);
   sa.x = x;
   sa.perm = perm;
   sa.expert_idx = expert_idx;
@@ -657,13 +671,7 @@ hipError_t launch_skinny_hb(const cmoe_dims& dm, const cmoe_weights& w, const ha
   sa.n_exp = dm.G * dm.K;
   sa.n_jobs = T * dm.k;
   sa.n_side = (sa.n_jobs + 7) & ~7;
-  if (nt)
-    hipLaunchKernelGGL((skinny_base_kernel<SIDE_T1, SK_COLS, true>), dim3(n_stream + sa.n_side), block, 0, st, x, perm,
-                       w1, offsets, dm.d_ff, dm.d, hb, nx, dm.G, w_blk, sa);
-  else
-    hipLaunchKernelGGL((skinny_base_kernel<SIDE_T1, SK_COLS, false>), dim3(n_stream + sa.n_side), block, 0, st, x, perm,
-                       w1, offsets, dm.d_ff, dm.d, hb, nx, dm.G, w_blk, sa);
-  return hipGetLastError();
+  return launch_stream<SIDE_T1>(dm, x, perm, w1, offsets, dm.d_ff, dm.d, hb, T, w_blk, sa, st);
 }
 
 hipError_t launch_skinny_resid_up(const cmoe_dims& dm, const cmoe_weights& w, int T, const int* perm,
@@ -688,23 +696,12 @@ hipError_t launch_skinny_resid_up(const cmoe_dims& dm, const cmoe_weights& w, in
 hipError_t launch_skinny_down(const cmoe_dims& dm, const cmoe_weights& w, const half_t* a, int T, const int* offsets,
                               half_t* y_base_sorted, const int* perm, const int* expert_idx, const float* gate,
                               const float* spart, int n_parts, float* ures, hipStream_t st) {
-  const int passes = (T + SK_COLS - 1) / SK_COLS, nx = dm.d / SK_ROWS;
-  const unsigned n_stream = (unsigned)nx * dm.G * passes;
-  dim3 block(256);
   SideArgs sa{};
   sa.x_div = 1;
   const half_t* w2 = w.packed ? (const half_t*)((const char*)w.packed + cmoe_packed(dm).w2) : (const half_t*)w.w2_base;
   const long w_blk = w.packed ? (long)dm.d * 32 : 0;
-  const bool nt = stream_once(dm);
-  if (ures == nullptr) {
-    if (nt)
-      hipLaunchKernelGGL((skinny_base_kernel<SIDE_NONE, SK_COLS, true>), dim3(n_stream), block, 0, st, a,
-                         (const int*)nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted, nx, dm.G, w_blk, sa);
-    else
-      hipLaunchKernelGGL((skinny_base_kernel<SIDE_NONE, SK_COLS, false>), dim3(n_stream), block, 0, st, a,
-                         (const int*)nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted, nx, dm.G, w_blk, sa);
-    return hipGetLastError();
-  }
+  if (ures == nullptr)
+    return launch_stream<SIDE_NONE>(dm, a, nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted, T, w_blk, sa, st);
   sa.perm = perm;
   sa.expert_idx = expert_idx;
   sa.gate = gate;
@@ -721,13 +718,7 @@ hipError_t launch_skinny_down(const cmoe_dims& dm, const cmoe_weights& w, const 
   sa.n_parts = n_parts;
   sa.n_jobs = T * ((dm.d + 2047) / 2048);
   sa.n_side = (sa.n_jobs + 7) & ~7;
-  if (nt)
-    hipLaunchKernelGGL((skinny_base_kernel<SIDE_URES, SK_COLS, true>), dim3(n_stream + sa.n_side), block, 0, st, a,
-                       (const int*)nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted, nx, dm.G, w_blk, sa);
-  else
-    hipLaunchKernelGGL((skinny_base_kernel<SIDE_URES, SK_COLS, false>), dim3(n_stream + sa.n_side), block, 0, st, a,
-                       (const int*)nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted, nx, dm.G, w_blk, sa);
-  return hipGetLastError();
+  return launch_stream<SIDE_URES>(dm, a, nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted, T, w_blk, sa, st);
 }
 
 // out[p][n] = sum_k W[g][n][k] X[p][k] for the rows p of group g (offsets [n_groups + 1],
@@ -743,17 +734,17 @@ hipError_t launch_skinny_rows(const half_t* X, const half_t* W, const int* offse
   if (max_rows > 16) {
     const int passes = (max_rows + 31) / 32;
     if (nt)
-      hipLaunchKernelGGL((skinny_base_kernel<SIDE_NONE, 32, true>), dim3((unsigned)nx * n_groups * passes), dim3(256), 0,
+      hipLaunchKernelGGL((skinny_base_kernel<SIDE_NONE, 32, true, false>), dim3((unsigned)nx * n_groups * passes), dim3(256), 0,
                          st, X, (const int*)nullptr, W, offsets, N, Kc, out, nx, n_groups, 0L, sa);
     else
-      hipLaunchKernelGGL((skinny_base_kernel<SIDE_NONE, 32, false>), dim3((unsigned)nx * n_groups * passes), dim3(256), 0,
+      hipLaunchKernelGGL((skinny_base_kernel<SIDE_NONE, 32, false, false>), dim3((unsigned)nx * n_groups * passes), dim3(256), 0,
                          st, X, (const int*)nullptr, W, offsets, N, Kc, out, nx, n_groups, 0L, sa);
   } else {
     if (nt)
-      hipLaunchKernelGGL((skinny_base_kernel<SIDE_NONE, 16, true>), dim3((unsigned)nx * n_groups), dim3(256), 0, st, X,
+      hipLaunchKernelGGL((skinny_base_kernel<SIDE_NONE, 16, true, false>), dim3((unsigned)nx * n_groups), dim3(256), 0, st, X,
                          (const int*)nullptr, W, offsets, N, Kc, out, nx, n_groups, 0L, sa);
     else
-      hipLaunchKernelGGL((skinny_base_kernel<SIDE_NONE, 16, false>), dim3((unsigned)nx * n_groups), dim3(256), 0, st, X,
+      hipLaunchKernelGGL((skinny_base_kernel<SIDE_NONE, 16, false, false>), dim3((unsigned)nx * n_groups), dim3(256), 0, st, X,
                          (const int*)nullptr, W, offsets, N, Kc, out, nx, n_groups, 0L, sa);
   }
   return hipGetLastError();

@@ -1,0 +1,34 @@
+"""The weight streams for few tokens (16 and 32 tokens of a cluster per workgroup, slots found from the
+offsets), over the rule's edge, single tokens, empty and overfull clusters, against the oracle."""
+import numpy as np
+import pytest
+
+import cmoe_inputs as ci
+from oracle import cmoe_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("G,T", [(1, 1), (1, 12), (1, 13), (2, 24), (2, 25), (2, 256), (5, 60), (5, 61), (5, 177),
+                                 (16, 256), (16, 193), (64, 3), (64, 255)])
+@pytest.mark.parametrize("skew", [0.0, 100.0])
+def test_weight_streams(G, T, skew):
+    import torch
+
+    import paper_2510_02345_amd as cm
+    cfg = ci.small_config("stream", T=T, d=192, d_ff=128, G=G, K=4, r=8, k=2, q=32, seed=T + G)
+    print(f"case {cfg} skew {skew}", flush=True)
+    w = ci.generate(cfg)
+    if skew:   # every token in the last cluster
+        w["cluster_bias"] = np.zeros(G, dtype=np.float32)
+        w["cluster_bias"][-1] = skew
+    ref = orc.forward_naive(w, w["x"], cfg.K, cfg.k, cfg.q)
+    for pack in (True, False):
+        layer = cm.Layer(cfg.d, cfg.d_ff, G, cfg.K, cfg.r, cfg.k, cfg.q, w, T, pack=pack)
+        out = layer.forward(torch.from_numpy(w["x"]).to("cuda:0"))
+        torch.cuda.synchronize()
+        for n in ("cluster_id", "expert_idx", "perm", "offsets"):
+            assert np.array_equal(out[n].cpu().numpy(), ref[n]), n
+        m = orc.error_metrics(out["y"].cpu().numpy(), ref["y"])   # the layer's bars (FP16 operands and results)
+        assert m["max_over_rms"] <= 1e-2 and m["mean_rel"] <= 2e-3, m
+        layer.close()
