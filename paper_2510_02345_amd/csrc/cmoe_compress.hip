@@ -448,10 +448,14 @@ __device__ __forceinline__ float cmp_nib(const uint8_t* row, int n) {
 // A workgroup takes 64 rows and CE_CT consecutive 64-column tiles of one expert: the U panel
 // of its rows is decoded once, the V panel per column tile, all global loads issued before
 // the first use; epart has one entry per workgroup.  A one-dimensional grid of
-// 8 * ceil(G * tiles / 8) * K workgroups.  The kernel is bound by the vector ALUs, not by
-// memory: rebuilding U V costs r FP32 FMAs per element (34 GFLOP for 64 experts of
-// 8192 x 2048 at r = 16, about 0.5 ms of issue) next to 2.4 GB of reads.
-constexpr int CE_CT = 4;
+// 8 * ceil(G * tiles / 8) * K workgroups.  U V takes r FP32 products per element (34 GFLOP for 64
+// experts of 8192 x 2048 at r = 16) next to 2.4 GB of reads, on the FP32 matrix instruction:
+// exact products, FP32 sums, twice the rate of the vector ALUs and two LDS values for 1024 products (FMAs
+// per thread wanted nine for eight and were bound by the LDS): 919 -> 778 us.
+// Columns are its rows (A = V), rows its columns (B = U); a wavefront owns 16 rows, and tile row
+// 4 q + i of block a holds column 8 q + 4 a + i of 32, so that blocks 0 and 1 give lane (t, q) the
+// eight consecutive columns 8 q .. 8 q + 7 of row t, as it loads them from W and base.
+constexpr int CE_CT = 4, CE_LD = 68;   // row pitch of the panels: at most two lanes of a fragment read on a bank
 __global__ __launch_bounds__(256) void cmp_error_kernel(const half_t* __restrict__ W, const half_t* __restrict__ base,
                                                         const uint8_t* __restrict__ u_q,
                                                         const half_t* __restrict__ u_s,
@@ -459,8 +463,8 @@ __global__ __launch_bounds__(256) void cmp_error_kernel(const half_t* __restrict
                                                         const half_t* __restrict__ v_s, int G, int K, int out_d, int in_d,
                                                         int r, int q, int tiles_x, int tiles_y,
                                                         float* __restrict__ epart) {
-  __shared__ float us[32][64];                               // U[rho][o0 + 0..63]
-  __shared__ __attribute__((aligned(16))) float vs[32][64];  // V[rho][i0 + 0..63]
+  __shared__ float us[32][CE_LD];   // U[rho][o0 + 0..63], zero from row r to the next multiple of 4
+  __shared__ float vs[32][CE_LD];   // V[rho][i0 + 0..63], likewise
   __shared__ float red[4][2];
   // Workgroups are dealt round-robin to the 8 XCDs; the K experts of one (cluster, tile) take
   // K consecutive workgroups of ONE XCD, so that the base tile they share is fetched from
@@ -471,7 +475,7 @@ __global__ __launch_bounds__(256) void cmp_error_kernel(const half_t* __restrict
   const int c = tc / per_c, e = c * K + local % K;
   const int tile_y = (tc % per_c) / tiles_x, tile_x = (tc % per_c) % tiles_x;
   const int o0 = tile_y * 64, tid = threadIdx.x;
-  const int row0 = tid >> 3, ch = tid & 7;
+  const int t16 = tid & 15, quad = (tid >> 4) & 3, row = (tid >> 6) * 16 + t16;
   const size_t me = (size_t)out_d * in_d;
   // Panels: thread tid < 8 r owns the 8 codes (one 32-bit word) of rank row tid / 8 at columns
   // 8 (tid % 8) .. + 7 of a 64-column tile and their scale (one scale when q is a multiple of
@@ -481,7 +485,7 @@ __global__ __launch_bounds__(256) void cmp_error_kernel(const half_t* __restrict
   const int prho = tid >> 3, pwd = tid & 7;
   const bool powner = words && prho < r;
   const size_t prow = (size_t)e * r + (powner ? prho : 0);
-  auto put = [&](float (*dst)[64], unsigned w, float sc) {
+  auto put = [&](float (*dst)[CE_LD], unsigned w, float sc) {
 #pragma unroll
     for (int b2 = 0; b2 < 4; ++b2) {
       const unsigned byte = (w >> (8 * b2)) & 0xffu;
@@ -508,11 +512,13 @@ __global__ __launch_bounds__(256) void cmp_error_kernel(const half_t* __restrict
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const size_t off = (size_t)(o0 + row0 + 32 * u) * in_d + (in ? i0 : 0) + ch * 8;
+      const size_t off = (size_t)(o0 + row) * in_d + (in ? i0 : 0) + 32 * u + quad * 8;
       w8[ct][u] = *(const half8*)(W + (size_t)e * me + off);
       b8[ct][u] = *(const half8*)(base + (size_t)c * me + off);
     }
   }
+  const int r4 = (r + 3) & ~3;
+  for (int idx = tid; idx < (r4 - r) * 64; idx += 256) us[r + idx / 64][idx % 64] = vs[r + idx / 64][idx % 64] = 0.f;
   if (words) {
     if (powner) put(us, uw, usc);
   } else {
@@ -538,29 +544,25 @@ __global__ __launch_bounds__(256) void cmp_error_kernel(const half_t* __restrict
       }
     }
     __syncthreads();   // us (first tile) and vs are complete
+    float4v uv[2][2] = {};   // [half of the 64 columns][block]
+    for (int rho = 0; rho < r4; rho += 4) {
+      const float uo = us[rho + quad][row];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int row = row0 + 32 * u;
-      float uv[8];
+      for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) uv[i] = 0.f;
-      for (int rho = 0; rho < r; ++rho) {
-        const float uo = us[rho][row];
-        const float4v va = *(const float4v*)&vs[rho][ch * 8], vb = *(const float4v*)&vs[rho][ch * 8 + 4];
+        for (int a = 0; a < 2; ++a)
+          uv[u][a] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+              vs[rho + quad][32 * u + 8 * (t16 >> 2) + 4 * a + (t16 & 3)], uo, uv[u][a], 0, 0, 0);
+    }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          uv[i] = fmaf(uo, va[i], uv[i]);
-          uv[4 + i] = fmaf(uo, vb[i], uv[4 + i]);
-        }
-      }
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const float w = (float)w8[ct][u][i];
-        const float dv = w - (float)b8[ct][u][i] - uv[i];
+        const float dv = w - (float)b8[ct][u][i] - uv[u][i >> 2][i & 3];
         se = fmaf(dv, dv, se);
         sw = fmaf(w, w, sw);
       }
-    }
   }
   float v[2] = {se, sw};
 #pragma unroll

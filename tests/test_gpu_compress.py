@@ -93,6 +93,29 @@ def test_reconstruction_error_of_a_given_stored_form():
         assert float(err[e]) == pytest.approx(want, rel=1e-4)
 
 
+# ranks off the matrix instruction's four rows, one and several column tiles per workgroup, a
+# ragged last one, group lengths with and without whole code words
+@pytest.mark.parametrize("r,q,out_d,in_d", [(1, 32, 64, 64), (3, 2, 128, 320), (7, 4, 64, 576), (13, 64, 192, 256),
+                                            (30, 32, 64, 128), (32, 64, 128, 640)])
+def test_reconstruction_error_at_odd_ranks_and_widths(r, q, out_d, in_d):
+    import paper_2510_02345_amd as cm
+    G, K = 3, 2
+    print(f"case r={r} q={q} {out_d}x{in_d}", flush=True)
+    W = ci.generate_dense_experts(G, K, out_d, in_d, rank=4, residual_rel=0.2, noise_rel=0.02, seed=73 + r)
+    base = orc.base_mean(W, G, K)
+    rng = np.random.default_rng(74 + r)
+    uq, us = ci.quantize_int4(rng.standard_normal((G * K, r, out_d)) * 0.05, q)
+    vq, vs = ci.quantize_int4(rng.standard_normal((G * K, r, in_d)) * 0.05, q)
+    err = cm.reconstruction_error(_dev(W), _dev(base), _dev(uq), _dev(us), _dev(vq), _dev(vs), G, K, r, q)
+    _sync()
+    for e in range(G * K):
+        U = orc.dequant_int4(uq[e], us[e], q).T
+        V = orc.dequant_int4(vq[e], vs[e], q)
+        want = orc.reconstruction_error(W[e], base[e // K], U, V)
+        # FP32 sums of r products and of 64 values a lane, halved over the lanes: far below 64 ulp
+        assert float(err[e]) == pytest.approx(want, rel=64 * 2.0 ** -23)
+
+
 CASES = [
     # (name, G, K, out, in, true rank, residual, noise, r, sketch, q)
     ("decaying", 2, 4, 256, 128, 12, 0.3, 0.01, 8, 16, 32),
