@@ -452,8 +452,9 @@ __device__ __forceinline__ float cmp_nib(const uint8_t* row, int n) {
 // the first use; epart has one entry per workgroup.  A one-dimensional grid of
 // 8 * ceil(G * tiles / 8) * K workgroups.  U V takes r FP32 products per element (34 GFLOP for 64
 // experts of 8192 x 2048 at r = 16) next to 2.4 GB of reads, on the FP32 matrix instruction:
-// exact products, FP32 sums, twice the rate of the vector ALUs and two LDS values for 1024 products (FMAs
-// per thread wanted nine for eight and were bound by the LDS): 919 -> 778 us.
+// exact products, FP32 sums, twice the rate of the vector ALUs, and a lane reads two LDS values for
+// its share of 16 products (FMAs per thread wanted nine for eight and were bound by the LDS):
+// 919 -> 778 us.  Panels of all column tiles in LDS behind one barrier cost occupancy: 0.1 ms slower.
 // Columns are its rows (A = V), rows its columns (B = U); a wavefront owns 16 rows, and tile row
 // 4 q + i of block a holds column 8 q + 4 a + i of 32, so that blocks 0 and 1 give lane (t, q) the
 // eight consecutive columns 8 q .. 8 q + 7 of row t, as it loads them from W and base.
