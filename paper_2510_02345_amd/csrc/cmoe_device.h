@@ -73,6 +73,24 @@ __device__ __forceinline__ int pi_row(int rho) {
 // read without conflicts but gives two-way conflicts on every 16-row read.
 __device__ __forceinline__ int swz(int row) { return ((row >> 2) & 3) ^ ((row >> 1) & 2); }
 
+// One 1-KiB direct-to-LDS load: lane l's 16 bytes land at lds_byte + 16 l.  The hardware asks for
+// one wait state between a scalar write of M0 and a load that goes to LDS through it, and the
+// compiler adds none inside an asm block: without the s_nop a load may still use the old M0.
+__device__ __forceinline__ void dma16(const void* g, unsigned lds_byte) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_byte) : "memory");
+}
+// The same with the non-temporal hint: the line is not kept in the caches behind the load.
+// For a matrix that is read once per call and is larger than the last-level cache this is
+// worth 9 % of the whole weight-streaming path (the two base streams go from 6.0 to 6.5-6.7
+// TB/s, and the router, whose rows and tokens are no longer evicted, gets faster too).
+__device__ __forceinline__ void dma16_nt(const void* g, unsigned lds_byte) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(g), "s"(lds_byte) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
 // Inclusive sum over the lanes of a wavefront by data-parallel-primitive moves (no LDS round
 // trips): rows of 16 lanes by shifts, then the row totals broadcast upwards.
 __device__ __forceinline__ int wave_inclusive_sum(int v) {

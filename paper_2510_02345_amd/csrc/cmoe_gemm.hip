@@ -67,15 +67,6 @@ struct TileCtx {
   half_t* smem;
 };
 
-// One 1-KiB direct-to-LDS load: lane l's 16 bytes land at lds_byte + 16 l.
-__device__ __forceinline__ void dma16(const void* g, unsigned lds_byte) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_byte) : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 // Where a tile of a group comes from.
 struct TileSrc {
   const GemmArgs& g;

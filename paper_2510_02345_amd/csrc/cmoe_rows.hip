@@ -93,13 +93,6 @@ struct RowsLds {
   static constexpr int ROWS = NA * 16 + RL_M, STAGE = ROWS * 128, SMEM = NS * STAGE;
   static constexpr int PER_WAVE = (ROWS / 8 + RW_WAVES - 1) / RW_WAVES;   // 1-KiB loads (8 rows) per wavefront and step
 };
-__device__ __forceinline__ void dma16(const void* g, unsigned lds_byte) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_byte) : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
 // acc[a] = rows of block a x the wavefront's 16 tokens.  row_of(i): source row i of the tile (NA * 16
 // weight rows, then the 64 tokens).  Ends with every load consumed; the caller's next use of
 // smem needs a barrier first.

@@ -23,22 +23,6 @@ constexpr int SK_RB = SK_ROWS / 32;  // 32-row blocks per workgroup
 constexpr int SK_OCC = 3;     // workgroups per CU the LDS budget is sized for
 constexpr int SK_WAVES = 4;   // wavefronts splitting the contraction
 
-// One 1-KiB direct-to-LDS load: lane l's 16 bytes land at lds_byte + 16 l.
-__device__ __forceinline__ void dma16(const void* g, unsigned lds_byte) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_byte) : "memory");
-}
-// The same with the non-temporal hint: the line is not kept in the caches behind the load.
-// For a matrix that is read once per call and is larger than the last-level cache this is
-// worth 9 % of the whole weight-streaming path (the two base streams go from 6.0 to 6.5-6.7
-// TB/s, and the router, whose rows and tokens are no longer evicted, gets faster too).
-__device__ __forceinline__ void dma16_nt(const void* g, unsigned lds_byte) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(g), "s"(lds_byte) : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 constexpr int SK_A_BYTES = SK_ROWS * 128;           // weight rows x 64 elements
 // Ring geometry of one wavefront for COLS token rows per pass (16, or 32 when the caller
 // has more than 16 rows per group: all 32 accumulator columns are then distinct).
