@@ -90,6 +90,9 @@ template <int N>
 __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
+// LDS reads and writes of this wavefront completed.  A bare barrier does not imply it: before a
+// stage that was read is refilled by loads that go to LDS, or what was written is read by others.
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // Inclusive sum over the lanes of a wavefront by data-parallel-primitive moves (no LDS round
 // trips): rows of 16 lanes by shifts, then the row totals broadcast upwards.

@@ -172,7 +172,7 @@ __device__ __forceinline__ void tile_big(const GemmArgs& g, const Epi& epi, char
     } else {
       wait_vm<0>();
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wait_lds();
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
@@ -269,7 +269,7 @@ __device__ __forceinline__ void tile_small(const GemmArgs& g, const Epi& epi, ch
       if (st + 1 < steps) {
         // step st + 1 has landed (own loads), then everyone's; every wavefront has left step st - 1
         if (st + NSTG - 2 < steps) wait_vm<(NSTG - 3) * PER>(); else wait_vm<0>();
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        wait_lds();
         __builtin_amdgcn_s_barrier();
         read(nxt, rd);
         if (st + NSTG - 1 < steps) issue(st + NSTG - 1, wr);
@@ -399,8 +399,9 @@ __global__ __launch_bounds__(256, 3) void gemm_thin_kernel(GemmArgs g, Epi epi) 
   int stage = 0, nstage = TL::NS - 1;
   for (int kt = 0; kt < KT; ++kt) {
     // block kt has landed (own loads), then everyone's; the stage refilled below was
-    // read during iteration kt - 1, which every wavefront has left
+    // read during iteration kt - 1, which every wavefront has left with its reads completed
     if (kt + TL::NS - 2 < KT) wait_vm<(TL::NS - 2) * TL::PER_WAVE>(); else wait_vm<0>();
+    wait_lds();
     __builtin_amdgcn_s_barrier();
     if (kt + TL::NS - 1 < KT) issue(kt + TL::NS - 1, nstage);
     const char* sb = smem + stage * TL::STAGE_BYTES + frag;

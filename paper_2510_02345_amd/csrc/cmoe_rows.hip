@@ -124,8 +124,9 @@ __device__ __forceinline__ void rows_product_lds(char* smem, int steps, int wave
   int stage = 0, nstage = RL::NS - 1;
   for (int it = 0; it < steps; ++it) {
     // step it has landed (own loads), then everyone's; the stage refilled below was read in
-    // step it - 1, which every wavefront has left
+    // step it - 1, which every wavefront has left with its reads completed
     if (it + RL::NS - 2 < steps) wait_vm<(RL::NS - 2) * RL::PER_WAVE>(); else wait_vm<0>();
+    wait_lds();
     __builtin_amdgcn_s_barrier();
     if (it + RL::NS - 1 < steps) issue(it + RL::NS - 1, nstage);
     const char* sb = smem + stage * RL::STAGE + t16 * 128;

@@ -94,7 +94,7 @@ __device__ __forceinline__ void skinny_stream(const half_t* wrow, size_t w_strid
 #pragma unroll
       for (int rb = 0; rb < SK_RB; ++rb) acc[rb] = mfma16(fa[rb], fb, acc[rb]);
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the stage has been read: it may be refilled
+    wait_lds();  // the stage has been read: it may be refilled
   };
   issue(it0, 0);
   for (int it = it0; it < it1; it += 2) {

@@ -48,3 +48,27 @@ def test_a_wait_state_between_m0_and_the_load_that_uses_it(kernels):
                 n += 1
                 assert not re.match(r"s_\w+ m0,", a), (name, a, b)
     assert n > 100
+
+
+def _waits_for_lds(i):
+    return i.startswith("s_waitcnt") and "lgkmcnt(0)" in i
+
+
+# The loops that refill a stage of LDS behind a bare barrier: the stage was read an iteration ago, and the
+# barrier is passed only with those reads completed, wherever the compiler puts the products.
+@pytest.mark.parametrize("kernel", ["route_rows_lds_kernel", "t1_rows_kernel", "gemm_thin_kernel"])
+def test_lds_reads_are_complete_before_a_stage_is_refilled(kernels, kernel):
+    n = 0
+    for name, ins in kernels.items():
+        if kernel not in name:
+            continue
+        for at, i in enumerate(ins):
+            if i != "s_barrier":
+                continue
+            # the instructions that run into the barrier from above
+            near = ins[max(at - 6, 0):at]
+            near = near[max((j + 1 for j, w in enumerate(near) if w.startswith("s_branch")), default=0):]
+            if any(re.fullmatch(r"s_waitcnt vmcnt\(\d+\)", w) for w in near):   # the wait for the stage's loads
+                n += 1
+                assert any(_waits_for_lds(w) for w in near), (name, near)
+    assert n
