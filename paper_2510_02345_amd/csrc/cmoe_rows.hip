@@ -378,6 +378,7 @@ __global__ __launch_bounds__(RW_THREADS, 2) void t1_rows_kernel(const half_t* __
     if (wave == 0) es[lane][j] = e0;
     need |= block_mask(e0, r);
   }
+  __syncthreads();   // es is complete
   need = wave_or(need);
   const half_t* vc = v1cat + (size_t)c * KRp * d;
   while (need != 0u) {

@@ -72,3 +72,14 @@ def test_lds_reads_are_complete_before_a_stage_is_refilled(kernels, kernel):
                 n += 1
                 assert any(_waits_for_lds(w) for w in near), (name, near)
     assert n
+
+
+def test_t1_rows_shares_its_expert_table_behind_a_barrier(kernels):
+    # wavefront 0 writes the table that all four read: a barrier of its own before the first stage's loads
+    found = [ins for name, ins in kernels.items() if "t1_rows_kernel" in name]
+    assert found
+    for ins in found:
+        written = max(at for at, i in enumerate(ins[:ins.index(next(filter(_to_lds, ins)))]) if i.startswith("ds_write_b32"))
+        shuffles = [at for at, i in enumerate(ins) if at > written and i.startswith("ds_bpermute")]
+        # the six shuffles that join the tile's needs come right behind the table
+        assert "s_barrier" in ins[written:shuffles[5]]
