@@ -597,7 +597,12 @@ __global__ __launch_bounds__(SORT_FEW) void sort_few_kernel(SortArgs a, int* __r
 }
 
 // The pair sort alone, for a permutation the caller already has: one workgroup per cluster, the
-// rows of the cluster in chunks of SORT_BLOCK.
+// rows of the cluster in chunks of SORT_BLOCK.  The token and the key of a thread's first PS_KEEP
+// rows (tid + j SORT_BLOCK) are read once, all loads in flight together, and stay in registers for
+// both passes; rows beyond come from memory in each pass, chunk by chunk.  Bound by that chain of
+// loads: with chunk after chunk read in both passes it took 7.8 instead of 6.8 us for 2 clusters of
+// 2048 rows, 14.4 instead of 12.6 us for 4 of 4096 and 17.4 instead of 14.3 us for 8 of 4096.
+constexpr int PS_KEEP = 8;
 __global__ __launch_bounds__(SORT_BLOCK) void pair_sort_kernel(const int* __restrict__ perm,
                                                               const int* __restrict__ offsets,
                                                               const int* __restrict__ expert_idx, int K, int k,
@@ -608,24 +613,26 @@ __global__ __launch_bounds__(SORT_BLOCK) void pair_sort_kernel(const int* __rest
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = blockIdx.x, lo = offsets[c], n = offsets[c + 1] - lo;
   if (n <= 0) return;
+  int tok[PS_KEEP], key[PS_KEEP];
+#pragma unroll
+  for (int j = 0; j < PS_KEEP; ++j) tok[j] = tid + j * SORT_BLOCK < n ? perm[lo + tid + j * SORT_BLOCK] : 0;
+#pragma unroll
+  for (int j = 0; j < PS_KEEP; ++j)
+    key[j] = tid + j * SORT_BLOCK < n ? pair_key(expert_idx, tok[j], c, K, k, two_keys) : 0;
   if (tid < 64) next[tid] = 0;
   __syncthreads();
-  for (int i = tid; i < n; i += SORT_BLOCK) atomicAdd(&next[pair_key(expert_idx, perm[lo + i], c, K, k, two_keys)], 1);
+#pragma unroll
+  for (int j = 0; j < PS_KEEP; ++j)
+    if (tid + j * SORT_BLOCK < n) atomicAdd(&next[key[j]], 1);
+  for (int i = tid + PS_KEEP * SORT_BLOCK; i < n; i += SORT_BLOCK)
+    atomicAdd(&next[pair_key(expert_idx, perm[lo + i], c, K, k, two_keys)], 1);
   __syncthreads();
   if (wave == 0) {
     const int cnt = next[lane];
-    int incl = cnt;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int v = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += v;
-    }
-    next[lane] = lo + incl - cnt;
+    next[lane] = lo + wave_inclusive_sum(cnt) - cnt;
   }
-  for (int i0 = 0; i0 < n; i0 += SORT_BLOCK) {   // chunks in order keep the sort stable
-    const int i = i0 + tid;
+  auto chunk = [&](int i, int tok, int key) {   // chunks in order keep the sort stable
     const bool in = i < n;
-    const int tok = in ? perm[lo + i] : 0, key = in ? pair_key(expert_idx, tok, c, K, k, two_keys) : 0;
     unsigned long long same = __ballot(in);   // lanes of this wavefront holding the same key
 #pragma unroll
     for (int b = 0; b < 6; ++b) {
@@ -651,6 +658,15 @@ __global__ __launch_bounds__(SORT_BLOCK) void pair_sort_kernel(const int* __rest
       next[tid] += add;
     }
     __syncthreads();
+  };
+#pragma unroll
+  for (int j = 0; j < PS_KEEP; ++j) {
+    if (j * SORT_BLOCK >= n) break;   // uniform over the workgroup
+    chunk(tid + j * SORT_BLOCK, tok[j], key[j]);
+  }
+  for (int i0 = PS_KEEP * SORT_BLOCK; i0 < n; i0 += SORT_BLOCK) {
+    const int i = i0 + tid, t = i < n ? perm[lo + i] : 0;
+    chunk(i, t, i < n ? pair_key(expert_idx, t, c, K, k, two_keys) : 0);
   }
 }
 

@@ -48,3 +48,26 @@ def test_pair_order_leaves_the_output_in_place(T, G, K, k):
     m = orc.error_metrics(out["y"].cpu().numpy(), ref["y"])   # the layer's bars (FP16 operands and results)
     assert m["max_over_rms"] <= 1e-2 and m["mean_rel"] <= 2e-3, m
     layer.close()
+
+
+# The pair sort of a permutation that the caller has: rows of one cluster up to, at and beyond what the
+# workgroup keeps in registers (8 x 1024), one and two keys.
+@pytest.mark.parametrize("T,G,k", [(257, 1, 2), (1025, 1, 2), (8192, 1, 1), (8193, 1, 2), (12000, 1, 2), (20000, 2, 2)])
+def test_pair_order_of_a_given_permutation(T, G, k):
+    import torch
+
+    import paper_2510_02345_amd as cm
+    print(f"case T={T} G={G} k={k}", flush=True)
+    cfg = ci.small_config("pairs2", T=T, d=64, d_ff=64, G=G, K=4, r=4, k=k, q=8, seed=T)
+    w = ci.generate(cfg)
+    ref = orc.forward_naive(w, w["x"], cfg.K, k, cfg.q)
+    layer = cm.Layer(cfg.d, cfg.d_ff, G, cfg.K, cfg.r, k, cfg.q, w, T)
+    x = torch.from_numpy(w["x"]).to("cuda:0")
+    c, e, g = layer.route(x)
+    perm, inv, off = layer.permute(c)
+    yb, s = layer.ffn_forward(x, perm, off, e, g)
+    y = layer.combine(yb, s, perm, inv, off, e, g)
+    torch.cuda.synchronize()
+    m = orc.error_metrics(y.cpu().numpy(), ref["y"])   # the layer's bars (FP16 operands and results)
+    assert m["max_over_rms"] <= 1e-2 and m["mean_rel"] <= 2e-3, m
+    layer.close()
