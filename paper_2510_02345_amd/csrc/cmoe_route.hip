@@ -556,10 +556,12 @@ __global__ __launch_bounds__(SORT_BLOCK) void sort_rank_kernel(SortArgs a, int m
   }
 }
 
-// Up to 256 items in up to 64 bins: one workgroup with a thread per item and no counters to clear.
+// Up to 1024 items in up to 64 bins: one workgroup with a thread per item and no counters to clear.
 // Lane g counts bin g of its wavefront from the same ballots that rank the items, the sum over the
 // bins is a wavefront scan, and one barrier joins the wavefronts (none for up to 64 items).
-constexpr int SORT_FEW = 256;
+// Against the general kernel, which clears and scans its counters: 3.5 -> 2.2 us for 300 items and
+// 2 bins, 4.0 -> 2.7 us for 1024, 4.1 -> 3.2 us for 1024 items and 64 bins.
+constexpr int SORT_FEW = SORT_BLOCK;
 __global__ __launch_bounds__(SORT_FEW) void sort_few_kernel(SortArgs a, int* __restrict__ perm, int* __restrict__ inv_perm,
                                                             int* __restrict__ offsets) {
   __shared__ int wc[SORT_FEW / 64][64];

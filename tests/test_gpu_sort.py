@@ -9,7 +9,7 @@ from oracle import cmoe_oracle as orc
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T", [1, 63, 64, 65, 256, 257, 1024, 1025, 4096, 4097, 131072, 131073, 150001])
+@pytest.mark.parametrize("T", [1, 63, 64, 65, 256, 257, 700, 1024, 1025, 4096, 4097, 131072, 131073, 150001])
 @pytest.mark.parametrize("G", [1, 5, 64])
 def test_permutation_is_the_stable_sort(T, G):
     import torch
