@@ -350,15 +350,22 @@ namespace {
 // sort_rank_kernel ranks a block; what it needs of the other blocks are the counts per bin over
 // all blocks and over the earlier ones.  It makes them itself
 //   - from the ids, up to SORT_SELF items (one launch),
-//   - from the per-block histograms of sort_hist_kernel, up to SORT_SUM_BLOCKS blocks (two),
+//   - from the per-block histograms of sort_hist_kernel, up to SORT_SUM_BLOCKS blocks and
+//     SORT_SUM_COUNTS counts (two),
 //   - else from those histograms after sort_scan_kernel has summed them over the blocks (three).
 // Everything here is latency, not bandwidth: a launch costs about as much as a block's ranks.
 // Histogram, scan, ranks and a one-workgroup-per-cluster pair sort were four launches: 21 -> 8 us
 // of kernel time at 4096 tokens and 2 clusters (now one launch), 31 -> 11 us at 16384 tokens
 // with Zipf loads and 27 -> 14 us at 32768 tokens and 8 clusters (two launches).
+// The third launch pays once every block's sums over the counts of all blocks take longer than it:
+// whole forward with 4096 bins (64 clusters of 64 keys) 138 us either way at 16 blocks, 237 us with
+// two launches and 231 with three at 32 blocks, 778 and 756 at 128; with 2048 bins 162 and 161 at
+// 32, 504 and 498 at 128; with 1024 bins no difference from 32 to 128; with 512 bins 98.8 and 101.3
+// at 64, 153 and 157 at 128.
 constexpr int SORT_BLOCK = PERMUTE_BLOCK, SORT_WAVES = SORT_BLOCK / 64;
 constexpr int SORT_SELF = 4 * SORT_BLOCK;
 constexpr int SORT_SUM_BLOCKS = 128;
+constexpr int SORT_SUM_COUNTS = 1 << 16;
 constexpr int SORT_BINS = 4096;   // bins of a sort: 64 clusters x 64 pair keys, 64 x 32 experts
 
 // Exclusive sum over the workgroup's 1024 threads, in thread order; contains one barrier, and
@@ -679,7 +686,8 @@ hipError_t go_sort(SortArgs a, int* perm, int* inv_perm, int* offsets, int* rowm
                    hipStream_t st) {
   a.n_blocks = (a.n + SORT_BLOCK - 1) / SORT_BLOCK;
   a.bins = PAIR ? a.n_ids * a.nk : a.n_ids;
-  const int mode = a.n <= SORT_SELF ? SORT_FROM_IDS : a.n_blocks <= SORT_SUM_BLOCKS ? SORT_FROM_HIST : SORT_FROM_SCAN;
+  const bool sum = a.n_blocks <= SORT_SUM_BLOCKS && a.n_blocks * a.bins <= SORT_SUM_COUNTS;
+  const int mode = a.n <= SORT_SELF ? SORT_FROM_IDS : sum ? SORT_FROM_HIST : SORT_FROM_SCAN;
   const dim3 grid(a.n_blocks), block(SORT_BLOCK);
   if (mode != SORT_FROM_IDS) hipLaunchKernelGGL((sort_hist_kernel<PAIR>), grid, block, 0, st, a, counts);
   if (mode == SORT_FROM_SCAN) hipLaunchKernelGGL(sort_scan_kernel, dim3((a.bins + 63) / 64), dim3(64), 0, st, a, counts);

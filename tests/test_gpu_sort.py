@@ -31,7 +31,9 @@ def test_permutation_is_the_stable_sort(T, G):
     layer.close()
 
 
-@pytest.mark.parametrize("T,G,K,k", [(300, 64, 8, 2), (5000, 64, 8, 2), (4097, 3, 32, 1), (4500, 2, 4, 4)])
+# with 4096 bins two launches up to 16 blocks of 1024 tokens and three above; with 32 bins up to 128 and above
+@pytest.mark.parametrize("T,G,K,k", [(300, 64, 8, 2), (5000, 64, 8, 2), (16384, 64, 8, 2), (16385, 64, 8, 2), (17409, 64, 8, 2),
+                                     (4097, 3, 32, 1), (4500, 2, 4, 4), (131073, 2, 4, 2)])
 def test_pair_order_leaves_the_output_in_place(T, G, K, k):
     import torch
 
