@@ -610,14 +610,30 @@ static bool stream_once(const cmoe_dims& dm) {
   return (size_t)dm.G * dm.d * dm.d_ff * sizeof(half_t) > ((size_t)96 << 20);
 }
 
-// One weight stream of the layer.  A workgroup takes 16 tokens of a cluster, or 32 where the
-// expected load of a cluster is above 12: then many clusters would be read twice (203 tokens on 8
-// clusters of 2048 x 8192: 93 -> 65 us per stream), below it the wider ring costs more than the
-// few second reads (two workgroups per CU instead of three).
+// Tokens of a cluster that a workgroup of a weight stream takes: 16, or 32 (two workgroups per CU
+// instead of three) where the second reading of a matrix by the passes of a cluster costs more.
+//   - Up to 16 tokens no cluster has a second pass.
+//   - A matrix that the caches keep is not read twice from memory, and while the workgroups of the
+//     16-token form are at most four per CU the passes of a cluster run side by side.  Whole forward
+//     of the 32-token and the 16-token form: one cluster of 768 x 3072, 32 tokens 27.9 and 27.1 us;
+//     one of 2048 x 8192, 32 tokens 48.5 and 46.7 us, 128 tokens (2304 workgroups) 61 and 69 us; four of
+//     1024 x 4096, 50 tokens 41.9 and 40.0 us, 128 tokens (1536 workgroups) 43.8 and 47 us.
+//   - Else the expected load of a cluster decides, above 12 tokens for the down-projection and above 13
+//     for the up-projection, whose launch also holds a workgroup per token and expert: 8 clusters of
+//     4096 x 14336, 104 tokens: both 32-token 345 us, the down-projection alone 338, neither 339;
+//     112 tokens: 352, 381, 410; of 2048 x 8192, 97 tokens: 126.7, 126.1, 134.
+inline int stream_cols(const cmoe_dims& dm, int T, bool down) {
+  if (T <= 16 || T <= (down ? 12 : 13) * dm.G) return 16;
+  const long narrow = (long)(dm.d_ff / SK_ROWS) * (dm.G + T / 16);   // workgroups, at most
+  return !stream_once(dm) && narrow <= 1024 ? 16 : 32;
+}
+
+// One weight stream of the layer.
 template <int SIDE>
-hipError_t launch_stream(const cmoe_dims& dm, const half_t* X, const int* gather, const half_t* W, const int* offsets, int N,
-                         int Kc, half_t* out, int T, long w_blk, const SideArgs& sa, hipStream_t st) {
-  const int nx = N / SK_ROWS, cols = T > 12 * dm.G ? 32 : 16;
+hipError_t launch_stream(const cmoe_dims& dm, int cols, const half_t* X, const int* gather, const half_t* W,
+                         const int* offsets, int N, int Kc, half_t* out, int T, long w_blk, const SideArgs& sa,
+                         hipStream_t st) {
+  const int nx = N / SK_ROWS;
   const int slots = T < dm.G + T / cols ? T : dm.G + T / cols;   // at most: a slot holds a token, all but G of them `cols`
   const dim3 grid((unsigned)nx * slots + sa.n_side), block(256);
   auto go = [&](auto kern) {
@@ -640,7 +656,9 @@ hipError_t launch_skinny_hb(const cmoe_dims& dm, const cmoe_weights& w, const ha
   // the re-tiled copy of W1 when the caller keeps one, else the canonical array
   const half_t* w1 = w.packed ? (const half_t*)((const char*)w.packed + cmoe_packed(dm).w1) : (const half_t*)w.w1_base;
   const long w_blk = w.packed ? (long)dm.d_ff * 32 : 0;
-  if (t1 == nullptr) return launch_stream<SIDE_NONE>(dm, x, perm, w1, offsets, dm.d_ff, dm.d, hb, T, w_blk, sa, st);
+  const int cols = stream_cols(dm, T, false);
+  if (t1 == nullptr)
+    return launch_stream<SIDE_NONE>(dm, cols, x, perm, w1, offsets, dm.d_ff, dm.d, hb, T, w_blk, sa, st);
   sa.x = x;
   sa.perm = perm;
   sa.expert_idx = expert_idx;
@@ -655,7 +673,7 @@ hipError_t launch_skinny_hb(const cmoe_dims& dm, const cmoe_weights& w, const ha
   sa.n_exp = dm.G * dm.K;
   sa.n_jobs = T * dm.k;
   sa.n_side = (sa.n_jobs + 7) & ~7;
-  return launch_stream<SIDE_T1>(dm, x, perm, w1, offsets, dm.d_ff, dm.d, hb, T, w_blk, sa, st);
+  return launch_stream<SIDE_T1>(dm, cols, x, perm, w1, offsets, dm.d_ff, dm.d, hb, T, w_blk, sa, st);
 }
 
 hipError_t launch_skinny_resid_up(const cmoe_dims& dm, const cmoe_weights& w, int T, const int* perm,
@@ -684,8 +702,9 @@ hipError_t launch_skinny_down(const cmoe_dims& dm, const cmoe_weights& w, const 
   sa.x_div = 1;
   const half_t* w2 = w.packed ? (const half_t*)((const char*)w.packed + cmoe_packed(dm).w2) : (const half_t*)w.w2_base;
   const long w_blk = w.packed ? (long)dm.d * 32 : 0;
+  const int cols = stream_cols(dm, T, true);
   if (ures == nullptr)
-    return launch_stream<SIDE_NONE>(dm, a, nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted, T, w_blk, sa, st);
+    return launch_stream<SIDE_NONE>(dm, cols, a, nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted, T, w_blk, sa, st);
   sa.perm = perm;
   sa.expert_idx = expert_idx;
   sa.gate = gate;
@@ -702,7 +721,7 @@ hipError_t launch_skinny_down(const cmoe_dims& dm, const cmoe_weights& w, const 
   sa.n_parts = n_parts;
   sa.n_jobs = T * ((dm.d + 2047) / 2048);
   sa.n_side = (sa.n_jobs + 7) & ~7;
-  return launch_stream<SIDE_URES>(dm, a, nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted, T, w_blk, sa, st);
+  return launch_stream<SIDE_URES>(dm, cols, a, nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted, T, w_blk, sa, st);
 }
 
 // out[p][n] = sum_k W[g][n][k] X[p][k] for the rows p of group g (offsets [n_groups + 1],

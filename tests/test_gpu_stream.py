@@ -9,15 +9,33 @@ from oracle import cmoe_oracle as orc
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("G,T", [(1, 1), (1, 12), (1, 13), (2, 24), (2, 25), (2, 256), (5, 60), (5, 61), (5, 177),
+@pytest.mark.parametrize("G,T", [(1, 1), (1, 12), (1, 16), (1, 17), (2, 24), (2, 25), (2, 256), (5, 60), (5, 61), (5, 177),
                                  (16, 256), (16, 193), (64, 3), (64, 255)])
 @pytest.mark.parametrize("skew", [0.0, 100.0])
 def test_weight_streams(G, T, skew):
+    _check(ci.small_config("stream", T=T, d=192, d_ff=128, G=G, K=4, r=8, k=2, q=32, seed=T + G), skew)
+
+
+# 32-token workgroups: more than 1024 workgroups of the 16-token form (64 row blocks of 2048 rows); the
+# up-projection takes them from 13 expected tokens on, the down-projection from 12
+@pytest.mark.parametrize("G,T", [(15, 180), (15, 181), (15, 195), (15, 196), (1, 255), (1, 256), (7, 144), (7, 160),
+                                 (6, 255)])
+@pytest.mark.parametrize("skew", [0.0, 100.0])
+def test_wide_weight_streams(G, T, skew):
+    _check(ci.small_config("wide", T=T, d=64, d_ff=2048, G=G, K=4, r=8, k=2, q=32, seed=T + G), skew)
+
+
+def test_wide_weight_streams_beyond_the_caches():
+    # bases above the size from which they are read without being kept
+    _check(ci.small_config("far", T=200, d=2048, d_ff=2048, G=13, K=4, r=8, k=2, q=32, seed=213), 0.0)
+
+
+def _check(cfg, skew):
     import torch
 
     import paper_2510_02345_amd as cm
-    cfg = ci.small_config("stream", T=T, d=192, d_ff=128, G=G, K=4, r=8, k=2, q=32, seed=T + G)
     print(f"case {cfg} skew {skew}", flush=True)
+    G, T = cfg.G, cfg.T
     w = ci.generate(cfg)
     if skew:   # every token in the last cluster
         w["cluster_bias"] = np.zeros(G, dtype=np.float32)
