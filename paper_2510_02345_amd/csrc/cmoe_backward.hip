@@ -451,14 +451,19 @@ __global__ __launch_bounds__(256) void bw_rankgrad_kernel(const half_t* __restri
     }
 }
 
-// out[i] = part[0][i] + part[1][i] + ... in split order, i < n (a multiple of 4)
-__global__ __launch_bounds__(256) void bw_rankgrad_finish_kernel(const float* __restrict__ part, size_t n, int split,
+// out[i] = part[0][i] + part[1][i] + ... in run order, i < n (a multiple of 4); all loads in flight
+// together (a loop over a run-time count waited for each in turn: FINOLD).
+template <int RUNS>
+__global__ __launch_bounds__(256) void bw_rankgrad_finish_kernel(const float* __restrict__ part, size_t n,
                                                                  float* __restrict__ out) {
   const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i >= n) return;
-  float4v acc = *(const float4v*)(part + i);
-  for (int sp = 1; sp < split; ++sp) acc += *(const float4v*)(part + sp * n + i);
-  *(float4v*)(out + i) = acc;
+  float4v v[RUNS];
+#pragma unroll
+  for (int sp = 0; sp < RUNS; ++sp) v[sp] = *(const float4v*)(part + sp * n + i);
+#pragma unroll
+  for (int sp = 1; sp < RUNS; ++sp) v[0] += v[sp];
+  *(float4v*)(out + i) = v[0];
 }
 
 // t[p][rho] *= gate[permm[p]] for the M sorted pair rows (32 rank columns each)
@@ -484,8 +489,12 @@ inline int row_runs(int E, int L, int cols) {
 constexpr int RG_COLS = 512, DR_COLS = 1024;   // columns of a workgroup
 
 void finish(const float* part, size_t n, int split, float* out, hipStream_t st) {
-  hipLaunchKernelGGL(bw_rankgrad_finish_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, st, part, n, split,
-                     out);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, st, part, n, out);
+  };
+  if (split == 4) go(bw_rankgrad_finish_kernel<4>);
+  else if (split == 8) go(bw_rankgrad_finish_kernel<8>);
+  else go(bw_rankgrad_finish_kernel<16>);
 }
 
 template <int R>

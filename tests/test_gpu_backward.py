@@ -76,6 +76,14 @@ def test_backward_small(cfg):
     _run(cfg)
 
 
+# Every run of an expert's rows holds several batches of 32 (the steady state of the factor-gradient
+# kernel), the last one ragged: 16 runs for both widths, 8 for d_ff, 4 for d.
+@pytest.mark.parametrize("r", [4, 8, 16, 32])
+@pytest.mark.parametrize("T,G,K,d,f", [(2491, 1, 2, 64, 128), (4803, 4, 4, 64, 4096), (4501, 8, 4, 4160, 64)])
+def test_backward_long_runs(r, T, G, K, d, f):
+    _run(ci.small_config("bw_runs", T=T, d=d, d_ff=f, G=G, K=K, r=r, k=2, q=8, seed=160 + r))
+
+
 def test_backward_config1():
     _run(ci.config(1))
 
