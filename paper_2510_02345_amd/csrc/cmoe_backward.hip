@@ -610,9 +610,9 @@ hipError_t launch_backward(const cmoe_dims& dm, const cmoe_weights& w, const hal
     if (err != hipSuccess) return err;    \
   } while (0)
 #define BW_GEMM(...) BW_CHECK(launch_gemm_plain(__VA_ARGS__, st))
-  // a product over expert groups, at most 64 groups per launch (the kernel finds the group of
-  // a tile by a linear walk over the offsets); rows are addressed absolutely, so a launch
-  // over a slice of the offsets needs no other change
+  // a product over expert groups, at most 64 groups per launch (one lane of a wavefront looks at
+  // each group: launch_gemm_plain takes no more); rows are addressed absolutely, so a launch over a
+  // slice of the offsets needs no other change
   auto rank_gemm = [&](const half_t* P, int L_, const half_t* X, int ldx, const int* gather, int x_div,
                        half_t* outp) -> hipError_t {
     for (int e0 = 0; e0 < E; e0 += 64) {

@@ -107,9 +107,10 @@ __device__ __forceinline__ int wave_inclusive_sum(int v) {
 }
 
 // Row tiles of bm rows that never straddle a group, dealt group after group.  offsets
-// [n_groups + 1], n_groups <= 64: lane g looks at group g, so that the search for a tile costs
-// one round trip to memory instead of one per group.
+// [n_groups + 1], at most MAX_GROUPS groups: lane g looks at group g, so that the search for a tile
+// costs one round trip to memory instead of one per group.  A group beyond would be passed over.
 struct RowTiles {
+  static constexpr int MAX_GROUPS = 64;
   int lo, hi, tiles, incl;   // per lane: rows and tiles of group `lane`, tiles up to and including it
   __device__ __forceinline__ RowTiles(const int* offsets, int n_groups, int bm) : lo(0), hi(0) {
     const int lane = threadIdx.x & 63;

@@ -969,11 +969,13 @@ hipError_t launch_gemm2_combine(const cmoe_dims& dm, const cmoe_weights& w, cons
 // Grouped product with a plain store, for callers outside the forward path:
 //   out[rowmap ? rowmap[p] : p][n] = sum_k X[row(p)][k_g + k] * W_g[n][k_g + k],
 // W_g = W + g * w_gstride, row(p) = gather ? gather[p] / x_div : p, rows p of group g in
-// [offsets[g], offsets[g+1]); k runs over [0, Kc) or over the group's krange.
+// [offsets[g], offsets[g+1]); k runs over [0, Kc) or over the group's krange.  At most
+// RowTiles::MAX_GROUPS groups.
 hipError_t launch_gemm_plain(const half_t* W, long w_gstride, int ldw, int N, const half_t* X, int ldx,
                              const int* gather, int x_div, int Kc, const int* offsets, int n_groups, int rows,
                              const int* krange, const int* rowmap, void* out, int ldo, bool out_f32,
                              hipStream_t st, long kstep_w, long kstep_x) {
+  if (n_groups > RowTiles::MAX_GROUPS) return hipErrorInvalidValue;
   GemmArgs g{W, w_gstride, ldw, N, X, ldx, gather, Kc, offsets, n_groups, (N + TileBig::BN - 1) / TileBig::BN};
   g.x_div = x_div;
   g.krange = krange;

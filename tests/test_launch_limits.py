@@ -1,0 +1,21 @@
+"""Limits that launchers check before any launch (no GPU needed)."""
+import ctypes as C
+import subprocess
+
+import paper_2510_02345_amd as cm
+
+HIP_ERROR_INVALID_VALUE = 1
+
+
+def test_grouped_product_takes_no_more_groups_than_lanes():
+    names = subprocess.run(["nm", "-D", "--defined-only", cm.binding.lib_path()], check=True, capture_output=True,
+                           text=True).stdout.split()
+    f = getattr(cm.lib(), next(n for n in names if "launch_gemm_plain" in n))
+    P, I, L = C.c_void_p, C.c_int, C.c_long
+    f.restype = I
+    # W, w_gstride, ldw, N, X, ldx, gather, x_div, Kc, offsets, n_groups, rows, krange, rowmap, out, ldo, out_f32, stream,
+    # kstep_w, kstep_x
+    f.argtypes = [P, L, I, I, P, I, P, I, I, P, I, I, P, P, P, I, C.c_bool, P, L, L]
+    for N in (32, 256):   # the thin and the tiled product
+        for out_f32 in (False, True):
+            assert f(None, 0, 64, N, None, 64, None, 1, 64, None, 65, 0, None, None, None, N, out_f32, None, 0, 0) == HIP_ERROR_INVALID_VALUE
