@@ -16,9 +16,9 @@
 // U1^T dh, V2 a; rank panels padded to 32 rows) run on the grouped matrix-core kernel of the
 // forward pass.  The two base gradients contract over the tokens of a cluster: they use
 // transposed copies that pad every cluster to a multiple of 32 columns and are stored in
-// 32-column blocks.  The ways back from rank space (U1 t, V2^T u, V1^T q) and the factor
-// gradients (r output rows per expert) are vector-ALU kernels that stream the pair rows of
-// an expert once.
+// 32-column blocks.  The ways back from rank space (U1 t, V2^T u, V1^T q; vector ALUs) and the
+// factor gradients (r output rows per expert; matrix cores) are kernels of their own that stream the
+// pair rows of an expert once.
 #include "cmoe_device.h"
 
 namespace {
@@ -452,7 +452,8 @@ __global__ __launch_bounds__(256) void bw_rankgrad_kernel(const half_t* __restri
 }
 
 // out[i] = part[0][i] + part[1][i] + ... in run order, i < n (a multiple of 4); all loads in flight
-// together (a loop over a run-time count waited for each in turn: FINOLD).
+// together (a loop over a run-time count waited for each
+// in turn: 6.2 instead of 2.7 us for 16 runs of 4 x 512 x 8 values).
 template <int RUNS>
 __global__ __launch_bounds__(256) void bw_rankgrad_finish_kernel(const float* __restrict__ part, size_t n,
                                                                  float* __restrict__ out) {

@@ -94,6 +94,10 @@ __device__ __forceinline__ void wait_vm() {
 // stage that was read is refilled by loads that go to LDS, or what was written is read by others.
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// Ranking key of a logit: a NaN ranks below every number (as -inf), so that the selections of the
+// router always return distinct, valid slots whatever the input holds.
+__device__ __forceinline__ float rank_key(float v) { return v == v ? v : -INFINITY; }
+
 // Inclusive sum over the lanes of a wavefront by data-parallel-primitive moves (no LDS round
 // trips): rows of 16 lanes by shifts, then the row totals broadcast upwards.
 __device__ __forceinline__ int wave_inclusive_sum(int v) {

@@ -184,7 +184,7 @@ struct cmoe_bw_layout {
   size_t t1, uy, qq, ss;                      // f16 [M][32] rank-space rows of the pairs
   size_t dxb, dxr;                            // f16 [T][d], [M][d]
   size_t xct, dyct, dhst, agt;                // f16 transposed copies, Tpad columns
-  size_t rgpart;                              // f32 [4][E][r][max(d, d_ff)] partial factor gradients
+  size_t rgpart;                              // f32 [runs][E][r][d or d_ff], runs by row_runs for each width: partial sums of factor and router gradients
   size_t total;
 };
 cmoe_bw_layout cmoe_backward_layout(const cmoe_dims& dm, int T);

@@ -18,10 +18,6 @@ __device__ __forceinline__ float dot8(half8 a, half8 b, float acc) {
   return acc;
 }
 
-// Ranking key of a logit: a NaN ranks below every number (as -inf), so that the selection
-// rounds below always return distinct, valid slots whatever the input holds.
-__device__ __forceinline__ float rank_key(float v) { return v == v ? v : -INFINITY; }
-
 // One round of (largest key, lowest lane) over the first n lanes, skipping lanes already
 // taken.  Returns the winning lane; marks it taken.
 __device__ __forceinline__ int select_round(float key, bool& taken, int lane, int n) {

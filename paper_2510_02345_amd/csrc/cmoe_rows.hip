@@ -153,10 +153,7 @@ struct RouteRowsArgs {
   float* gate;
 };
 
-// A candidate of a selection: larger key first, lowest index among equals.  A NaN logit ranks
-// as -inf, so that a selection always returns distinct, valid slots.
-__device__ __forceinline__ float rank_key(float v) { return v == v ? v : -INFINITY; }
-// The best candidate of a group of 8 lanes.
+// The best candidate of a group of 8 lanes: larger key first, lowest index among equals.
 __device__ __forceinline__ int best_of_8(float key, int idx) {
 #pragma unroll
   for (int off = 1; off < 8; off <<= 1) {
@@ -300,11 +297,18 @@ __global__ __launch_bounds__(RW_THREADS, 2) void route_rows_lds_kernel(RouteRows
   }
 }
 
-// Up to this many tokens the 32-token workgroups with their split contraction are faster (fewer
-// than one workgroup per CU: what counts is the chain of steps): 5.6 against 7.7 us at 4096
-// tokens of width 768 and 10 router rows, 7.9 against 9.2 us at 8000 of 1024 and 20 rows.  Above it
-// the loads count: 12 against 12 us at 16384 of 1024, 65 against 36 us at 32768 of 2048 and 72
-// rows (one 128-row matrix-core tile against 128 tokens took 41).
+// Up to this many tokens the 32-token workgroups with their split contraction are taken: fewer than
+// one workgroup per CU, and what counts is the chain of steps.  Few router rows, us of the 32- and
+// of the 64-token form: 10 rows of width 2048 9.6 and 11.5 at 8192 tokens, of width 4096 15.9
+// and 16.8; 20 rows of width 1024 7.7 and 9.3.  Above the line the loads count: 16384 tokens, 20 rows
+// of width 1024 11.1 and 9.6, 72 rows of width 2048 33 and 16, of width 8192 101 and 48.  (One
+// 128-row matrix-core tile against 128 tokens took 30 at 32768 tokens and 72 rows of width 2048,
+// the 64-token form 27.)
+// Many wide rows below the line are the 64-token form's as well by time (8192 tokens, 72 rows of width
+// 1024 11.1 and 10.6, 2048 17.3 and 15.1, 4096 29.5 and 23.7; 128 rows of width 8192 76 and 55) but not
+// by accuracy: one chain of sums over the whole width against four gives the gates twice the
+// error against 64 bits (72 rows of width 2048: 2.0e-7 against 1.0e-7, 128 of 8192: 5.0e-7
+// against 2.1e-7), so the number of tokens alone decides.
 constexpr int ROUTE_SPLIT_T = 8192;
 template <int NA, bool MULTI>
 hipError_t go_route_na(const RouteRowsArgs& a, hipStream_t st) {

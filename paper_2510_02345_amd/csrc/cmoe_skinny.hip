@@ -1,7 +1,7 @@
 // Weight-streaming path of the expert computation for small token counts (Sec. 3.2).
 // With only a handful of tokens per cluster the layer is bound by reading every base
 // matrix once from HBM, so the two shared-base products are pure streams: a workgroup owns
-// 32 weight rows of one cluster and 16 of its tokens, its four wavefronts split the
+// 32 weight rows of one cluster and 16 or 32 of its tokens, its four wavefronts split the
 // contraction dimension, and both operands travel global -> LDS by DMA into per-wavefront
 // rings.  The per-expert rank-r terms (INT4 factors dequantised on the fly, Sec. 3.4) are
 // small kernels of their own or ride along in the stream launches.

@@ -169,7 +169,7 @@ def test_backward_is_deterministic():
 
 
 def test_backward_more_than_64_experts():
-    # 160 and 128 experts: pairs sorted by expert in two passes, rank products in slices of 64 experts
+    # 160 and 128 experts: rank products in slices of 64 experts
     _run(ci.small_config("bw_many", T=400, d=64, d_ff=128, G=20, K=8, r=4, k=2, q=8, seed=151))
     _run(ci.small_config("bw_many_clusters", T=3000, d=64, d_ff=128, G=64, K=2, r=8, k=2, q=16, seed=152))
 
