@@ -12,13 +12,16 @@
 //   dB1_c = sum_{t in c} (sum_j dh_m) x_t^T     dB2_c = sum_{t in c} dy_t (sum_j g_m a_m)^T
 //   dU1_e = sum_m dh_m (V1 x_t)^T   dV1_e = sum_m (U1^T dh_m) x_t^T
 //   dU2_e = sum_m g_m dy_t (V2 a_m)^T   dV2_e = sum_m g_m (U2^T dy_t) a_m^T
-// The five products with a base and the four products into rank space (V1 x, U2^T dy,
-// U1^T dh, V2 a; rank panels padded to 32 rows) run on the grouped matrix-core kernel of the
-// forward pass.  The two base gradients contract over the tokens of a cluster: they use
-// transposed copies that pad every cluster to a multiple of 32 columns and are stored in
-// 32-column blocks.  The ways back from rank space (U1 t, V2^T u, V1^T q; vector ALUs) and the
-// factor gradients (r output rows per expert; matrix cores) are kernels of their own that stream the
-// pair rows of an expert once.
+// The five products with a base run on the grouped matrix-core kernel of the forward pass.  The two
+// base gradients contract over the tokens of a cluster: they use transposed copies that pad every
+// cluster to a multiple of 32 columns and are stored in 32-column blocks.
+//   Up to two experts per token and 128 rank rows per cluster, everything between hb, dab and the
+// operands of the last three base products is one kernel (cmoe_backward_mid.hip), V1 x and U2^T dy come
+// from the forward pass's kernel, and V1^T q joins the epilogue of the input gradient.
+//   Else the four products into rank space (V1 x, U2^T dy, U1^T dh, V2 a; rank panels padded to 32
+// rows) run on the grouped kernel, and the ways back from rank space (U1 t, V2^T u, V1^T q; vector
+// ALUs), the activations and the factor gradients are kernels of their own on the pair rows.
+// The gradients of V1 and U2 stream the tokens of an expert once in either form.
 #include "cmoe_device.h"
 
 namespace {
@@ -49,54 +52,44 @@ __global__ __launch_bounds__(256) void bw_panel_kernel(const uint8_t* __restrict
   }
 }
 
-// Column ranges of the group-padded transposed copies and, for every padded column qc, the
-// sorted row it holds (-1: padding), the source row perm[row] / div and its gate.
-// krange[2g] = first column of group g, krange[2g+1] = its rows rounded up to 32.
+// Column ranges of the cluster-padded transposed copies and, for every padded column qc, its source row
+// perm[row] (-1: padding).  krange[2g] = first column of cluster g, krange[2g+1] = its rows rounded up
+// to 32.  es != NULL: the experts (local to the cluster) and gates of the rows, in their order.
 __global__ __launch_bounds__(256) void bw_map_kernel(const int* __restrict__ off, const int* __restrict__ perm,
-                                                     const float* __restrict__ gate, int n_groups, int div, int Npad,
-                                                     int* __restrict__ krange, int* __restrict__ srow,
-                                                     int* __restrict__ ssrc, float* __restrict__ sgate) {
-  __shared__ int start[65];
-  if (threadIdx.x == 0) {
-    int at = 0;
-    for (int g = 0; g < n_groups; ++g) {
-      start[g] = at;
-      at += (off[g + 1] - off[g] + 31) / 32 * 32;
-    }
-    start[n_groups] = at;
+                                                     int n_groups, int Npad, int* __restrict__ krange,
+                                                     int* __restrict__ ssrc, const int* __restrict__ expert_idx,
+                                                     const float* __restrict__ gate, int K, int k, int* __restrict__ es,
+                                                     float* __restrict__ gs) {
+  __shared__ int start[65], first[65];
+  if (threadIdx.x < 64) {
+    const int lane = threadIdx.x, lo = lane < n_groups ? off[lane] : 0, n = lane < n_groups ? off[lane + 1] - lo : 0;
+    const int pad = (n + 31) / 32 * 32, incl = wave_inclusive_sum(pad);
+    if (lane < n_groups) start[lane] = incl - pad, first[lane] = lo;
+    if (lane == 63) start[n_groups] = incl;
+    if (lane == n_groups - 1) first[n_groups] = lo + n;
+    if (blockIdx.x == 0 && lane < n_groups) krange[2 * lane] = incl - pad, krange[2 * lane + 1] = pad;
   }
   __syncthreads();
-  if (blockIdx.x == 0)
-    for (int g = threadIdx.x; g < n_groups; g += 256) {
-      krange[2 * g] = start[g];
-      krange[2 * g + 1] = start[g + 1] - start[g];
-    }
   const int qc = blockIdx.x * 256 + threadIdx.x;
   if (qc >= Npad) return;
-  int row = -1;
+  int row = -1, c = 0;
   for (int g = 0; g < n_groups; ++g)
     if (qc >= start[g] && qc < start[g + 1]) {
       const int local = qc - start[g];
-      if (local < off[g + 1] - off[g]) row = off[g] + local;
+      if (local < first[g + 1] - first[g]) row = first[g] + local, c = g;
     }
-  srow[qc] = row;
-  const int m = row >= 0 ? perm[row] : 0;
-  ssrc[qc] = row >= 0 ? m / div : -1;
-  if (sgate != nullptr) sgate[qc] = row >= 0 ? gate[m] : 0.f;
+  const int tok = row >= 0 ? perm[row] : -1;
+  ssrc[qc] = tok;
+  if (es != nullptr && row >= 0)
+    for (int j = 0; j < k; ++j) {
+      es[(size_t)row * k + j] = min(max(expert_idx[(size_t)tok * k + j] - c * K, 0), K - 1);
+      gs[(size_t)row * k + j] = gate[(size_t)tok * k + j];
+    }
 }
 
-__global__ __launch_bounds__(256) void bw_zero_kernel(int* __restrict__ p, int n) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
+__global__ __launch_bounds__(256) void bw_zero_kernel(int* __restrict__ p, size_t n) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n) p[i] = 0;
-}
-
-// offx[g] = g * I (g <= n_groups) and gidx[p] = p % I for the n_groups * I rows of a
-// weight gradient.
-__global__ __launch_bounds__(256) void bw_rows_kernel(int n_groups, int I, int* __restrict__ offx,
-                                                      int* __restrict__ gidx) {
-  const size_t p = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (p <= (size_t)n_groups) offx[p] = (int)p * I;
-  if (p < (size_t)n_groups * I) gidx[p] = (int)(p % I);
 }
 
 // One token per block.  For its k pairs (sorted rows p_j = invm[t k + j]):
@@ -228,58 +221,54 @@ __global__ __launch_bounds__(256) void bw_drouter_kernel(const half_t* __restric
   *(float4v*)(part + ((size_t)sp * E + e) * d + col) = float4v{acc[0], acc[1], acc[2], acc[3]};
 }
 
-// out[z][i][qc] = scale[qc] * src[z][idx[qc]][i] (zero where idx[qc] < 0; idx == NULL: row
-// qc), i < I (a multiple of 16), qc < Npad (a multiple of 64); with blocked != 0 the same
-// values in the layout [Npad / 32][I][32].  Matrices z whose group in
-// skip_off is empty are skipped.  src_blk != 0: src[z] is stored as [I / 32][rows][32] with
-// src_blk = rows * 32 (the re-tiled copy of a base matrix) instead of row-major with row
-// stride ld.  Block (Npad / 64, ceil(I / 64), Z): 64 x 64 tile through LDS.
-__global__ __launch_bounds__(256) void bw_transpose_kernel(const half_t* __restrict__ src, int ld, long src_blk, int I,
-                                                           const int* __restrict__ idx,
-                                                           const float* __restrict__ scale, int Npad,
-                                                           const int* __restrict__ skip_off, size_t zstride,
-                                                           int blocked, half_t* __restrict__ out) {
+// Transposed copies in 32-column blocks: out[z] = [Npad / 32][I][32] with out[z][qc / 32][i][qc % 32] =
+// src[z][idx[qc]][i] (zero where idx[qc] < 0; idx == NULL: row qc), i < I (a multiple of 64), qc < Npad (a
+// multiple of 64).  Matrices z whose group in skip_off is empty are skipped.  src_blk != 0: src[z] is
+// stored as [I / 32][rows][32] with src_blk = rows * 32 (the re-tiled copy of a base matrix) instead
+// of row-major with row stride ld.  64 x 64 tiles through LDS, two copies of as many tiles a launch:
+// block (tile, copy, z).
+struct TransposeJob {
+  const half_t* src;
+  half_t* out;
+  const int* idx;
+  long src_blk;
+  int ld, I, Npad;
+};
+struct TransposeJobs {
+  TransposeJob j[2];
+};
+__global__ __launch_bounds__(256) void bw_transpose_kernel(TransposeJobs jobs, const int* __restrict__ skip_off,
+                                                           size_t zstride) {
   __shared__ half_t tile[64][72];
   const int z = blockIdx.z;
   if (skip_off != nullptr && skip_off[z + 1] == skip_off[z]) return;
-  src += z * zstride;
-  out += z * zstride;
-  const int q0 = blockIdx.x * 64, i0 = blockIdx.y * 64, tid = threadIdx.x;
+  const TransposeJob& jb = jobs.j[blockIdx.y];
+  const half_t* src = jb.src + z * zstride;
+  half_t* out = jb.out + z * zstride;
+  const int nx = jb.Npad / 64, q0 = blockIdx.x % nx * 64, i0 = blockIdx.x / nx * 64, tid = threadIdx.x;
+  const int l = tid >> 2, part = tid & 3;
   {
-    const int ql = tid >> 2, part = tid & 3;
-    const int row = idx != nullptr ? idx[q0 + ql] : q0 + ql;
+    const int row = jb.idx != nullptr ? jb.idx[q0 + l] : q0 + l;
     half8 a = {0, 0, 0, 0, 0, 0, 0, 0}, b = a;
-    if (row >= 0 && i0 + part * 16 < I) {
+    if (row >= 0) {
       const int col = i0 + part * 16;   // 16 columns inside one 32-column block
-      const half_t* sp = src_blk ? src + (size_t)(col >> 5) * src_blk + (size_t)row * 32 + (col & 31)
-                                 : src + (size_t)row * ld + col;
+      const half_t* sp = jb.src_blk ? src + (size_t)(col >> 5) * jb.src_blk + (size_t)row * 32 + (col & 31)
+                                    : src + (size_t)row * jb.ld + col;
       a = *(const half8*)sp;
       b = *(const half8*)(sp + 8);
-      if (scale != nullptr) {
-        const float s = scale[q0 + ql];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          a[i] = (half_t)(s * (float)a[i]);
-          b[i] = (half_t)(s * (float)b[i]);
-        }
-      }
     }
-    *(half8*)&tile[ql][part * 16] = a;
-    *(half8*)&tile[ql][part * 16 + 8] = b;
+    *(half8*)&tile[l][part * 16] = a;
+    *(half8*)&tile[l][part * 16 + 8] = b;
   }
   __syncthreads();
-  const int il = tid >> 2, part = tid & 3;
-  if (i0 + il >= I) return;
   half8 a, b;
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
-    a[u] = tile[part * 16 + u][il];
-    b[u] = tile[part * 16 + 8 + u][il];
+    a[u] = tile[part * 16 + u][l];
+    b[u] = tile[part * 16 + 8 + u][l];
   }
-  // blocked: [Npad / 32][I][32], the operand layout whose contraction blocks are contiguous
   const int qq = q0 + part * 16;
-  half_t* dst = blocked ? out + ((size_t)(qq >> 5) * I + i0 + il) * 32 + (qq & 31)
-                        : out + (size_t)(i0 + il) * Npad + qq;
+  half_t* dst = out + ((size_t)(qq >> 5) * jb.I + i0 + l) * 32 + (qq & 31);
   *(half8*)dst = a;
   *(half8*)(dst + 8) = b;
 }
@@ -362,15 +351,18 @@ void rankexpand(int r, const half_t* t, const half_t* P, int L, const int* offe,
 // 8 x 8 values in registers gives the B operands of the matrix cores (eight rows of one
 // column), and the accumulators leave room for the next 32 rows in flight.  The t rows
 // are transposed through LDS, wavefront by wavefront.
-// Block (ceil(L / 512), E, split).
+// Two gradients of the same width a launch, block (ceil(L / 512), E, 2 split): (t0, D0), (t1, D1).
 template <int R>
-__global__ __launch_bounds__(256) void bw_rankgrad_kernel(const half_t* __restrict__ t, const half_t* __restrict__ D,
+__global__ __launch_bounds__(256) void bw_rankgrad_kernel(const half_t* __restrict__ t0, const half_t* __restrict__ D0,
+                                                          const half_t* __restrict__ t1, const half_t* __restrict__ D1,
                                                           int L, const int* __restrict__ offe,
                                                           const int* __restrict__ permm, int k, int gather,
                                                           int E, float* __restrict__ part) {
   constexpr int RB = R == 32 ? 2 : 1;   // 16-row blocks of rank rows
   __shared__ __attribute__((aligned(16))) half_t st[4][RB * 16][40];
-  const int e = blockIdx.y, sp = blockIdx.z, split = gridDim.z;
+  const int e = blockIdx.y, split = gridDim.z / 2, second = (int)blockIdx.z >= split, sp = blockIdx.z - second * split;
+  const half_t *t = second ? t1 : t0, *D = second ? D1 : D0;
+  part += second * ((size_t)split * E * R * L);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 15, q = lane >> 4;
   const int col = (blockIdx.x * 4 + wave) * 128 + 8 * c, colc = min(col, L - 8);
   if (col - 8 * c >= L) return;
@@ -451,14 +443,16 @@ __global__ __launch_bounds__(256) void bw_rankgrad_kernel(const half_t* __restri
     }
 }
 
-// out[i] = part[0][i] + part[1][i] + ... in run order, i < n (a multiple of 4); all loads in flight
-// together (a loop over a run-time count waited for each
+// out[i] = part[0][i] + part[1][i] + ... in run order, i < n (a multiple of 4), grid.y times (out0, out1); all
+// loads in flight together (a loop over a run-time count waited for each
 // in turn: 6.2 instead of 2.7 us for 16 runs of 4 x 512 x 8 values).
 template <int RUNS>
 __global__ __launch_bounds__(256) void bw_rankgrad_finish_kernel(const float* __restrict__ part, size_t n,
-                                                                 float* __restrict__ out) {
+                                                                 float* __restrict__ out0, float* __restrict__ out1) {
   const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i >= n) return;
+  float* out = blockIdx.y ? out1 : out0;
+  part += blockIdx.y * (RUNS * n);
   float4v v[RUNS];
 #pragma unroll
   for (int sp = 0; sp < RUNS; ++sp) v[sp] = *(const float4v*)(part + sp * n + i);
@@ -489,48 +483,57 @@ inline int row_runs(int E, int L, int cols) {
 }
 constexpr int RG_COLS = 512, DR_COLS = 1024;   // columns of a workgroup
 
-void finish(const float* part, size_t n, int split, float* out, hipStream_t st) {
+// One or two (out1 != NULL) sums of n values.
+void finish(const float* part, size_t n, int split, float* out0, float* out1, hipStream_t st) {
   auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, st, part, n, out);
+    hipLaunchKernelGGL(kern, dim3((unsigned)((n / 4 + 255) / 256), out1 ? 2 : 1), dim3(256), 0, st, part, n, out0, out1);
   };
   if (split == 4) go(bw_rankgrad_finish_kernel<4>);
   else if (split == 8) go(bw_rankgrad_finish_kernel<8>);
   else go(bw_rankgrad_finish_kernel<16>);
 }
 
+struct RankGrad {
+  const half_t *t, *D;
+  float* out;
+};
 template <int R>
-void rankgrad_r(const half_t* t, const half_t* D, int L, const int* offe, const int* permm, int k, int gather,
-                int E, float* part, float* out, hipStream_t st) {
+void rankgrad_r(const RankGrad& a, const RankGrad& b, int L, const int* offe, const int* permm, int k, int gather, int E,
+                float* part, hipStream_t st) {
   const int split = row_runs(E, L, RG_COLS);
-  hipLaunchKernelGGL(bw_rankgrad_kernel<R>, dim3((L + RG_COLS - 1) / RG_COLS, E, split), dim3(256), 0, st, t, D, L, offe,
-                     permm, k, gather, E, part);
-  finish(part, (size_t)E * R * L, split, out, st);
+  hipLaunchKernelGGL(bw_rankgrad_kernel<R>, dim3((L + RG_COLS - 1) / RG_COLS, E, 2 * split), dim3(256), 0, st, a.t, a.D, b.t,
+                     b.D, L, offe, permm, k, gather, E, part);
+  finish(part, (size_t)E * R * L, split, a.out, b.out, st);
 }
 
-void rankgrad(int r, const half_t* t, const half_t* D, int L, const int* offe, const int* permm, int k, int gather,
-              int E, float* part, float* out, hipStream_t st) {
+// Two factor gradients of width L.
+void rankgrad(int r, const RankGrad& a, const RankGrad& b, int L, const int* offe, const int* permm, int k, int gather,
+              int E, float* part, hipStream_t st) {
   switch (r) {
-    case 4: rankgrad_r<4>(t, D, L, offe, permm, k, gather, E, part, out, st); break;
-    case 8: rankgrad_r<8>(t, D, L, offe, permm, k, gather, E, part, out, st); break;
-    case 16: rankgrad_r<16>(t, D, L, offe, permm, k, gather, E, part, out, st); break;
-    default: rankgrad_r<32>(t, D, L, offe, permm, k, gather, E, part, out, st); break;
+    case 4: rankgrad_r<4>(a, b, L, offe, permm, k, gather, E, part, st); break;
+    case 8: rankgrad_r<8>(a, b, L, offe, permm, k, gather, E, part, st); break;
+    case 16: rankgrad_r<16>(a, b, L, offe, permm, k, gather, E, part, st); break;
+    default: rankgrad_r<32>(a, b, L, offe, permm, k, gather, E, part, st); break;
   }
 }
 
 inline size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 
-void transpose(const half_t* src, int ld, int I, const int* idx, const float* scale, int Npad, half_t* out,
-               hipStream_t st) {
-  hipLaunchKernelGGL(bw_transpose_kernel, dim3(Npad / 64, (I + 63) / 64, 1), dim3(256), 0, st, src, ld, 0L, I, idx, scale,
-                     Npad, (const int*)nullptr, (size_t)0, 1, out);
+// The transposed, cluster-padded copies of two matrices of I columns whose rows idx names.
+void transpose_rows(const half_t* a, const half_t* b, int I, const int* idx, int Npad, half_t* ta, half_t* tb,
+                    hipStream_t st) {
+  const TransposeJobs jobs{{{a, ta, idx, 0L, I, I, Npad}, {b, tb, idx, 0L, I, I, Npad}}};
+  hipLaunchKernelGGL(bw_transpose_kernel, dim3((unsigned)(Npad / 64) * (I / 64), 2, 1), dim3(256), 0, st, jobs,
+                     (const int*)nullptr, (size_t)0);
 }
 
 }  // namespace
 
 cmoe_bw_layout cmoe_backward_layout(const cmoe_dims& dm, int T) {
-  cmoe_bw_layout L;
+  cmoe_bw_layout L{};
   const size_t E = (size_t)dm.G * dm.K, G = dm.G, Tz = (size_t)(T > 0 ? T : 0), M = Tz * dm.k;
-  const size_t d = dm.d, f = dm.d_ff, r = dm.r;
+  const size_t d = dm.d, f = dm.d_ff, r = dm.r, KRp = dm.KRp;
+  const bool mid = bw_mid_ok(dm);
   L.M = (int)M;
   L.Tpad = (int)((Tz + 32 * G + 63) / 64 * 64);
   const size_t Tp = L.Tpad;
@@ -540,7 +543,8 @@ cmoe_bw_layout cmoe_backward_layout(const cmoe_dims& dm, int T) {
     off = up256(off + bytes);
     return at;
   };
-  L.counts = take(sizeof(int) * sort_counts(M, E));
+  const size_t counts_t = sort_counts(Tz, 64 * G), counts_m = sort_counts(M, E);
+  L.counts = take(sizeof(int) * (counts_t > counts_m ? counts_t : counts_m));
   L.permc = take(sizeof(int) * Tz);
   L.invc = take(sizeof(int) * Tz);
   L.offc = take(sizeof(int) * (G + 1));
@@ -548,40 +552,56 @@ cmoe_bw_layout cmoe_backward_layout(const cmoe_dims& dm, int T) {
   L.invm = take(sizeof(int) * M);
   L.offe = take(sizeof(int) * (E + 1));
   L.krange_c = take(sizeof(int) * 2 * G);
-  L.srow_c = take(sizeof(int) * Tp);
   L.ssrc_c = take(sizeof(int) * Tp);
-  L.offx_f = take(sizeof(int) * (G + 1));
-  L.gidx_f = take(sizeof(int) * G * f);
-  L.offx_d = take(sizeof(int) * (G + 1));
-  L.gidx_d = take(sizeof(int) * G * d);
   L.dl = take(sizeof(float) * M);
-  L.v1p = take(sizeof(half_t) * E * 32 * d);
-  L.u2p = take(sizeof(half_t) * E * 32 * d);
-  L.u1p = take(sizeof(half_t) * E * 32 * f);
-  L.v2p = take(sizeof(half_t) * E * 32 * f);
   L.w1bt = take(sizeof(half_t) * G * f * d);
   L.w2bt = take(sizeof(half_t) * G * f * d);
   L.hb = take(sizeof(half_t) * Tz * f);
   L.dab = take(sizeof(half_t) * Tz * f);
-  L.rh = take(sizeof(half_t) * M * f);
-  L.rda = take(sizeof(half_t) * M * f);
-  L.a16 = take(sizeof(half_t) * M * f);
-  L.dh16 = take(sizeof(half_t) * M * f);
   L.dhsum16 = take(sizeof(half_t) * Tz * f);
-  L.ag16 = take(sizeof(half_t) * Tz * f);
-  L.t1 = take(sizeof(half_t) * M * 32);
-  L.uy = take(sizeof(half_t) * M * 32);
   L.qq = take(sizeof(half_t) * M * 32);
   L.ss = take(sizeof(half_t) * M * 32);
-  L.dxb = take(sizeof(half_t) * Tz * d);
-  L.dxr = take(sizeof(half_t) * M * d);
   L.xct = take(sizeof(half_t) * d * Tp);
   L.dyct = take(sizeof(half_t) * d * Tp);
   L.dhst = take(sizeof(half_t) * f * Tp);
   L.agt = take(sizeof(half_t) * f * Tp);
-  const size_t runs_f = row_runs((int)E, dm.d_ff, RG_COLS) * f, runs_d = row_runs((int)E, dm.d, RG_COLS) * d;
+  if (mid) {
+    const size_t chunks = bw_mid_chunks(dm), slots = bw_mid_slots(dm, (int)Tz);
+    L.perm2 = take(sizeof(int) * Tz);
+    L.rowmap = take(sizeof(int) * Tz);
+    L.es = take(sizeof(int) * M);
+    L.gs = take(sizeof(float) * M);
+    L.v1p = take(sizeof(half_t) * G * KRp * d);
+    L.u2p = take(sizeof(half_t) * G * KRp * d);
+    L.u1p = take(sizeof(half_t) * G * KRp * f);
+    L.v2p = take(sizeof(half_t) * G * KRp * f);
+    L.t1 = take(sizeof(half_t) * M * r);
+    L.uy = take(sizeof(half_t) * M * r);
+    L.q16 = take(sizeof(half_t) * M * r);
+    L.qpart = take(sizeof(float) * chunks * M * r);
+    L.spart = take(sizeof(float) * chunks * M * r);
+    L.dotp = take(sizeof(float) * chunks * M);
+    L.dup = take(sizeof(float) * slots * KRp * f);
+    L.dvp = take(sizeof(float) * slots * KRp * f);
+  } else {
+    L.v1p = take(sizeof(half_t) * E * RP * d);
+    L.u2p = take(sizeof(half_t) * E * RP * d);
+    L.u1p = take(sizeof(half_t) * E * RP * f);
+    L.v2p = take(sizeof(half_t) * E * RP * f);
+    L.rh = take(sizeof(half_t) * M * f);
+    L.rda = take(sizeof(half_t) * M * f);
+    L.a16 = take(sizeof(half_t) * M * f);
+    L.dh16 = take(sizeof(half_t) * M * f);
+    L.ag16 = take(sizeof(half_t) * Tz * f);
+    L.t1 = take(sizeof(half_t) * M * RP);
+    L.uy = take(sizeof(half_t) * M * RP);
+    L.dxb = take(sizeof(half_t) * Tz * d);
+    L.dxr = take(sizeof(half_t) * M * d);
+  }
+  // partial sums of two factor gradients of a width, or of the router gradient
+  const size_t runs_f = mid ? 0 : row_runs((int)E, dm.d_ff, RG_COLS) * f, runs_d = row_runs((int)E, dm.d, RG_COLS) * d;
   const size_t runs_r = row_runs((int)E, dm.d, DR_COLS) * d;
-  const size_t runs = r * (runs_f > runs_d ? runs_f : runs_d);
+  const size_t runs = 2 * r * (runs_f > runs_d ? runs_f : runs_d);
   L.rgpart = take(sizeof(float) * E * (runs > runs_r ? runs : runs_r));
   L.total = off;
   return L;
@@ -594,23 +614,27 @@ hipError_t launch_backward(const cmoe_dims& dm, const cmoe_weights& w, const hal
   auto I = [&](size_t o) { return (int*)(ws + o); };
   auto H = [&](size_t o) { return (half_t*)(ws + o); };
   auto F = [&](size_t o) { return (float*)(ws + o); };
-  int *permc = I(L.permc), *offc = I(L.offc), *permm = I(L.permm), *invm = I(L.invm), *offe = I(L.offe);
+  int *offc = I(L.offc), *permm = I(L.permm), *invm = I(L.invm), *offe = I(L.offe);
   int* krc = I(L.krange_c);
   float* dl = out.d_logits ? out.d_logits : F(L.dl);
+  float* part = F(L.rgpart);
   const long mat = (long)f * d;
+  const bool mid = bw_mid_ok(dm);
+  // rows in cluster order; where the middle is one kernel, ordered by expert pair inside a cluster
+  int* permc = I(mid ? L.perm2 : L.permc);
   // the bases: from the re-tiled copy when the caller keeps one (the canonical arrays may
   // then be absent), else the canonical arrays
   const bool pk = w.packed != nullptr;
   const cmoe_packed_layout PL = cmoe_packed(dm);
-  const half_t* w1b = pk ? (const half_t*)((const char*)w.packed + PL.w1) : (const half_t*)w.w1_base;
-  const half_t* w2b = pk ? (const half_t*)((const char*)w.packed + PL.w2) : (const half_t*)w.w2_base;
+  const char* pkb = (const char*)w.packed;
+  const half_t* w1b = pk ? (const half_t*)(pkb + PL.w1) : (const half_t*)w.w1_base;
+  const half_t* w2b = pk ? (const half_t*)(pkb + PL.w2) : (const half_t*)w.w2_base;
   hipError_t err;
 #define BW_CHECK(call)                    \
   do {                                    \
     err = (call);                         \
     if (err != hipSuccess) return err;    \
   } while (0)
-#define BW_GEMM(...) BW_CHECK(launch_gemm_plain(__VA_ARGS__, st))
   // a product over expert groups, at most 64 groups per launch (one lane of a wavefront looks at
   // each group: launch_gemm_plain takes no more); rows are addressed absolutely, so a launch over a
   // slice of the offsets needs no other change
@@ -626,96 +650,107 @@ hipError_t launch_backward(const cmoe_dims& dm, const cmoe_weights& w, const hal
 
   // tokens sorted by cluster (of their first selected expert), pairs sorted by expert (both stable)
   if (T > 0) {
-    BW_CHECK(launch_sort_ids(expert_idx, k, dm.K, T, G, permc, I(L.invc), offc, I(L.counts), st));
+    if (mid)
+      BW_CHECK(launch_sort_pairs(dm, expert_idx, k, dm.K, expert_idx, T, I(L.permc), I(L.invc), offc, I(L.counts),
+                                 I(L.rowmap), permc, st));
+    else
+      BW_CHECK(launch_sort_ids(expert_idx, k, dm.K, T, G, permc, I(L.invc), offc, I(L.counts), st));
     BW_CHECK(launch_sort_ids(expert_idx, 1, 1, M, E, permm, invm, offe, I(L.counts), st));
   } else {
-    hipLaunchKernelGGL(bw_zero_kernel, dim3(1), dim3(256), 0, st, offc, G + 1);
-    hipLaunchKernelGGL(bw_zero_kernel, dim3((E + 256) / 256), dim3(256), 0, st, offe, E + 1);
+    hipLaunchKernelGGL(bw_zero_kernel, dim3(1), dim3(256), 0, st, offc, (size_t)(G + 1));
+    hipLaunchKernelGGL(bw_zero_kernel, dim3((E + 256) / 256), dim3(256), 0, st, offe, (size_t)(E + 1));
   }
-  hipLaunchKernelGGL(bw_map_kernel, dim3((Tpad + 255) / 256), dim3(256), 0, st, offc, permc, (const float*)nullptr, G,
-                     1, Tpad, krc, I(L.srow_c), I(L.ssrc_c), (float*)nullptr);
-  hipLaunchKernelGGL(bw_rows_kernel, dim3((unsigned)(((size_t)G * f + 256) / 256)), dim3(256), 0, st, G, f,
-                     I(L.offx_f), I(L.gidx_f));
-  hipLaunchKernelGGL(bw_rows_kernel, dim3((unsigned)(((size_t)G * d + 256) / 256)), dim3(256), 0, st, G, d,
-                     I(L.offx_d), I(L.gidx_d));
+  int* es = mid ? I(L.es) : nullptr;
+  float* gs = mid ? F(L.gs) : nullptr;
+  hipLaunchKernelGGL(bw_map_kernel, dim3((Tpad + 255) / 256), dim3(256), 0, st, offc, permc, G, Tpad, krc, I(L.ssrc_c),
+                     expert_idx, gate, dm.K, k, es, gs);
   // no token: the products below find empty groups and write zero gradients
   if (T > 0) {
-    // operand panels: rank factors and transposed bases
-    const int q = dm.q;
-    hipLaunchKernelGGL(bw_panel_kernel, dim3((d + 255) / 256, E), dim3(256), 0, st, (const uint8_t*)w.v1_q,
-                       (const half_t*)w.v1_s, d, q, r, offe, H(L.v1p));
-    hipLaunchKernelGGL(bw_panel_kernel, dim3((f + 255) / 256, E), dim3(256), 0, st, (const uint8_t*)w.u1_q,
-                       (const half_t*)w.u1_s, f, q, r, offe, H(L.u1p));
-    hipLaunchKernelGGL(bw_panel_kernel, dim3((d + 255) / 256, E), dim3(256), 0, st, (const uint8_t*)w.u2_q,
-                       (const half_t*)w.u2_s, d, q, r, offe, H(L.u2p));
-    hipLaunchKernelGGL(bw_panel_kernel, dim3((f + 255) / 256, E), dim3(256), 0, st, (const uint8_t*)w.v2_q,
-                       (const half_t*)w.v2_s, f, q, r, offe, H(L.v2p));
     // w1bt = B1^T ([d][d_ff] per cluster), w2bt = B2^T ([d_ff][d]), both in 32-column blocks
-    hipLaunchKernelGGL(bw_transpose_kernel, dim3(f / 64, d / 64, G), dim3(256), 0, st, w1b, d, pk ? (long)f * 32 : 0L, d,
-                       (const int*)nullptr, (const float*)nullptr, f, offc, (size_t)mat, 1, H(L.w1bt));
-    hipLaunchKernelGGL(bw_transpose_kernel, dim3(d / 64, f / 64, G), dim3(256), 0, st, w2b, f, pk ? (long)d * 32 : 0L, f,
-                       (const int*)nullptr, (const float*)nullptr, d, offc, (size_t)mat, 1, H(L.w2bt));
+    const TransposeJobs bases{{{w1b, H(L.w1bt), nullptr, pk ? (long)f * 32 : 0L, d, d, f},
+                               {w2b, H(L.w2bt), nullptr, pk ? (long)d * 32 : 0L, f, f, d}}};
+    hipLaunchKernelGGL(bw_transpose_kernel, dim3((unsigned)(f / 64) * (d / 64), 2, G), dim3(256), 0, st, bases, offc,
+                       (size_t)mat);
+    // transposed, cluster-padded copies for the base gradients (contraction over tokens)
+    transpose_rows(x, dy, d, I(L.ssrc_c), Tpad, H(L.xct), H(L.dyct), st);
     BW_CHECK(hipGetLastError());
-
-    // h = B1 x + U1 (V1 x): base product per token (token order), rank part per pair
-    if (pk)   // packed W1: [d/32][d_ff][32] per cluster
-      BW_CHECK(launch_gemm_plain(w1b, mat, 32, f, x, d, permc, 1, d, offc, G, T, nullptr, permc,
-                                 H(L.hb), f, false, st, (long)f * 32, 0));
-    else
-      BW_GEMM(w1b, mat, d, f, x, d, permc, 1, d, offc, G, T, nullptr, permc, H(L.hb), f, false);
-    BW_CHECK(rank_gemm(H(L.v1p), d, x, d, permm, k, H(L.t1)));
-    rankexpand(r, H(L.t1), H(L.u1p), f, offe, nullptr, E, H(L.rh), st);
-    // da = B2^T dy + V2^T (U2^T dy)
-    BW_CHECK(launch_gemm_plain(H(L.w2bt), mat, 32, f, dy, d, permc, 1, d, offc, G, T, nullptr, permc, H(L.dab), f, false,
-                               st, (long)f * 32, 0));
-    BW_CHECK(rank_gemm(H(L.u2p), d, dy, d, permm, k, H(L.uy)));
-    rankexpand(r, H(L.uy), H(L.v2p), f, offe, nullptr, E, H(L.rda), st);
-    if (k <= 2)
-      hipLaunchKernelGGL(bw_act_kernel<2>, dim3(T), dim3(256), 0, st, H(L.hb), H(L.dab), H(L.rh), H(L.rda), invm, gate, k,
-                         f, H(L.a16), H(L.dh16), H(L.dhsum16), H(L.ag16), dl);
-    else
-      hipLaunchKernelGGL(bw_act_kernel<8>, dim3(T), dim3(256), 0, st, H(L.hb), H(L.dab), H(L.rh), H(L.rda), invm, gate, k,
-                         f, H(L.a16), H(L.dh16), H(L.dhsum16), H(L.ag16), dl);
-    // dx = B1^T (sum_j dh) + sum_j V1^T (U1^T dh) + gate path
-    BW_CHECK(launch_gemm_plain(H(L.w1bt), mat, 32, d, H(L.dhsum16), f, permc, 1, f, offc, G, T, nullptr, permc, H(L.dxb), d,
-                               false, st, (long)d * 32, 0));
-    BW_CHECK(rank_gemm(H(L.u1p), f, H(L.dh16), f, nullptr, 1, H(L.qq)));
-    rankexpand(r, H(L.qq), H(L.v1p), d, offe, permm, E, H(L.dxr), st);
-    hipLaunchKernelGGL(bw_dx_kernel, dim3(T, (d / 4 + 255) / 256), dim3(256), 0, st, H(L.dxb), H(L.dxr), dl, expert_idx,
-                       (const half_t*)w.router_expert, k, d, out.dx);
-    // s = V2 a per pair
-    BW_CHECK(rank_gemm(H(L.v2p), f, H(L.a16), f, nullptr, 1, H(L.ss)));
-    // transposed, cluster-padded copies for the base gradients (contraction over tokens),
-    // stored in 32-column blocks
-    const int* ssrc_c = I(L.ssrc_c);
-    transpose(x, d, d, ssrc_c, nullptr, Tpad, H(L.xct), st);
-    transpose(dy, d, d, ssrc_c, nullptr, Tpad, H(L.dyct), st);
-    transpose(H(L.dhsum16), f, f, ssrc_c, nullptr, Tpad, H(L.dhst), st);
-    transpose(H(L.ag16), f, f, ssrc_c, nullptr, Tpad, H(L.agt), st);
+    const long w1_step = pk ? (long)f * 32 : 0L;   // packed W1: [d/32][d_ff][32] per cluster
+    const int w1_ld = pk ? 32 : d;
+    if (mid) {
+      // factor panels by cluster: V1, U1^T and V2 from the packed copy if there is one
+      const half_t* v1cat = pk ? (const half_t*)(pkb + PL.v1cat) : H(L.v1p);
+      const half_t* u1t = pk ? (const half_t*)(pkb + PL.u1t) : H(L.u1p);
+      const half_t* v2p = pk ? (const half_t*)(pkb + PL.v2p) : H(L.v2p);
+      if (!pk) BW_CHECK(launch_dequant_ffn(dm, w, offc, H(L.v1p), H(L.u1p), H(L.v2p), nullptr, st));
+      BW_CHECK(launch_dequant_rows(dm, w.u2_q, w.u2_s, offc, d, H(L.u2p), st));
+      BW_CHECK(launch_t1_pair(dm, T, permc, offc, expert_idx, x, v1cat, H(L.t1), dy, H(L.u2p), H(L.uy), st));
+      BW_CHECK(launch_gemm_blocked(w1b, mat, w1_ld, w1_step, f, x, d, permc, d, offc, G, T, H(L.hb), st));
+      BW_CHECK(launch_gemm_blocked(H(L.w2bt), mat, 32, (long)f * 32, f, dy, d, permc, d, offc, G, T, H(L.dab), st));
+      const bw_mid_args a{H(L.hb), H(L.dab), H(L.t1), H(L.uy), u1t, v2p, es, gs, offc, offe, krc, H(L.dhsum16),
+                          H(L.dhst), H(L.agt), F(L.qpart), F(L.spart), F(L.dotp), F(L.dup), F(L.dvp), T};
+      BW_CHECK(launch_bw_mid(dm, a, st));
+      BW_CHECK(launch_bw_mid_sums(dm, a, permc, invm, H(L.q16), H(L.qq), H(L.ss), dl, out.du1, out.dv2, st));
+      BW_CHECK(launch_gemm_input_grad(dm, H(L.w1bt), H(L.dhsum16), T, offc, v1cat, offe, H(L.q16), es, permc, dl,
+                                      (const half_t*)w.router_expert, out.dx, st));
+    } else {
+      const int q = dm.q;
+      auto panel = [&](const void* qv, const void* sv, int L_, half_t* o) {
+        hipLaunchKernelGGL(bw_panel_kernel, dim3((L_ + 255) / 256, E), dim3(256), 0, st, (const uint8_t*)qv, (const half_t*)sv,
+                           L_, q, r, offe, o);
+      };
+      panel(w.v1_q, w.v1_s, d, H(L.v1p));
+      panel(w.u1_q, w.u1_s, f, H(L.u1p));
+      panel(w.u2_q, w.u2_s, d, H(L.u2p));
+      panel(w.v2_q, w.v2_s, f, H(L.v2p));
+      // h = B1 x + U1 (V1 x): base product per token (token order), rank part per pair
+      BW_CHECK(launch_gemm_plain(w1b, mat, w1_ld, f, x, d, permc, 1, d, offc, G, T, nullptr, permc, H(L.hb), f, false, st,
+                                 w1_step, 0));
+      BW_CHECK(rank_gemm(H(L.v1p), d, x, d, permm, k, H(L.t1)));
+      rankexpand(r, H(L.t1), H(L.u1p), f, offe, nullptr, E, H(L.rh), st);
+      // da = B2^T dy + V2^T (U2^T dy)
+      BW_CHECK(launch_gemm_plain(H(L.w2bt), mat, 32, f, dy, d, permc, 1, d, offc, G, T, nullptr, permc, H(L.dab), f, false,
+                                 st, (long)f * 32, 0));
+      BW_CHECK(rank_gemm(H(L.u2p), d, dy, d, permm, k, H(L.uy)));
+      rankexpand(r, H(L.uy), H(L.v2p), f, offe, nullptr, E, H(L.rda), st);
+      if (k <= 2)
+        hipLaunchKernelGGL(bw_act_kernel<2>, dim3(T), dim3(256), 0, st, H(L.hb), H(L.dab), H(L.rh), H(L.rda), invm, gate, k,
+                           f, H(L.a16), H(L.dh16), H(L.dhsum16), H(L.ag16), dl);
+      else
+        hipLaunchKernelGGL(bw_act_kernel<8>, dim3(T), dim3(256), 0, st, H(L.hb), H(L.dab), H(L.rh), H(L.rda), invm, gate, k,
+                           f, H(L.a16), H(L.dh16), H(L.dhsum16), H(L.ag16), dl);
+      // dx = B1^T (sum_j dh) + sum_j V1^T (U1^T dh) + gate path
+      BW_CHECK(launch_gemm_plain(H(L.w1bt), mat, 32, d, H(L.dhsum16), f, permc, 1, f, offc, G, T, nullptr, permc, H(L.dxb),
+                                 d, false, st, (long)d * 32, 0));
+      BW_CHECK(rank_gemm(H(L.u1p), f, H(L.dh16), f, nullptr, 1, H(L.qq)));
+      rankexpand(r, H(L.qq), H(L.v1p), d, offe, permm, E, H(L.dxr), st);
+      hipLaunchKernelGGL(bw_dx_kernel, dim3(T, (d / 4 + 255) / 256), dim3(256), 0, st, H(L.dxb), H(L.dxr), dl, expert_idx,
+                         (const half_t*)w.router_expert, k, d, out.dx);
+      // s = V2 a per pair
+      BW_CHECK(rank_gemm(H(L.v2p), f, H(L.a16), f, nullptr, 1, H(L.ss)));
+      transpose_rows(H(L.dhsum16), H(L.ag16), f, I(L.ssrc_c), Tpad, H(L.dhst), H(L.agt), st);
+      // the gate of the pair goes into the rank-space rows of the two factor gradients of the second matrix
+      hipLaunchKernelGGL(bw_scale_kernel, dim3((M * 4 + 255) / 256), dim3(256), 0, st, H(L.ss), permm, gate, M);
+      hipLaunchKernelGGL(bw_scale_kernel, dim3((M * 4 + 255) / 256), dim3(256), 0, st, H(L.uy), permm, gate, M);
+      rankgrad(r, {H(L.t1), H(L.dh16), out.du1}, {H(L.uy), H(L.a16), out.dv2}, f, offe, permm, k, 0, E, part, st);
+    }
     BW_CHECK(hipGetLastError());
+  } else {
+    const size_t n = (size_t)E * r * f;
+    hipLaunchKernelGGL(bw_zero_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (int*)out.du1, n);
+    hipLaunchKernelGGL(bw_zero_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (int*)out.dv2, n);
   }
   const int runs = row_runs(E, d, DR_COLS);
   hipLaunchKernelGGL(bw_drouter_kernel, dim3(E, (d + DR_COLS - 1) / DR_COLS, runs), dim3(256), 0, st, x, permm, offe, dl,
-                     k, d, E, F(L.rgpart));
-  finish(F(L.rgpart), (size_t)E * d, runs, out.d_router_expert, st);
+                     k, d, E, part);
+  finish(part, (size_t)E * d, runs, out.d_router_expert, nullptr, st);
   // base gradients: contraction over the tokens of a cluster
   // (operands in the blocked layout [Tpad / 32][rows][32]: row stride 32, block stride rows * 32)
-  BW_CHECK(launch_gemm_plain(H(L.xct), 0, 32, d, H(L.dhst), 32, I(L.gidx_f), 1, Tpad, I(L.offx_f), G, G * f, krc,
-                             nullptr, out.dw1_base, d, true, st, (long)d * 32, (long)f * 32));
-  BW_CHECK(launch_gemm_plain(H(L.agt), 0, 32, f, H(L.dyct), 32, I(L.gidx_d), 1, Tpad, I(L.offx_d), G, G * d, krc,
-                             nullptr, out.dw2_base, f, true, st, (long)f * 32, (long)d * 32));
-  // factor gradients: contraction over the pairs of an expert, streamed once
-  float* part = F(L.rgpart);
-  rankgrad(r, H(L.t1), H(L.dh16), f, offe, permm, k, 0, E, part, out.du1, st);
-  rankgrad(r, H(L.qq), x, d, offe, permm, k, 1, E, part, out.dv1, st);
-  // the gate of the pair goes into the rank-space rows of the two products of the second matrix
-  if (M > 0) {
-    hipLaunchKernelGGL(bw_scale_kernel, dim3((M * 4 + 255) / 256), dim3(256), 0, st, H(L.ss), permm, gate, M);
-    hipLaunchKernelGGL(bw_scale_kernel, dim3((M * 4 + 255) / 256), dim3(256), 0, st, H(L.uy), permm, gate, M);
-  }
-  rankgrad(r, H(L.ss), dy, d, offe, permm, k, 1, E, part, out.du2, st);
-  rankgrad(r, H(L.uy), H(L.a16), f, offe, permm, k, 0, E, part, out.dv2, st);
-#undef BW_GEMM
+  BW_CHECK(launch_gemm_plain(H(L.xct), 0, 32, d, H(L.dhst), 32, nullptr, 1, Tpad, nullptr, G, G * f, krc, nullptr,
+                             out.dw1_base, d, true, st, (long)d * 32, (long)f * 32));
+  BW_CHECK(launch_gemm_plain(H(L.agt), 0, 32, f, H(L.dyct), 32, nullptr, 1, Tpad, nullptr, G, G * d, krc, nullptr,
+                             out.dw2_base, f, true, st, (long)f * 32, (long)d * 32));
+  // factor gradients of V1 and U2: contraction over the pairs of an expert, streamed once
+  rankgrad(r, {H(L.qq), x, out.dv1}, {H(L.ss), dy, out.du2}, d, offe, permm, k, 1, E, part, st);
 #undef BW_CHECK
   return hipGetLastError();
 }

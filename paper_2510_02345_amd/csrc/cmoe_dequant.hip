@@ -146,3 +146,13 @@ hipError_t launch_dequant_u2(const cmoe_dims& dm, const cmoe_weights& w, const i
   hipLaunchKernelGGL(dequant_kernel, dim3(total), dim3(256), 0, st, js, dm.q, dm.K, dm.r, dm.KRp, dm.G, offsets);
   return hipGetLastError();
 }
+
+// One factor's row-preserving panel [G][KRp][L].
+hipError_t launch_dequant_rows(const cmoe_dims& dm, const uint8_t* qv, const void* sv, const int* offsets, int L,
+                               half_t* out, hipStream_t st) {
+  DequantJobs js{};
+  unsigned total = 0;
+  add_job(js, total, dm, qv, sv, out, L, 0);
+  hipLaunchKernelGGL(dequant_kernel, dim3(total), dim3(256), 0, st, js, dm.q, dm.K, dm.r, dm.KRp, dm.G, offsets);
+  return hipGetLastError();
+}

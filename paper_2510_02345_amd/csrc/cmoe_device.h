@@ -94,6 +94,24 @@ __device__ __forceinline__ void wait_vm() {
 // stage that was read is refilled by loads that go to LDS, or what was written is read by others.
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// Transposing LDS read of 16-bit elements: the 16 lanes of a group (l / 16) read a 4 x 16 matrix, lane i
+// the four consecutive elements 4 (i % 4) .. of matrix row i / 4 at its own address p, and lane i
+// gets column i, element u of the result being row u.  Two of them make a matrix-core operand of a
+// tile stored with the contraction index along its rows.
+__device__ __forceinline__ half4 lds_read_tr(const void* p) {
+  typedef short s4 __attribute__((__vector_size__(4 * sizeof(short))));
+  return __builtin_bit_cast(half4, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                       (__attribute__((address_space(3))) s4*)(__attribute__((address_space(3))) void*)p));
+}
+__device__ __forceinline__ half8 join8(const half4& a, const half4& b) {
+  return half8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+}
+// What this wavefront wrote to LDS is read by its own lanes behind this (no barrier needed).
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Ranking key of a logit: a NaN ranks below every number (as -inf), so that the selections of the
 // router always return distinct, valid slots whatever the input holds.
 __device__ __forceinline__ float rank_key(float v) { return v == v ? v : -INFINITY; }
@@ -116,13 +134,20 @@ __device__ __forceinline__ int wave_inclusive_sum(int v) {
 struct RowTiles {
   static constexpr int MAX_GROUPS = 64;
   int lo, hi, tiles, incl;   // per lane: rows and tiles of group `lane`, tiles up to and including it
-  __device__ __forceinline__ RowTiles(const int* offsets, int n_groups, int bm) : lo(0), hi(0) {
+  // rows_each != 0: every group has that many rows and offsets is not read
+  __device__ __forceinline__ RowTiles(const int* offsets, int n_groups, int bm, int rows_each = 0) : lo(0), hi(0) {
     const int lane = threadIdx.x & 63;
-    if (lane < n_groups) lo = offsets[lane], hi = offsets[lane + 1];
+    if (lane < n_groups) {
+      lo = rows_each ? lane * rows_each : offsets[lane];
+      hi = rows_each ? lo + rows_each : offsets[lane + 1];
+    }
     tiles = (hi - lo + bm - 1) / bm;
     incl = wave_inclusive_sum(tiles);
   }
   __device__ __forceinline__ int total() const { return __builtin_amdgcn_readlane(incl, 63); }
+  // the tiles of group c are [first_tile(c), end_tile(c))
+  __device__ __forceinline__ int first_tile(int c) const { return __builtin_amdgcn_readlane(incl - tiles, c); }
+  __device__ __forceinline__ int end_tile(int c) const { return __builtin_amdgcn_readlane(incl, c); }
   // group c of tile `slot`, its first row m0 and the end m_end of the group's rows; false: past the last tile
   __device__ __forceinline__ bool find(int slot, int bm, int& c, int& m0, int& m_end) const {
     const unsigned long long past = __ballot(incl > slot);

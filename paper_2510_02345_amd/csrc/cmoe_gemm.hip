@@ -60,6 +60,9 @@ struct GemmArgs {
   // (plain row-major rows).  An operand stored as [K / 32][rows][32] has ld = 32 and a
   // step of rows * 32: the 16 rows of one load instruction are then 1 KiB of contiguous memory.
   long kstep_w, kstep_x;
+  // rows_each != 0: every group has that many rows (offsets is not read) and row p of group c reads
+  // row p - c * rows_each of X, which all groups share
+  int rows_each;
 };
 
 struct TileCtx {
@@ -88,7 +91,7 @@ struct TileSrc {
       base = g.W + (size_t)c * g.w_cstride + (size_t)min(n0 + pi_row(row), g.N - 1) * g.ldw + (size_t)k_lo * kstep_w;
     } else {
       const int p = min(m0 + row - bn, m_end - 1);
-      base = g.X + (size_t)(g.gather ? (g.x_div > 1 ? g.gather[p] / g.x_div : g.gather[p]) : p) * g.ldx +
+      base = g.X + (size_t)(g.gather ? (g.x_div > 1 ? g.gather[p] / g.x_div : g.gather[p]) : p - c * g.rows_each) * g.ldx +
              (size_t)k_lo * kstep_x;
     }
     return base + ((pos ^ swz(row)) << 3);
@@ -326,7 +329,7 @@ __global__ __launch_bounds__(512, 1) void gemm_kernel(GemmArgs g, Epi epi) {
   constexpr int SMEM = SB > SH ? (SB > SQ ? SB : SQ) : (SH > SQ ? SH : SQ);
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
   const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
-  const RowTiles rt(g.offsets, g.G, TileBig::BM);
+  const RowTiles rt(g.offsets, g.G, TileBig::BM, g.rows_each);
   const int slots = rt.total(), tiles = slots * g.n_tiles;
   const int lo = (int)((long)tiles * xcd >> 3), mine = (int)((long)tiles * (xcd + 1) >> 3) - lo;
   int full = mine / XCD_CUS * XCD_CUS, cut = 0;   // log2 of the parts a leftover tile is cut into
@@ -458,6 +461,129 @@ struct EpiStoreT {
   }
 };
 using EpiStore = EpiStoreT<half_t>;
+
+// The same in 32-column blocks, out[n / 32][p][n % 32] (rows p in tile order): the layout in which the
+// middle of the backward pass and a further product read whole KiBs.
+struct EpiStoreBlocked {
+  using Quarter = TileQuad;
+  half_t* out;
+  int T, N;
+  template <class TL>
+  static constexpr int smem_bytes() { return TL::SMEM_BYTES; }
+  template <class TL>
+  __device__ void run(const TileCtx& t, float4v (&acc)[TL::NA][TL::MT]) const {
+    const int t16 = t.lane & 15, q = t.lane >> 4;
+#pragma unroll
+    for (int b = 0; b < TL::MT; ++b) {
+      const int p = t.m0 + t.wm * TL::WM + b * 16 + t16;
+      if (p >= t.m_end) continue;
+#pragma unroll
+      for (int P = 0; P < TL::NP; ++P) {
+        const int nb = t.n0 + t.wn * TL::WN + 32 * P;
+        if (nb >= N) continue;   // N is a multiple of 32
+        *(half8*)(out + ((size_t)(nb >> 5) * T + p) * 32 + 8 * q) = pack_half8(acc[2 * P][b], acc[2 * P + 1][b]);
+      }
+    }
+  }
+};
+
+// ---------------------------------------------------------------- epilogue: input gradient
+// acc = (B1^T sum_j dh_j) blocks (rows n of d).  Adds the rank part of the pairs as one more contraction
+// over the cluster's rank rows, V1cat^T qext (qext[m][e_j r + rho] = q_j[rho], as EpiDownCombine does
+// for the second matrix), and the gate path sum_j dl_j v_{e_j} in FP32, and writes FP32 rows in
+// token order.  The panel V1cat is stored with the contraction index along its rows, so its
+// fragments are transposing LDS reads.  K*r <= 128.
+struct EpiInputGrad {
+  using Quarter = TileQuad;
+  const half_t* v1cat;          // [G][KRp][d]
+  const int* offe;              // [G K + 1] pair rows of the experts: the panel rows of an expert without any are zero
+  const half_t* q;              // [T][k][r], tile order
+  const int* es;                // [T][k] experts local to the cluster, tile order
+  const int* rperm;             // token of tile row p
+  const float* dl;              // [T][k], token order
+  const half_t* router_expert;  // [G K][d]
+  float* dx;                    // [T][d], token order
+  int k, K, r, KRp, d;
+  template <class TL>
+  static constexpr int panel_bytes() { return 128 * (TL::BN + 8) * 2; }
+  template <class TL>
+  static constexpr int smem_bytes() {
+    constexpr int need = panel_bytes<TL>() + TL::BM * (128 + 8) * 2;
+    return need > TL::SMEM_BYTES ? need : TL::SMEM_BYTES;
+  }
+  template <class TL>
+  __device__ void run(const TileCtx& t, float4v (&acc)[TL::NA][TL::MT]) const {
+    const int t16 = t.lane & 15, q4 = t.lane >> 4;
+    constexpr int LDV = TL::BN + 8;
+    const int lds = KRp + 8, n_chunks = KRp / 32;
+    half_t* sV = t.smem;                                // [KRp][LDV]
+    half_t* sS = t.smem + panel_bytes<TL>() / 2;        // [BM][lds]
+    const half_t* vc = v1cat + (size_t)t.c * KRp * d;
+    __syncthreads();  // the stage buffers are free
+    constexpr int CPR = TL::BN / 8;
+    for (int idx = t.tid; idx < KRp * CPR; idx += TL::NT) {
+      const int row = idx / CPR, ch = idx % CPR;
+      const int e = t.c * K + min(row / r, K - 1);
+      half8 v = *(const half8*)(vc + (size_t)row * d + min(t.n0 + ch * 8, d - 8));
+      if (offe[e + 1] == offe[e]) v = half8{0, 0, 0, 0, 0, 0, 0, 0};
+      *(half8*)(sV + row * LDV + ch * 8) = v;
+    }
+    for (int i = t.tid; i < TL::BM * lds / 8; i += TL::NT) ((half8*)sS)[i] = half8{0, 0, 0, 0, 0, 0, 0, 0};
+    __syncthreads();
+    const int r4 = r / 4;
+    for (int idx = t.tid; idx < TL::BM * k * r4; idx += TL::NT) {
+      const int rho = idx % r4 * 4, j = (idx / r4) % k, m = idx / (r4 * k), p = t.m0 + m;
+      if (p >= t.m_end) continue;
+      *(half4*)(sS + m * lds + es[(size_t)p * k + j] * r + rho) = *(const half4*)(q + ((size_t)p * k + j) * r + rho);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < TL::MT; ++b) {
+      const int m = t.wm * TL::WM + b * 16 + t16, p = t.m0 + m;
+      const bool valid = p < t.m_end;
+      const size_t pc = valid ? p : t.m_end - 1;
+      const size_t tok = rperm[pc];
+      unsigned mine = 0;
+      for (int j = 0; j < k; ++j) {
+        const int e = es[pc * k + j];
+        mine |= (0xffffffffu >> (31 - ((e * r + r - 1) >> 5))) & (0xffffffffu << ((e * r) >> 5));
+      }
+      if (!valid) mine = 0;
+      unsigned cmask = 0;
+      for (int kc = 0; kc < n_chunks; ++kc)
+        if (__ballot((mine >> kc) & 1u) != 0ull) cmask |= 1u << kc;
+#pragma unroll
+      for (int P = 0; P < TL::NP; ++P) {
+        const int nl = t.wn * TL::WN + 32 * P;
+        if (t.n0 + nl >= d) continue;
+        for (unsigned mm = cmask; mm != 0u; mm &= mm - 1u) {
+          const int kc = __builtin_ctz(mm);
+          const half8 fb = *(const half8*)(sS + m * lds + kc * 32 + 8 * q4);
+          // rows n = 8 (i / 4) + 4 hh + i % 4 of the pair block, contraction elements 8 q4 ..
+          const half_t* a0 = sV + (kc * 32 + 8 * q4 + (t16 >> 2)) * LDV + nl + 8 * (t16 & 3);
+#pragma unroll
+          for (int hh = 0; hh < 2; ++hh)
+            acc[2 * P + hh][b] =
+                mfma32(join8(lds_read_tr(a0 + 4 * hh), lds_read_tr(a0 + 4 * LDV + 4 * hh)), fb, acc[2 * P + hh][b]);
+        }
+        if (!valid) continue;
+        float4v o0 = acc[2 * P][b], o1 = acc[2 * P + 1][b];
+        for (int j = 0; j < k; ++j) {
+          const float c = dl[tok * k + j];
+          const half8 v = *(const half8*)(router_expert + ((size_t)t.c * K + es[pc * k + j]) * d + t.n0 + nl + 8 * q4);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            o0[i] = fmaf(c, (float)v[i], o0[i]);
+            o1[i] = fmaf(c, (float)v[4 + i], o1[i]);
+          }
+        }
+        float* dst = dx + tok * d + t.n0 + nl + 8 * q4;
+        *(float4v*)dst = o0;
+        *(float4v*)(dst + 4) = o1;
+      }
+    }
+  }
+};
 
 // ---------------------------------------------------------------- epilogue: down-projection + combine
 // acc = (W2_base A)^T blocks.  Adds the residual of the second matrix as one more
@@ -972,7 +1098,8 @@ hipError_t launch_gemm2_combine(const cmoe_dims& dm, const cmoe_weights& w, cons
 // Grouped product with a plain store, for callers outside the forward path:
 //   out[rowmap ? rowmap[p] : p][n] = sum_k X[row(p)][k_g + k] * W_g[n][k_g + k],
 // W_g = W + g * w_gstride, row(p) = gather ? gather[p] / x_div : p, rows p of group g in
-// [offsets[g], offsets[g+1]); k runs over [0, Kc) or over the group's krange.  At most
+// [offsets[g], offsets[g+1]); k runs over [0, Kc) or over the group's krange.  offsets == NULL (with a
+// FP32 output): the groups have rows / n_groups rows each and all read the same rows of X.  At most
 // RowTiles::MAX_GROUPS groups.
 hipError_t launch_gemm_plain(const half_t* W, long w_gstride, int ldw, int N, const half_t* X, int ldx,
                              const int* gather, int x_div, int Kc, const int* offsets, int n_groups, int rows,
@@ -982,6 +1109,7 @@ hipError_t launch_gemm_plain(const half_t* W, long w_gstride, int ldw, int N, co
   GemmArgs g{W, w_gstride, ldw, N, X, ldx, gather, Kc, offsets, n_groups, (N + TileBig::BN - 1) / TileBig::BN};
   g.x_div = x_div;
   g.krange = krange;
+  if (offsets == nullptr) g.rows_each = rows / n_groups;
   g.kstep_w = kstep_w;
   g.kstep_x = kstep_x;
   if (N <= 64 && !out_f32) {
@@ -997,6 +1125,27 @@ hipError_t launch_gemm_plain(const half_t* W, long w_gstride, int ldw, int N, co
   }
   EpiStore epi{(half_t*)out, rowmap, ldo, N};
   return launch_gemm(g, rows, epi, st);
+}
+
+// out[n / 32][p][n % 32] = sum_k W_c[n][k] X[gather[p]][k] for the sorted rows p of cluster c.
+hipError_t launch_gemm_blocked(const half_t* W, long w_gstride, int ldw, long kstep_w, int N, const half_t* X, int ldx,
+                               const int* gather, int Kc, const int* offsets, int n_groups, int rows, half_t* out,
+                               hipStream_t st) {
+  GemmArgs g{W, w_gstride, ldw, N, X, ldx, gather, Kc, offsets, n_groups, (N + TileBig::BN - 1) / TileBig::BN};
+  g.kstep_w = kstep_w;
+  return launch_gemm(g, rows, EpiStoreBlocked{out, rows, N}, st);
+}
+
+// dx[rperm[p]] = B1^T dhsum[p] + sum_j V1^T q_j + sum_j dl_j v_{e_j}; w1t = B1^T in 32-column blocks, dhsum
+// [d_ff / 32][T][32].
+hipError_t launch_gemm_input_grad(const cmoe_dims& dm, const half_t* w1t, const half_t* dhsum, int T, const int* offsets,
+                                  const half_t* v1cat, const int* offe, const half_t* q, const int* es, const int* rperm,
+                                  const float* dl, const half_t* router_expert, float* dx, hipStream_t st) {
+  GemmArgs g{w1t, (long)dm.d * dm.d_ff, 32, dm.d, dhsum, 32, nullptr, dm.d_ff, offsets, dm.G,
+             (dm.d + TileBig::BN - 1) / TileBig::BN};
+  g.kstep_w = (long)dm.d * 32;
+  g.kstep_x = (long)T * 32;
+  return launch_gemm(g, T, EpiInputGrad{v1cat, offe, q, es, rperm, dl, router_expert, dx, dm.k, dm.K, dm.r, dm.KRp, dm.d}, st);
 }
 
 // packed[c][(k / 32) * N + n][k % 32] = base[c][n][k].  A workgroup takes 64 rows n (four

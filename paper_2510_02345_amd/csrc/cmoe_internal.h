@@ -119,14 +119,20 @@ hipError_t launch_permute_static(const cmoe_dims& dm, const int* cluster_id, int
                                  int* offsets, hipStream_t st);
 hipError_t launch_pair_sort(const cmoe_dims& dm, const int* perm, const int* offsets, const int* expert_idx, int* rowmap,
                             int* perm2, hipStream_t st);
-hipError_t launch_sort_pairs(const cmoe_dims& dm, const int* cluster_id, const int* expert_idx, int T, int* perm,
-                             int* inv_perm, int* offsets, int* counts, int* rowmap, int* perm2, hipStream_t st);
+hipError_t launch_sort_pairs(const cmoe_dims& dm, const int* ids, int stride, int div, const int* expert_idx, int T,
+                             int* perm, int* inv_perm, int* offsets, int* counts, int* rowmap, int* perm2,
+                             hipStream_t st);
 hipError_t launch_sort_ids(const int* ids, int stride, int div, int n, int bins, int* perm, int* inv_perm, int* offsets,
                            int* counts, hipStream_t st);
 hipError_t launch_dequant_ffn(const cmoe_dims& dm, const cmoe_weights& w, const int* offsets, half_t* v1cat,
                               half_t* u1t, half_t* v2p, half_t* u2t, hipStream_t st);
 hipError_t launch_dequant_u2(const cmoe_dims& dm, const cmoe_weights& w, const int* offsets, half_t* u2t,
                              hipStream_t st);
+hipError_t launch_dequant_rows(const cmoe_dims& dm, const uint8_t* qv, const void* sv, const int* offsets, int L,
+                               half_t* out, hipStream_t st);
+hipError_t launch_t1_pair(const cmoe_dims& dm, int T, const int* perm, const int* offsets, const int* expert_idx,
+                          const half_t* x0, const half_t* v0, half_t* t0, const half_t* x1, const half_t* v1, half_t* t1,
+                          hipStream_t st);
 hipError_t launch_t1(const cmoe_dims& dm, const half_t* x, int x_div, int T, const int* perm, const int* offsets,
                      const int* expert_idx, const half_t* v1cat, half_t* t1ext, hipStream_t st);
 hipError_t launch_gemm1(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int x_div, int T, const int* perm,
@@ -174,17 +180,20 @@ hipError_t launch_combine(const cmoe_dims& dm, const half_t* u2t, const half_t* 
 // the transposed copies whose groups (clusters) are padded to 32.
 struct cmoe_bw_layout {
   int M, Tpad;
-  size_t counts, permc, invc, offc, permm, invm, offe, krange_c;
-  size_t srow_c, ssrc_c;
-  size_t offx_f, gidx_f, offx_d, gidx_d, dl;
-  size_t v1p, u2p, u1p, v2p;                  // f16 rank panels [E][32][L]
+  size_t counts, permc, invc, offc, permm, invm, offe, krange_c, ssrc_c, dl;
   size_t w1bt, w2bt;                          // f16 transposed bases
-  size_t hb, dab, rh, rda;                    // f16 [T][d_ff] x2 (token order), [M][d_ff] x2 (sorted pairs)
-  size_t a16, dh16, dhsum16, ag16;            // f16 [M][d_ff] x2, [T][d_ff] x2
-  size_t t1, uy, qq, ss;                      // f16 [M][32] rank-space rows of the pairs
-  size_t dxb, dxr;                            // f16 [T][d], [M][d]
+  size_t hb, dab, dhsum16;                    // f16 [T][d_ff]: token order, or [d_ff/32][T][32] by cluster (mid)
+  size_t qq, ss;                              // f16 [M][32] rank-space rows of the pairs, sorted by expert
   size_t xct, dyct, dhst, agt;                // f16 transposed copies, Tpad columns
-  size_t rgpart;                              // f32 [runs][E][r][d or d_ff], runs by row_runs for each width: partial sums of factor and router gradients
+  size_t v1p, u2p, u1p, v2p;                  // f16 rank panels, [E][32][L] or by cluster (mid)
+  size_t t1, uy;                              // f16 rank-space rows: [M][32] sorted pairs, or [T][k][r] tile order (mid)
+  // bw_mid_ok
+  size_t perm2, rowmap, es, gs, q16;          // rows by cluster and expert pair: token, place, experts, gates, q [T][k][r]
+  size_t qpart, spart, dotp, dup, dvp;        // f32 partial sums of the middle kernel
+  // else
+  size_t rh, rda, a16, dh16;                  // f16 [M][d_ff], sorted pairs
+  size_t ag16, dxb, dxr;                      // f16 [T][d_ff], [T][d], [M][d]
+  size_t rgpart;                              // f32 partial sums of factor and router gradients, runs by row_runs for each width
   size_t total;
 };
 cmoe_bw_layout cmoe_backward_layout(const cmoe_dims& dm, int T);
@@ -195,4 +204,32 @@ hipError_t launch_gemm_plain(const half_t* W, long w_gstride, int ldw, int N, co
                              const int* gather, int x_div, int Kc, const int* offsets, int n_groups, int rows,
                              const int* krange, const int* rowmap, void* out, int ldo, bool out_f32, hipStream_t st,
                              long kstep_w = 0, long kstep_x = 0);
+hipError_t launch_gemm_blocked(const half_t* W, long w_gstride, int ldw, long kstep_w, int N, const half_t* X, int ldx,
+                               const int* gather, int Kc, const int* offsets, int n_groups, int rows, half_t* out,
+                               hipStream_t st);
+hipError_t launch_gemm_input_grad(const cmoe_dims& dm, const half_t* w1t, const half_t* dhsum, int T, const int* offsets,
+                                  const half_t* v1cat, const int* offe, const half_t* q, const int* es, const int* rperm,
+                                  const float* dl, const half_t* router_expert, float* dx, hipStream_t st);
+// The middle of the backward pass (cmoe_backward_mid.hip), top_k <= 2 and KRp <= 128 (bw_mid_ok).
+struct bw_mid_args {
+  const half_t *hb, *dab;        // [d_ff / 32][T][32] base parts of h and da, rows in tile order
+  const half_t *t1, *uy;         // [T][k][r] V1 x and U2^T dy of the pairs, tile order
+  const half_t *u1t, *v2p;       // [G][d_ff][KRp], [G][KRp][d_ff] factor panels
+  const int* es;                 // [T][k] experts local to the cluster, tile order
+  const float* gs;               // [T][k] gates, tile order
+  const int *offsets, *offe;     // [G + 1], [G K + 1]
+  const int* krange;             // [2 G] first column of a cluster in the transposed copies (and its columns)
+  half_t* dhsum;                 // [d_ff / 32][T][32] sum_j dh_j
+  half_t *dhst, *agt;            // [Tpad / 32][d_ff][32] transposed sum_j dh_j and sum_j g_j a_j
+  float *qpart, *spart, *dotp;   // [chunks][T][k][r] x2, [chunks][T][k]: partial U1^T dh, g V2 a, da . a
+  float *du, *dv;                // [slots][KRp][d_ff] partial factor gradients
+  int T;
+};
+inline bool bw_mid_ok(const cmoe_dims& dm) { return dm.k <= 2 && dm.KRp <= 128; }
+int bw_mid_chunks(const cmoe_dims& dm);
+int bw_mid_run(const cmoe_dims& dm, int T);     // tokens of a run
+int bw_mid_slots(const cmoe_dims& dm, int T);   // runs, at most
+hipError_t launch_bw_mid(const cmoe_dims& dm, const bw_mid_args& a, hipStream_t st);
+hipError_t launch_bw_mid_sums(const cmoe_dims& dm, const bw_mid_args& a, const int* perm2, const int* invm, half_t* q16,
+                              half_t* qq, half_t* ss, float* dl, float* du1, float* dv2, hipStream_t st);
 hipError_t launch_pack_bases(const cmoe_dims& dm, const cmoe_weights& w, half_t* packed, hipStream_t st);

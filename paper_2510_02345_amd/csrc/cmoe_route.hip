@@ -711,11 +711,13 @@ hipError_t launch_pair_sort(const cmoe_dims& dm, const int* perm, const int* off
   return hipGetLastError();
 }
 
-// The permutation and the pair order of a step together.  counts: sort_counts(T, G * 64) ints.
-hipError_t launch_sort_pairs(const cmoe_dims& dm, const int* cluster_id, const int* expert_idx, int T, int* perm,
-                             int* inv_perm, int* offsets, int* counts, int* rowmap, int* perm2, hipStream_t st) {
+// The permutation and the pair order of a step together; the cluster of token i is ids[i * stride] / div.
+// counts: sort_counts(T, G * 64) ints.
+hipError_t launch_sort_pairs(const cmoe_dims& dm, const int* ids, int stride, int div, const int* expert_idx, int T,
+                             int* perm, int* inv_perm, int* offsets, int* counts, int* rowmap, int* perm2,
+                             hipStream_t st) {
   const int two = two_keys_of(dm);
-  SortArgs a{cluster_id, 1, 1, T, dm.G, expert_idx, dm.K, dm.k, two, two ? dm.K * dm.K : dm.K, 0, 0};
+  SortArgs a{ids, stride, div, T, dm.G, expert_idx, dm.K, dm.k, two, two ? dm.K * dm.K : dm.K, 0, 0};
   return go_sort<true>(a, perm, inv_perm, offsets, rowmap, perm2, counts, st);
 }
 

@@ -363,12 +363,17 @@ __device__ __forceinline__ void t1_store(half_t* t1, int p, int rr, const int* e
       *(half4*)(t1 + ((size_t)p * k + j) * r + (rr - e0)) = half4{(half_t)s[0], (half_t)s[1], (half_t)s[2], (half_t)s[3]};
   }
 }
-__global__ __launch_bounds__(RW_THREADS, 2) void t1_rows_kernel(const half_t* __restrict__ x, int x_div,
+struct T1Src {
+  const half_t *x, *v1cat;
+  half_t* t1;
+};
+__global__ __launch_bounds__(RW_THREADS, 2) void t1_rows_kernel(T1Src s0, T1Src s1, int x_div,
                                                                     const int* __restrict__ perm,
                                                                     const int* __restrict__ offsets,
                                                                     const int* __restrict__ expert_idx,
-                                                                    const half_t* __restrict__ v1cat, int d, int G, int K,
-                                                                    int k, int r, int KRp, half_t* __restrict__ t1) {
+                                                                    int d, int G, int K, int k, int r, int KRp) {
+  const half_t *x = blockIdx.y ? s1.x : s0.x, *v1cat = blockIdx.y ? s1.v1cat : s0.v1cat;
+  half_t* t1 = blockIdx.y ? s1.t1 : s0.t1;
   __shared__ __attribute__((aligned(1024))) char smem[RowsLds<T1_NA>::SMEM];
   __shared__ int es[RL_M][8];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -433,7 +438,17 @@ hipError_t launch_route_multi_rows(const cmoe_dims& dm, const cmoe_weights& w, c
 
 hipError_t launch_t1(const cmoe_dims& dm, const half_t* x, int x_div, int T, const int* perm, const int* offsets,
                      const int* expert_idx, const half_t* v1cat, half_t* t1, hipStream_t st) {
-  hipLaunchKernelGGL(t1_rows_kernel, dim3((T + RL_M - 1) / RL_M + dm.G), dim3(RW_THREADS), 0, st, x, x_div > 1 ? x_div : 1,
-                     perm, offsets, expert_idx, v1cat, dm.d, dm.G, dm.K, dm.k, dm.r, dm.KRp, t1);
+  const T1Src s{x, v1cat, t1};
+  hipLaunchKernelGGL(t1_rows_kernel, dim3((T + RL_M - 1) / RL_M + dm.G), dim3(RW_THREADS), 0, st, s, s, x_div > 1 ? x_div : 1,
+                     perm, offsets, expert_idx, dm.d, dm.G, dm.K, dm.k, dm.r, dm.KRp);
+  return hipGetLastError();
+}
+
+// Two such products of the same tokens and experts in one launch.
+hipError_t launch_t1_pair(const cmoe_dims& dm, int T, const int* perm, const int* offsets, const int* expert_idx,
+                          const half_t* x0, const half_t* v0, half_t* t0, const half_t* x1, const half_t* v1, half_t* t1,
+                          hipStream_t st) {
+  hipLaunchKernelGGL(t1_rows_kernel, dim3((T + RL_M - 1) / RL_M + dm.G, 2), dim3(RW_THREADS), 0, st, T1Src{x0, v0, t0},
+                     T1Src{x1, v1, t1}, 1, perm, offsets, expert_idx, dm.d, dm.G, dm.K, dm.k, dm.r, dm.KRp);
   return hipGetLastError();
 }

@@ -84,6 +84,60 @@ def test_backward_long_runs(r, T, G, K, d, f):
     _run(ci.small_config("bw_runs", T=T, d=d, d_ff=f, G=G, K=K, r=r, k=2, q=8, seed=160 + r))
 
 
+# The middle kernel (top-k <= 2, K * r <= 128): every rank, one and two experts per token, panels of 32, 64, 96 and
+# 128 rank rows, hidden widths that are and are not whole chunks of 128 units, clusters of one token, of whole
+# and of ragged 32-token tiles, several runs of tiles; k = 3 and K * r = 160 are just beyond it.
+@pytest.mark.parametrize("r,K,k", [(4, 32, 2), (4, 8, 1), (8, 12, 2), (8, 16, 1), (16, 8, 2), (16, 4, 2), (16, 8, 1),
+                                   (32, 4, 2), (32, 3, 1), (32, 5, 2), (16, 8, 3)])
+@pytest.mark.parametrize("T,G,d,f", [(33, 5, 64, 64), (1024, 1, 128, 320), (2113, 2, 64, 1984)])
+def test_backward_middle(r, K, k, T, G, d, f):
+    _run(ci.small_config("bw_mid", T=T, d=d, d_ff=f, G=G, K=K, r=r, k=k, q=8, seed=170 + r))
+
+
+def test_backward_infinite_gradients_stay_with_their_expert():
+    # one token's dy overflows the products of its own experts: the factor gradients of the other
+    # experts, also of those that share its tiles and rank passes, stay finite
+    import torch
+    import paper_2510_02345_amd as cm
+    cfg = ci.small_config("bw_inf", T=200, d=64, d_ff=128, G=1, K=8, r=8, k=2, q=8, seed=156)
+    w = ci.generate(cfg)
+    dy = np.random.default_rng(3).standard_normal((cfg.T, cfg.d)).astype(np.float16)
+    dy[57] = np.float16(6e4)
+    layer = cm.Layer(cfg.d, cfg.d_ff, cfg.G, cfg.K, cfg.r, cfg.k, cfg.q, w, cfg.T)
+    x = _dev(w["x"])
+    f = layer.forward(x)
+    out = layer.backward(x, _dev(dy), f["expert_idx"], f["gate"])
+    torch.cuda.synchronize()
+    own = set(f["expert_idx"][57].tolist())
+    bad = set()
+    for n in ("du1", "dv1", "du2", "dv2"):
+        bad |= set((~torch.isfinite(out[n])).flatten(1).any(1).nonzero()[:, 0].tolist())
+    assert bad and bad <= own, (bad, own)
+    layer.close()
+
+
+def test_backward_unused_experts_weights_never_used():
+    # an expert without a token, in a cluster that has some: its stored factors may hold anything
+    cfg = ci.small_config("bw_unused", T=40, d=64, d_ff=128, G=2, K=8, r=8, k=2, q=8, seed=157)
+    w = ci.generate(cfg)
+    _, eidx, _, _, _ = orc.route(w["x"], w["router_cluster"], w["router_expert"], cfg.K, cfg.k, w["cluster_bias"])
+    used = np.unique(eidx)
+    w["router_expert"] = w["router_expert"].copy()
+    drop = int(used[0])   # an expert that tokens would choose: its routing vector turned away from them
+    xm = w["x"].astype(np.float64)
+    v = w["router_expert"][drop].astype(np.float64)
+    w["x"] = (xm - np.outer(np.maximum(xm @ v, 0) / (v @ v) * 3.0, v)).astype(np.float16)
+    cid, eidx, gate, _, _ = orc.route(w["x"], w["router_cluster"], w["router_expert"], cfg.K, cfg.k, w["cluster_bias"])
+    unused = sorted(set(range(cfg.G * cfg.K)) - set(np.unique(eidx).tolist()))
+    assert any(e // cfg.K in set(cid.tolist()) for e in unused)
+    for e in unused:
+        for n in ("v1", "u1", "v2", "u2"):
+            w[n + "_s"][e] = np.float16(np.nan)
+    out, _ = _run(cfg, w)
+    for n in ("du1", "dv1", "du2", "dv2"):
+        assert not out[n][unused].any()
+
+
 def test_backward_config1():
     _run(ci.config(1))
 
