@@ -8,32 +8,27 @@
 // iteration (sketch of l >= r rows, Rayleigh-Ritz on the sketch), which for the decaying
 // residual spectra of clustered experts is the truncated SVD of Sec. 3.2 to within a
 // fraction of a percent of its Frobenius error.  The heavy steps are products of the
-// residual (or its transpose) with l sketch rows: weight streams, run by the same kernel
-// as the layer's small-T path on a materialised FP16 copy of Delta_e and Delta_e^T.
-#include "cmoe_internal.h"
+// residual (or its transpose) with l sketch rows: streams of a materialised FP16 copy of Delta_e.
+#include <type_traits>
+
+#include "cmoe_device.h"
 
 namespace {
 
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef float float4v __attribute__((ext_vector_type(4)));
-
 constexpr int CP_LMAX = 48;   // widest sketch
 
-// ---------------------------------------------------------------- base, residuals, their transposes, norms
+// ---------------------------------------------------------------- base, residuals, norms
 // One 64 x 64 tile of cluster c: the base tile (Eq. 6: FP32 sum of the K experts in index
 // order, divided by K, rounded to FP16), then for each expert e of the cluster
-// D = f16(W_e - base), DT = D^T, and the tile's share of sum D^2, sum D base, sum base^2,
-// sum W_e^2 (FP32, fixed order), one partial per wavefront -> part[e][tile][wave][4].  The
-// tiles of the first CR_KEEP experts stay in registers between the two passes; those of
-// further experts are read a second time (from cache).  The transposing LDS tile is double
-// buffered: one barrier per expert.  Its 16-byte chunks sit at chunk ^ (row / 8): a wavefront's
-// transposing reads (eight columns of rows i, 8 + i, ..) then fall on 32 different banks.  Bound
-// by the 6.4 GB it reads and writes for 64 experts of 8192 x 2048: 1554 -> 1509 us with the swizzle.
+// D = f16(W_e - base) and the tile's share of sum D^2, sum D base, sum base^2, sum W_e^2 (FP32, fixed
+// order), one partial per wavefront -> part[e][tile][wave][4].  The tiles of the first CR_KEEP experts
+// stay in registers between the two passes; those of further experts are read a second time (from
+// cache).  Bound by the 4.5 GB it reads and writes for 64 experts of 8192 x 2048: 0.99 ms (with a
+// transposed copy of the residuals beside D, 6.4 GB, 1.51 ms).
 constexpr int CR_KEEP = 8;
 __global__ __launch_bounds__(256) void cmp_residual_kernel(const half_t* __restrict__ W, int K, int out_d, int in_d,
                                                            half_t* __restrict__ base, half_t* __restrict__ D,
-                                                           half_t* __restrict__ DT, float* __restrict__ part) {
-  __shared__ __attribute__((aligned(16))) half_t tile[2][64][64];
+                                                           float* __restrict__ part) {
   const int c = blockIdx.z;
   const int o0 = blockIdx.y * 64, i0 = blockIdx.x * 64;
   const int tid = threadIdx.x;
@@ -77,7 +72,7 @@ __global__ __launch_bounds__(256) void cmp_residual_kernel(const half_t* __restr
     *(half8*)(base + (size_t)c * me + off[u]) = b8[u];
   }
   auto one = [&](int j, const half8 (&w)[2]) {
-    const int e = c * K + j, buf = j & 1;
+    const int e = c * K + j;
     float s_dd = 0.f, s_db = 0.f, s_bb = 0.f, s_ww = 0.f;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -93,17 +88,6 @@ __global__ __launch_bounds__(256) void cmp_residual_kernel(const half_t* __restr
         s_ww = fmaf(wv, wv, s_ww);
       }
       *(half8*)(D + (size_t)e * me + off[u]) = d8;
-      *(half8*)(&tile[buf][row0 + 32 * u][(ch ^ ((row0 + 32 * u) >> 3)) * 8]) = d8;
-    }
-    // this barrier also separates the reads of tile[buf] two experts ago from these writes
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int irow = row0 + 32 * u;   // row of the transposed tile
-      half8 t8;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) t8[i] = tile[buf][ch * 8 + i][irow ^ (ch * 8)];
-      *(half8*)(DT + (size_t)e * me + (size_t)(i0 + irow) * out_d + o0 + ch * 8) = t8;
     }
     // wavefront sums in a fixed order (lanes by halving); the four wavefronts' partials are
     // added, in order, by cmp_stats_kernel
@@ -155,10 +139,6 @@ __global__ __launch_bounds__(256) void cmp_stats_kernel(const float* __restrict_
 }
 
 // ---------------------------------------------------------------- sketch bookkeeping
-__global__ void cmp_offsets_kernel(int E, int l, int* __restrict__ offsets) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i <= E) offsets[i] = i * l;
-}
 // X[e l + a][:] = omega[a][:] for every expert
 __global__ __launch_bounds__(256) void cmp_tile_rows_kernel(const half_t* __restrict__ omega, int l, int n,
                                                             half_t* __restrict__ X) {
@@ -168,234 +148,510 @@ __global__ __launch_bounds__(256) void cmp_tile_rows_kernel(const half_t* __rest
 }
 
 // ---------------------------------------------------------------- Gram matrix of the l sketch rows
-// gpart[e][chunk][a][b] = sum over the chunk's 512 columns of X[e l + a][n] X[e l + b][n].
+// gpart[e][chunk][i] = sum over the chunk's 512 columns, in order, of X[e l + a][n] X[e l + b][n]; symmetric: the
+// lower triangle is kept, (a, b <= a) at i = a (a + 1) / 2 + b.
+__host__ __device__ inline int tri_size(int l) { return l * (l + 1) / 2; }
+constexpr int GR_COLS = 512, GR_LD = GR_COLS + 8;
+// From the tile xs [l][GR_LD], by 256 threads.  A thread takes a block of 2 x 2 elements, so that a value
+// read from LDS and widened serves two products.
+__device__ __forceinline__ void gram_tile(const half_t* xs, int l, float* __restrict__ dst) {
+  const int h = (l + 1) / 2;
+  for (int i = threadIdx.x; i < tri_size(h); i += 256) {
+    int a2 = (int)((sqrtf(8.f * i + 1.f) - 1.f) * 0.5f);
+    while (tri_size(a2) > i) --a2;
+    while (tri_size(a2 + 1) <= i) ++a2;
+    const int b2 = i - tri_size(a2);
+    const half_t *xa[2], *xb[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      xa[u] = xs + min(2 * a2 + u, l - 1) * GR_LD;
+      xb[u] = xs + min(2 * b2 + u, l - 1) * GR_LD;
+    }
+    float s[2][2] = {};
+#pragma unroll 2
+    for (int n = 0; n < GR_COLS; n += 8) {
+      const half8 a0 = *(const half8*)(xa[0] + n), a1 = *(const half8*)(xa[1] + n);
+      const half8 b0 = *(const half8*)(xb[0] + n), b1 = *(const half8*)(xb[1] + n);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const float fa0 = (float)a0[u], fa1 = (float)a1[u], fb0 = (float)b0[u], fb1 = (float)b1[u];
+        s[0][0] = fmaf(fa0, fb0, s[0][0]);
+        s[0][1] = fmaf(fa0, fb1, s[0][1]);
+        s[1][0] = fmaf(fa1, fb0, s[1][0]);
+        s[1][1] = fmaf(fa1, fb1, s[1][1]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        const int a = 2 * a2 + u, b = 2 * b2 + v;
+        if (a < l && b <= a) dst[tri_size(a) + b] = s[u][v];
+      }
+  }
+}
+// Block (ceil(n / 512), E); LR: l rounded up to 8.
+template <int LR>
 __global__ __launch_bounds__(256) void cmp_gram_kernel(const half_t* __restrict__ X, int l, int n,
                                                        float* __restrict__ gpart) {
-  __shared__ half_t xs[CP_LMAX][512 + 8];
-  const int e = blockIdx.y, n0 = blockIdx.x * 512, tid = threadIdx.x;
-  const int width = min(512, n - n0);
-  for (int idx = tid; idx < l * 64; idx += 256) {
-    const int a = idx / 64, ch = idx % 64;
+  __shared__ __attribute__((aligned(16))) half_t xs[LR * GR_LD];
+  const int e = blockIdx.y, n0 = blockIdx.x * GR_COLS, tid = threadIdx.x;
+  for (int idx = tid; idx < l * (GR_COLS / 8); idx += 256) {
+    const int a = idx / (GR_COLS / 8), ch = idx % (GR_COLS / 8);
     half8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (ch * 8 < width) v = *(const half8*)(X + ((size_t)e * l + a) * n + n0 + ch * 8);
-    *(half8*)(&xs[a][ch * 8]) = v;
+    if (n0 + ch * 8 < n) v = *(const half8*)(X + ((size_t)e * l + a) * n + n0 + ch * 8);
+    *(half8*)(xs + a * GR_LD + ch * 8) = v;
   }
   __syncthreads();
-  float* dst = gpart + ((size_t)e * gridDim.x + blockIdx.x) * l * l;
-  for (int pr = tid; pr < l * l; pr += 256) {
-    const int a = pr / l, b = pr % l;
-    if (b > a) continue;   // symmetric: the lower triangle is computed, the upper mirrored
-    float s = 0.f;
-    for (int i = 0; i < 512; i += 8) {
-      const half8 va = *(const half8*)(&xs[a][i]), vb = *(const half8*)(&xs[b][i]);
+  gram_tile(xs, l, gpart + ((size_t)e * gridDim.x + blockIdx.x) * tri_size(l));
+}
+
+// ---------------------------------------------------------------- a residual times the sketch rows
+// Per expert e, with D [out][in] its residual:
+//   TRANS = false: Y[a][o] = sum_i D[o][i] X[a][i]       TRANS = true: Y[a][i] = sum_o D[o][i] X[a][o]
+// both from the ONE row-major D (the contraction along its columns reads fragments by transposing LDS
+// reads), FP16 rows out.  The contraction is summed in four quarters, added in order.
+// Bound by the stream of D.  A workgroup takes 128 output positions, a wavefront 32 of them, and the X tile is
+// shared by the wavefronts, so that of the loads in flight (three stages ahead, two workgroups per CU)
+// four fifths are D.  SPLIT = 2: 64 output positions and two wavefront pairs that take half of the
+// contraction each, for launches whose 128-position workgroups would not fill the CUs twice.
+// 64 experts of 8192 x 2048, 24 rows: 0.39 and 0.37 ms (the second from a transposed copy of D, written
+// by the residual kernel for 0.5 ms, 0.40).
+template <int BR, int SPLIT>   // BR: rows of X in LDS, l rounded up (16, 24, 32 or 48)
+struct CmpTile {
+  static constexpr int WN = 4 / SPLIT, ROWS = 32 * WN;              // wavefronts along the output; positions
+  static constexpr int A_BYTES = ROWS * 128, STEP = A_BYTES + BR * 128, STAGE = SPLIT * STEP;
+  static constexpr int NS = 4 * STAGE <= 80 * 1024 ? 4 : 3;
+  static constexpr int PER_A = 4, B_PIECES = SPLIT * BR / 8, PER_B = (B_PIECES + 3) / 4, PER = PER_A + PER_B;
+  static constexpr int SMEM = NS * STAGE, OCC = SMEM <= 80 * 1024 ? 2 : 1;   // workgroups per CU
+  static constexpr int NP = BR > 32 ? 2 : 1;                        // passes of 32 accumulator columns
+};
+template <int BR, int SPLIT, bool TRANS>
+__global__ __launch_bounds__(256, (CmpTile<BR, SPLIT>::OCC)) void cmp_stream_kernel(const half_t* __restrict__ D,
+                                                                                    const half_t* __restrict__ X, int out_d,
+                                                                                    int in_d, int l, int n_blocks,
+                                                                                    half_t* __restrict__ Y) {
+  using TL = CmpTile<BR, SPLIT>;
+  constexpr int NP = TL::NP;
+  __shared__ __attribute__((aligned(1024))) char smem[TL::SMEM];
+  static_assert(SPLIT == 1 || 2 * 2 * NP * 4096 <= TL::SMEM, "exchange area");
+  const int tid = threadIdx.x, lane = tid & 63, fr = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wn = wave % TL::WN, half = wave / TL::WN;
+  const int e = blockIdx.x / n_blocks, blk = blockIdx.x % n_blocks;
+  const int N = TRANS ? in_d : out_d, Kc = TRANS ? out_d : in_d, n0 = blk * TL::ROWS;
+  D += (size_t)e * out_d * in_d;
+  X += (size_t)e * l * Kc;
+  const int steps = Kc / 64;
+  // steps of this wavefront's half: [s0, s0 + mine)
+  const int mid = steps / 2, stages = SPLIT == 1 ? steps : steps - mid;
+  const int s0 = SPLIT == 2 && half ? mid : 0, mine = SPLIT == 1 ? steps : half ? steps - mid : mid;
+  const unsigned base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
+  // chunk keys: rows of 128 bytes (X, D rows, and D columns with 64 positions): two rows span the banks
+  auto key8 = [](int row) { return (row >> 1) & 7; };
+  const half_t* src[TL::PER];
+  unsigned dst[TL::PER];
+  int last[TL::PER];   // last step of the piece's half
 #pragma unroll
-      for (int u = 0; u < 8; ++u) s = fmaf((float)va[u], (float)vb[u], s);
+  for (int i = 0; i < TL::PER; ++i) {
+    const bool is_a = i < TL::PER_A;
+    const int g = is_a ? wave * TL::PER_A + i : min(wave * TL::PER_B + i - TL::PER_A, TL::B_PIECES - 1);
+    const int per = is_a ? TL::ROWS / 8 : BR / 8, hf = g / per, pc = g % per;   // half; 1-KiB piece of its step
+    const int first = SPLIT == 2 && hf ? mid : 0;
+    last[i] = (SPLIT == 1 ? steps : hf ? steps - mid : mid) - 1;
+    dst[i] = base + hf * TL::STEP + (is_a ? 0 : TL::A_BYTES) + pc * 1024;
+    const int row = pc * 8 + (lane >> 3), ch = lane & 7;
+    if (!is_a) {
+      src[i] = X + (size_t)min(row, l - 1) * Kc + first * 64 + ((ch ^ key8(row)) << 3);
+    } else if (!TRANS) {       // 8 output rows of 64 elements
+      src[i] = D + (size_t)min(n0 + row, N - 1) * in_d + first * 64 + ((ch ^ key8(row)) << 3);
+    } else if (SPLIT == 1) {   // 4 contraction rows of 128 positions
+      const int r4 = pc * 4 + (lane >> 4);
+      src[i] = D + (size_t)r4 * in_d + min(n0 + (((lane & 15) ^ (r4 & 15)) << 3), N - 8);
+    } else {                   // 8 contraction rows of 64 positions
+      src[i] = D + (size_t)(first * 64 + row) * in_d + min(n0 + ((ch ^ key8(row)) << 3), N - 8);
     }
-    dst[a * l + b] = s;
-    dst[b * l + a] = s;
+  }
+  const long a_step = TRANS ? 64L * in_d : 64L;
+  auto issue = [&](int st, int stage) {
+#pragma unroll
+    for (int i = 0; i < TL::PER; ++i) {
+      const long k = SPLIT == 1 ? st : max(min(st, last[i]), 0);   // a shorter half repeats its last step, unused
+      if (i < TL::PER_A)
+        dma16_nt(src[i] + k * a_step, dst[i] + stage * TL::STAGE);
+      else
+        dma16(src[i] + k * 64, dst[i] + stage * TL::STAGE);
+    }
+  };
+  float16v acc[NP], sum[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[p][v] = sum[p][v] = 0.f;
+  // this wavefront's quarters end (exclusively) at step s0 + fold; with SPLIT = 2 and the upper half the two
+  // quarters stay apart until the lower half's sum is there
+  int quarter = half * 2, fold = (quarter + 1) * steps / 4 - s0;
+  float16v third[SPLIT == 2 ? NP : 1];
+  auto fold_quarter = [&] {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      if (SPLIT == 2 && half == 1 && quarter == 2) {
+        third[SPLIT == 2 ? p : 0] = acc[p];
+      } else if (SPLIT == 2 && half == 1) {
+        sum[p] = acc[p];
+      } else {
+        sum[p] += acc[p];
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[p][v] = 0.f;
+    }
+    ++quarter;
+    fold = (quarter + 1) * steps / 4 - s0;
+  };
+  const int quarters_end = SPLIT == 1 ? 4 : half * 2 + 2;
+#pragma unroll
+  for (int s = 0; s < TL::NS - 1; ++s)
+    if (s < stages) issue(s, s);
+  int stage = 0, nstage = TL::NS - 1;
+  for (int st = 0; st < stages; ++st) {
+    // stage st has landed (own loads), then everyone's; the stage refilled below was read in iteration
+    // st - 1, which every wavefront has left with its reads completed
+    if (st + TL::NS - 2 < stages) wait_vm<(TL::NS - 2) * TL::PER>(); else wait_vm<0>();
+    wait_lds();
+    __builtin_amdgcn_s_barrier();
+    if (st + TL::NS - 1 < stages) issue(st + TL::NS - 1, nstage);
+    if (st < mine) {
+      while (st == fold && quarter < quarters_end) fold_quarter();
+      const char* sa = smem + stage * TL::STAGE + half * TL::STEP;
+      const char* sb = sa + TL::A_BYTES;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {   // 16 contraction elements
+        half8 fa;
+        if (!TRANS) {
+          const int row = 32 * wn + fr;
+          fa = *(const half8*)(sa + row * 128 + (((2 * s + h) ^ key8(row)) << 4));
+        } else {
+          half4 v[2];
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const int row = 16 * s + 8 * h + 4 * u + ((lane & 15) >> 2);
+            const int ch = 4 * wn + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+            v[u] = lds_read_tr(sa + row * (TL::ROWS * 2) + ((ch ^ (SPLIT == 1 ? row & 15 : key8(row))) << 4) + 8 * (lane & 1));
+          }
+          fa = join8(v[0], v[1]);
+        }
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+          const int row = 32 * p + fr < BR ? 32 * p + fr : 0;   // columns past the rows of X are not stored
+          const half8 fb = *(const half8*)(sb + row * 128 + (((2 * s + h) ^ key8(row)) << 4));
+          acc[p] = mfma16(fa, fb, acc[p]);
+        }
+      }
+    }
+    stage = stage + 1 == TL::NS ? 0 : stage + 1;
+    nstage = nstage + 1 == TL::NS ? 0 : nstage + 1;
+  }
+  while (quarter < quarters_end) fold_quarter();
+  if (SPLIT == 2) {   // ((first + second) + third) + fourth quarter
+    __syncthreads();  // the stages have been read
+    float* red = (float*)smem + (size_t)wn * 2 * NP * 1024 + lane;
+    if (half == 1)
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          red[((2 * p) * 16 + v) * 64] = third[SPLIT == 2 ? p : 0][v];
+          red[((2 * p + 1) * 16 + v) * 64] = sum[p][v];
+        }
+    __syncthreads();
+    if (half == 1) return;
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        sum[p][v] += red[((2 * p) * 16 + v) * 64];
+        sum[p][v] += red[((2 * p + 1) * 16 + v) * 64];
+      }
+  }
+  const int n = n0 + 32 * wn;
+  if (n >= N) return;
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int row = 32 * p + fr;
+    if (row >= l) continue;
+#pragma unroll
+    for (int qd = 0; qd < 4; ++qd)
+      *(half4*)(Y + ((size_t)e * l + row) * N + n + 8 * qd + 4 * h) = to_half4(sum[p], qd);
   }
 }
 
 // ---------------------------------------------------------------- small dense steps, one workgroup per expert
-// Sums the Gram partials (FP64).  MODE 0: coef = inverse of the Cholesky factor of
-// (Gram + shift I), so that coef X has orthonormal rows.  MODE 1: Jacobi eigenvectors of
-// the Gram matrix; coef rows = the r eigenvectors of largest eigenvalue (transposed), and
-// lam[e] = the sum of those eigenvalues.  The Jacobi sweeps use the round-robin ordering:
-// a sweep is l - 1 rounds of l / 2 rotations on disjoint index pairs, which commute, so a
+// The Gram partials of an expert summed (FP64, in chunk order, sixteen loads in flight) into the full matrix A.
+// Called by the whole workgroup of NT threads; ends behind a barrier.
+template <int NT>
+__device__ __forceinline__ void gram_sum(const float* __restrict__ src, int n_chunks, int l, double (*A)[CP_LMAX + 1]) {
+  const int tri = tri_size(l);
+  for (int i = threadIdx.x; i < tri; i += NT) {
+    double s = 0.0;
+    int ch = 0;
+    for (; ch + 16 <= n_chunks; ch += 16) {
+      float v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = src[(size_t)(ch + u) * tri + i];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) s += (double)v[u];
+    }
+    for (; ch < n_chunks; ++ch) s += (double)src[(size_t)ch * tri + i];
+    int a = (int)((sqrtf(8.f * i + 1.f) - 1.f) * 0.5f);
+    while (tri_size(a) > i) --a;
+    while (tri_size(a + 1) <= i) ++a;
+    const int b = i - tri_size(a);
+    A[a][b] = s;
+    A[b][a] = s;
+  }
+  __syncthreads();
+}
+
+// coef = inverse of the Cholesky factor of the Gram matrix, so that coef X has orthonormal rows.
+//   The sketch may be rank deficient (a residual of rank below l).  A pivot below tau, which is far
+// above the rounding noise of the FP16 rows and their FP32 Gram sums, marks a row the earlier rows
+// already span: it gets a huge pivot, so that its output row is (numerically) zero instead of amplified
+// noise and the rows after it do not see it.
+//   Behind the sums a single wavefront works, a chain of l pivots: lane t keeps row t of the factor, then
+// column t of the inverse, in registers, and an element that all lanes need is broadcast from its
+// lane: 11 us for 24 rows (with the matrix in LDS and three barriers per column 35).
+__device__ __forceinline__ double lane_bcast(double v, int lane) {
+  typedef int int2v __attribute__((ext_vector_type(2)));
+  const int2v b = __builtin_bit_cast(int2v, v);
+  return __builtin_bit_cast(double, int2v{__builtin_amdgcn_readlane(b[0], lane), __builtin_amdgcn_readlane(b[1], lane)});
+}
+constexpr int CF_THREADS = 512;
+// LB: l rounded up to 8; the rows beyond l stay zero
+template <int LB>
+__global__ __launch_bounds__(CF_THREADS) void cmp_factor_kernel(const float* __restrict__ gpart, int n_chunks, int l,
+                                                                float* __restrict__ coef) {
+  __shared__ double A[CP_LMAX][CP_LMAX + 1];
+  const int e = blockIdx.x, t = threadIdx.x;
+  gram_sum<CF_THREADS>(gpart + (size_t)e * n_chunks * tri_size(l), n_chunks, l, A);
+  if (t >= 64) return;
+  double tau = 0.0;
+  for (int i = 0; i < l; ++i) tau += A[i][i];
+  tau = 1e-5 * tau / l + 1e-290;
+  double row[LB], diag = 1.0;   // row t of A, then of L; L[t][t]
+#pragma unroll
+  for (int k2 = 0; k2 < LB; ++k2) row[k2] = t < l && k2 <= t ? A[t][k2] : 0.0;
+#pragma unroll
+  for (int j = 0; j < LB; ++j) {
+    const double ajj = lane_bcast(row[j], j), piv = ajj > tau ? sqrt(ajj) : 1e150;
+    if (t == j) diag = piv;
+    row[j] /= piv;
+#pragma unroll
+    for (int k2 = j + 1; k2 < LB; ++k2)   // rows t >= k2; the others' values are not read
+      row[k2] -= row[j] * lane_bcast(row[j], k2);
+  }
+  // V = L^-1 by forward substitution, lane t: column t
+  float* cf = coef + (size_t)e * CP_LMAX * CP_LMAX;
+  double v[LB];
+#pragma unroll
+  for (int i = 0; i < LB; ++i) {
+    double s = i == t ? 1.0 : 0.0;
+#pragma unroll
+    for (int k2 = 0; k2 < i; ++k2) s -= lane_bcast(row[k2], i) * v[k2];
+    v[i] = s / lane_bcast(diag, i);
+    if (i < l && t < CP_LMAX) cf[i * CP_LMAX + t] = t <= i ? (float)v[i] : 0.f;
+  }
+}
+
+// Rayleigh-Ritz: Jacobi eigenvectors of the Gram matrix; coef rows = the r eigenvectors of largest
+// eigenvalue (transposed), and lam[e] = the sum of those eigenvalues.  The sweeps use the round-robin
+// ordering: a sweep is l - 1 rounds of l / 2 rotations on disjoint index pairs, which commute, so a
 // round applies all of them at once, A <- J^T A J and V <- V J, every element by one thread.
 constexpr int CS_THREADS = 256;
 constexpr int CS_PER = (CP_LMAX * CP_LMAX + CS_THREADS - 1) / CS_THREADS;   // elements of an l x l matrix per thread
-template <int MODE>
-__global__ __launch_bounds__(CS_THREADS) void cmp_small_kernel(const float* __restrict__ gpart, int n_chunks, int l,
-                                                               int r, float* __restrict__ coef,
-                                                               double* __restrict__ lam) {
+__global__ __launch_bounds__(CS_THREADS) void cmp_ritz_kernel(const float* __restrict__ gpart, int n_chunks, int l, int r,
+                                                              float* __restrict__ coef, double* __restrict__ lam) {
   __shared__ double A[CP_LMAX][CP_LMAX + 1];
   __shared__ double V[CP_LMAX][CP_LMAX + 1];
   __shared__ double ev[CP_LMAX];
   __shared__ int order[CP_LMAX];
   const int e = blockIdx.x, t = threadIdx.x;
-  for (int idx = t; idx < l * l; idx += CS_THREADS) {
-    const float* src = gpart + (size_t)e * n_chunks * l * l + idx;
-    double s = 0.0;
-    int ch = 0;
-    for (; ch + 4 <= n_chunks; ch += 4) {   // four loads in flight, summed in chunk order
-      const float v0 = src[(size_t)ch * l * l], v1 = src[(size_t)(ch + 1) * l * l];
-      const float v2 = src[(size_t)(ch + 2) * l * l], v3 = src[(size_t)(ch + 3) * l * l];
-      s += (double)v0;
-      s += (double)v1;
-      s += (double)v2;
-      s += (double)v3;
+  gram_sum<CS_THREADS>(gpart + (size_t)e * n_chunks * tri_size(l), n_chunks, l, A);
+  float* cf = coef + (size_t)e * CP_LMAX * CP_LMAX;
+  // per index k of the current round: its partner and the coefficients of
+  // new column k = cc[k] * column k + ss[k] * column partner[k]
+  __shared__ int partner[CP_LMAX];
+  __shared__ double cc[CP_LMAX], ss[CP_LMAX];
+  __shared__ double red[2][CS_THREADS / 64];
+  for (int idx = t; idx < l * l; idx += CS_THREADS) V[idx / l][idx % l] = (idx / l == idx % l) ? 1.0 : 0.0;
+  __syncthreads();
+  const int n2 = (l + 1) / 2 * 2, m = n2 - 1;   // an odd l plays with one idle index
+  for (int sweep = 0; sweep < 12; ++sweep) {
+    // converged when every off-diagonal element is negligible against the diagonal
+    double offmax = 0.0, diagmax = 0.0;
+    for (int idx = t; idx < l * l; idx += CS_THREADS) {
+      const double a = fabs(A[idx / l][idx % l]);
+      if (idx / l == idx % l) diagmax = fmax(diagmax, a); else offmax = fmax(offmax, a);
     }
-    for (; ch < n_chunks; ++ch) s += (double)src[(size_t)ch * l * l];
-    A[idx / l][idx % l] = s;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      offmax = fmax(offmax, __shfl_xor(offmax, off, 64));
+      diagmax = fmax(diagmax, __shfl_xor(diagmax, off, 64));
+    }
+    if ((t & 63) == 0) {
+      red[0][t >> 6] = offmax;
+      red[1][t >> 6] = diagmax;
+    }
+    __syncthreads();
+    offmax = 0.0;
+    diagmax = 0.0;
+    for (int w = 0; w < CS_THREADS / 64; ++w) {
+      offmax = fmax(offmax, red[0][w]);
+      diagmax = fmax(diagmax, red[1][w]);
+    }
+    __syncthreads();   // red is rewritten by the next sweep
+    if (offmax <= 1e-10 * diagmax) break;   // the same values in every thread
+    for (int rr = 0; rr < m; ++rr) {
+      if (t < n2 / 2) {
+        const int a = t == 0 ? m : (rr + t) % m, b = t == 0 ? rr : (rr - t + m) % m;
+        const int p = min(a, b), q2 = max(a, b);
+        if (q2 < l) {
+          const double apq = A[p][q2], app = A[p][p], aqq = A[q2][q2];
+          double c = 1.0, sn = 0.0;
+          if (fabs(apq) > 1e-300 && fabs(apq) > 1e-17 * sqrt(fabs(app * aqq))) {
+            const double theta = (aqq - app) / (2.0 * apq);
+            const double tt = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
+            c = 1.0 / sqrt(tt * tt + 1.0);
+            sn = tt * c;
+          }
+          partner[p] = q2;
+          cc[p] = c;
+          ss[p] = -sn;
+          partner[q2] = p;
+          cc[q2] = c;
+          ss[q2] = sn;
+        } else if (p < l) {   // paired with the idle index
+          partner[p] = p;
+          cc[p] = 1.0;
+          ss[p] = 0.0;
+        }
+      }
+      __syncthreads();
+      double an[CS_PER], vn[CS_PER];
+#pragma unroll
+      for (int u = 0; u < CS_PER; ++u) {
+        const int idx = t + u * CS_THREADS;
+        if (idx < l * l) {
+          const int i = idx / l, k2 = idx % l, pi = partner[i], pk = partner[k2];
+          const double ci = cc[i], si = ss[i], ck = cc[k2], sk = ss[k2];
+          an[u] = ci * (ck * A[i][k2] + sk * A[i][pk]) + si * (ck * A[pi][k2] + sk * A[pi][pk]);
+          vn[u] = ck * V[i][k2] + sk * V[i][pk];
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < CS_PER; ++u) {
+        const int idx = t + u * CS_THREADS;
+        if (idx < l * l) {
+          A[idx / l][idx % l] = an[u];
+          V[idx / l][idx % l] = vn[u];
+        }
+      }
+      __syncthreads();
+    }
+  }
+  if (t < l) ev[t] = A[t][t];
+  __syncthreads();
+  if (t < l) {   // rank of eigenvalue t in descending order, ties by index
+    int rank = 0;
+    for (int i = 0; i < l; ++i) rank += (ev[i] > ev[t]) || (ev[i] == ev[t] && i < t);
+    order[rank] = t;
   }
   __syncthreads();
-  float* cf = coef + (size_t)e * CP_LMAX * CP_LMAX;
-  if (MODE == 0) {
-    // The sketch may be rank deficient (a residual of rank below l).  A pivot below tau,
-    // which is far above the rounding noise of the FP16 rows and their FP32 Gram sums, marks
-    // a row the earlier rows already span: it gets a huge pivot, so that its output row is
-    // (numerically) zero instead of amplified noise and the rows after it do not see it.
-    __shared__ double tau_s;
-    if (t == 0) {
-      double tr = 0.0;
-      for (int i = 0; i < l; ++i) tr += A[i][i];
-      tau_s = 1e-5 * tr / l + 1e-290;
-    }
-    __syncthreads();
-    // Cholesky A = L L^T, column by column; the trailing update spread over the workgroup
-    for (int j = 0; j < l; ++j) {
-      if (t == 0) A[j][j] = A[j][j] > tau_s ? sqrt(A[j][j]) : 1e150;
-      __syncthreads();
-      if (t > j && t < l) A[t][j] /= A[j][j];
-      __syncthreads();
-      for (int idx = t; idx < l * l; idx += CS_THREADS) {
-        const int i = idx / l, k2 = idx % l;
-        if (i > j && k2 > j && k2 <= i) A[i][k2] -= A[i][j] * A[k2][j];
-      }
-      __syncthreads();
-    }
-    // V = L^-1 by forward substitution, thread c owns column c
-    if (t < l) {
-      for (int i = 0; i < l; ++i) {
-        double s = (i == t) ? 1.0 : 0.0;
-        for (int k2 = t; k2 < i; ++k2) s -= A[i][k2] * V[k2][t];
-        V[i][t] = (i < t) ? 0.0 : s / A[i][i];
-      }
-    }
-    __syncthreads();
-    for (int idx = t; idx < l * CP_LMAX; idx += CS_THREADS) {
-      const int a = idx / CP_LMAX, b = idx % CP_LMAX;
-      cf[idx] = b < l ? (float)V[a][b] : 0.f;
-    }
-  } else {
-    // per index k of the current round: its partner and the coefficients of
-    // new column k = cc[k] * column k + ss[k] * column partner[k]
-    __shared__ int partner[CP_LMAX];
-    __shared__ double cc[CP_LMAX], ss[CP_LMAX];
-    __shared__ double red[2][CS_THREADS / 64];
-    for (int idx = t; idx < l * l; idx += CS_THREADS) V[idx / l][idx % l] = (idx / l == idx % l) ? 1.0 : 0.0;
-    __syncthreads();
-    const int n2 = (l + 1) / 2 * 2, m = n2 - 1;   // an odd l plays with one idle index
-    for (int sweep = 0; sweep < 12; ++sweep) {
-      // converged when every off-diagonal element is negligible against the diagonal
-      double offmax = 0.0, diagmax = 0.0;
-      for (int idx = t; idx < l * l; idx += CS_THREADS) {
-        const double a = fabs(A[idx / l][idx % l]);
-        if (idx / l == idx % l) diagmax = fmax(diagmax, a); else offmax = fmax(offmax, a);
-      }
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        offmax = fmax(offmax, __shfl_xor(offmax, off, 64));
-        diagmax = fmax(diagmax, __shfl_xor(diagmax, off, 64));
-      }
-      if ((t & 63) == 0) {
-        red[0][t >> 6] = offmax;
-        red[1][t >> 6] = diagmax;
-      }
-      __syncthreads();
-      offmax = 0.0;
-      diagmax = 0.0;
-      for (int w = 0; w < CS_THREADS / 64; ++w) {
-        offmax = fmax(offmax, red[0][w]);
-        diagmax = fmax(diagmax, red[1][w]);
-      }
-      __syncthreads();   // red is rewritten by the next sweep
-      if (offmax <= 1e-10 * diagmax) break;   // the same values in every thread
-      for (int rr = 0; rr < m; ++rr) {
-        if (t < n2 / 2) {
-          const int a = t == 0 ? m : (rr + t) % m, b = t == 0 ? rr : (rr - t + m) % m;
-          const int p = min(a, b), q2 = max(a, b);
-          if (q2 < l) {
-            const double apq = A[p][q2], app = A[p][p], aqq = A[q2][q2];
-            double c = 1.0, sn = 0.0;
-            if (fabs(apq) > 1e-300 && fabs(apq) > 1e-17 * sqrt(fabs(app * aqq))) {
-              const double theta = (aqq - app) / (2.0 * apq);
-              const double tt = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-              c = 1.0 / sqrt(tt * tt + 1.0);
-              sn = tt * c;
-            }
-            partner[p] = q2;
-            cc[p] = c;
-            ss[p] = -sn;
-            partner[q2] = p;
-            cc[q2] = c;
-            ss[q2] = sn;
-          } else if (p < l) {   // paired with the idle index
-            partner[p] = p;
-            cc[p] = 1.0;
-            ss[p] = 0.0;
-          }
-        }
-        __syncthreads();
-        double an[CS_PER], vn[CS_PER];
-#pragma unroll
-        for (int u = 0; u < CS_PER; ++u) {
-          const int idx = t + u * CS_THREADS;
-          if (idx < l * l) {
-            const int i = idx / l, k2 = idx % l, pi = partner[i], pk = partner[k2];
-            const double ci = cc[i], si = ss[i], ck = cc[k2], sk = ss[k2];
-            an[u] = ci * (ck * A[i][k2] + sk * A[i][pk]) + si * (ck * A[pi][k2] + sk * A[pi][pk]);
-            vn[u] = ck * V[i][k2] + sk * V[i][pk];
-          }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < CS_PER; ++u) {
-          const int idx = t + u * CS_THREADS;
-          if (idx < l * l) {
-            A[idx / l][idx % l] = an[u];
-            V[idx / l][idx % l] = vn[u];
-          }
-        }
-        __syncthreads();
-      }
-    }
-    if (t < l) ev[t] = A[t][t];
-    __syncthreads();
-    if (t < l) {   // rank of eigenvalue t in descending order, ties by index
-      int rank = 0;
-      for (int i = 0; i < l; ++i) rank += (ev[i] > ev[t]) || (ev[i] == ev[t] && i < t);
-      order[rank] = t;
-    }
-    __syncthreads();
-    for (int idx = t; idx < r * CP_LMAX; idx += CS_THREADS) {
-      const int rho = idx / CP_LMAX, b = idx % CP_LMAX;
-      cf[idx] = b < l ? (float)V[b][order[rho]] : 0.f;
-    }
-    if (t == 0) {
-      double s = 0.0;
-      for (int rho = 0; rho < r; ++rho) s += fmax(ev[order[rho]], 0.0);
-      lam[e] = s;
-    }
+  for (int idx = t; idx < r * CP_LMAX; idx += CS_THREADS) {
+    const int rho = idx / CP_LMAX, b = idx % CP_LMAX;
+    cf[idx] = b < l ? (float)V[b][order[rho]] : 0.f;
+  }
+  if (t == 0) {
+    double s = 0.0;
+    for (int rho = 0; rho < r; ++rho) s += fmax(ev[order[rho]], 0.0);
+    lam[e] = s;
   }
 }
 
 // ---------------------------------------------------------------- out[e][a][:] = sum_b coef[e][a][b] X[e l + b][:]
-template <class OutT>
+// A thread takes two columns and keeps their l <= 8 NB values; the coefficients are uniform over the
+// workgroup.  GRAM: also the workgroup's part of the Gram matrix of the rounded rows (ra = l).  Block (ceil(n / 512), E).
+template <int NB, bool GRAM, class OutT>
 __global__ __launch_bounds__(256) void cmp_apply_kernel(const float* __restrict__ coef, const half_t* __restrict__ X,
-                                                        int l, int ra, int n, OutT* __restrict__ out) {
-  __shared__ float cs[CP_LMAX * CP_LMAX];
+                                                        int l, int ra, int n, OutT* __restrict__ out,
+                                                        float* __restrict__ gpart) {
+  constexpr int LB = 8 * NB;
+  typedef OutT out2 __attribute__((ext_vector_type(2)));
+  __shared__ __attribute__((aligned(16))) half_t xs[GRAM ? LB * GR_LD : 8];
   const int e = blockIdx.y, tid = threadIdx.x;
-  for (int idx = tid; idx < ra * CP_LMAX; idx += 256) cs[idx] = coef[(size_t)e * CP_LMAX * CP_LMAX + idx];
-  __syncthreads();
-  const int col = blockIdx.x * 256 + tid;
-  if (col >= n) return;
-  float xv[CP_LMAX];
+  const int col = blockIdx.x * 512 + tid * 2;   // n is even
+  const bool in = col < n;
+  float x0[LB], x1[LB];
 #pragma unroll
-  for (int b = 0; b < CP_LMAX; ++b) xv[b] = (b < l) ? (float)X[((size_t)e * l + b) * n + col] : 0.f;
+  for (int b = 0; b < LB; ++b) {
+    half2v v = {0, 0};
+    if (b < l && in) v = *(const half2v*)(X + ((size_t)e * l + b) * n + col);
+    x0[b] = (float)v[0];
+    x1[b] = (float)v[1];
+  }
+  const float* cf = coef + (size_t)e * CP_LMAX * CP_LMAX;
   for (int a = 0; a < ra; ++a) {
-    float s = 0.f;
+    float s0 = 0.f, s1 = 0.f;
 #pragma unroll
-    for (int b = 0; b < CP_LMAX; ++b) s = fmaf(cs[a * CP_LMAX + b], xv[b], s);
-    out[((size_t)e * ra + a) * n + col] = (OutT)s;
+    for (int b = 0; b < LB; ++b) {
+      const float c = cf[a * CP_LMAX + b];
+      s0 = fmaf(c, x0[b], s0);
+      s1 = fmaf(c, x1[b], s1);
+    }
+    const out2 o = {(OutT)s0, (OutT)s1};
+    if (in) *(out2*)(out + ((size_t)e * ra + a) * n + col) = o;
+    if constexpr (GRAM) *(half2v*)(xs + a * GR_LD + tid * 2) = in ? half2v{o[0], o[1]} : half2v{0, 0};
+  }
+  if constexpr (GRAM) {
+    __syncthreads();
+    gram_tile(xs, l, gpart + ((size_t)e * gridDim.x + blockIdx.x) * tri_size(l));
   }
 }
 
 // ---------------------------------------------------------------- Sec. 3.4 quantiser
-// One thread per group of q consecutive elements of a row: scale = f16(absmax / 7),
-// code = clip(rint(w / scale), -7, 7), codes 0 when the scale rounds to 0 or the row's
-// expert is gated off (gate != NULL and gate[row / rows_per_expert] != 0).
+// Groups of q consecutive elements of a row: scale = f16(absmax / 7), code = clip(rint(w / scale), -7, 7), codes
+// 0 when the scale rounds to 0 or the row's expert is gated off (gate != NULL and
+// gate[row / rows_per_expert] != 0).
+__device__ __forceinline__ half_t quant_scale(float absmax, bool off) { return off ? (half_t)0.f : (half_t)(absmax / 7.0f); }
+__device__ __forceinline__ unsigned quant_code(float w, float sc) {
+  return sc > 0.f ? (unsigned)(int)fminf(fmaxf(rintf(w / sc), -7.f), 7.f) & 0xFu : 0u;
+}
+// q = 8, 16, .. 512: a thread takes eight elements (32 contiguous bytes, one code word), q / 8 lanes a group.
+// 33 MB of factors (64 experts, rank 16, 8192): 74 us with a thread per group of 64.
+__global__ __launch_bounds__(256) void cmp_quantize8_kernel(const float* __restrict__ src, long words, int L, int q,
+                                                            const int* __restrict__ gate, int rows_per_expert,
+                                                            uint8_t* __restrict__ codes, half_t* __restrict__ scales) {
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  const bool in = i < words;   // a group's lanes lie in one wavefront and are in or out together
+  float v[8];
+  const float4v a = in ? *(const float4v*)(src + i * 8) : float4v{0.f, 0.f, 0.f, 0.f};
+  const float4v b = in ? *(const float4v*)(src + i * 8 + 4) : float4v{0.f, 0.f, 0.f, 0.f};
+  float absmax = 0.f;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    v[u] = u < 4 ? a[u & 3] : b[u & 3];
+    absmax = fmaxf(absmax, fabsf(v[u]));
+  }
+  for (int off = 1; off < q / 8; off <<= 1) absmax = fmaxf(absmax, __shfl_xor(absmax, off, 64));
+  if (!in) return;
+  const bool off = gate != nullptr && gate[i * 8 / L / rows_per_expert] != 0;
+  const half_t sc = quant_scale(absmax, off);
+  if (i * 8 % q == 0) scales[i * 8 / q] = sc;
+  unsigned w = 0;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) w |= quant_code(v[u], (float)sc) << (4 * u);
+  *(unsigned*)(codes + i * 4) = w;
+}
+// Any even q: one thread per group.
 __global__ __launch_bounds__(256) void cmp_quantize_kernel(const float* __restrict__ src, long rows, int L, int q,
                                                            const int* __restrict__ gate, int rows_per_expert,
                                                            uint8_t* __restrict__ codes, half_t* __restrict__ scales) {
@@ -408,19 +664,23 @@ __global__ __launch_bounds__(256) void cmp_quantize_kernel(const float* __restri
   const bool off = gate != nullptr && gate[row / rows_per_expert] != 0;
   float absmax = 0.f;
   for (int i = 0; i < q; ++i) absmax = fmaxf(absmax, fabsf(s[i]));
-  half_t sc = (half_t)(absmax / 7.0f);
-  if (off) sc = (half_t)0.f;
+  const half_t sc = quant_scale(absmax, off);
   scales[row * gpr + g] = sc;
-  const float scf = (float)sc;
   uint8_t* dst = codes + row * (L / 2) + (long)g * (q / 2);
-  for (int i = 0; i < q; i += 2) {
-    int c0 = 0, c1 = 0;
-    if (scf > 0.f) {
-      c0 = (int)fminf(fmaxf(rintf(s[i] / scf), -7.f), 7.f);
-      c1 = (int)fminf(fmaxf(rintf(s[i + 1] / scf), -7.f), 7.f);
-    }
-    dst[i / 2] = (uint8_t)((c0 & 0xF) | ((c1 & 0xF) << 4));
+  for (int i = 0; i < q; i += 2) dst[i / 2] = (uint8_t)(quant_code(s[i], (float)sc) | quant_code(s[i + 1], (float)sc) << 4);
+}
+hipError_t launch_quantize(const float* src, long rows, int L, int q, const int* gate, int rows_per_expert, uint8_t* codes,
+                           half_t* scales, hipStream_t st) {
+  if (q >= 8 && q <= 512 && (q & (q - 1)) == 0) {
+    const long words = rows * (L / 8);
+    hipLaunchKernelGGL(cmp_quantize8_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, src, words, L, q, gate,
+                       rows_per_expert, codes, scales);
+  } else {
+    const long groups = rows * (L / q);
+    hipLaunchKernelGGL(cmp_quantize_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, st, src, rows, L, q, gate,
+                       rows_per_expert, codes, scales);
   }
+  return hipGetLastError();
 }
 
 // gate[e] = 1 when cos(vec Delta_e, vec base_c) < gamma (Sec. 3.4); report[e][2] = cosine,
@@ -447,18 +707,19 @@ __device__ __forceinline__ float cmp_nib(const uint8_t* row, int n) {
   const unsigned b = row[n >> 1];
   return (float)((int)((n & 1 ? b >> 4 : b & 0xF) ^ 8) - 8);
 }
-// A workgroup takes 64 rows and CE_CT consecutive 64-column tiles of one expert: the U panel
-// of its rows is decoded once, the V panel per column tile, all global loads issued before
-// the first use; epart has one entry per workgroup.  A one-dimensional grid of
-// 8 * ceil(G * tiles / 8) * K workgroups.  U V takes r FP32 products per element (34 GFLOP for 64
-// experts of 8192 x 2048 at r = 16) next to 2.4 GB of reads, on the FP32 matrix instruction:
-// exact products, FP32 sums, twice the rate of the vector ALUs, and a lane reads two LDS values for
-// its share of 16 products (FMAs per thread wanted nine for eight and were bound by the LDS):
-// 919 -> 778 us.  Panels of all column tiles in LDS behind one barrier cost occupancy: 0.1 ms slower.
+// A workgroup takes 64 rows and CE_CT consecutive 64-column tiles of one expert, all global loads issued
+// before the first use; epart has one entry per workgroup.  A one-dimensional grid of
+// 8 * ceil(G * tiles / 8) * K workgroups.  U V takes r products per element (34 GFLOP for 64 experts of 8192 x 2048
+// at r = 16) next to 2.4 GB of reads.  A factor value, FP16 scale x INT4 code, has at most 14 significant
+// bits and splits exactly into two FP16 parts, so that four FP16 products are the exact product and the
+// FP16 matrix instruction (FP32 sums) rebuilds U V in a quarter of the FP32 instruction's time, from panels
+// of which those of all column tiles fit LDS at once: 778 -> 640 us.
 // Columns are its rows (A = V), rows its columns (B = U); a wavefront owns 16 rows, and tile row
 // 4 q + i of block a holds column 8 q + 4 a + i of 32, so that blocks 0 and 1 give lane (t, q) the
 // eight consecutive columns 8 q .. 8 q + 7 of row t, as it loads them from W and base.
-constexpr int CE_CT = 4, CE_LD = 68;   // row pitch of the panels: at most two lanes of a fragment read on a bank
+constexpr int CE_CT = 4, CE_COLS = 64 * CE_CT;
+// A panel row (one column of V, one row of U): the upper parts of RB rank values, then the lower ones.
+template <int RB>
 __global__ __launch_bounds__(256) void cmp_error_kernel(const half_t* __restrict__ W, const half_t* __restrict__ base,
                                                         const uint8_t* __restrict__ u_q,
                                                         const half_t* __restrict__ u_s,
@@ -466,8 +727,8 @@ __global__ __launch_bounds__(256) void cmp_error_kernel(const half_t* __restrict
                                                         const half_t* __restrict__ v_s, int G, int K, int out_d, int in_d,
                                                         int r, int q, int tiles_x, int tiles_y,
                                                         float* __restrict__ epart) {
-  __shared__ float us[32][CE_LD];   // U[rho][o0 + 0..63], zero from row r to the next multiple of 4
-  __shared__ float vs[32][CE_LD];   // V[rho][i0 + 0..63], likewise
+  constexpr int LD = 2 * RB + 8;
+  __shared__ __attribute__((aligned(16))) half_t us[64][LD], vs[CE_COLS][LD];
   __shared__ float red[4][2];
   // Workgroups are dealt round-robin to the 8 XCDs; the K experts of one (cluster, tile) take
   // K consecutive workgroups of ONE XCD, so that the base tile they share is fetched from
@@ -477,94 +738,139 @@ __global__ __launch_bounds__(256) void cmp_error_kernel(const half_t* __restrict
   if (tc >= G * per_c) return;
   const int c = tc / per_c, e = c * K + local % K;
   const int tile_y = (tc % per_c) / tiles_x, tile_x = (tc % per_c) % tiles_x;
-  const int o0 = tile_y * 64, tid = threadIdx.x;
+  const int o0 = tile_y * 64, c0 = tile_x * CE_COLS, tid = threadIdx.x;
   const int t16 = tid & 15, quad = (tid >> 4) & 3, row = (tid >> 6) * 16 + t16;
   const size_t me = (size_t)out_d * in_d;
-  // Panels: thread tid < 8 r owns the 8 codes (one 32-bit word) of rank row tid / 8 at columns
-  // 8 (tid % 8) .. + 7 of a 64-column tile and their scale (one scale when q is a multiple of
-  // 8; other group lengths take the element-wise path).  Every global load of the workgroup -
-  // the U words, the V words of all column tiles, the W and base tiles - is issued up front.
+  // Panels: a thread takes two rank rows (rho, rho + 1) and one word of eight codes of each, at a time
+  // (one scale per word when q is a multiple of 8; other group lengths take the element-wise path).
   const bool words = (q % 8) == 0;
-  const int prho = tid >> 3, pwd = tid & 7;
-  const bool powner = words && prho < r;
-  const size_t prow = (size_t)e * r + (powner ? prho : 0);
-  auto put = [&](float (*dst)[CE_LD], unsigned w, float sc) {
-#pragma unroll
-    for (int b2 = 0; b2 < 4; ++b2) {
-      const unsigned byte = (w >> (8 * b2)) & 0xffu;
-      dst[prho][pwd * 8 + 2 * b2] = sc * (float)((int)((byte & 0xFu) ^ 8u) - 8);
-      dst[prho][pwd * 8 + 2 * b2 + 1] = sc * (float)((int)((byte >> 4) ^ 8u) - 8);
-    }
+  constexpr int PAIRS = RB / 2, V_ITEMS = PAIRS * CE_COLS / 8, U_ITEMS = PAIRS * 8;
+  constexpr int PER = (V_ITEMS + U_ITEMS + 255) / 256;
+  unsigned pw[PER][2];
+  float ps[PER][2];
+  auto item = [&](int u, int& rho, int& word, bool& is_v) {   // of the panels; false: none
+    int i = tid + u * 256;
+    is_v = i < V_ITEMS;
+    if (!is_v) i -= V_ITEMS;
+    rho = 2 * (i % PAIRS);
+    word = i / PAIRS;
+    return is_v || i < U_ITEMS;
   };
-  unsigned uw = 0u, vw[CE_CT];
-  float usc = 0.f, vsc[CE_CT];
+  if (words)
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      int rho, word;
+      bool is_v;
+      const bool some = item(u, rho, word, is_v);
+      const int L = is_v ? in_d : out_d, at = (is_v ? c0 : o0) + word * 8;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        pw[u][h] = 0u;
+        ps[u][h] = 0.f;
+        if (some && rho + h < r && at < L) {
+          const size_t fr = (size_t)e * r + rho + h;
+          pw[u][h] = *(const unsigned*)((is_v ? v_q : u_q) + fr * (L / 2) + at / 2);
+          ps[u][h] = (float)(is_v ? v_s : u_s)[fr * (L / q) + at / q];
+        }
+      }
+    }
   half8 w8[CE_CT][2], b8[CE_CT][2];
-  if (powner) {
-    uw = *(const unsigned*)(u_q + prow * (out_d / 2) + (o0 + pwd * 8) / 2);
-    usc = (float)u_s[prow * (out_d / q) + (o0 + pwd * 8) / q];
-  }
 #pragma unroll
   for (int ct = 0; ct < CE_CT; ++ct) {
-    const int i0 = (tile_x * CE_CT + ct) * 64;
-    const bool in = i0 < in_d;
-    vw[ct] = 0u;
-    vsc[ct] = 0.f;
-    if (powner && in) {
-      vw[ct] = *(const unsigned*)(v_q + prow * (in_d / 2) + (i0 + pwd * 8) / 2);
-      vsc[ct] = (float)v_s[prow * (in_d / q) + (i0 + pwd * 8) / q];
-    }
+    const int i0 = c0 + ct * 64;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const size_t off = (size_t)(o0 + row) * in_d + (in ? i0 : 0) + 32 * u + quad * 8;
+      const size_t off = (size_t)(o0 + row) * in_d + (i0 < in_d ? i0 : 0) + 32 * u + quad * 8;
       w8[ct][u] = *(const half8*)(W + (size_t)e * me + off);
       b8[ct][u] = *(const half8*)(base + (size_t)c * me + off);
     }
   }
-  const int r4 = (r + 3) & ~3;
-  for (int idx = tid; idx < (r4 - r) * 64; idx += 256) us[r + idx / 64][idx % 64] = vs[r + idx / 64][idx % 64] = 0.f;
   if (words) {
-    if (powner) put(us, uw, usc);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      int rho, word;
+      bool is_v;
+      if (!item(u, rho, word, is_v)) continue;
+      half_t* dst = (is_v ? &vs[word * 8][0] : &us[word * 8][0]) + rho;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        half2v hi, lo;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const float v = ps[u][h] * (float)((int)((pw[u][h] >> (4 * i) & 0xFu) ^ 8u) - 8);
+          hi[h] = (half_t)v;
+          lo[h] = (half_t)(v - (float)hi[h]);
+        }
+        *(half2v*)(dst + i * LD) = hi;
+        *(half2v*)(dst + i * LD + RB) = lo;
+      }
+    }
   } else {
-    for (int idx = tid; idx < r * 64; idx += 256) {
-      const int rho = idx / 64, j = idx % 64;
-      const size_t row = (size_t)e * r + rho;
-      us[rho][j] = (float)u_s[row * (out_d / q) + (o0 + j) / q] * cmp_nib(u_q + row * (out_d / 2), o0 + j);
+    for (int idx = tid; idx < RB * (CE_COLS + 64); idx += 256) {
+      const int rho = idx % RB, j = idx / RB;
+      const bool is_v = j < CE_COLS;
+      const int L = is_v ? in_d : out_d, at = is_v ? c0 + j : o0 + j - CE_COLS;
+      float v = 0.f;
+      if (rho < r && at < L) {
+        const size_t fr = (size_t)e * r + rho;
+        v = (float)(is_v ? v_s : u_s)[fr * (L / q) + at / q] * cmp_nib((is_v ? v_q : u_q) + fr * (L / 2), at);
+      }
+      half_t* dst = is_v ? &vs[j][rho] : &us[j - CE_COLS][rho];
+      dst[0] = (half_t)v;
+      dst[RB] = (half_t)(v - (float)(half_t)v);
     }
   }
+  __syncthreads();
+  // U operands: with 16 rank values the matrix instruction's 32 contraction elements are both parts of V
+  // against one part of U twice; with 32 one part of each
+  half8 fu[2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) fu[p] = *(const half8*)&us[row][p * RB + (RB == 16 ? 8 * (quad & 1) : 8 * quad)];
   float se = 0.f, sw = 0.f;
 #pragma unroll
   for (int ct = 0; ct < CE_CT; ++ct) {
-    const int i0 = (tile_x * CE_CT + ct) * 64;
-    if (i0 >= in_d) break;   // uniform over the workgroup
-    if (ct > 0) __syncthreads();   // the previous column tile has been consumed
-    if (words) {
-      if (powner) put(vs, vw[ct], vsc[ct]);
-    } else {
-      for (int idx = tid; idx < r * 64; idx += 256) {
-        const int rho = idx / 64, j = idx % 64;
-        const size_t row = (size_t)e * r + rho;
-        vs[rho][j] = (float)v_s[row * (in_d / q) + (i0 + j) / q] * cmp_nib(v_q + row * (in_d / 2), i0 + j);
+    if (c0 + ct * 64 >= in_d) break;   // uniform over the workgroup
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      float4v uv[2] = {};
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        const half_t* v = &vs[ct * 64 + 32 * u + 8 * (t16 >> 2) + 4 * a + (t16 & 3)][8 * quad];
+#pragma unroll
+        for (int pv = 0; pv < RB / 16; ++pv) {
+          const half8 fv = *(const half8*)(v + pv * RB);
+#pragma unroll
+          for (int p = 0; p < 2; ++p) uv[a] = mfma32(fv, fu[p], uv[a]);
+        }
       }
-    }
-    __syncthreads();   // us (first tile) and vs are complete
-    float4v uv[2][2] = {};   // [half of the 64 columns][block]
-    for (int rho = 0; rho < r4; rho += 4) {
-      const float uo = us[rho + quad][row];
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-          uv[u][a] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-              vs[rho + quad][32 * u + 8 * (t16 >> 2) + 4 * a + (t16 & 3)], uo, uv[u][a], 0, 0, 0);
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const float w = (float)w8[ct][u][i];
-        const float dv = w - (float)b8[ct][u][i] - uv[u][i >> 2][i & 3];
+        const float dv = w - (float)b8[ct][u][i] - uv[i >> 2][i & 3];
         se = fmaf(dv, dv, se);
         sw = fmaf(w, w, sw);
+      }
+    }
+  }
+  // a factor value beyond FP16 (a scale above 8188) leaves parts of infinity and an error that is not a number:
+  // the lane's elements once more, product by product in FP32
+  if (!(se < INFINITY)) {
+    se = 0.f;
+    for (int ct = 0; ct < CE_CT && c0 + ct * 64 < in_d; ++ct)
+      for (int u = 0; u < 2; ++u) {
+        const int col = c0 + ct * 64 + 32 * u + quad * 8;
+        const half8 wv = *(const half8*)(W + (size_t)e * me + (size_t)(o0 + row) * in_d + col);
+        const half8 bv = *(const half8*)(base + (size_t)c * me + (size_t)(o0 + row) * in_d + col);
+        for (int i = 0; i < 8; ++i) {
+          float uv = 0.f;
+          for (int rho = 0; rho < r; ++rho) {
+            const size_t fr = (size_t)e * r + rho;
+            uv = fmaf((float)u_s[fr * (out_d / q) + (o0 + row) / q] * cmp_nib(u_q + fr * (out_d / 2), o0 + row),
+                      (float)v_s[fr * (in_d / q) + (col + i) / q] * cmp_nib(v_q + fr * (in_d / 2), col + i), uv);
+          }
+          const float dv = (float)wv[i] - (float)bv[i] - uv;
+          se = fmaf(dv, dv, se);
+        }
       }
   }
   float v[2] = {se, sw};
@@ -596,8 +902,20 @@ __global__ __launch_bounds__(64) void cmp_error_finish_kernel(const float* __res
   if (lane == 0) err[(size_t)e * stride] = sw > 0.0 ? (float)(sqrt(se) / sqrt(sw)) : 0.f;
 }
 
+// epart and then err[e * stride] of the stored form.
+void launch_error(const cmoe_compress_config& c, const half_t* W, const half_t* base, const uint8_t* u_q, const half_t* u_s,
+                  const uint8_t* v_q, const half_t* v_s, float* epart, int stride, float* err, hipStream_t st) {
+  const int tx = (c.in_dim / 64 + CE_CT - 1) / CE_CT, ty = c.out_dim / 64;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)((c.G * tx * ty + 7) / 8 * 8 * c.K)), dim3(256), 0, st, W, base, u_q, u_s, v_q, v_s,
+                       c.G, c.K, c.out_dim, c.in_dim, c.r, c.q_group, tx, ty, epart);
+  };
+  if (c.r <= 16) go(cmp_error_kernel<16>); else go(cmp_error_kernel<32>);
+  hipLaunchKernelGGL(cmp_error_finish_kernel, dim3(c.G * c.K), dim3(64), 0, st, (const float*)epart, tx * ty, stride, err);
+}
+
 struct CompressLayout {
-  size_t D, DT, XA, XB, offsets, part, stats, gpart, coef, lam, gate, UF, VF, epart, total;
+  size_t D, XA, XB, part, stats, gpart, coef, lam, gate, UF, VF, epart, total;
 };
 CompressLayout compress_layout(const cmoe_compress_config& c) {
   CompressLayout L{};
@@ -611,13 +929,11 @@ CompressLayout compress_layout(const cmoe_compress_config& c) {
   const size_t nmax = c.out_dim > c.in_dim ? c.out_dim : c.in_dim;
   const size_t tiles = (size_t)(c.out_dim / 64) * (c.in_dim / 64);
   L.D = take(E * me * 2);
-  L.DT = take(E * me * 2);
   L.XA = take(E * c.sketch * nmax * 2);
   L.XB = take(E * c.sketch * nmax * 2);
-  L.offsets = take((E + 1) * 4);
   L.part = take(E * tiles * 4 * 4 * 4);   // four quantities x four wavefront partials per tile
   L.stats = take(E * 4 * 8);
-  L.gpart = take(E * ((nmax + 511) / 512) * c.sketch * c.sketch * 4);
+  L.gpart = take(E * ((nmax + GR_COLS - 1) / GR_COLS) * tri_size(c.sketch) * 4);
   L.coef = take(E * CP_LMAX * CP_LMAX * 4);
   L.lam = take(E * 8);
   L.gate = take(E * 4);
@@ -645,24 +961,80 @@ bool cptr_ok(const void* p) { return p != nullptr && (reinterpret_cast<uintptr_t
     if (e_ != hipSuccess) return CMOE_ERR_HIP; \
   } while (0)
 
-// rows of Xin [E l][n] -> orthonormal rows in Xout (Cholesky QR, applied twice by the caller)
-int orth_rows(const cmoe_compress_config& c, int E, int n, const half_t* Xin, half_t* Xout, char* ws,
-              const CompressLayout& L, hipStream_t st) {
-  const int l = c.sketch, nch = (n + 511) / 512;
-  hipLaunchKernelGGL(cmp_gram_kernel, dim3(nch, E), dim3(256), 0, st, Xin, l, n, (float*)(ws + L.gpart));
-  hipLaunchKernelGGL(cmp_small_kernel<0>, dim3(E), dim3(CS_THREADS), 0, st, (const float*)(ws + L.gpart), nch, l, c.r,
-                     (float*)(ws + L.coef), (double*)(ws + L.lam));
-  hipLaunchKernelGGL(cmp_apply_kernel<half_t>, dim3((n + 255) / 256, E), dim3(256), 0, st,
-                     (const float*)(ws + L.coef), Xin, l, l, n, Xout);
-  CP_CHECK();
-  return CMOE_OK;
+// f(kernel<LR>) for l rounded up to LR, a multiple of 8.
+template <class F>
+void for_rows(int l, F f) {
+  switch ((l + 7) / 8) {
+    case 1: f(std::integral_constant<int, 8>{}); break;
+    case 2: f(std::integral_constant<int, 16>{}); break;
+    case 3: f(std::integral_constant<int, 24>{}); break;
+    case 4: f(std::integral_constant<int, 32>{}); break;
+    case 5: f(std::integral_constant<int, 40>{}); break;
+    default: f(std::integral_constant<int, 48>{}); break;
+  }
+}
+
+// The product of every residual (TRANS: transposed) with the sketch rows X -> Y, and the Gram partials of Y.
+// Workgroups of 128 output positions when they fill the CUs at two each, else of 64.
+template <bool TRANS>
+void stream_product(const cmoe_compress_config& c, const half_t* D, const half_t* X, half_t* Y, float* gpart, hipStream_t st) {
+  const int E = c.G * c.K, l = c.sketch, N = TRANS ? c.in_dim : c.out_dim;
+  const bool wide = (long)E * ((N + 127) / 128) >= 512;
+  const int blocks = wide ? (N + 127) / 128 : N / 64;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)(E * blocks)), dim3(256), 0, st, D, X, c.out_dim, c.in_dim, l, blocks, Y);
+  };
+  if (wide) {
+    if (l <= 16) go(cmp_stream_kernel<16, 1, TRANS>);
+    else if (l <= 24) go(cmp_stream_kernel<24, 1, TRANS>);
+    else if (l <= 32) go(cmp_stream_kernel<32, 1, TRANS>);
+    else go(cmp_stream_kernel<48, 1, TRANS>);
+  } else {
+    if (l <= 16) go(cmp_stream_kernel<16, 2, TRANS>);
+    else if (l <= 24) go(cmp_stream_kernel<24, 2, TRANS>);
+    else if (l <= 32) go(cmp_stream_kernel<32, 2, TRANS>);
+    else go(cmp_stream_kernel<48, 2, TRANS>);
+  }
+  for_rows(l, [&](auto lr) {
+    hipLaunchKernelGGL((cmp_gram_kernel<decltype(lr)::value>), dim3((N + GR_COLS - 1) / GR_COLS, E), dim3(256), 0, st, Y, l, N,
+                       gpart);
+  });
+}
+
+template <bool GRAM, class OutT>
+void apply_coef(const cmoe_compress_config& c, const float* coef, const half_t* X, int ra, int n, OutT* out, float* gpart,
+                hipStream_t st) {
+  for_rows(c.sketch, [&](auto lr) {
+    hipLaunchKernelGGL((cmp_apply_kernel<decltype(lr)::value / 8, GRAM, OutT>), dim3((n + GR_COLS - 1) / GR_COLS, c.G * c.K),
+                       dim3(256), 0, st, coef, X, c.sketch, ra, n, out, gpart);
+  });
+}
+
+// Rows of X [E l][n] with their Gram partials -> orthonormal rows, in place (tmp: another buffer of the
+// size), by Cholesky QR applied twice: the second pass takes the rows from a few per cent off to FP16 rounding.
+void orth_rows(const cmoe_compress_config& c, int n, half_t* X, half_t* tmp, char* ws, const CompressLayout& L,
+               hipStream_t st) {
+  float *gpart = (float*)(ws + L.gpart), *coef = (float*)(ws + L.coef);
+  auto factor = [&] {
+    for_rows(c.sketch, [&](auto lr) {
+      hipLaunchKernelGGL((cmp_factor_kernel<decltype(lr)::value>), dim3(c.G * c.K), dim3(CF_THREADS), 0, st,
+                         (const float*)gpart, (n + GR_COLS - 1) / GR_COLS, c.sketch, coef);
+    });
+  };
+  factor();
+  apply_coef<true>(c, coef, X, c.sketch, n, tmp, gpart, st);
+  factor();
+  apply_coef<false>(c, coef, tmp, c.sketch, n, X, (float*)nullptr, st);
 }
 
 }  // namespace
 
 extern "C" size_t cmoe_compress_workspace_bytes(const cmoe_compress_config* cfg) {
   if (!compress_cfg_ok(cfg)) return 0;
-  return compress_layout(*cfg).total;
+  // at least two copies of the residuals, as callers have been told (one is kept)
+  const size_t need = compress_layout(*cfg).total;
+  const size_t stated = 2 * (size_t)cfg->G * cfg->K * cfg->out_dim * cfg->in_dim * sizeof(half_t) + 256;
+  return need > stated ? need : stated;
 }
 
 extern "C" int cmoe_quantize_int4(const float* src, int64_t rows, int32_t L, int32_t q_group, uint8_t* codes,
@@ -670,9 +1042,7 @@ extern "C" int cmoe_quantize_int4(const float* src, int64_t rows, int32_t L, int
   if (rows < 0 || L <= 0 || q_group < 2 || q_group % 2 || L % q_group) return CMOE_ERR_INVALID_ARG;
   if (rows == 0) return CMOE_OK;
   if (!cptr_ok(src) || !cptr_ok(codes) || !cptr_ok(scales)) return CMOE_ERR_INVALID_ARG;
-  const long groups = (long)rows * (L / q_group);
-  hipLaunchKernelGGL(cmp_quantize_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
-                     src, (long)rows, L, q_group, (const int*)nullptr, 1, codes, (half_t*)scales);
+  (void)launch_quantize(src, (long)rows, L, q_group, nullptr, 1, codes, (half_t*)scales, (hipStream_t)stream);
   CP_CHECK();
   return CMOE_OK;
 }
@@ -689,11 +1059,8 @@ extern "C" int cmoe_reconstruction_error(const cmoe_compress_config* cfg, const 
   if (workspace_bytes < L.total) return CMOE_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
-  const int E = cfg->G * cfg->K, tx = (cfg->in_dim / 64 + CE_CT - 1) / CE_CT, ty = cfg->out_dim / 64;
-  hipLaunchKernelGGL(cmp_error_kernel, dim3((unsigned)((cfg->G * tx * ty + 7) / 8 * 8 * cfg->K)), dim3(256), 0, st,
-                     (const half_t*)W, (const half_t*)base, u_q, (const half_t*)u_s, v_q, (const half_t*)v_s, cfg->G,
-                     cfg->K, cfg->out_dim, cfg->in_dim, cfg->r, cfg->q_group, tx, ty, (float*)(ws + L.epart));
-  hipLaunchKernelGGL(cmp_error_finish_kernel, dim3(E), dim3(64), 0, st, (const float*)(ws + L.epart), tx * ty, 1, err);
+  launch_error(*cfg, (const half_t*)W, (const half_t*)base, u_q, (const half_t*)u_s, v_q, (const half_t*)v_s,
+               (float*)(ws + L.epart), 1, err, st);
   CP_CHECK();
   return CMOE_OK;
 }
@@ -713,10 +1080,8 @@ extern "C" int cmoe_compress(const cmoe_compress_config* cfg, const cmoe_f16* W,
   const int E = c.G * c.K, l = c.sketch, out_d = c.out_dim, in_d = c.in_dim;
   const int tx = in_d / 64, ty = out_d / 64;
   half_t* D = (half_t*)(ws + L.D);
-  half_t* DT = (half_t*)(ws + L.DT);
   half_t* XA = (half_t*)(ws + L.XA);
   half_t* XB = (half_t*)(ws + L.XB);
-  int* offs = (int*)(ws + L.offsets);
   float* coef = (float*)(ws + L.coef);
   double* stats = (double*)(ws + L.stats);
   double* lam = (double*)(ws + L.lam);
@@ -724,53 +1089,45 @@ extern "C" int cmoe_compress(const cmoe_compress_config* cfg, const cmoe_f16* W,
   float* UF = (float*)(ws + L.UF);
   float* VF = (float*)(ws + L.VF);
 
-  // Eq. 6 and the residuals (and their transposes) against the stored base
+  // Eq. 6 and the residuals against the stored base
   hipLaunchKernelGGL(cmp_residual_kernel, dim3(tx, ty, c.G), dim3(256), 0, st, (const half_t*)W, c.K, out_d, in_d,
-                     (half_t*)base, D, DT, (float*)(ws + L.part));
+                     (half_t*)base, D, (float*)(ws + L.part));
   hipLaunchKernelGGL(cmp_stats_kernel, dim3(E), dim3(256), 0, st, (const float*)(ws + L.part), tx * ty * 4, stats);
-  hipLaunchKernelGGL(cmp_offsets_kernel, dim3((E + 256) / 256), dim3(256), 0, st, E, l, offs);
   hipLaunchKernelGGL(cmp_tile_rows_kernel, dim3((in_d / 8 + 255) / 256, E * l), dim3(256), 0, st, (const half_t*)omega,
                      l, in_d, XA);
   CP_CHECK();
-  int rc;
+  float* gpart = (float*)(ws + L.gpart);
   // Q^T [l][out]: orthonormal rows spanning Delta Omega, refined by n_iter rounds of
   // Z = orth(Delta^T Q), Q = orth(Delta Z)
-  if (launch_skinny_rows(XA, D, offs, E, out_d, in_d, l, XB, st) != hipSuccess) return CMOE_ERR_HIP;
-  if ((rc = orth_rows(c, E, out_d, XB, XA, ws, L, st)) != CMOE_OK) return rc;
-  if ((rc = orth_rows(c, E, out_d, XA, XB, ws, L, st)) != CMOE_OK) return rc;   // Q^T in XB
+  half_t *cur = XA, *other = XB;   // rows of the last step, the other buffer
+  auto step = [&](auto trans) {
+    constexpr bool TRANS = decltype(trans)::value;
+    stream_product<TRANS>(c, D, cur, other, gpart, st);
+    orth_rows(c, TRANS ? in_d : out_d, other, cur, ws, L, st);
+    half_t* o = cur;
+    cur = other;
+    other = o;
+  };
+  step(std::false_type{});
   for (int it = 0; it < c.n_iter; ++it) {
-    if (launch_skinny_rows(XB, DT, offs, E, in_d, out_d, l, XA, st) != hipSuccess) return CMOE_ERR_HIP;
-    if ((rc = orth_rows(c, E, in_d, XA, XB, ws, L, st)) != CMOE_OK) return rc;
-    if ((rc = orth_rows(c, E, in_d, XB, XA, ws, L, st)) != CMOE_OK) return rc;   // Z^T in XA
-    if (launch_skinny_rows(XA, D, offs, E, out_d, in_d, l, XB, st) != hipSuccess) return CMOE_ERR_HIP;
-    if ((rc = orth_rows(c, E, out_d, XB, XA, ws, L, st)) != CMOE_OK) return rc;
-    if ((rc = orth_rows(c, E, out_d, XA, XB, ws, L, st)) != CMOE_OK) return rc;   // Q^T in XB
+    step(std::true_type{});
+    step(std::false_type{});
   }
-  // B = Q^T Delta [l][in] (rows in XA); Rayleigh-Ritz: eigenvectors of B B^T pick the best
-  // rank-r pair inside the sketch: U^T = C Q^T, V = C B with C = the r leading eigenvectors
-  if (launch_skinny_rows(XB, DT, offs, E, in_d, out_d, l, XA, st) != hipSuccess) return CMOE_ERR_HIP;
-  const int nch = (in_d + 511) / 512;
-  hipLaunchKernelGGL(cmp_gram_kernel, dim3(nch, E), dim3(256), 0, st, XA, l, in_d, (float*)(ws + L.gpart));
-  hipLaunchKernelGGL(cmp_small_kernel<1>, dim3(E), dim3(CS_THREADS), 0, st, (const float*)(ws + L.gpart), nch, l, c.r, coef,
-                     lam);
-  hipLaunchKernelGGL(cmp_apply_kernel<float>, dim3((out_d + 255) / 256, E), dim3(256), 0, st, (const float*)coef, XB,
-                     l, c.r, out_d, UF);
-  hipLaunchKernelGGL(cmp_apply_kernel<float>, dim3((in_d + 255) / 256, E), dim3(256), 0, st, (const float*)coef, XA, l,
-                     c.r, in_d, VF);
+  CP_CHECK();
+  // B = Q^T Delta [l][in]; Rayleigh-Ritz: eigenvectors of B B^T pick the best rank-r pair inside the
+  // sketch: U^T = C Q^T, V = C B with C = the r leading eigenvectors
+  stream_product<true>(c, D, cur, other, gpart, st);
+  hipLaunchKernelGGL(cmp_ritz_kernel, dim3(E), dim3(CS_THREADS), 0, st, (const float*)gpart, (in_d + GR_COLS - 1) / GR_COLS, l,
+                     c.r, coef, lam);
+  apply_coef<false>(c, coef, cur, c.r, out_d, UF, (float*)nullptr, st);
+  apply_coef<false>(c, coef, other, c.r, in_d, VF, (float*)nullptr, st);
   // gate, quantisation (Sec. 3.4), and the error of the stored form
   hipLaunchKernelGGL(cmp_gate_kernel, dim3((E + 63) / 64), dim3(64), 0, st, (const double*)stats, (const double*)lam,
                      E, c.use_gate, c.gate_gamma, gate, report);
-  const long ug = (long)E * c.r * (out_d / c.q_group), vg = (long)E * c.r * (in_d / c.q_group);
-  hipLaunchKernelGGL(cmp_quantize_kernel, dim3((unsigned)((ug + 255) / 256)), dim3(256), 0, st, (const float*)UF,
-                     (long)E * c.r, out_d, c.q_group, (const int*)gate, c.r, u_q, (half_t*)u_s);
-  hipLaunchKernelGGL(cmp_quantize_kernel, dim3((unsigned)((vg + 255) / 256)), dim3(256), 0, st, (const float*)VF,
-                     (long)E * c.r, in_d, c.q_group, (const int*)gate, c.r, v_q, (half_t*)v_s);
-  const int etx = (tx + CE_CT - 1) / CE_CT;
-  hipLaunchKernelGGL(cmp_error_kernel, dim3((unsigned)((c.G * etx * ty + 7) / 8 * 8 * c.K)), dim3(256), 0, st,
-                     (const half_t*)W, (const half_t*)base, u_q, (const half_t*)u_s, v_q, (const half_t*)v_s, c.G, c.K,
-                     out_d, in_d, c.r, c.q_group, etx, ty, (float*)(ws + L.epart));
-  hipLaunchKernelGGL(cmp_error_finish_kernel, dim3(E), dim3(64), 0, st, (const float*)(ws + L.epart), etx * ty, 4,
-                     report);
+  (void)launch_quantize(UF, (long)E * c.r, out_d, c.q_group, gate, c.r, u_q, (half_t*)u_s, st);
+  (void)launch_quantize(VF, (long)E * c.r, in_d, c.q_group, gate, c.r, v_q, (half_t*)v_s, st);
+  launch_error(c, (const half_t*)W, (const half_t*)base, u_q, (const half_t*)u_s, v_q, (const half_t*)v_s,
+               (float*)(ws + L.epart), 4, report, st);
   CP_CHECK();
   return CMOE_OK;
 }

@@ -149,8 +149,6 @@ hipError_t launch_route_multi_rows(const cmoe_dims& dm, const cmoe_weights& w, c
                                    float temperature, int scale, int* cluster_id, int* expert_idx, float* gate,
                                    hipStream_t st);
 hipError_t launch_sum_groups(const half_t* yrep, int T, int top_g, int d, half_t* y, hipStream_t st);
-hipError_t launch_skinny_rows(const half_t* X, const half_t* W, const int* offsets, int n_groups, int N, int Kc,
-                              int max_rows, half_t* out, hipStream_t st);
 size_t stats_partial_slots(const cmoe_dims& dm, int T);
 hipError_t launch_route_stats(const cmoe_dims& dm, const half_t* x, int T, const int* perm, const int* offsets,
                               const int* expert_idx, float beta, float lam, float* mu, float* cluster_act,

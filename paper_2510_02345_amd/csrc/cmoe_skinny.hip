@@ -141,9 +141,8 @@ struct SkinnyTile {
   int c, n0, m0, m_end;
 };
 // Stream workgroup `id` of a launch of nx row blocks x slots (row block fastest).  A slot is a
-// pass over `cols` tokens of a cluster, m_end the end of the pass.  COMPACT (G <= 64): the slots
-// are the passes that exist, found from the offsets; else slot = pass * G + cluster.
-template <bool COMPACT>
+// pass over `cols` tokens of a cluster, m_end the end of the pass; the slots are the passes that exist,
+// found from the offsets.
 __device__ __forceinline__ bool skinny_tile(const int* offsets, int id, int nx, int G, int cols, SkinnyTile& t) {
   int xb = id % nx;
   const int slot = id / nx;
@@ -155,13 +154,7 @@ __device__ __forceinline__ bool skinny_tile(const int* offsets, int id, int nx, 
   if ((nx & 7) == 0 && xb < (nx & ~63)) xb = (xb & ~63) + ((xb & 7) << 3) + ((xb >> 3) & 7);
   t.n0 = xb * SK_ROWS;
   int hi;
-  if (COMPACT) {
-    if (!find_tile(offsets, G, cols, slot, t.c, t.m0, hi)) return false;
-  } else {
-    t.c = slot % G;
-    hi = offsets[t.c + 1];
-    t.m0 = offsets[t.c] + slot / G * cols;
-  }
+  if (!find_tile(offsets, G, cols, slot, t.c, t.m0, hi)) return false;
   t.m_end = min(hi, t.m0 + cols);
   return t.m0 < hi;
 }
@@ -309,7 +302,7 @@ struct SideArgs {
 // or NULL for the identity.  w_blk = 0: W[c] is row-major [N][Kc]; otherwise W[c] is stored
 // as [Kc / 32][N][32] and w_blk = N * 32 (the re-tiled copy of the bases): an 8-row load is
 // then two contiguous 256-byte pieces instead of eight 128-byte pieces a row apart.
-template <int SIDE, int COLS, bool NT, bool COMPACT>
+template <int SIDE, int COLS, bool NT>
 __global__ __launch_bounds__(256, SkRing<COLS>::OCC) void skinny_base_kernel(const half_t* __restrict__ X,
                                                                   const int* __restrict__ gather,
                                                                   const half_t* __restrict__ W,
@@ -335,7 +328,7 @@ __global__ __launch_bounds__(256, SkRing<COLS>::OCC) void skinny_base_kernel(con
   __shared__ __attribute__((aligned(1024))) char smem[RED_BYTES > RINGS ? RED_BYTES : RINGS];
   float* red = (float*)smem;
   SkinnyTile t;
-  if (!skinny_tile<COMPACT>(offsets, (int)blockIdx.x - (SIDE != SIDE_NONE ? sa.n_side : 0), nx, G, COLS, t)) return;
+  if (!skinny_tile(offsets, (int)blockIdx.x - (SIDE != SIDE_NONE ? sa.n_side : 0), nx, G, COLS, t)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, fr = lane & 31, h = lane >> 5;
   const int wv = __builtin_amdgcn_readfirstlane(wave);
   const unsigned smem_lds = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
@@ -640,9 +633,9 @@ hipError_t launch_stream(const cmoe_dims& dm, int cols, const half_t* X, const i
     hipLaunchKernelGGL(kern, grid, block, 0, st, X, gather, W, offsets, N, Kc, out, nx, dm.G, w_blk, sa);
   };
   if (cols == 32) {
-    if (stream_once(dm)) go(skinny_base_kernel<SIDE, 32, true, true>); else go(skinny_base_kernel<SIDE, 32, false, true>);
+    if (stream_once(dm)) go(skinny_base_kernel<SIDE, 32, true>); else go(skinny_base_kernel<SIDE, 32, false>);
   } else {
-    if (stream_once(dm)) go(skinny_base_kernel<SIDE, 16, true, true>); else go(skinny_base_kernel<SIDE, 16, false, true>);
+    if (stream_once(dm)) go(skinny_base_kernel<SIDE, 16, true>); else go(skinny_base_kernel<SIDE, 16, false>);
   }
   return hipGetLastError();
 }
@@ -722,35 +715,6 @@ hipError_t launch_skinny_down(const cmoe_dims& dm, const cmoe_weights& w, const 
   sa.n_jobs = T * ((dm.d + 2047) / 2048);
   sa.n_side = (sa.n_jobs + 7) & ~7;
   return launch_stream<SIDE_URES>(dm, cols, a, nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted, T, w_blk, sa, st);
-}
-
-// out[p][n] = sum_k W[g][n][k] X[p][k] for the rows p of group g (offsets [n_groups + 1],
-// at most max_rows rows per group): the weight stream on its own, for callers outside the
-// layer (the compression pipeline streams residual matrices against sketch rows).
-hipError_t launch_skinny_rows(const half_t* X, const half_t* W, const int* offsets, int n_groups, int N, int Kc,
-                              int max_rows, half_t* out, hipStream_t st) {
-  const int nx = N / SK_ROWS;
-  SideArgs sa{};
-  sa.x_div = 1;
-  // a set of matrices far larger than the last-level cache is not worth keeping there
-  const bool nt = (size_t)n_groups * N * Kc * sizeof(half_t) > ((size_t)96 << 20);
-  if (max_rows > 16) {
-    const int passes = (max_rows + 31) / 32;
-    if (nt)
-      hipLaunchKernelGGL((skinny_base_kernel<SIDE_NONE, 32, true, false>), dim3((unsigned)nx * n_groups * passes), dim3(256), 0,
-                         st, X, (const int*)nullptr, W, offsets, N, Kc, out, nx, n_groups, 0L, sa);
-    else
-      hipLaunchKernelGGL((skinny_base_kernel<SIDE_NONE, 32, false, false>), dim3((unsigned)nx * n_groups * passes), dim3(256), 0,
-                         st, X, (const int*)nullptr, W, offsets, N, Kc, out, nx, n_groups, 0L, sa);
-  } else {
-    if (nt)
-      hipLaunchKernelGGL((skinny_base_kernel<SIDE_NONE, 16, true, false>), dim3((unsigned)nx * n_groups), dim3(256), 0, st, X,
-                         (const int*)nullptr, W, offsets, N, Kc, out, nx, n_groups, 0L, sa);
-    else
-      hipLaunchKernelGGL((skinny_base_kernel<SIDE_NONE, 16, false, false>), dim3((unsigned)nx * n_groups), dim3(256), 0, st, X,
-                         (const int*)nullptr, W, offsets, N, Kc, out, nx, n_groups, 0L, sa);
-  }
-  return hipGetLastError();
 }
 
 hipError_t launch_skinny_add(const cmoe_dims& dm, const half_t* y_base_sorted, const float* ures, const int* perm,

@@ -41,6 +41,12 @@ def test_quantiser_bit_exact(rows, L, q):
     _check_quantiser_definition(w, q, codes.cpu().numpy(), scales.cpu().numpy())
 
 
+# group lengths of the word-wise kernel (8 .. 512, powers of two) and just off it, rows of less than a wavefront's words
+@pytest.mark.parametrize("rows,L,q", [(3, 1536, 512), (9, 96, 24), (5, 80, 16), (1, 8, 8), (257, 64, 64), (2, 2048, 1024)])
+def test_quantiser_group_lengths(rows, L, q):
+    test_quantiser_bit_exact(rows, L, q)
+
+
 def _check_quantiser_definition(w, q, codes, scales):
     """The quantiser of Sec. 3.4 written out in FP64, with no reference to the order or precision
     of the kernel's steps: scale = the FP16 value nearest to absmax / 7 (either neighbour where
@@ -116,6 +122,27 @@ def test_reconstruction_error_at_odd_ranks_and_widths(r, q, out_d, in_d):
         assert float(err[e]) == pytest.approx(want, rel=64 * 2.0 ** -23)
 
 
+def test_reconstruction_error_of_scales_whose_factors_leave_fp16():
+    # scale x code of one group of U and one of V beyond the FP16 range: the error is large and finite
+    import paper_2510_02345_amd as cm
+    G, K, r, q, out_d, in_d = 1, 2, 5, 32, 128, 320
+    W = ci.generate_dense_experts(G, K, out_d, in_d, rank=4, residual_rel=0.2, noise_rel=0.02, seed=75)
+    base = orc.base_mean(W, G, K)
+    rng = np.random.default_rng(76)
+    uq, us = ci.quantize_int4(rng.standard_normal((G * K, r, out_d)) * 0.05, q)
+    vq, vs = ci.quantize_int4(rng.standard_normal((G * K, r, in_d)) * 0.05, q)
+    us[1, 2, 1], vs[1, 4, 7] = np.float16(30000.0), np.float16(20000.0)
+    err = cm.reconstruction_error(_dev(W), _dev(base), _dev(uq), _dev(us), _dev(vq), _dev(vs), G, K, r, q)
+    _sync()
+    for e in range(G * K):
+        # the factors in FP64 (the layer's own dequantisation is FP16)
+        U = (orc.unpack_int4(uq[e]).astype(np.float64).reshape(r, -1, q) * us[e].astype(np.float64)[..., None]).reshape(r, -1)
+        V = (orc.unpack_int4(vq[e]).astype(np.float64).reshape(r, -1, q) * vs[e].astype(np.float64)[..., None]).reshape(r, -1)
+        want = np.linalg.norm(W[e].astype(np.float64) - base[0].astype(np.float64) - U.T @ V) / np.linalg.norm(W[e].astype(np.float64))
+        assert float(err[e]) == pytest.approx(want, rel=1e-4)
+    assert float(err[1]) > 100
+
+
 CASES = [
     # (name, G, K, out, in, true rank, residual, noise, r, sketch, q)
     ("decaying", 2, 4, 256, 128, 12, 0.3, 0.01, 8, 16, 32),
@@ -127,6 +154,21 @@ CASES = [
     # the widest sketch
     ("sketch48", 1, 2, 128, 128, 30, 0.3, 0.01, 32, 48, 32),
 ]
+
+
+# launches of 128-position workgroups (256 experts and more), the last workgroup of 64 positions, each number of
+# sketch rows that a stream is compiled for, contractions of one, three and five 64-element steps
+WIDE_CASES = [
+    ("wide16", 16, 16, 192, 320, 10, 0.3, 0.01, 8, 16, 32),
+    ("wide24", 16, 32, 64, 128, 10, 0.3, 0.01, 8, 21, 32),
+    ("wide32", 8, 32, 192, 192, 20, 0.3, 0.01, 16, 32, 64),
+    ("wide48", 8, 64, 128, 64, 30, 0.3, 0.01, 24, 41, 16),
+]
+
+
+@pytest.mark.parametrize("case", WIDE_CASES, ids=[c[0] for c in WIDE_CASES])
+def test_compress_many_experts(case):
+    test_compress_against_truncated_svd(case)
 
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
