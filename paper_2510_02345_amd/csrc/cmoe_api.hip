@@ -250,24 +250,29 @@ extern "C" int cmoe_permute_static(cmoe_handle* h, const int32_t* cluster_id, in
 
 // y_fused != NULL: when the shapes allow it, the down-projection also applies the residual of
 // the second matrix and writes y in token order (y_base_sorted is then not produced);
-// *fused tells the caller whether that happened.  sorted: the rows' expert-pair order is
-// already in the workspace (permute_step).
+// *fused tells the caller whether that happened.  step != NULL: a whole step's call.
+struct ffn_step {
+  // above SKINNY_T tokens the rows' expert-pair order is already in the workspace (permute_step); below, the
+  // permutation is still to be made, from cluster_id, together with the first stream
+  const int32_t* cluster_id;
+  int32_t *perm, *inv_perm, *offsets;
+};
 static int ffn_impl(cmoe_handle* h, const cmoe_weights* w, const cmoe_f16* x, int32_t T, const int32_t* perm,
                     const int32_t* offsets, const int32_t* expert_idx, const float* gate, cmoe_f16* y_base_sorted,
-                    float* s_down, cmoe_f16* y_fused, bool* fused, int x_div, bool sorted, void* workspace,
+                    float* s_down, cmoe_f16* y_fused, bool* fused, int x_div, const ffn_step* step, void* workspace,
                     size_t workspace_bytes, void* stream);
 
 extern "C" int cmoe_ffn_forward(cmoe_handle* h, const cmoe_weights* w, const cmoe_f16* x, int32_t T,
                                 const int32_t* perm, const int32_t* offsets, const int32_t* expert_idx,
                                 const float* gate, cmoe_f16* y_base_sorted, float* s_down, void* workspace,
                                 size_t workspace_bytes, void* stream) {
-  return ffn_impl(h, w, x, T, perm, offsets, expert_idx, gate, y_base_sorted, s_down, nullptr, nullptr, 1, false,
+  return ffn_impl(h, w, x, T, perm, offsets, expert_idx, gate, y_base_sorted, s_down, nullptr, nullptr, 1, nullptr,
                   workspace, workspace_bytes, stream);
 }
 
 static int ffn_impl(cmoe_handle* h, const cmoe_weights* w, const cmoe_f16* x, int32_t T, const int32_t* perm,
                     const int32_t* offsets, const int32_t* expert_idx, const float* gate, cmoe_f16* y_base_sorted,
-                    float* s_down, cmoe_f16* y_fused, bool* fused, int x_div, bool sorted, void* workspace,
+                    float* s_down, cmoe_f16* y_fused, bool* fused, int x_div, const ffn_step* step, void* workspace,
                     size_t workspace_bytes, void* stream) {
   if (fused) *fused = false;
   if (!handle_ok(h) || T < 0) return CMOE_ERR_INVALID_ARG;
@@ -296,20 +301,25 @@ static int ffn_impl(cmoe_handle* h, const cmoe_weights* w, const cmoe_f16* x, in
     // few tokens: the layer is bound by streaming the base matrices once; the small
     // per-expert products ride along in the two stream launches
     const int n_parts = (dm.d_ff + SKINNY_SN - 1) / SKINNY_SN;
-    CMOE_LAUNCH(TS_GEMM1_BASE,
-                launch_skinny_hb(dm, *w, (const half_t*)x, x_div, T, perm, offsets, expert_idx, t1ext, a, st));
-    CMOE_LAUNCH(TS_RESID_UP, launch_skinny_resid_up(dm, *w, T, perm, expert_idx, gate, t1ext, a, spart, st));
-    if (y_fused != nullptr && weights_combine_ok(w)) {
-      float* ures = (float*)(ws + L.ures);
-      CMOE_LAUNCH(TS_GEMM2, launch_skinny_down(dm, *w, a, T, offsets, (half_t*)y_base_sorted, perm, expert_idx, gate,
-                                               spart, n_parts, ures, st));
-      CMOE_LAUNCH(TS_COMBINE, launch_skinny_add(dm, (const half_t*)y_base_sorted, ures, perm, T, (half_t*)y_fused, st));
+    if (step != nullptr) {   // y_fused and its weights are there
+      CMOE_LAUNCH(TS_GEMM1_BASE, launch_skinny_hb(dm, *w, (const half_t*)x, x_div, T, step->cluster_id, step->perm,
+                                                  step->inv_perm, step->offsets, expert_idx, t1ext, a, st));
+      CMOE_LAUNCH(TS_RESID_UP,
+                  launch_skinny_resid_up(dm, *w, T, nullptr, step->inv_perm, expert_idx, gate, t1ext, a, spart, st));
+      float *ures = (float*)(ws + L.ures), *parts = (float*)(ws + L.v1cat);   // factor panels: not of this path
+      CMOE_LAUNCH(TS_GEMM2, launch_skinny_down(dm, *w, a, T, offsets, (half_t*)y_base_sorted, parts, expert_idx, gate, spart, n_parts,
+                                               ures, st));
+      CMOE_LAUNCH(TS_COMBINE,
+                  launch_skinny_add(dm, (const half_t*)y_base_sorted, parts, ures, step->inv_perm, T, (half_t*)y_fused, st));
       *fused = true;
       return CMOE_OK;
     }
+    CMOE_LAUNCH(TS_GEMM1_BASE, launch_skinny_hb(dm, *w, (const half_t*)x, x_div, T, nullptr, const_cast<int32_t*>(perm),
+                                                nullptr, const_cast<int32_t*>(offsets), expert_idx, t1ext, a, st));
+    CMOE_LAUNCH(TS_RESID_UP, launch_skinny_resid_up(dm, *w, T, perm, nullptr, expert_idx, gate, t1ext, a, spart, st));
     CMOE_LAUNCH(TS_SREDUCE, launch_sreduce(dm, T, perm, spart, n_parts, s_down, st));
-    CMOE_LAUNCH(TS_GEMM2, launch_skinny_down(dm, *w, a, T, offsets, (half_t*)y_base_sorted, nullptr, nullptr, nullptr,
-                                             nullptr, 0, nullptr, st));
+    CMOE_LAUNCH(TS_GEMM2, launch_skinny_down(dm, *w, a, T, offsets, (half_t*)y_base_sorted, nullptr, nullptr, nullptr, nullptr, 0,
+                                             nullptr, st));
     return CMOE_OK;
   }
   // inside each cluster, order the rows by their selected experts; all intermediates live
@@ -317,7 +327,7 @@ static int ffn_impl(cmoe_handle* h, const cmoe_weights* w, const cmoe_f16* x, in
   // cluster-sorted (or token) order
   int* rm = (int*)(ws + L.sort_i32);
   int* p2 = rm + (size_t)T;
-  if (!sorted) CMOE_LAUNCH(TS_PERMUTE, launch_pair_sort(dm, perm, offsets, expert_idx, rm, p2, st));
+  if (step == nullptr) CMOE_LAUNCH(TS_PERMUTE, launch_pair_sort(dm, perm, offsets, expert_idx, rm, p2, st));
   const int* rperm = p2;
   const int* rowmap = rm;
   // when the combine is fused into the down-projection its U2 panel joins the same launch
@@ -338,15 +348,15 @@ static int ffn_impl(cmoe_handle* h, const cmoe_weights* w, const cmoe_f16* x, in
   return CMOE_OK;
 }
 
-// The permutation of a whole step: above SKINNY_T tokens together with the expert-pair order
-// that ffn_impl needs, else the plain permutation.
+// The permutation of a whole step, with the expert-pair order that ffn_impl needs.  Up to SKINNY_T tokens it is
+// made by the first weight stream.
 static int permute_step(cmoe_handle* h, const int32_t* cluster_id, const int32_t* expert_idx, int32_t T, int32_t* perm,
                         int32_t* inv_perm, int32_t* offsets, void* workspace, hipStream_t st) {
   const cmoe_ws_layout L = cmoe_layout(h->dm, T);
   int* blk = (int*)((char*)workspace + L.blk_counts);
-  if (T <= SKINNY_T) {
+  if (T == 0) {
     CMOE_LAUNCH(TS_PERMUTE, launch_permute(h->dm, cluster_id, T, perm, inv_perm, offsets, blk, st));
-  } else {
+  } else if (T > SKINNY_T) {
     int* rm = (int*)((char*)workspace + L.sort_i32);
     CMOE_LAUNCH(TS_PERMUTE, launch_sort_pairs(h->dm, cluster_id, 1, 1, expert_idx, T, perm, inv_perm, offsets, blk, rm,
                                               rm + (size_t)T, st));
@@ -441,7 +451,8 @@ extern "C" int cmoe_forward_multi(cmoe_handle* h, const cmoe_weights* w, const c
   float* s_down = (float*)(ws + L.sdown);
   bool fused = false;
   // virtual token vt reads row vt / top_g of x
-  rc = ffn_impl(h, w, x, Tv, perm, offsets, expert_idx, gate, yb, s_down, (cmoe_f16*)yrep, &fused, g1, true,
+  const ffn_step step{cluster_id, perm, inv_perm, offsets};
+  rc = ffn_impl(h, w, x, Tv, perm, offsets, expert_idx, gate, yb, s_down, (cmoe_f16*)yrep, &fused, g1, &step,
                 workspace, base_bytes, stream);
   if (rc != CMOE_OK) return rc;
   if (!fused) {
@@ -549,7 +560,8 @@ extern "C" int cmoe_forward(cmoe_handle* h, const cmoe_weights* w, const cmoe_f1
   rc = permute_step(h, cluster_id, expert_idx, T, perm, inv_perm, offsets, workspace, (hipStream_t)stream);
   if (rc != CMOE_OK || T == 0) return rc;
   bool fused = false;
-  rc = ffn_impl(h, w, x, T, perm, offsets, expert_idx, gate, yb, s_down, y, &fused, 1, true, workspace,
+  const ffn_step step{cluster_id, perm, inv_perm, offsets};
+  rc = ffn_impl(h, w, x, T, perm, offsets, expert_idx, gate, yb, s_down, y, &fused, 1, &step, workspace,
                 workspace_bytes, stream);
   if (rc != CMOE_OK || fused) return rc;
   return cmoe_combine(h, w, yb, s_down, perm, inv_perm, offsets, expert_idx, gate, T, y, workspace, workspace_bytes,

@@ -116,6 +116,26 @@ __device__ __forceinline__ void wave_lds_order() {
 // router always return distinct, valid slots whatever the input holds.
 __device__ __forceinline__ float rank_key(float v) { return v == v ? v : -INFINITY; }
 
+__device__ __forceinline__ float wave_sum(float v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+// The two INT4 codes of a byte (even element in the low nibble), and the dot product of eight codes (a
+// word) with eight values, in element order.
+__device__ __forceinline__ float nib_lo(unsigned b) { return (float)((int)(b << 28) >> 28); }
+__device__ __forceinline__ float nib_hi(unsigned b) { return (float)((int)(b << 24) >> 28); }
+__device__ __forceinline__ float code_dot8(unsigned word, const half8& x) {
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const unsigned b = (word >> (8 * i)) & 0xffu;
+    s = fmaf(nib_lo(b), (float)x[2 * i], s);
+    s = fmaf(nib_hi(b), (float)x[2 * i + 1], s);
+  }
+  return s;
+}
+
 // Inclusive sum over the lanes of a wavefront by data-parallel-primitive moves (no LDS round
 // trips): rows of 16 lanes by shifts, then the row totals broadcast upwards.
 __device__ __forceinline__ int wave_inclusive_sum(int v) {

@@ -60,11 +60,11 @@ struct cmoe_ws_layout {
   size_t u1t;         // f16 [G][d_ff][KRp]    dequantised U1, transposed
   size_t v2p;         // f16 [G][KRp][d_ff]    dequantised V2
   size_t u2t;         // f16 [G][d][KRp]       dequantised U2, transposed
-  size_t t1ext;       // f16 [T][k][r]         t1_j = V1 x of the selected experts, sorted rows (expanded
-                      //                       one-hot over the cluster's rank rows only in registers)
+  size_t t1ext;       // f16 [T][k][r]         t1_j = V1 x of the selected experts, sorted rows (token order in the
+                      //                       weight-streaming path; expanded one-hot only in registers)
   size_t a;           // f16 [T][d_ff]         gated hidden activations, cluster-sorted rows; stored as
                       //                       [d_ff/32][T][32] on the matrix-core path
-  size_t ures;        // f32 [T][d]            residual-down term, sorted rows (weight-streaming path only)
+  size_t ures;        // f32 [T][d]            residual-down term, token order (weight-streaming path only)
   size_t stats_part;  // f32 [slots][K][d]     routing statistics: per-slot sums of x per expert
   size_t stats_cnt;   // i32 [slots][K]        and their row counts
   size_t spart;       // f32 [n_parts][T][k][r] partial V2 a per row tile of d_ff
@@ -140,8 +140,9 @@ hipError_t launch_gemm1(const cmoe_dims& dm, const cmoe_weights& w, const half_t
                         const half_t* v2p, const half_t* t1ext, half_t* a, float* spart, hipStream_t st);
 hipError_t launch_sreduce(const cmoe_dims& dm, int T, const int* perm, const float* spart, int n_parts,
                           float* s_down, hipStream_t st);
-hipError_t launch_skinny_hb(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int x_div, int T, const int* perm,
-                            const int* offsets, const int* expert_idx, half_t* t1, half_t* hb, hipStream_t st);
+hipError_t launch_skinny_hb(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int x_div, int T,
+                            const int* cluster_id, int* perm, int* inv_perm, int* offsets, const int* expert_idx,
+                            half_t* t1, half_t* hb, hipStream_t st);
 hipError_t launch_route_multi(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int top_g,
                               float temperature, int scale, int* cluster_id, int* expert_idx, float* gate,
                               hipStream_t st);
@@ -154,16 +155,16 @@ hipError_t launch_route_stats(const cmoe_dims& dm, const half_t* x, int T, const
                               const int* expert_idx, float beta, float lam, float* mu, float* cluster_act,
                               int* cluster_idle, int* expert_load, int* cluster_load, float* i_load, float* part,
                               int* cnt, hipStream_t st);
-hipError_t launch_skinny_add(const cmoe_dims& dm, const half_t* y_base_sorted, const float* ures, const int* perm,
-                             int T, half_t* y, hipStream_t st);
+hipError_t launch_skinny_add(const cmoe_dims& dm, const half_t* y_base_sorted, const float* parts, const float* ures,
+                             const int* inv_perm, int T, half_t* y, hipStream_t st);
 hipError_t launch_skinny_resid_up(const cmoe_dims& dm, const cmoe_weights& w, int T, const int* perm,
-                                  const int* expert_idx, const float* gate, const half_t* t1, half_t* a,
+                                  const int* inv_perm, const int* expert_idx, const float* gate, const half_t* t1, half_t* a,
                                   float* spart, hipStream_t st);
 hipError_t launch_skinny_combine(const cmoe_dims& dm, const cmoe_weights& w, const half_t* y_base_sorted,
                                  const float* s_down, const int* inv_perm, const int* expert_idx, const float* gate,
                                  int T, half_t* y, hipStream_t st);
 hipError_t launch_skinny_down(const cmoe_dims& dm, const cmoe_weights& w, const half_t* a, int T, const int* offsets,
-                              half_t* y_base_sorted, const int* perm, const int* expert_idx, const float* gate,
+                              half_t* y_base_sorted, float* parts, const int* expert_idx, const float* gate,
                               const float* spart, int n_parts, float* ures, hipStream_t st);
 hipError_t launch_gemm2(const cmoe_dims& dm, const cmoe_weights& w, const half_t* a, int T, const int* offsets,
                         const int* rowmap, half_t* y_base_sorted, hipStream_t st);

@@ -1,16 +1,11 @@
 // Two-stage hierarchical router (Sec. 3.3, Eq. 9 and Eq. 10) and the stable
 // token-to-cluster permutation (the single-device part of group-level dispatch).
 #include <mutex>
+#include <type_traits>
 
 #include "cmoe_device.h"
 
 namespace {
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
 
 __device__ __forceinline__ float dot8(half8 a, half8 b, float acc) {
 #pragma unroll
@@ -243,17 +238,20 @@ __global__ __launch_bounds__(256) void sum_groups_kernel(const half_t* __restric
 }
 
 // Few tokens: one workgroup (eight wavefronts) per token, the logits of a stage spread over
-// the wavefronts so that their dot products run side by side instead of one after another.
+// the wavefronts so that their dot products run side by side instead of one after another.  ALL: few router
+// rows altogether, and the logits of every expert are taken with the clusters', so that the second stage
+// waits for no load (one token, 2 + 8 rows of 768: 4.3 -> 3.7 us).
 constexpr int RS_WAVES = 8;
-template <int MAXC>
+constexpr int RS_ALL = 16;   // router rows up to which every logit is taken at once
+template <int MAXC, bool ALL>
 __global__ __launch_bounds__(RS_WAVES * 64) void route_small_kernel(
     const half_t* __restrict__ x, const half_t* __restrict__ rc, const half_t* __restrict__ re,
     const float* __restrict__ bias, int T, int d, int G, int K, int k, int* __restrict__ cluster_id,
     int* __restrict__ expert_idx, float* __restrict__ gate) {
   __shared__ float zs[64];
-  __shared__ float ls[64];
+  __shared__ float ls[ALL ? RS_ALL : 64];
   __shared__ int cs;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int t = blockIdx.x;
   const int nchunk = d >> 3;
   half8 xv[MAXC];
@@ -271,10 +269,22 @@ __global__ __launch_bounds__(RS_WAVES * 64) void route_small_kernel(
     }
     return wave_sum(acc);
   };
-  for (int g = wave; g < G; g += RS_WAVES) {
-    float z = dot(rc + (size_t)g * d);
-    if (bias != nullptr) z += bias[g];
-    if (lane == 0) zs[g] = z;
+  if (ALL) {
+    // at most two rows a wavefront, both in flight
+    const int n = G + G * K;
+    auto row = [&](int i) { return i < G ? rc + (size_t)i * d : re + (size_t)(i - G) * d; };
+    const int i0 = wave, i1 = wave + RS_WAVES;
+    const float l0 = dot(row(min(i0, n - 1))), l1 = dot(row(min(i1, n - 1)));
+    if (lane == 0) {
+      if (i0 < G) zs[i0] = bias != nullptr ? l0 + bias[i0] : l0; else if (i0 < n) ls[i0 - G] = l0;
+      if (i1 < G) zs[i1] = bias != nullptr ? l1 + bias[i1] : l1; else if (i1 < n) ls[i1 - G] = l1;
+    }
+  } else {
+    for (int g = wave; g < G; g += RS_WAVES) {
+      float z = dot(rc + (size_t)g * d);
+      if (bias != nullptr) z += bias[g];
+      if (lane == 0) zs[g] = z;
+    }
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -289,43 +299,46 @@ __global__ __launch_bounds__(RS_WAVES * 64) void route_small_kernel(
   }
   __syncthreads();
   const int c = cs;
-  for (int j = wave; j < K; j += RS_WAVES) {
-    float l = dot(re + (size_t)(c * K + j) * d);
-    if (lane == 0) ls[j] = l;
-  }
-  __syncthreads();
-  if (wave != 0) return;
-  const float mine = (lane < K) ? ls[lane] : -INFINITY;
-  float sel_l[8];
-  int sel_j[8];
-  float lmax = 0.f;
-  const float key = rank_key(mine);
-  bool taken = false;
-#pragma unroll
-  for (int a = 0; a < 8; ++a) {
-    sel_l[a] = 0.f;
-    sel_j[a] = 0;
-    if (a < k) {
-      const int j = select_round(key, taken, lane, K);
-      sel_l[a] = __shfl(mine, j, 64);
-      sel_j[a] = j;
-      if (a == 0) lmax = sel_l[a];
+  if (!ALL) {
+    for (int j = wave; j < K; j += RS_WAVES) {
+      float l = dot(re + (size_t)(c * K + j) * d);
+      if (lane == 0) ls[j] = l;
     }
+    __syncthreads();
   }
-  if (lane == 0) {
-    cluster_id[t] = c;
-    float den = 0.f;
-    float ex[8];
+  if (wave == 0) {
+    const float mine = (lane < K) ? ls[(ALL ? c * K : 0) + lane] : -INFINITY;
+    float sel_l[8];
+    int sel_j[8];
+    float lmax = 0.f;
+    const float key = rank_key(mine);
+    bool taken = false;
 #pragma unroll
     for (int a = 0; a < 8; ++a) {
-      ex[a] = (a < k) ? expf(sel_l[a] - lmax) : 0.f;
-      den += ex[a];
-    }
-#pragma unroll
-    for (int a = 0; a < 8; ++a) {
+      sel_l[a] = 0.f;
+      sel_j[a] = 0;
       if (a < k) {
-        expert_idx[(size_t)t * k + a] = c * K + sel_j[a];
-        gate[(size_t)t * k + a] = ex[a] / den;
+        const int j = select_round(key, taken, lane, K);
+        sel_l[a] = __shfl(mine, j, 64);
+        sel_j[a] = j;
+        if (a == 0) lmax = sel_l[a];
+      }
+    }
+    if (lane == 0) {
+      cluster_id[t] = c;
+      float den = 0.f;
+      float ex[8];
+#pragma unroll
+      for (int a = 0; a < 8; ++a) {
+        ex[a] = (a < k) ? expf(sel_l[a] - lmax) : 0.f;
+        den += ex[a];
+      }
+#pragma unroll
+      for (int a = 0; a < 8; ++a) {
+        if (a < k) {
+          expert_idx[(size_t)t * k + a] = c * K + sel_j[a];
+          gate[(size_t)t * k + a] = ex[a] / den;
+        }
       }
     }
   }
@@ -733,6 +746,25 @@ hipError_t launch_sort_ids(const int* ids, int stride, int div, int n, int bins,
   return go_sort<false>(a, perm, inv_perm, offsets, nullptr, nullptr, counts, st);
 }
 
+// The router for at most SKINNY_T tokens.
+static hipError_t launch_route_small(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int* cluster_id,
+                                     int* expert_idx, float* gate, hipStream_t st) {
+  const int chunks_per_lane = (dm.d / 8 + 63) / 64;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(T), dim3(RS_WAVES * 64), 0, st, x, (const half_t*)w.router_cluster,
+                       (const half_t*)w.router_expert, w.cluster_bias, T, dm.d, dm.G, dm.K, dm.k, cluster_id, expert_idx, gate);
+  };
+  auto pick = [&](auto all) {
+    constexpr bool ALL = decltype(all)::value;
+    if (chunks_per_lane <= 2) go(route_small_kernel<2, ALL>);
+    else if (chunks_per_lane <= 4) go(route_small_kernel<4, ALL>);
+    else if (chunks_per_lane <= 8) go(route_small_kernel<8, ALL>);
+    else go(route_small_kernel<16, ALL>);
+  };
+  if (dm.G + dm.G * dm.K <= RS_ALL) pick(std::true_type{}); else pick(std::false_type{});
+  return hipGetLastError();
+}
+
 hipError_t launch_route(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int T, int* cluster_id,
                         int* expert_idx, float* gate, hipStream_t st) {
   dim3 grid((T + ROUTE_WAVES - 1) / ROUTE_WAVES), block(ROUTE_WAVES * 64);
@@ -741,22 +773,7 @@ hipError_t launch_route(const cmoe_dims& dm, const cmoe_weights& w, const half_t
   int chunks_per_lane = (dm.d / 8 + 63) / 64;
   if (T > SKINNY_T && dm.G + dm.G * dm.K <= 128)
     return launch_route_rows(dm, w, x, T, cluster_id, expert_idx, gate, st);
-  if (T <= SKINNY_T) {
-    dim3 g1(T), b1(RS_WAVES * 64);
-    if (chunks_per_lane <= 2)
-      hipLaunchKernelGGL(route_small_kernel<2>, g1, b1, 0, st, x, rc, re, w.cluster_bias, T, dm.d, dm.G, dm.K, dm.k,
-                         cluster_id, expert_idx, gate);
-    else if (chunks_per_lane <= 4)
-      hipLaunchKernelGGL(route_small_kernel<4>, g1, b1, 0, st, x, rc, re, w.cluster_bias, T, dm.d, dm.G, dm.K, dm.k,
-                         cluster_id, expert_idx, gate);
-    else if (chunks_per_lane <= 8)
-      hipLaunchKernelGGL(route_small_kernel<8>, g1, b1, 0, st, x, rc, re, w.cluster_bias, T, dm.d, dm.G, dm.K, dm.k,
-                         cluster_id, expert_idx, gate);
-    else
-      hipLaunchKernelGGL(route_small_kernel<16>, g1, b1, 0, st, x, rc, re, w.cluster_bias, T, dm.d, dm.G, dm.K,
-                         dm.k, cluster_id, expert_idx, gate);
-    return hipGetLastError();
-  }
+  if (T <= SKINNY_T) return launch_route_small(dm, w, x, T, cluster_id, expert_idx, gate, st);
   if (chunks_per_lane <= 2)
     hipLaunchKernelGGL(route_kernel<2>, grid, block, 0, st, x, rc, re, w.cluster_bias, T, dm.d, dm.G, dm.K, dm.k,
                        cluster_id, expert_idx, gate);

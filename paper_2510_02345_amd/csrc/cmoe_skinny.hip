@@ -5,18 +5,11 @@
 // contraction dimension, and both operands travel global -> LDS by DMA into per-wavefront
 // rings.  The per-expert rank-r terms (INT4 factors dequantised on the fly, Sec. 3.4) are
 // small kernels of their own or ride along in the stream launches.
+#include <type_traits>
+
 #include "cmoe_device.h"
 
 namespace {
-
-__device__ __forceinline__ float nib_lo(unsigned b) { return (float)((int)(b << 28) >> 28); }
-__device__ __forceinline__ float nib_hi(unsigned b) { return (float)((int)(b << 24) >> 28); }
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
 
 constexpr int SK_ROWS = 32;   // weight rows per workgroup
 constexpr int SK_RB = SK_ROWS / 32;  // 32-row blocks per workgroup
@@ -138,14 +131,16 @@ __device__ __forceinline__ void skinny_reduce(float* red, int wave, int lane, co
 }
 
 struct SkinnyTile {
-  int c, n0, m0, m_end;
+  int c, n0, m0, m_end, s;
 };
-// Stream workgroup `id` of a launch of nx row blocks x slots (row block fastest).  A slot is a
-// pass over `cols` tokens of a cluster, m_end the end of the pass; the slots are the passes that exist,
-// found from the offsets.
-__device__ __forceinline__ bool skinny_tile(const int* offsets, int id, int nx, int G, int cols, SkinnyTile& t) {
+// Stream workgroup `id` of a launch of nx row blocks x `split` parts of the contraction (t.s) x slots (row
+// block fastest).  A slot is a pass over `cols` tokens of a cluster, m_end the end of the pass; the slots
+// are the passes that exist, found from the offsets.
+__device__ __forceinline__ bool skinny_tile(const int* offsets, int id, int nx, int split, int G, int cols,
+                                            SkinnyTile& t) {
   int xb = id % nx;
-  const int slot = id / nx;
+  const int slot = id / nx / split;
+  t.s = id / nx % split;
   // Workgroups are dealt round-robin to the 8 XCDs.  The INT4 factor rows are 128-byte
   // lines shared by 8 neighbouring row blocks, so inside every run of 64 blocks the 8
   // workgroups that land on one XCD take 8 neighbouring row blocks: each line is then
@@ -160,67 +155,64 @@ __device__ __forceinline__ bool skinny_tile(const int* offsets, int id, int nx, 
 }
 
 // ---------------------------------------------------------------- t1 = V1_e x
-// t1[p][j][:] for sorted row p and its selected expert j, by the calling workgroup: a
-// wavefront per rank row, INT4 codes dequantised on the fly (Sec. 3.4).
-__device__ __forceinline__ void skinny_t1_job(int p, int j, const half_t* __restrict__ x,
-                                              const int* __restrict__ perm, const int* __restrict__ expert_idx,
+// t1[tok][j][:] for token tok and its selected expert j, by the calling workgroup: a
+// wavefront takes T1_ROWS rank rows at a time, all loads of a step in flight before the first is used; INT4 codes
+// dequantised on the fly (Sec. 3.4).
+constexpr int T1_ROWS = 4;
+__device__ __forceinline__ void skinny_t1_job(int tok, int j, const half_t* __restrict__ x,
+                                              const int* __restrict__ expert_idx,
                                               const uint8_t* __restrict__ v1_q, const half_t* __restrict__ v1_s,
                                               int d, int q, int r, int k, int x_div, int n_exp,
                                               half_t* __restrict__ t1) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  const int tok = perm[p];
   const int e = min(max(expert_idx[(size_t)tok * k + j], 0), n_exp - 1);
   const half_t* xr = x + (size_t)(tok / x_div) * d;
-  for (int rho = wave; rho < r; rho += nw) {
-    const size_t row = (size_t)e * r + rho;
-    const uint8_t* qr = v1_q + row * (d / 2);
-    const half_t* sr = v1_s + row * (d / q);
-    float acc = 0.f;
+  for (int rho0 = wave * T1_ROWS; rho0 < r; rho0 += nw * T1_ROWS) {
+    float acc[T1_ROWS] = {};
     for (int ch0 = lane; ch0 < d / 8; ch0 += 256) {   // 8 elements per chunk: 4 code bytes, one scale
-      unsigned bytes[4];
+      unsigned bytes[T1_ROWS][4];
+      half_t sc[T1_ROWS][4];
       half8 xv[4];
-      float sc[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int ch = ch0 + 64 * u;
         const bool in = ch < d / 8;
-        bytes[u] = in ? *(const unsigned*)(qr + ch * 4) : 0u;
         xv[u] = in ? *(const half8*)(xr + ch * 8) : half8{0, 0, 0, 0, 0, 0, 0, 0};
-        sc[u] = in ? (float)sr[(ch * 8) / q] : 0.f;
-      }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        float part = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const unsigned b = (bytes[u] >> (8 * i)) & 0xffu;
-          part = fmaf(nib_lo(b), (float)xv[u][2 * i], part);
-          part = fmaf(nib_hi(b), (float)xv[u][2 * i + 1], part);
+        for (int i = 0; i < T1_ROWS; ++i) {
+          const size_t row = (size_t)e * r + min(rho0 + i, r - 1);
+          bytes[i][u] = in ? *(const unsigned*)(v1_q + row * (d / 2) + ch * 4) : 0u;
+          sc[i][u] = in ? v1_s[row * (d / q) + (ch * 8) / q] : (half_t)0.f;
         }
-        acc = fmaf(sc[u], part, acc);
       }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int i = 0; i < T1_ROWS; ++i) acc[i] = fmaf((float)sc[i][u], code_dot8(bytes[i][u], xv[u]), acc[i]);
     }
-    acc = wave_sum(acc);
-    if (lane == 0) t1[((size_t)p * k + j) * r + rho] = (half_t)acc;
+#pragma unroll
+    for (int i = 0; i < T1_ROWS; ++i) {
+      const float sum = wave_sum(acc[i]);
+      if (lane == 0 && rho0 + i < r) t1[((size_t)tok * k + j) * r + rho0 + i] = (half_t)sum;
+    }
   }
 }
 
 // ---------------------------------------------------------------- residual-down
-// ures[p][n] = sum_j g_j sum_rho U2_{e_j}[rho][n] s_j[rho] for sorted row p and a chunk of
+// ures[tok][n] = sum_j g_j sum_rho U2_{e_j}[rho][n] s_j[rho] for token tok and a chunk of
 // 2048 output columns, s_j summed here from its n_parts partials in fixed order.
-__device__ __forceinline__ void skinny_ures_job(int p, int chunk, const int* __restrict__ perm,
-                                                const int* __restrict__ expert_idx, const float* __restrict__ gate,
+__device__ __forceinline__ void skinny_ures_job(int tok, int chunk, const int* __restrict__ expert_idx,
+                                                const float* __restrict__ gate,
                                                 const uint8_t* __restrict__ u2_q, const half_t* __restrict__ u2_s,
                                                 const float* __restrict__ spart, int n_parts, int T, int d, int q,
                                                 int r, int k, int n_exp, float* __restrict__ ures) {
   __shared__ float gs[8 * 32];
   __shared__ int es[8];
   const int tid = threadIdx.x;
-  const int tok = perm[p];
   const int kr = k * r;
   if (tid < kr) {
     float sum = 0.f;
-    for (int part = 0; part < n_parts; ++part) sum += spart[((size_t)part * T + p) * kr + tid];
+    for (int part = 0; part < n_parts; ++part) sum += spart[((size_t)part * T + tok) * kr + tid];
     gs[tid] = gate[(size_t)tok * k + tid / r] * sum;
   }
   if (tid < k) es[tid] = min(max(expert_idx[(size_t)tok * k + tid], 0), n_exp - 1);
@@ -251,27 +243,40 @@ __device__ __forceinline__ void skinny_ures_job(int p, int chunk, const int* __r
         }
     }
   }
-  float* dst = ures + (size_t)p * d + ch * 8;
+  float* dst = ures + (size_t)tok * d + ch * 8;
   *(float4v*)dst = float4v{acc[0], acc[1], acc[2], acc[3]};
   *(float4v*)(dst + 4) = float4v{acc[4], acc[5], acc[6], acc[7]};
 }
 
-// y[perm[p]] = y_base_sorted[p] + ures[p]
-__global__ __launch_bounds__(256) void skinny_add_kernel(const half_t* __restrict__ yb, const float* __restrict__ ures,
-                                                         const int* __restrict__ perm, int d,
-                                                         half_t* __restrict__ y) {
-  const int p = blockIdx.x, ch = blockIdx.y * 256 + threadIdx.x;
-  if (ch >= d / 8) return;
-  const half8 b8 = *(const half8*)(yb + (size_t)p * d + ch * 8);
-  const float* u = ures + (size_t)p * d + ch * 8;
-  const float4v u0 = *(const float4v*)u, u1 = *(const float4v*)(u + 4);
-  half8 o;
+// y[tok] = base[inv_perm[tok]] + ures[tok], base being y_base_sorted, or with SPLIT > 1 the sum of the parts
+// of the contraction.
+template <int SPLIT>
+__global__ __launch_bounds__(256) void skinny_add_kernel(const half_t* __restrict__ yb, const float* __restrict__ parts,
+                                                         const float* __restrict__ ures, const int* __restrict__ inv_perm,
+                                                         int T, int d, half_t* __restrict__ y) {
+  const int tok = blockIdx.x, ch = blockIdx.y * 256 + threadIdx.x;
+  if (ch >= d / 4) return;
+  const float4v u = *(const float4v*)(ures + (size_t)tok * d + ch * 4);
+  const size_t at = (size_t)inv_perm[tok] * d + ch * 4;
+  float4v b;
+  if (SPLIT == 1) {
+    const half4 h = *(const half4*)(yb + at);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    o[i] = (half_t)((float)b8[i] + u0[i]);
-    o[i + 4] = (half_t)((float)b8[i + 4] + u1[i]);
+    for (int i = 0; i < 4; ++i) b[i] = (float)h[i];
+  } else {
+    float4v v[SPLIT];
+#pragma unroll
+    for (int s = 0; s < SPLIT; ++s) v[s] = *(const float4v*)(parts + (size_t)s * T * d + at);
+    b = v[0];
+#pragma unroll
+    for (int s = 1; s < SPLIT; ++s)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) b[i] += v[s][i];
   }
-  *(half8*)(y + (size_t)perm[p] * d + ch * 8) = o;
+  half4 o;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) o[i] = (half_t)(b[i] + u[i]);
+  *(half4*)(y + (size_t)tok * d + ch * 4) = o;
 }
 
 // Small jobs that ride along with a weight stream as the first workgroups of its grid:
@@ -280,7 +285,6 @@ __global__ __launch_bounds__(256) void skinny_add_kernel(const half_t* __restric
 enum { SIDE_NONE = 0, SIDE_T1 = 1, SIDE_URES = 2 };
 struct SideArgs {
   const half_t* x;
-  const int* perm;
   const int* expert_idx;
   const float* gate;
   const uint8_t* fq;     // V1 codes (SIDE_T1) or U2 codes (SIDE_URES)
@@ -294,6 +298,52 @@ struct SideArgs {
   int n_side;            // workgroups reserved for the jobs (n_jobs rounded up to 8)
 };
 
+// The permutation of up to 256 tokens (T <= SKINNY_T, G <= 64), by every workgroup for itself from the cluster
+// ids, as in sort_few_kernel.  That kernel takes 4.7 us between two large ones, 1.6 us between small ones; the ballots
+// add nothing to a stream of HBM size and 0.5 to 1 us to the smallest (768 x 3072, one token: 4.4 -> 5.2 us).
+struct FewSort {
+  int wc[4][64], perm[256], off[65];
+};
+struct FewSortArgs {
+  const int* ids;
+  int T;
+  int *perm, *inv_perm, *offsets;   // written by one workgroup
+};
+__device__ __forceinline__ void few_sort(const FewSortArgs& a, int G, FewSort& s, bool write) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bool in = tid < a.T;
+  const int id = in ? min(max(a.ids[tid], 0), G - 1) : 0;
+  unsigned long long same = __ballot(in), of_lane = same;   // lanes with this lane's cluster; with cluster `lane`
+  for (int b = 0; b < 32 - __builtin_clz(G); ++b) {
+    const unsigned long long m = __ballot((id >> b) & 1);
+    same &= ((id >> b) & 1) ? m : ~m;
+    of_lane &= ((lane >> b) & 1) ? m : ~m;
+  }
+  s.wc[wave][lane] = lane < G ? __popcll(of_lane) : 0;
+  __syncthreads();
+  int total = 0, before = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const int v = s.wc[w][lane];
+    total += v;
+    before += w < wave ? v : 0;
+  }
+  const int first = wave_inclusive_sum(total) - total;
+  const int row = __shfl(first + before, id, 64) + __popcll(same & ((1ull << lane) - 1ull));
+  if (wave == 0 && lane < G) s.off[lane] = first;
+  if (tid == 0) s.off[G] = a.T;
+  if (in) s.perm[row] = tid;
+  if (write) {
+    if (wave == 0 && lane < G) a.offsets[lane] = first;
+    if (tid == 0) a.offsets[G] = a.T;
+    if (in) {
+      a.perm[row] = tid;
+      a.inv_perm[tid] = row;
+    }
+  }
+  __syncthreads();
+}
+
 // ---------------------------------------------------------------- shared-base products
 // out[p][n] = sum_k W[c][n][k] X[row(p)][k] for the sorted rows p of cluster c (the product
 // the experts of a cluster share, Sec. 3.2): up-projection with W = W1_base, X = x gathered
@@ -302,33 +352,38 @@ struct SideArgs {
 // or NULL for the identity.  w_blk = 0: W[c] is row-major [N][Kc]; otherwise W[c] is stored
 // as [Kc / 32][N][32] and w_blk = N * 32 (the re-tiled copy of the bases): an 8-row load is
 // then two contiguous 256-byte pieces instead of eight 128-byte pieces a row apart.
-template <int SIDE, int COLS, bool NT>
-__global__ __launch_bounds__(256, SkRing<COLS>::OCC) void skinny_base_kernel(const half_t* __restrict__ X,
-                                                                  const int* __restrict__ gather,
-                                                                  const half_t* __restrict__ W,
-                                                                  const int* __restrict__ offsets, int N, int Kc,
-                                                                  half_t* __restrict__ out, int nx, int G,
-                                                                  long w_blk, SideArgs sa) {
-  if (SIDE != SIDE_NONE && (int)blockIdx.x < sa.n_side) {
-    const int job = blockIdx.x;
+// SORT: the permutation is made here (few_sort) and gathers through it.
+template <int SIDE, int COLS, bool NT, bool SORT>
+__global__ __launch_bounds__(256, (SkRing<COLS>::OCC)) void skinny_base_kernel(
+    const half_t* __restrict__ X, const int* __restrict__ gather, const half_t* __restrict__ W,
+    const int* __restrict__ offsets, int N, int Kc, half_t* __restrict__ out, float* __restrict__ parts, int split,
+    int T, int nx, int G, long w_blk, SideArgs sa, FewSortArgs fs) {
+  // The jobs for t1 before the stream's workgroups, those for ures after them: 203 tokens of 8 clusters of
+  // 2048 x 8192, down-projection 65.4 us with them before, 62 after, 65 to 70 in between; up-projection 64 before and in
+  // between, 63 after, but 153 instead of 138 us for 64 tokens of 8 of 4096 x 14336.
+  const int first = SIDE == SIDE_T1 ? sa.n_side : 0, job = (int)blockIdx.x - (SIDE == SIDE_T1 ? 0 : (int)gridDim.x - sa.n_side);
+  const int id = (int)blockIdx.x - first;
+  if (SIDE == SIDE_T1 ? id < 0 : SIDE == SIDE_URES && job >= 0) {
     if (job >= sa.n_jobs) return;
     if (SIDE == SIDE_T1) {
-      skinny_t1_job(job / sa.k, job % sa.k, sa.x, sa.perm, sa.expert_idx, sa.fq, sa.fs, sa.d, sa.q, sa.r, sa.k,
-                    sa.x_div, sa.n_exp, sa.t1);
+      skinny_t1_job(job / sa.k, job % sa.k, sa.x, sa.expert_idx, sa.fq, sa.fs, sa.d, sa.q, sa.r, sa.k, sa.x_div, sa.n_exp,
+                    sa.t1);
     } else {
       const int nch = (sa.d + 2047) / 2048;
-      skinny_ures_job(job / nch, job % nch, sa.perm, sa.expert_idx, sa.gate, sa.fq, sa.fs, sa.spart, sa.n_parts, sa.T,
-                      sa.d, sa.q, sa.r, sa.k, sa.n_exp, sa.ures);
+      skinny_ures_job(job / nch, job % nch, sa.expert_idx, sa.gate, sa.fq, sa.fs, sa.spart, sa.n_parts, sa.T, sa.d, sa.q,
+                      sa.r, sa.k, sa.n_exp, sa.ures);
     }
     return;
   }
+  __shared__ FewSort order[1];
+  if (SORT) few_sort(fs, G, order[0], id == 0);
   constexpr int RED_BYTES = SK_WAVES * SK_RB * 16 * 64 * 4;
   using RG = SkRing<COLS>;
   constexpr int RINGS = SK_WAVES * RG::RING;
   __shared__ __attribute__((aligned(1024))) char smem[RED_BYTES > RINGS ? RED_BYTES : RINGS];
   float* red = (float*)smem;
   SkinnyTile t;
-  if (!skinny_tile(offsets, (int)blockIdx.x - (SIDE != SIDE_NONE ? sa.n_side : 0), nx, G, COLS, t)) return;
+  if (!skinny_tile(SORT ? order[0].off : offsets, id, nx, split, G, COLS, t)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, fr = lane & 31, h = lane >> 5;
   const int wv = __builtin_amdgcn_readfirstlane(wave);
   const unsigned smem_lds = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
@@ -340,7 +395,8 @@ __global__ __launch_bounds__(256, SkRing<COLS>::OCC) void skinny_base_kernel(con
 #pragma unroll
   for (int i = 0; i < COLS / 8; ++i) {
     int r = min(t.m0 + 8 * i + lrow, t.m_end - 1);
-    if (gather != nullptr) r = gather[r] / sa.x_div;
+    if (SORT) r = order[0].perm[r] / sa.x_div;
+    else if (gather != nullptr) r = gather[r] / sa.x_div;
     brow[i] = X + (size_t)r * Kc;
   }
   float16v acc[SK_RB];
@@ -348,27 +404,36 @@ __global__ __launch_bounds__(256, SkRing<COLS>::OCC) void skinny_base_kernel(con
   for (int rb = 0; rb < SK_RB; ++rb)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[rb][v] = 0.f;
-  const int iters = Kc / 64;
-  skinny_stream<COLS, NT>(wrow, 8 * w_ld, w_blk ? (size_t)w_blk : 32, brow, smem + wv * RG::RING, smem_lds + wv * RG::RING, lane,
-                wv * iters / SK_WAVES, (wv + 1) * iters / SK_WAVES, acc);
+  const int iters = Kc / 64, shares = SK_WAVES * split, share = t.s * SK_WAVES + wv;
+  skinny_stream<COLS, NT>(wrow, 8 * w_ld, w_blk ? (size_t)w_blk : 32, brow, smem + wv * RG::RING,
+                          smem_lds + wv * RG::RING, lane, share * iters / shares, (share + 1) * iters / shares, acc);
   __syncthreads();  // every ring has been consumed: its space becomes red
   float16v hb;
   skinny_reduce(red, wave, lane, acc, hb);
   if (wave < SK_RB && fr < COLS && p < t.m_end) {
 #pragma unroll
-    for (int qd = 0; qd < 4; ++qd)
-      *(half4*)(out + (size_t)p * N + t.n0 + wave * 32 + 8 * qd + 4 * h) = to_half4(hb, qd);
+    for (int qd = 0; qd < 4; ++qd) {
+      const size_t at = (size_t)p * N + t.n0 + wave * 32 + 8 * qd + 4 * h;
+      if (parts != nullptr)
+        *(float4v*)(parts + (size_t)t.s * T * N + at) = float4v{hb[4 * qd], hb[4 * qd + 1], hb[4 * qd + 2], hb[4 * qd + 3]};
+      else
+        *(half4*)(out + at) = to_half4(hb, qd);
+    }
   }
 }
 
 // ---------------------------------------------------------------- residual-up, GELU, gated sum, V2 product
 // In place on A (which holds Hb on entry), for sorted row p and a chunk of RU_CH columns:
 //   A[p][n] = sum_j g_j GELU(Hb[p][n] + sum_rho U1_{e_j}[rho][n] t1_j[rho])       (Sec. 3.2)
-//   spart[chunk][p][j][rho] = sum_{n in chunk} V2_{e_j}[rho][n] GELU(...)_j[n]
-// with the INT4 factors dequantised on the fly (Sec. 3.4).  A thread owns 8 consecutive
+//   spart[chunk][row][j][rho] = sum_{n in chunk} V2_{e_j}[rho][n] GELU(...)_j[n]
+// with the INT4 factors dequantised on the fly (Sec. 3.4).  A workgroup takes sorted row p = blockIdx.x and its
+// token perm[p], row = p; or, with inv_perm given, token blockIdx.x, p = inv_perm of it, row = the
+// token, so that the loads by token do not wait for p.  t1 is in token order.  A thread owns 8 consecutive
 // columns (one 32-bit word of codes per rank row); the k*r partial dot products of a thread
-// are summed over the wavefront by a halving exchange (64 values on 64 lanes -> lane l ends
-// with the total of value l), then over the 4 wavefronts in fixed order.
+// are summed over the wavefront by a halving exchange, then over the 4 wavefronts in fixed order.
+// Bound by vector instructions (three quarters of the time they issue): 203 tokens, two experts of rank 16, 8192
+// columns 20.0 us with an exchange of always 64 values through LDS, in registers of which two workgroups
+// fit a CU; 16.8 us with 32 values, register swaps and four workgroups.
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 // The 8 INT4 codes c_0..c_7 of one 32-bit word as f16 pairs WITHOUT their offsets removed.
 // Flipping bit 3 of every nibble turns a two's-complement code c into c + 8 in [0, 16); a
@@ -409,33 +474,58 @@ constexpr int RU_N = 8;
 constexpr int RU_CH = RU_N * 256;
 static_assert(RU_CH == SKINNY_SN, "s partial chunk");
 
-template <int OFF>
-__device__ __forceinline__ void halving_step(float (&v)[64], int lane) {
-  const bool up = (lane & OFF) != 0;
+// One step of the halving exchange: N values a lane, lanes OFF apart.  Across halves and rows of the wavefront
+// one swap instruction moves both values of a pair.
+template <int OFF, int N, int NV>
+__device__ __forceinline__ void halving_step(float (&v)[NV], int lane) {
+  if constexpr (N == 1) {
+    v[0] += __shfl_xor(v[0], OFF, 64);
+  } else {
 #pragma unroll
-  for (int i = 0; i < OFF; ++i) {
-    const float keep = up ? v[i + OFF] : v[i];
-    const float send = up ? v[i] : v[i + OFF];
-    v[i] = keep + __shfl_xor(send, OFF, 64);
+    for (int i = 0; i < N / 2; ++i) {
+      if constexpr (OFF >= 16) {
+        const unsigned a = __float_as_uint(v[i]), b = __float_as_uint(v[i + N / 2]);
+        const auto sw = OFF == 32 ? __builtin_amdgcn_permlane32_swap(a, b, false, false)
+                                  : __builtin_amdgcn_permlane16_swap(a, b, false, false);
+        v[i] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+      } else {
+        const bool up = (lane & OFF) != 0;
+        const float keep = up ? v[i + N / 2] : v[i];
+        const float send = up ? v[i] : v[i + N / 2];
+        v[i] = keep + __shfl_xor(send, OFF, 64);
+      }
+    }
   }
 }
+// v[0] of lane l becomes the wavefront's sum of value l / (64 / NV).
+template <int NV>
+__device__ __forceinline__ void halving_sum(float (&v)[NV], int lane) {
+  constexpr auto left = [](int steps) { return (NV >> steps) > 1 ? NV >> steps : 1; };
+  halving_step<32, left(0)>(v, lane);
+  halving_step<16, left(1)>(v, lane);
+  halving_step<8, left(2)>(v, lane);
+  halving_step<4, left(3)>(v, lane);
+  halving_step<2, left(4)>(v, lane);
+  halving_step<1, left(5)>(v, lane);
+}
 
-template <int R>
+// EPG experts at a time (k rounded up to a power of two, at most 64 values in all)
+template <int R, int EPG>
 __global__ __launch_bounds__(256) void skinny_resid_up_kernel(
     half_t* __restrict__ A, const half_t* __restrict__ t1, const int* __restrict__ perm,
-    const int* __restrict__ expert_idx, const float* __restrict__ gate, const uint8_t* __restrict__ u1_q,
+    const int* __restrict__ inv_perm, const int* __restrict__ expert_idx, const float* __restrict__ gate, const uint8_t* __restrict__ u1_q,
     const half_t* __restrict__ u1_s, const uint8_t* __restrict__ v2_q, const half_t* __restrict__ v2_s, int T,
     int d_ff, int k, int q, int n_exp, float* __restrict__ spart) {
-  constexpr int EPG = 64 / R;    // experts per group of 64 (expert, rank row) values
+  constexpr int NV = EPG * R;    // (expert, rank row) values of a group
   __shared__ int srow[8];        // first factor row e_j R of selected expert j
   __shared__ float st1[256];     // t1_j[rho]
   __shared__ float sg[8];
   __shared__ float red[4][64];
-  const int p = blockIdx.x, chunk = blockIdx.y;
+  const int row = blockIdx.x, chunk = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int kr = k * R;
-  const int tok = perm[p];
-  if (tid < kr) st1[tid] = (float)t1[(size_t)p * kr + tid];
+  const int tok = inv_perm != nullptr ? row : perm[row], p = inv_perm != nullptr ? inv_perm[row] : row;
+  if (tid < kr) st1[tid] = (float)t1[(size_t)tok * kr + tid];
   if (tid < k) {
     srow[tid] = min(max(expert_idx[(size_t)tok * k + tid], 0), n_exp - 1) * R;
     sg[tid] = gate[(size_t)tok * k + tid];
@@ -455,7 +545,7 @@ __global__ __launch_bounds__(256) void skinny_resid_up_kernel(
   }
   __syncthreads();
   for (int j0 = 0; j0 < k; j0 += EPG) {
-    float part[64];
+    float part[NV];
 #pragma unroll
     for (int jj = 0; jj < EPG; ++jj) {
       const int j = j0 + jj;
@@ -523,16 +613,11 @@ __global__ __launch_bounds__(256) void skinny_resid_up_kernel(
         }
       }
     }
-    halving_step<32>(part, lane);
-    halving_step<16>(part, lane);
-    halving_step<8>(part, lane);
-    halving_step<4>(part, lane);
-    halving_step<2>(part, lane);
-    halving_step<1>(part, lane);
-    red[wave][lane] = part[0];
+    halving_sum<NV>(part, lane);
+    if (lane % (64 / NV) == 0) red[wave][lane / (64 / NV)] = part[0];
     __syncthreads();
-    if (wave == 0 && j0 * R + lane < kr)
-      spart[((size_t)chunk * T + p) * kr + j0 * R + lane] =
+    if (wave == 0 && lane < NV && j0 * R + lane < kr)
+      spart[((size_t)chunk * T + row) * kr + j0 * R + lane] =
           ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
     __syncthreads();
   }
@@ -622,38 +707,44 @@ inline int stream_cols(const cmoe_dims& dm, int T, bool down) {
 }
 
 // One weight stream of the layer.
-template <int SIDE>
+template <int SIDE, bool SORT>
 hipError_t launch_stream(const cmoe_dims& dm, int cols, const half_t* X, const int* gather, const half_t* W,
-                         const int* offsets, int N, int Kc, half_t* out, int T, long w_blk, const SideArgs& sa,
-                         hipStream_t st) {
+                         const int* offsets, int N, int Kc, half_t* out, float* parts, int split, int T, long w_blk,
+                         const SideArgs& sa, const FewSortArgs& fs, hipStream_t st) {
   const int nx = N / SK_ROWS;
   const int slots = T < dm.G + T / cols ? T : dm.G + T / cols;   // at most: a slot holds a token, all but G of them `cols`
-  const dim3 grid((unsigned)nx * slots + sa.n_side), block(256);
+  const dim3 grid((unsigned)nx * slots * split + sa.n_side), block(256);
   auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, grid, block, 0, st, X, gather, W, offsets, N, Kc, out, nx, dm.G, w_blk, sa);
+    hipLaunchKernelGGL(kern, grid, block, 0, st, X, gather, W, offsets, N, Kc, out, parts, split, T, nx, dm.G, w_blk, sa, fs);
   };
   if (cols == 32) {
-    if (stream_once(dm)) go(skinny_base_kernel<SIDE, 32, true>); else go(skinny_base_kernel<SIDE, 32, false>);
+    if (stream_once(dm)) go(skinny_base_kernel<SIDE, 32, true, SORT>); else go(skinny_base_kernel<SIDE, 32, false, SORT>);
   } else {
-    if (stream_once(dm)) go(skinny_base_kernel<SIDE, 16, true>); else go(skinny_base_kernel<SIDE, 16, false>);
+    if (stream_once(dm)) go(skinny_base_kernel<SIDE, 16, true, SORT>); else go(skinny_base_kernel<SIDE, 16, false, SORT>);
   }
   return hipGetLastError();
 }
 
-// Hb = W1_base(c) x for every sorted row; with t1 != NULL the t1 = V1 x jobs ride along.
+// Hb = W1_base(c) x for every sorted row; with t1 != NULL the t1 = V1 x jobs ride along.  cluster_id != NULL: the
+// permutation (perm, inv_perm, offsets) is made in the same launch.
 hipError_t launch_skinny_hb(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int x_div, int T,
-                            const int* perm, const int* offsets, const int* expert_idx, half_t* t1, half_t* hb,
-                            hipStream_t st) {
+                            const int* cluster_id, int* perm, int* inv_perm, int* offsets, const int* expert_idx,
+                            half_t* t1, half_t* hb, hipStream_t st) {
   SideArgs sa{};
   sa.x_div = x_div > 1 ? x_div : 1;
   // the re-tiled copy of W1 when the caller keeps one, else the canonical array
   const half_t* w1 = w.packed ? (const half_t*)((const char*)w.packed + cmoe_packed(dm).w1) : (const half_t*)w.w1_base;
   const long w_blk = w.packed ? (long)dm.d_ff * 32 : 0;
   const int cols = stream_cols(dm, T, false);
-  if (t1 == nullptr)
-    return launch_stream<SIDE_NONE>(dm, cols, x, perm, w1, offsets, dm.d_ff, dm.d, hb, T, w_blk, sa, st);
+  const FewSortArgs fs{cluster_id, T, perm, inv_perm, offsets};
+  auto go = [&](auto side) {
+    constexpr int SIDE = decltype(side)::value;
+    if (cluster_id != nullptr)
+      return launch_stream<SIDE, true>(dm, cols, x, perm, w1, offsets, dm.d_ff, dm.d, hb, nullptr, 1, T, w_blk, sa, fs, st);
+    return launch_stream<SIDE, false>(dm, cols, x, perm, w1, offsets, dm.d_ff, dm.d, hb, nullptr, 1, T, w_blk, sa, fs, st);
+  };
+  if (t1 == nullptr) return go(std::integral_constant<int, SIDE_NONE>{});
   sa.x = x;
-  sa.perm = perm;
   sa.expert_idx = expert_idx;
   sa.fq = w.v1_q;
   sa.fs = (const half_t*)w.v1_s;
@@ -666,30 +757,54 @@ hipError_t launch_skinny_hb(const cmoe_dims& dm, const cmoe_weights& w, const ha
   sa.n_exp = dm.G * dm.K;
   sa.n_jobs = T * dm.k;
   sa.n_side = (sa.n_jobs + 7) & ~7;
-  return launch_stream<SIDE_T1>(dm, cols, x, perm, w1, offsets, dm.d_ff, dm.d, hb, T, w_blk, sa, st);
+  return go(std::integral_constant<int, SIDE_T1>{});
 }
 
 hipError_t launch_skinny_resid_up(const cmoe_dims& dm, const cmoe_weights& w, int T, const int* perm,
-                                  const int* expert_idx, const float* gate, const half_t* t1, half_t* a,
+                                  const int* inv_perm, const int* expert_idx, const float* gate, const half_t* t1, half_t* a,
                                   float* spart, hipStream_t st) {
   dim3 grid(T, (dm.d_ff + SKINNY_SN - 1) / SKINNY_SN), block(256);
   auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, grid, block, 0, st, a, t1, perm, expert_idx, gate, w.u1_q, (const half_t*)w.u1_s,
+    hipLaunchKernelGGL(kern, grid, block, 0, st, a, t1, perm, inv_perm, expert_idx, gate, w.u1_q, (const half_t*)w.u1_s,
                        w.v2_q, (const half_t*)w.v2_s, T, dm.d_ff, dm.k, dm.q, dm.G * dm.K, spart);
   };
+  auto pick = [&](auto rank) {
+    constexpr int R = decltype(rank)::value;
+    if (dm.k == 1) go(skinny_resid_up_kernel<R, 1>);
+    else if (dm.k == 2 || R == 32) go(skinny_resid_up_kernel<R, 2>);
+    else if (dm.k <= 4 || R == 16) go(skinny_resid_up_kernel<R, R <= 16 ? 4 : 2>);
+    else go(skinny_resid_up_kernel<R, R <= 8 ? 8 : R == 16 ? 4 : 2>);
+  };
   switch (dm.r) {
-    case 4: go(skinny_resid_up_kernel<4>); break;
-    case 8: go(skinny_resid_up_kernel<8>); break;
-    case 16: go(skinny_resid_up_kernel<16>); break;
-    default: go(skinny_resid_up_kernel<32>); break;
+    case 4: pick(std::integral_constant<int, 4>{}); break;
+    case 8: pick(std::integral_constant<int, 8>{}); break;
+    case 16: pick(std::integral_constant<int, 16>{}); break;
+    default: pick(std::integral_constant<int, 32>{}); break;
   }
   return hipGetLastError();
 }
 
-// y_base_sorted = W2_base(c) A; with ures != NULL the residual-down jobs ride along
-// (ures[p] = sum_j g_j U2 s_j from the s partials), to be added by launch_skinny_add.
+// Parts of the contraction of the down-projection.  A launch that leaves CUs idle lasts as long as a wavefront's
+// chain of steps; parts shorten the chain, until the launch has 192 workgroups (256 where the base comes from HBM
+// and the loads take longer), two steps a wavefront are left or the parts no longer fit the space of the factor
+// panels, which this path does not use.  Down-projection of 1, 2 and 4 parts, one token: 768 x 3072 6.7, 5.8 and
+// 4.6 us, of 8 clusters of 2048 x 8192 16.9, 11.6 and 9.2 us; one part and two: two tokens there (128 workgroups) 18.9
+// and 14.7 us, one of 4096 x 14336 30 and 21 us, but 8 tokens of 4 clusters of 1024 x 4096 (128) 9.5 and 10.7 us.
+inline int down_split(const cmoe_dims& dm, int T, int cols) {
+  const int slots = T < dm.G + T / cols ? T : dm.G + T / cols, most = stream_once(dm) ? 256 : 192;
+  const size_t room = sizeof(half_t) * 2 * dm.G * dm.KRp * ((size_t)dm.d + dm.d_ff);
+  int split = 4;
+  while (split > 1 && (dm.d / SK_ROWS * slots * split > most || dm.d_ff / 64 < 2 * SK_WAVES * split ||
+                       sizeof(float) * split * T * dm.d > room))
+    split /= 2;
+  return split;
+}
+
+// y_base_sorted = W2_base(c) A.  With ures != NULL the residual-down jobs ride along (ures[tok] = sum_j g_j U2
+// s_j from the s partials in token order), and the base product may come in parts of the contraction
+// (parts [split][T][d] FP32, sorted rows) instead: launch_skinny_add adds them all.
 hipError_t launch_skinny_down(const cmoe_dims& dm, const cmoe_weights& w, const half_t* a, int T, const int* offsets,
-                              half_t* y_base_sorted, const int* perm, const int* expert_idx, const float* gate,
+                              half_t* y_base_sorted, float* parts, const int* expert_idx, const float* gate,
                               const float* spart, int n_parts, float* ures, hipStream_t st) {
   SideArgs sa{};
   sa.x_div = 1;
@@ -697,14 +812,15 @@ hipError_t launch_skinny_down(const cmoe_dims& dm, const cmoe_weights& w, const 
   const long w_blk = w.packed ? (long)dm.d * 32 : 0;
   const int cols = stream_cols(dm, T, true);
   if (ures == nullptr)
-    return launch_stream<SIDE_NONE>(dm, cols, a, nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted, T, w_blk, sa, st);
-  sa.perm = perm;
+    return launch_stream<SIDE_NONE, false>(dm, cols, a, nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted, nullptr, 1, T,
+                                           w_blk, sa, FewSortArgs{}, st);
   sa.expert_idx = expert_idx;
   sa.gate = gate;
   sa.fq = w.u2_q;
   sa.fs = (const half_t*)w.u2_s;
   sa.spart = spart;
   sa.ures = ures;
+  const int split = down_split(dm, T, cols);
   sa.T = T;
   sa.d = dm.d;
   sa.q = dm.q;
@@ -714,13 +830,22 @@ hipError_t launch_skinny_down(const cmoe_dims& dm, const cmoe_weights& w, const 
   sa.n_parts = n_parts;
   sa.n_jobs = T * ((dm.d + 2047) / 2048);
   sa.n_side = (sa.n_jobs + 7) & ~7;
-  return launch_stream<SIDE_URES>(dm, cols, a, nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted, T, w_blk, sa, st);
+  return launch_stream<SIDE_URES, false>(dm, cols, a, nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted,
+                                         split > 1 ? parts : nullptr, split, T, w_blk, sa,
+                                         FewSortArgs{}, st);
 }
 
-hipError_t launch_skinny_add(const cmoe_dims& dm, const half_t* y_base_sorted, const float* ures, const int* perm,
-                             int T, half_t* y, hipStream_t st) {
-  hipLaunchKernelGGL(skinny_add_kernel, dim3(T, (dm.d / 8 + 255) / 256), dim3(256), 0, st, y_base_sorted, ures, perm,
-                     dm.d, y);
+hipError_t launch_skinny_add(const cmoe_dims& dm, const half_t* y_base_sorted, const float* parts, const float* ures,
+                             const int* inv_perm, int T, half_t* y, hipStream_t st) {
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(T, (dm.d / 4 + 255) / 256), dim3(256), 0, st, y_base_sorted, parts, ures, inv_perm, T,
+                       dm.d, y);
+  };
+  switch (down_split(dm, T, stream_cols(dm, T, true))) {
+    case 1: go(skinny_add_kernel<1>); break;
+    case 2: go(skinny_add_kernel<2>); break;
+    default: go(skinny_add_kernel<4>); break;
+  }
   return hipGetLastError();
 }
 

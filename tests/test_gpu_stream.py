@@ -30,6 +30,22 @@ def test_wide_weight_streams_beyond_the_caches():
     _check(ci.small_config("far", T=200, d=2048, d_ff=2048, G=13, K=4, r=8, k=2, q=32, seed=213), 0.0)
 
 
+# parts of the down-projection's contraction: 4, 2 and 1 of 32, 17 and 15 steps, uneven shares; as many parts as the
+# scratch space holds to the byte (40 tokens), one token more; the largest launch that is split, the next one
+@pytest.mark.parametrize("d,d_ff,G,T", [(256, 2048, 2, 1), (256, 1088, 2, 3), (256, 960, 2, 3), (512, 2048, 1, 40),
+                                        (512, 2048, 1, 41), (192, 2112, 4, 7), (3072, 1024, 1, 1), (3136, 1024, 1, 1)])
+def test_parts_of_the_contraction(d, d_ff, G, T):
+    _check(ci.small_config("parts", T=T, d=d, d_ff=d_ff, G=G, K=4, r=8, k=2, q=32, seed=T + G), 0.0)
+
+
+# residual terms: groups of experts whose rank rows fill 1 to 64 lanes; routers of 16 rows (all logits at once), of 17
+@pytest.mark.parametrize("G,K,r,k", [(2, 8, 4, 1), (2, 8, 4, 3), (2, 8, 4, 8), (2, 8, 8, 1), (2, 8, 8, 5), (2, 8, 16, 1),
+                                     (2, 8, 16, 3), (2, 8, 16, 8), (2, 8, 32, 1), (2, 8, 32, 3), (2, 7, 8, 2),
+                                     (1, 16, 8, 2), (1, 15, 16, 8), (8, 1, 32, 1)])
+def test_groups_of_experts(G, K, r, k):
+    _check(ci.small_config("groups", T=5, d=128, d_ff=2112, G=G, K=K, r=r, k=k, q=32, seed=r + k), 0.0)
+
+
 def _check(cfg, skew):
     import torch
 
@@ -47,6 +63,8 @@ def _check(cfg, skew):
         torch.cuda.synchronize()
         for n in ("cluster_id", "expert_idx", "perm", "offsets"):
             assert np.array_equal(out[n].cpu().numpy(), ref[n]), n
+        inv = out["inv_perm"].cpu().numpy()
+        assert np.array_equal(inv[ref["perm"]], np.arange(T)), "inv_perm"
         m = orc.error_metrics(out["y"].cpu().numpy(), ref["y"])   # the layer's bars (FP16 operands and results)
         assert m["max_over_rms"] <= 1e-2 and m["mean_rel"] <= 2e-3, m
         layer.close()
