@@ -86,8 +86,11 @@ extern "C" int cmoe_destroy(cmoe_handle* h) {
 // SKINNY_T tokens, matrix cores above) lay the buffer out differently, so a buffer "for up to
 // T_max tokens" must hold the larger of the two: each layout grows with T inside its own
 // range, hence the largest weight-streaming layout is that of min(T_max, SKINNY_T).
+// Above SKINNY_T the size stated also holds parts of the down-projection's contraction (ffn_impl); a call that
+// brings no more than its layout goes without.
+constexpr size_t SPLIT_BYTES = sizeof(float) * GEMM_PARTS * GEMM_PART + sizeof(int) * GEMM_PARTS;
 static size_t workspace_for_up_to(const cmoe_dims& dm, int T_max) {
-  const size_t big = cmoe_layout(dm, T_max).total;
+  const size_t big = T_max > SKINNY_T ? align_up(cmoe_layout(dm, T_max).total, 256) + SPLIT_BYTES : 0;
   const size_t small = cmoe_layout(dm, T_max < SKINNY_T ? T_max : SKINNY_T).total;
   return big > small ? big : small;
 }
@@ -317,7 +320,7 @@ static int ffn_impl(cmoe_handle* h, const cmoe_weights* w, const cmoe_f16* x, in
     CMOE_LAUNCH(TS_GEMM1_BASE, launch_skinny_hb(dm, *w, (const half_t*)x, x_div, T, nullptr, const_cast<int32_t*>(perm),
                                                 nullptr, const_cast<int32_t*>(offsets), expert_idx, t1ext, a, st));
     CMOE_LAUNCH(TS_RESID_UP, launch_skinny_resid_up(dm, *w, T, perm, nullptr, expert_idx, gate, t1ext, a, spart, st));
-    CMOE_LAUNCH(TS_SREDUCE, launch_sreduce(dm, T, perm, spart, n_parts, s_down, st));
+    CMOE_LAUNCH(TS_SREDUCE, launch_sreduce(dm, T, perm, spart, n_parts, s_down, nullptr, st));
     CMOE_LAUNCH(TS_GEMM2, launch_skinny_down(dm, *w, a, T, offsets, (half_t*)y_base_sorted, nullptr, nullptr, nullptr, nullptr, 0,
                                              nullptr, st));
     return CMOE_OK;
@@ -337,10 +340,14 @@ static int ffn_impl(cmoe_handle* h, const cmoe_weights* w, const cmoe_f16* x, in
   CMOE_LAUNCH(TS_T1, launch_t1(dm, (const half_t*)x, x_div, T, rperm, offsets, expert_idx, v1cat, t1ext, st));
   CMOE_LAUNCH(TS_GEMM1, launch_gemm1(dm, *w, (const half_t*)x, x_div, T, rperm, offsets, expert_idx, gate, u1t, v2p,
                                      t1ext, a, spart, st));
-  CMOE_LAUNCH(TS_SREDUCE, launch_sreduce(dm, T, rperm, spart, (dm.d_ff + G1_BN - 1) / G1_BN, s_down, st));
+  // space for parts of the contraction behind the layout, when the caller has brought it
+  const size_t split_at = align_up(L.total, 256);
+  float* parts = fuse && workspace_bytes >= split_at + SPLIT_BYTES ? (float*)(ws + split_at) : nullptr;
+  int* arrivals = parts != nullptr ? (int*)(parts + (size_t)GEMM_PARTS * GEMM_PART) : nullptr;
+  CMOE_LAUNCH(TS_SREDUCE, launch_sreduce(dm, T, rperm, spart, (dm.d_ff + G1_BN - 1) / G1_BN, s_down, arrivals, st));
   if (fuse) {
     CMOE_LAUNCH(TS_GEMM2, launch_gemm2_combine(dm, *w, a, T, offsets, rperm, u2t, s_down, expert_idx, gate,
-                                               (half_t*)y_fused, st));
+                                               (half_t*)y_fused, parts, arrivals, st));
     *fused = true;
     return CMOE_OK;
   }
@@ -435,8 +442,10 @@ extern "C" int cmoe_forward_multi(cmoe_handle* h, const cmoe_weights* w, const c
     return CMOE_ERR_INVALID_ARG;
   const int g1 = opt->top_g, Tv = T * g1;
   if (workspace == nullptr || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return CMOE_ERR_WORKSPACE;
-  const size_t base_bytes = align_up(cmoe_layout(h->dm, Tv).total, 256), rb = rep_bytes(h->dm, (size_t)Tv);
+  size_t base_bytes = align_up(cmoe_layout(h->dm, Tv).total, 256);
+  const size_t rb = rep_bytes(h->dm, (size_t)Tv), more = Tv > SKINNY_T ? align_up(SPLIT_BYTES, 256) : 0;
   if (workspace_bytes < base_bytes + rb) return CMOE_ERR_WORKSPACE;
+  if (workspace_bytes >= base_bytes + more + rb) base_bytes += more;
   hipStream_t st = (hipStream_t)stream;
   const cmoe_dims& dm = h->dm;
   char* ws = (char*)workspace;

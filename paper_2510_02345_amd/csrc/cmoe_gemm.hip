@@ -63,6 +63,10 @@ struct GemmArgs {
   // rows_each != 0: every group has that many rows (offsets is not read) and row p of group c reads
   // row p - c * rows_each of X, which all groups share
   int rows_each;
+  // scratch for parts of the contraction (gemm_kernel), NULL: none.  [GEMM_PARTS] tiles of accumulators, and as
+  // many arrival counts, zero before the launch
+  float4v* parts;
+  int* arrivals;
 };
 
 struct TileCtx {
@@ -76,10 +80,14 @@ struct TileSrc {
   int c, n0, m0, m_end;
   int k_lo, KT;           // first 32-element block and number of blocks
   long kstep_w, kstep_x;
-  __device__ __forceinline__ TileSrc(const GemmArgs& g_, int c_, int n0_, int m0_, int m_end_)
+  // s, split: part s of 2^split of the contraction
+  __device__ __forceinline__ TileSrc(const GemmArgs& g_, int c_, int n0_, int m0_, int m_end_, int s = 0, int split = 0)
       : g(g_), c(c_), n0(n0_), m0(m0_), m_end(m_end_) {
     k_lo = g.krange ? g.krange[2 * c] / 32 : 0;
     KT = (g.krange ? g.krange[2 * c + 1] : g.Kc) / 32;
+    const int from = (s * KT) >> split;
+    KT = (((s + 1) * KT) >> split) - from;
+    k_lo += from;
     kstep_w = g.kstep_w ? g.kstep_w : 32;
     kstep_x = g.kstep_x ? g.kstep_x : 32;
   }
@@ -208,9 +216,11 @@ __device__ __forceinline__ void tile_big(const GemmArgs& g, const Epi& epi, char
 // of the next stage are read while the matrix cores work on the current one.  Measured on
 // 128 x 128 (204 workgroups, contraction 3072): 32 us, of which 0.42 us per 64 elements; with one
 // set of eight wavefronts of 64 x 32 in ping-pong 40 us.
+// With split > 0 the workgroup computes part s of 2^split of the contraction, and the last to arrive of the parts
+// (number `first` on of g.parts) adds them, in their order, and runs the epilogue; nobody waits.
 template <class TL, class Epi>
 __device__ __forceinline__ void tile_small(const GemmArgs& g, const Epi& epi, char* smem, int c, int n_tile, int n0, int m0,
-                                           int m_end) {
+                                           int m_end, int s = 0, int split = 0, int first = 0) {
   constexpr int NSTG = TL::NS / 2, HALF = TL::STAGE_BYTES, STAGE = 2 * HALF;
   constexpr int PIECES = (TL::BN + TL::BM) / 16, PER = PIECES / 4;   // 16-row pieces of a block, per wavefront of a set
   constexpr int NA = TL::NA, NB = 4;   // 16-row and 16-token blocks of a wavefront in the main loop
@@ -219,7 +229,7 @@ __device__ __forceinline__ void tile_small(const GemmArgs& g, const Epi& epi, ch
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int set = wave >> 2, w4 = wave & 3, wn = w4 % TL::WAVES_N, wmh = w4 / TL::WAVES_N;
-  const TileSrc src(g, c, n0, m0, m_end);
+  const TileSrc src(g, c, n0, m0, m_end, s, split);
   const unsigned smem_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)smem;
   const int KT = src.KT, steps = (KT + 1) / 2;   // an odd last block is set 0's; set 1 loads it too and ignores it
   const half_t* gsrc[PER];
@@ -306,6 +316,47 @@ __device__ __forceinline__ void tile_small(const GemmArgs& g, const Epi& epi, ch
       for (int b = 0; b < 2; ++b) out[a][b] += recv[(a * 2 + b) * 64];
   }
   __syncthreads();   // the epilogue may use the space
+  if constexpr (Epi::SPLITS && TL::BN * TL::BM == GEMM_PART) {
+    if (split > 0) {
+      // The parts go through memory that all CUs see: stores and loads at device scope, completed before the
+      // arrival is counted.  (With ordinary stores and a fence every workgroup writes back its whole L2.)
+      constexpr int PART = GEMM_PART / 2;   // pairs of values
+      typedef unsigned long long u64;
+      u64* mine = (u64*)g.parts + (size_t)(first + s) * PART + tid;
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const u64* v = (const u64*)&out[a][b];
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            __hip_atomic_store(mine + ((a * 2 + b) * 2 + h) * TL::NT, v[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      wait_vm<0>();
+      __syncthreads();
+      int* last = (int*)smem;
+      if (tid == 0)
+        *last = __hip_atomic_fetch_add(g.arrivals + first, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (1 << split) - 1;
+      __syncthreads();
+      if (!*last) return;
+      const u64* all = (const u64*)g.parts + (size_t)first * PART + tid;
+      for (int i = 0; i < 1 << split; ++i) {
+        u64 v[NA * 4];
+#pragma unroll
+        for (int n = 0; n < NA * 4; ++n)
+          v[n] = __hip_atomic_load(all + (size_t)i * PART + n * TL::NT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int n = 0; n < NA * 4; ++n) {
+          float4v& o = out[n / 4][n / 2 % 2];
+          const int h = n % 2 * 2;
+          const float lo = __uint_as_float((unsigned)v[n]), hi = __uint_as_float((unsigned)(v[n] >> 32));
+          o[h] = i == 0 ? lo : o[h] + lo;
+          o[h + 1] = i == 0 ? hi : o[h + 1] + hi;
+        }
+      }
+      __syncthreads();   // *last has been read
+    }
+  }
   TileCtx ctx{c, n_tile, n0, m0, m_end, wn, wmh * 2 + set, lane, tid, (half_t*)smem};
   epi.template run<TL>(ctx, out);
 }
@@ -320,7 +371,15 @@ __device__ __forceinline__ void tile_small(const GemmArgs& g, const Epi& epi, ch
 // tile's time), which is also how a launch with few tiles fills the machine.  Up-projection of
 // 777 tokens (64 tiles, contraction 1024): 50 -> 29 us in 220 quarters; 16384 tokens with Zipf
 // loads (132 tiles per XCD): 282 -> 250 us, its down-projection (33 tiles) 190 -> 168 us.
+// Where the quarters of the leftover still leave CUs idle, the down-projection also cuts their contraction, into as many
+// parts as there are CUs (and 8 blocks of it in a part): one more exchange of the sums, through memory,
+// costs about 8 us (with ordinary stores and a device fence in each workgroup 30), a step of 64 elements takes 0.42.
+// 4 clusters of 1024 x 4096: 777 tokens (2 tiles per XCD) 41 -> 29 us, 1200 (3) 43 -> 35; 2 of 768 x 3072,
+// 300 tokens 30 -> 23; 8 of 2048 x 8192, 300 tokens (8, upper quarters only) 73 -> 63; 16384 Zipf tokens, whole
+// forward 429 -> 422.
 constexpr int XSM = 4, XSN = 8, XCD_CUS = 32;
+constexpr int MAX_SPLIT = 3;   // log2 of the parts of the contraction of a quarter, at most
+static_assert(8 * XCD_CUS == GEMM_PARTS, "a part per CU");
 template <class Epi>
 __global__ __launch_bounds__(512, 1) void gemm_kernel(GemmArgs g, Epi epi) {
   using Quarter = typename Epi::Quarter;
@@ -334,8 +393,18 @@ __global__ __launch_bounds__(512, 1) void gemm_kernel(GemmArgs g, Epi epi) {
   const int lo = (int)((long)tiles * xcd >> 3), mine = (int)((long)tiles * (xcd + 1) >> 3) - lo;
   int full = mine / XCD_CUS * XCD_CUS, cut = 0;   // log2 of the parts a leftover tile is cut into
   if (mine - full > XCD_CUS / 2) full = mine; else cut = mine - full > XCD_CUS / 4 ? 1 : 2;
+  int pieces = cut, split = 0;   // log2 of a leftover tile's pieces and of the parts of the contraction of each
+  if constexpr (Epi::SPLITS) {
+    const int left = mine - full;
+    if (g.parts != nullptr && cut == 2 && left > 0) {
+      // no group with more tokens than a quarter: its lower quarters are empty
+      if (__ballot(rt.hi - rt.lo > Quarter::BM) == 0ull) pieces = TileBig::BN / Quarter::BN == 2 ? 1 : 0;
+      while (split < MAX_SPLIT && left << (pieces + split + 1) <= XCD_CUS && g.Kc / 32 >= 16 << split) ++split;
+    }
+  }
   const bool big = local < full;
-  const int t = big ? lo + local : lo + full + ((local - full) >> cut), part = (local - full) & ((1 << cut) - 1);
+  const int v = local - full, t = big ? lo + local : lo + full + (v >> (pieces + split)),
+            part = (v >> split) & ((1 << pieces) - 1);
   if (t >= lo + mine) return;
   const int per_group = XSM * g.n_tiles, vg = t / per_group, rem = t % per_group;
   const int sm = min(XSM, slots - vg * XSM);                      // row tiles of the super-tile
@@ -354,15 +423,18 @@ __global__ __launch_bounds__(512, 1) void gemm_kernel(GemmArgs g, Epi epi) {
     constexpr int ACROSS = TileBig::BN / Quarter::BN;
     n0 += part % ACROSS * Quarter::BN;
     m0 += part / ACROSS * Quarter::BM;
-    if (n0 < g.N && m0 < m_end) tile_small<Quarter, Epi>(g, epi, smem, c, n_tile, n0, m0, m_end);
+    if (n0 < g.N && m0 < m_end)
+      tile_small<Quarter, Epi>(g, epi, smem, c, n_tile, n0, m0, m_end, v & ((1 << split) - 1), split,
+                                xcd * XCD_CUS + (v & -(1 << split)));
   }
 }
 
 template <class Epi>
 hipError_t launch_gemm(const GemmArgs& g, int T, const Epi& epi, hipStream_t st) {
   const int tiles = ((T + TileBig::BM - 1) / TileBig::BM + g.G) * g.n_tiles;   // at most
-  // a leftover of up to XCD_CUS / 4 tiles per XCD becomes 4 workgroups each, up to XCD_CUS / 2 two
-  hipLaunchKernelGGL((gemm_kernel<Epi>), dim3((unsigned)(8 * ((tiles + 7) / 8 + 3 * XCD_CUS / 4))), dim3(512), 0, st, g, epi);
+  // the leftover tiles of an XCD, one at least, become up to XCD_CUS workgroups
+  const int extra = g.parts != nullptr ? XCD_CUS - 1 : 3 * XCD_CUS / 4;
+  hipLaunchKernelGGL((gemm_kernel<Epi>), dim3((unsigned)(8 * ((tiles + 7) / 8 + extra))), dim3(512), 0, st, g, epi);
   return hipGetLastError();
 }
 
@@ -432,6 +504,7 @@ __global__ __launch_bounds__(256, 3) void gemm_thin_kernel(GemmArgs g, Epi epi) 
 // consecutive outputs of a pair block for its token in one piece.
 template <class OutT>
 struct EpiStoreT {
+  static constexpr bool SPLITS = false;
   using Quarter = TileQuad;
   OutT* out;
   const int* rowmap;  // row p of the tile order is written to out[rowmap[p]] (NULL: identity)
@@ -465,6 +538,7 @@ using EpiStore = EpiStoreT<half_t>;
 // The same in 32-column blocks, out[n / 32][p][n % 32] (rows p in tile order): the layout in which the
 // middle of the backward pass and a further product read whole KiBs.
 struct EpiStoreBlocked {
+  static constexpr bool SPLITS = false;
   using Quarter = TileQuad;
   half_t* out;
   int T, N;
@@ -494,6 +568,7 @@ struct EpiStoreBlocked {
 // token order.  The panel V1cat is stored with the contraction index along its rows, so its
 // fragments are transposing LDS reads.  K*r <= 128.
 struct EpiInputGrad {
+  static constexpr bool SPLITS = false;
   using Quarter = TileQuad;
   const half_t* v1cat;          // [G][KRp][d]
   const int* offe;              // [G K + 1] pair rows of the experts: the panel rows of an expert without any are zero
@@ -592,6 +667,7 @@ struct EpiInputGrad {
 // of a 16-token block needs are skipped), and writes the rows straight to token order, 16
 // bytes per lane.  K*r <= 128.
 struct EpiDownCombine {
+  static constexpr bool SPLITS = true;
   using Quarter = TileQuad;
   const half_t* u2t;     // [G][d][KRp]
   const float* s_down;   // [T][k][r], token order
@@ -687,6 +763,7 @@ struct EpiDownCombine {
 // otherwise they are read from global memory.
 template <int R, int KMAX, bool STAGE>
 struct EpiFusedUp {
+  static constexpr bool SPLITS = false;
   using Quarter = TileSlab;   // one s partial per 256 rows of d_ff whatever the tile
   const half_t* u1t;  // [G][d_ff][KRp]
   const half_t* v2p;  // [G][KRp][d_ff]
@@ -895,12 +972,13 @@ struct EpiFusedUp {
 // s_down[perm[p]][w] = sum over row tiles of spart[tile][p][w], in a fixed order: a block
 // owns 256 consecutive outputs (four per lane, k * r is a multiple of 4 so they belong to one
 // token), its NW wavefronts each sum every NW-th tile, and the NW sums are added in
-// wavefront order.
+// wavefront order.  zero != NULL: the arrival counts of the down-projection that follows are cleared.
 template <int NW, class ST>
 __global__ __launch_bounds__(64 * NW) void sreduce_kernel(const ST* __restrict__ spart,
                                                           const int* __restrict__ perm, int T, int kr, int n_tiles,
-                                                          float* __restrict__ s_down) {
+                                                          float* __restrict__ s_down, int* __restrict__ zero) {
   __shared__ float4v part[NW][64];
+  if (zero != nullptr && blockIdx.x == 0 && threadIdx.x < GEMM_PARTS) zero[threadIdx.x] = 0;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const size_t total = (size_t)T * kr;
   const size_t idx = ((size_t)blockIdx.x * 64 + lane) * 4;
@@ -1047,14 +1125,14 @@ hipError_t launch_gemm1(const cmoe_dims& dm, const cmoe_weights& w, const half_t
 }
 
 hipError_t launch_sreduce(const cmoe_dims& dm, int T, const int* perm, const float* spart, int n_parts,
-                          float* s_down, hipStream_t st) {
+                          float* s_down, int* zero, hipStream_t st) {
   int kr = dm.k * dm.r;
   size_t n = (size_t)T * kr;
   const dim3 grid((unsigned)((n + 255) / 256));
   if (n_parts > 128)
-    hipLaunchKernelGGL((sreduce_kernel<16, float>), grid, dim3(1024), 0, st, spart, perm, T, kr, n_parts, s_down);
+    hipLaunchKernelGGL((sreduce_kernel<16, float>), grid, dim3(1024), 0, st, spart, perm, T, kr, n_parts, s_down, zero);
   else
-    hipLaunchKernelGGL((sreduce_kernel<4, float>), grid, dim3(256), 0, st, spart, perm, T, kr, n_parts, s_down);
+    hipLaunchKernelGGL((sreduce_kernel<4, float>), grid, dim3(256), 0, st, spart, perm, T, kr, n_parts, s_down, zero);
   return hipGetLastError();
 }
 
@@ -1083,13 +1161,25 @@ hipError_t launch_combine(const cmoe_dims& dm, const half_t* u2t, const half_t* 
 }
 
 // Down-projection with the residual of the second matrix and the return to token order
-// fused into its epilogue (K*r <= 128).  rperm: token of each row of A.
+// fused into its epilogue (K*r <= 128).  rperm: token of each row of A.  parts, arrivals: scratch for parts of the
+// contraction (GEMM_PARTS of GEMM_PART values; counts, zero), NULL: not split.
 hipError_t launch_gemm2_combine(const cmoe_dims& dm, const cmoe_weights& w, const half_t* a, int T,
                                 const int* offsets, const int* rperm, const half_t* u2t, const float* s_down,
-                                const int* expert_idx, const float* gate, half_t* y, hipStream_t st) {
+                                const int* expert_idx, const float* gate, half_t* y, float* parts, int* arrivals,
+                                hipStream_t st) {
   GemmArgs g{(const half_t*)w.w2_base, (long)dm.d * dm.d_ff, dm.d_ff, dm.d, a, 32, nullptr, dm.d_ff, offsets,
              dm.G, (dm.d + TileBig::BN - 1) / TileBig::BN};
   g.kstep_x = (long)T * 32;
+  // an XCD can be left with few enough tiles to split: four, or eight of groups that hold no more than a quarter's
+  // tokens (a launch prepared for it has more workgroups, which cost 0.7 us where they find nothing to do)
+  const int least = ((T + TileBig::BM - 1) / TileBig::BM) * g.n_tiles, most = least + dm.G * g.n_tiles;
+  const int few = XCD_CUS / (T <= TileQuad::BM * dm.G ? 4 : 8);
+  bool can = false;
+  for (int mine = least / 8; mine <= (most + 7) / 8 && !can; ++mine) can = mine % XCD_CUS >= 1 && mine % XCD_CUS <= few;
+  if (can) {
+    g.parts = (float4v*)parts;
+    g.arrivals = arrivals;
+  }
   use_packed_base(g, dm, w, true);
   EpiDownCombine epi{u2t, s_down, rperm, expert_idx, gate, y, dm.k, dm.K, dm.r, dm.KRp, dm.d};
   return launch_gemm(g, T, epi, st);

@@ -53,6 +53,9 @@ struct cmoe_handle {
 };
 
 // Workspace layout for T tokens (byte offsets, all 256-byte aligned).
+// Parts of the contraction of the matrix-core down-projection: at most one per CU, each a tile of FP32 sums.
+constexpr int GEMM_PARTS = 256, GEMM_PART = 128 * 128;
+
 struct cmoe_ws_layout {
   size_t blk_counts;  // int32 [n_blocks + 1][64 G] permute: per-block counts of (cluster, pair key)
   size_t sort_i32;    // int32 [2][T]          expert-pair order inside clusters: rowmap, perm2
@@ -139,7 +142,7 @@ hipError_t launch_gemm1(const cmoe_dims& dm, const cmoe_weights& w, const half_t
                         const int* offsets, const int* expert_idx, const float* gate, const half_t* u1t,
                         const half_t* v2p, const half_t* t1ext, half_t* a, float* spart, hipStream_t st);
 hipError_t launch_sreduce(const cmoe_dims& dm, int T, const int* perm, const float* spart, int n_parts,
-                          float* s_down, hipStream_t st);
+                          float* s_down, int* zero, hipStream_t st);
 hipError_t launch_skinny_hb(const cmoe_dims& dm, const cmoe_weights& w, const half_t* x, int x_div, int T,
                             const int* cluster_id, int* perm, int* inv_perm, int* offsets, const int* expert_idx,
                             half_t* t1, half_t* hb, hipStream_t st);
@@ -170,7 +173,8 @@ hipError_t launch_gemm2(const cmoe_dims& dm, const cmoe_weights& w, const half_t
                         const int* rowmap, half_t* y_base_sorted, hipStream_t st);
 hipError_t launch_gemm2_combine(const cmoe_dims& dm, const cmoe_weights& w, const half_t* a, int T,
                                 const int* offsets, const int* rperm, const half_t* u2t, const float* s_down,
-                                const int* expert_idx, const float* gate, half_t* y, hipStream_t st);
+                                const int* expert_idx, const float* gate, half_t* y, float* parts, int* arrivals,
+                                hipStream_t st);
 hipError_t launch_combine(const cmoe_dims& dm, const half_t* u2t, const half_t* y_base_sorted, const float* s_down,
                           const int* perm, const int* offsets, const int* expert_idx, const float* gate, int T,
                           half_t* y, hipStream_t st);

@@ -23,7 +23,18 @@ def test_down_projection_tiles(T):
     _check(ci.small_config("tiles2", T=T, d=1088, d_ff=192, G=2, K=4, r=8, k=2, q=32, seed=T))
 
 
-def _check(cfg):
+# parts of its contraction: one or two tiles per XCD in quarters of up to eight parts (66 and 16 steps, the latter with
+# uneven loads), groups that fill only the upper quarters, up to four and more tiles per XCD, one after a full round;
+# and the same calls with a workspace that holds no parts
+@pytest.mark.parametrize("T,G,d_ff", [(300, 2, 2112), (400, 4, 1024), (500, 4, 2112), (1000, 8, 1088), (1400, 2, 2112),
+                                      (2000, 3, 1024), (13000, 1, 512)])
+def test_down_projection_parts(T, G, d_ff):
+    cfg = ci.small_config("parts", T=T, d=1088, d_ff=d_ff, G=G, K=4, r=8, k=2, q=32, seed=T)
+    _check(cfg)
+    _check(cfg, drop=4 * 256 * 128 * 128 + 4 * 256)
+
+
+def _check(cfg, drop=0):
     import torch
 
     import paper_2510_02345_amd as cm
@@ -31,6 +42,7 @@ def _check(cfg):
     w = ci.generate(cfg)
     ref = orc.forward_naive(w, w["x"], cfg.K, cfg.k, cfg.q)
     layer = cm.Layer(cfg.d, cfg.d_ff, cfg.G, cfg.K, cfg.r, cfg.k, cfg.q, w, cfg.T)
+    layer.ws = layer.ws[:layer.ws.numel() - drop]
     out = layer.forward(torch.from_numpy(w["x"]).to("cuda:0"))
     torch.cuda.synchronize()
     m = orc.error_metrics(out["y"].cpu().numpy(), ref["y"])   # the layer's bars (FP16 operands and results)
