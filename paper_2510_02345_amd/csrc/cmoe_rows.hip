@@ -9,8 +9,9 @@ namespace {
 
 // ---------------------------------------------------------------- few tokens
 // With less than a workgroup per CU a launch takes as long as its chain of loads: a workgroup takes
-// only 32 tokens, its four wavefronts split the contraction, and the matrix-core fragments are
-// loaded straight from memory into registers (no LDS staging, no barrier in the loop).  A
+// only 32 tokens, its four wavefronts split the contraction, and there is no barrier in the loop: each has
+// a ring of its own (rows_product_ring), or, for many rows, loads the matrix-core fragments straight from
+// memory into registers.  A
 // 64-element step of a row is one whole 128-byte line: lane (t, q) takes its elements 8 q .. 8 q + 7
 // and 32 + 8 q .. 32 + 8 q + 7, two instructions that each read 64 contiguous bytes of 16 rows.
 constexpr int RW_M = 32, RW_MT = RW_M / 16;   // tokens of a workgroup
@@ -56,6 +57,66 @@ __device__ __forceinline__ void rows_product(const half_t* const (&wr)[NA], cons
           for (int b = 0; b < RW_MT; ++b) acc[a][b] = mfma32(fw[u & 1][a][s], fx[u][b][s], acc[a][b]);
       if (it + u + RW_AHEAD < it1) load_x(fx[u], it + u + RW_AHEAD);
     }
+  }
+}
+
+// The same for up to 80 weight rows, with both operands global -> LDS by direct loads of whole lines, NS - 1 steps ahead, in a ring of the
+// wavefront's own (no barrier).  row_of(i): source row i of the tile (NA * 16 weight rows, then the 32 tokens).
+// Loads straight into registers read half lines, twice as many requests.  Router of 20 rows of width 1024, 777 tokens
+// 7.0 -> 5.7 us, 72 rows of width 2048, 4000 tokens 16.8 -> 12.2.
+template <int NA>
+struct RowsRing {
+  static constexpr int ROWS = NA * 16 + RW_M, STAGE = ROWS * 128, DMA = ROWS / 8;
+  static constexpr int NS = 36 * 1024 / STAGE;   // of the four wavefronts: one workgroup per CU
+  static constexpr int SMEM = RW_WAVES * NS * STAGE;
+};
+template <int NA, class RowF>
+__device__ __forceinline__ void rows_product_ring(char* ring, int lane, RowF row_of, int it0, int it1,
+                                                  float4v (&acc)[NA][RW_MT]) {
+  using RR = RowsRing<NA>;
+  static_assert(RR::NS >= 2 && (RR::NS - 1) * RR::DMA < 64, "loads in flight");
+  if (it0 >= it1) return;
+  const unsigned base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)ring;
+  const int t16 = lane & 15, q = lane >> 4;
+  const half_t* src[RR::DMA];
+#pragma unroll
+  for (int i = 0; i < RR::DMA; ++i) {
+    const int row = i * 8 + (lane >> 3);
+    src[i] = row_of(row) + (((lane & 7) ^ ((row >> 1) & 7)) << 3);
+  }
+  auto issue = [&](int it, int stage) {
+#pragma unroll
+    for (int i = 0; i < RR::DMA; ++i) dma16(src[i] + (size_t)it * 64, base + stage * RR::STAGE + i * 1024);
+  };
+  const int sw = (t16 >> 1) & 7;   // tile rows of a fragment start at multiples of 16
+#pragma unroll
+  for (int i = 0; i < RR::NS - 1; ++i)
+    if (it0 + i < it1) issue(it0 + i, i);
+  int rd = 0, wr = RR::NS - 1;
+  for (int it = it0; it < it1; ++it) {
+    if (it + RR::NS - 1 < it1) {
+      wait_lds();   // the stage refilled was read in step it - 1
+      issue(it + RR::NS - 1, wr);
+      wait_vm<(RR::NS - 1) * RR::DMA>();
+    } else {
+      wait_vm<0>();   // the last steps have all been issued
+    }
+    const char* sb = ring + rd * RR::STAGE + t16 * 128;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int ch = ((4 * s + q) ^ sw) << 4;
+      half8 fb[RW_MT];
+#pragma unroll
+      for (int b = 0; b < RW_MT; ++b) fb[b] = *(const half8*)(sb + (NA + b) * 16 * 128 + ch);
+#pragma unroll
+      for (int a = 0; a < NA; ++a) {
+        const half8 fa = *(const half8*)(sb + a * 16 * 128 + ch);
+#pragma unroll
+        for (int b = 0; b < RW_MT; ++b) acc[a][b] = mfma32(fa, fb[b], acc[a][b]);
+      }
+    }
+    rd = rd + 1 == RR::NS ? 0 : rd + 1;
+    wr = wr + 1 == RR::NS ? 0 : wr + 1;
   }
 }
 
@@ -247,7 +308,11 @@ __device__ __forceinline__ const half_t* router_row(const RouteRowsArgs& a, int 
 // 8 lanes take the token's decision.
 template <int NA, bool MULTI>
 __global__ __launch_bounds__(RW_THREADS) void route_rows_kernel(RouteRowsArgs a) {
-  __shared__ float4v red[RW_WAVES * NA * RW_MT * 64];
+  constexpr bool RING = NA <= 5;
+  constexpr int RED = RW_WAVES * NA * RW_MT * 64 * 16;
+  __shared__ __attribute__((aligned(1024))) char smem[RING && RowsRing<RING ? NA : 1>::SMEM > RED
+                                                          ? RowsRing<RING ? NA : 1>::SMEM : RED];
+  float4v* red = (float4v*)smem;
   constexpr int LD = NA * 16 + 4;
   __shared__ float lg[RW_M][LD];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -263,8 +328,17 @@ __global__ __launch_bounds__(RW_THREADS) void route_rows_kernel(RouteRowsArgs a)
   for (int i = 0; i < NA; ++i)
 #pragma unroll
     for (int b = 0; b < RW_MT; ++b) acc[i][b] = float4v{0.f, 0.f, 0.f, 0.f};
-  const int steps = a.d / 64;
-  rows_product<NA>(wr, xr, wave * steps / RW_WAVES, (wave + 1) * steps / RW_WAVES, acc);
+  const int steps = a.d / 64, it0 = wave * steps / RW_WAVES, it1 = (wave + 1) * steps / RW_WAVES;
+  if constexpr (RING) {
+    rows_product_ring<NA>(smem + wave * RowsRing<NA>::NS * RowsRing<NA>::STAGE, lane,
+                          [&](int row) {
+                            return row < NA * 16 ? router_row(a, row) : a.x + (size_t)min(m0 + row - NA * 16, a.T - 1) * a.d;
+                          },
+                          it0, it1, acc);
+    __syncthreads();   // the rings have been read
+  } else {
+    rows_product<NA>(wr, xr, it0, it1, acc);
+  }
   rows_reduce<NA>(red, wave, lane, acc,
                   [&](int i, int b, const float4v& s) { *(float4v*)&lg[b * 16 + t16][i * 16 + 4 * q] = s; });
   __syncthreads();
@@ -300,7 +374,7 @@ __global__ __launch_bounds__(RW_THREADS, 2) void route_rows_lds_kernel(RouteRows
 // Up to this many tokens the 32-token workgroups with their split contraction are taken: fewer than
 // one workgroup per CU, and what counts is the chain of steps.  Few router rows, us of the 32- and
 // of the 64-token form: 10 rows of width 2048 9.6 and 11.5 at 8192 tokens, of width 4096 15.9
-// and 16.8; 20 rows of width 1024 7.7 and 9.3.  Above the line the loads count: 16384 tokens, 20 rows
+// and 16.8; 20 rows of width 1024 7.7 and 9.3 (all before the rings, which take 7.0 for the last).  Above the line the loads count: 16384 tokens, 20 rows
 // of width 1024 11.1 and 9.6, 72 rows of width 2048 33 and 16, of width 8192 101 and 48.  (One
 // 128-row matrix-core tile against 128 tokens took 30 at 32768 tokens and 72 rows of width 2048,
 // the 64-token form 27.)
@@ -345,11 +419,12 @@ __device__ __forceinline__ unsigned wave_or(unsigned v) {
   for (int off = 1; off < 64; off <<= 1) v |= (unsigned)__shfl_xor((int)v, off, 64);
   return __builtin_amdgcn_readfirstlane(v);
 }
-// Takes up to T1_NA blocks out of `need`; entries past their number repeat the first.
-__device__ __forceinline__ int take_blocks(unsigned& need, int (&blk)[T1_NA]) {
+// Takes up to N blocks out of `need`; entries past their number repeat the first.
+template <int N>
+__device__ __forceinline__ int take_blocks(unsigned& need, int (&blk)[N]) {
   int n = 0;
 #pragma unroll
-  for (int i = 0; i < T1_NA; ++i) {
+  for (int i = 0; i < N; ++i) {
     blk[i] = need ? __builtin_ctz(need) : blk[0];
     if (need) ++n, need &= need - 1u;
   }
@@ -418,6 +493,66 @@ __global__ __launch_bounds__(RW_THREADS, 2) void t1_rows_kernel(T1Src s0, T1Src 
   }
 }
 
+// The same for few tokens: 32 per workgroup, a quarter of the contraction per wavefront, which halves the bytes
+// that a CU has to fetch (about 25 GB/s here, however many loads are in flight: more stages in the kernel
+// above are slower) and quarters the chain of steps.  777 tokens of 4 clusters of width 1024 9.2 -> 7.4 us,
+// 4096 of 2 of width 768 7.8 -> 6.3, 4000 of 8 of width 2048 21.3 -> 17.7.
+constexpr int TS_NA = 4;
+__global__ __launch_bounds__(RW_THREADS) void t1_rows_split_kernel(T1Src s0, T1Src s1, int x_div,
+                                                                       const int* __restrict__ perm,
+                                                                       const int* __restrict__ offsets,
+                                                                       const int* __restrict__ expert_idx,
+                                                                       int d, int G, int K, int k, int r, int KRp) {
+  const half_t *x = blockIdx.y ? s1.x : s0.x, *v1cat = blockIdx.y ? s1.v1cat : s0.v1cat;
+  half_t* t1 = blockIdx.y ? s1.t1 : s0.t1;
+  constexpr int R2 = RowsRing<2>::SMEM, R4 = RowsRing<TS_NA>::SMEM;
+  __shared__ __attribute__((aligned(1024))) char smem[R2 > R4 ? R2 : R4];
+  __shared__ int es[RW_M][8];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t16 = lane & 15, q = lane >> 4;
+  int c, m0, m_end;
+  if (!find_tile(offsets, G, RW_M, blockIdx.x, c, m0, m_end)) return;
+  const int tok = perm[min(m0 + (lane & (RW_M - 1)), m_end - 1)];
+  unsigned need = 0u;
+  for (int j = 0; j < k; ++j) {
+    const int e0 = min(max(expert_idx[(size_t)tok * k + j] - c * K, 0), K - 1) * r;
+    if (tid < RW_M) es[tid][j] = e0;
+    need |= block_mask(e0, r);
+  }
+  need = wave_or(need);
+  const half_t* vc = v1cat + (size_t)c * KRp * d;
+  const int steps = d / 64, it0 = wave * steps / RW_WAVES, it1 = (wave + 1) * steps / RW_WAVES;
+  while (need != 0u) {
+    int blk[TS_NA];
+    const int n = take_blocks(need, blk);
+    unsigned order = 0u;   // the blocks' numbers, eight bits each
+#pragma unroll
+    for (int i = 0; i < TS_NA; ++i) order |= (unsigned)blk[i] << (8 * i);
+    auto pass = [&](auto na) {
+      constexpr int NA = decltype(na)::value;
+      float4v acc[NA][RW_MT];
+#pragma unroll
+      for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int b = 0; b < RW_MT; ++b) acc[i][b] = float4v{0.f, 0.f, 0.f, 0.f};
+      rows_product_ring<NA>(smem + wave * RowsRing<NA>::NS * RowsRing<NA>::STAGE, lane,
+                            [&](int row) {
+                              const int src = __shfl(tok, (row - NA * 16) & (RW_M - 1), 64) / x_div;
+                              return row < NA * 16 ? vc + ((size_t)((order >> (8 * (row >> 4))) & 255) * 16 + (row & 15)) * d
+                                                   : x + (size_t)src * d;
+                            },
+                            it0, it1, acc);
+      __syncthreads();   // es is complete, the rings have been read
+      rows_reduce<NA>((float4v*)smem, wave, lane, acc, [&](int i, int b, const float4v& s) {
+        const int m = b * 16 + t16, p = m0 + m;
+        if (i < n && p < m_end) t1_store(t1, p, (int)((order >> (8 * i)) & 255) * 16 + 4 * q, es[m], k, r, s);
+      });
+      __syncthreads();   // the sums have been read
+    };
+    if (n <= 2) pass(std::integral_constant<int, 2>{}); else pass(std::integral_constant<int, TS_NA>{});
+  }
+}
+
 }  // namespace
 
 // Router for more than SKINNY_T tokens and at most 128 router rows (G + G*K).
@@ -436,19 +571,28 @@ hipError_t launch_route_multi_rows(const cmoe_dims& dm, const cmoe_weights& w, c
   return go_route<true>(a, st);
 }
 
+// The form for few tokens takes a CU's whole LDS: while its launch is at most a workgroup per CU, what counts is
+// the chain of steps.  Above, us of the 64- and the 32-token form: 8192 tokens of 4 clusters of width 1024 (260
+// workgroups) 9.7 and 11.9, 11000 of 2 of width 768 8.2 and 11.5.
+static hipError_t go_t1(const cmoe_dims& dm, int T, int n, T1Src s0, T1Src s1, int x_div, const int* perm, const int* offsets,
+                        const int* expert_idx, hipStream_t st) {
+  auto go = [&](auto kern, int m) {
+    hipLaunchKernelGGL(kern, dim3((T + m - 1) / m + dm.G, n), dim3(RW_THREADS), 0, st, s0, s1, x_div > 1 ? x_div : 1, perm,
+                       offsets, expert_idx, dm.d, dm.G, dm.K, dm.k, dm.r, dm.KRp);
+  };
+  if (((T + RW_M - 1) / RW_M + dm.G) * n > 256) go(t1_rows_kernel, RL_M); else go(t1_rows_split_kernel, RW_M);
+  return hipGetLastError();
+}
+
 hipError_t launch_t1(const cmoe_dims& dm, const half_t* x, int x_div, int T, const int* perm, const int* offsets,
                      const int* expert_idx, const half_t* v1cat, half_t* t1, hipStream_t st) {
   const T1Src s{x, v1cat, t1};
-  hipLaunchKernelGGL(t1_rows_kernel, dim3((T + RL_M - 1) / RL_M + dm.G), dim3(RW_THREADS), 0, st, s, s, x_div > 1 ? x_div : 1,
-                     perm, offsets, expert_idx, dm.d, dm.G, dm.K, dm.k, dm.r, dm.KRp);
-  return hipGetLastError();
+  return go_t1(dm, T, 1, s, s, x_div, perm, offsets, expert_idx, st);
 }
 
 // Two such products of the same tokens and experts in one launch.
 hipError_t launch_t1_pair(const cmoe_dims& dm, int T, const int* perm, const int* offsets, const int* expert_idx,
                           const half_t* x0, const half_t* v0, half_t* t0, const half_t* x1, const half_t* v1, half_t* t1,
                           hipStream_t st) {
-  hipLaunchKernelGGL(t1_rows_kernel, dim3((T + RL_M - 1) / RL_M + dm.G, 2), dim3(RW_THREADS), 0, st, T1Src{x0, v0, t0},
-                     T1Src{x1, v1, t1}, 1, perm, offsets, expert_idx, dm.d, dm.G, dm.K, dm.k, dm.r, dm.KRp);
-  return hipGetLastError();
+  return go_t1(dm, T, 2, T1Src{x0, v0, t0}, T1Src{x1, v1, t1}, 1, perm, offsets, expert_idx, st);
 }

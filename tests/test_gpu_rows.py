@@ -36,10 +36,22 @@ def test_router_rows(T, G, K, k, d):
 # that hold one to 64 tokens
 @pytest.mark.parametrize("T,K,r,k", [(257, 2, 16, 2), (600, 8, 8, 1), (900, 8, 16, 4), (1300, 16, 32, 3), (321, 32, 16, 8)])
 def test_rank_rows_of_selected_experts(T, K, r, k):
+    _check_rank_rows(T, 128, K, r, k)
+
+
+# uneven shares of the contraction, rings that go round, and both sides of the line between the forms of 32 and
+# of 64 tokens (256 workgroups of the former, three clusters)
+@pytest.mark.parametrize("T,d,K,r,k", [(300, 832, 4, 16, 2), (300, 832, 32, 16, 8), (700, 2048, 8, 16, 2),
+                                       (8096, 192, 8, 8, 2), (8097, 192, 8, 8, 2)])
+def test_rank_rows_of_both_forms(T, d, K, r, k):
+    _check_rank_rows(T, d, K, r, k)
+
+
+def _check_rank_rows(T, d, K, r, k):
     import torch
 
     import paper_2510_02345_amd as cm
-    cfg = ci.small_config("t1", T=T, d=128, d_ff=64, G=3, K=K, r=r, k=k, q=8, factor_std=0.2, seed=T)
+    cfg = ci.small_config("t1", T=T, d=d, d_ff=64, G=3, K=K, r=r, k=k, q=8, factor_std=0.2, seed=T)
     print(f"case {cfg}", flush=True)
     w = ci.generate(cfg)
     ref = orc.forward_naive(w, w["x"], K, k, cfg.q)
