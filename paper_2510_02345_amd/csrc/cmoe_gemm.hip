@@ -566,7 +566,7 @@ struct EpiStoreBlocked {
 // over the cluster's rank rows, V1cat^T qext (qext[m][e_j r + rho] = q_j[rho], as EpiDownCombine does
 // for the second matrix), and the gate path sum_j dl_j v_{e_j} in FP32, and writes FP32 rows in
 // token order.  The panel V1cat is stored with the contraction index along its rows, so its
-// fragments are transposing LDS reads.  K*r <= 128.
+// fragments are transposing LDS reads.  K*r <= 128, k <= 2.
 struct EpiInputGrad {
   static constexpr bool SPLITS = false;
   using Quarter = TileQuad;
@@ -609,7 +609,16 @@ struct EpiInputGrad {
     for (int idx = t.tid; idx < TL::BM * k * r4; idx += TL::NT) {
       const int rho = idx % r4 * 4, j = (idx / r4) % k, m = idx / (r4 * k), p = t.m0 + m;
       if (p >= t.m_end) continue;
-      *(half4*)(sS + m * lds + es[(size_t)p * k + j] * r + rho) = *(const half4*)(q + ((size_t)p * k + j) * r + rho);
+      const int* ep = es + (size_t)p * k;
+      const half_t* qp = q + (size_t)p * k * r + rho;
+      half4 v = *(const half4*)(qp + j * r);
+      // a token that names its expert twice: the sum of both, which both of its pairs write (k <= 2)
+      if (k == 2 && ep[0] == ep[1]) {
+        const half4 o = *(const half4*)(qp + (1 - j) * r);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = (half_t)((float)v[i] + (float)o[i]);
+      }
+      *(half4*)(sS + m * lds + ep[j] * r + rho) = v;
     }
     __syncthreads();
 #pragma unroll

@@ -21,7 +21,7 @@ def _dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
 
 
-def _run(cfg, w=None, dy_scale=1.0, pack=True, drop_canonical=False):
+def _run(cfg, w=None, dy_scale=1.0, pack=True, drop_canonical=False, selection=None):
     import torch
     import paper_2510_02345_amd as cm
     print(f"case {cfg}", flush=True)
@@ -29,6 +29,8 @@ def _run(cfg, w=None, dy_scale=1.0, pack=True, drop_canonical=False):
     rng = np.random.default_rng(cfg.seed + 7)
     dy = (dy_scale * rng.standard_normal((cfg.T, cfg.d))).astype(np.float16)
     cid, eidx, gate, _, _ = orc.route(w["x"], w["router_cluster"], w["router_expert"], cfg.K, cfg.k, w["cluster_bias"])
+    if selection is not None:
+        eidx, gate = selection(eidx, gate)
     ref = orc.backward_naive(w, w["x"], dy, eidx, gate, cfg.K, cfg.q)
     layer = cm.Layer(cfg.d, cfg.d_ff, cfg.G, cfg.K, cfg.r, cfg.k, cfg.q, w, cfg.T, pack=pack)
     if drop_canonical:
@@ -114,6 +116,17 @@ def test_backward_infinite_gradients_stay_with_their_expert():
         bad |= set((~torch.isfinite(out[n])).flatten(1).any(1).nonzero()[:, 0].tolist())
     assert bad and bad <= own, (bad, own)
     layer.close()
+
+
+@pytest.mark.parametrize("r,K", [(8, 4), (32, 5)])   # the middle kernel's path, and beyond it (K * r = 160)
+def test_backward_of_a_token_that_names_an_expert_twice(r, K):
+    # the selection is the caller's: both pairs of such a token count
+    def selection(eidx, gate):
+        eidx = eidx.copy()
+        eidx[::2, 1] = eidx[::2, 0]
+        return eidx, gate
+    _run(ci.small_config("bw_twice", T=150, d=128, d_ff=256, G=2, K=K, r=r, k=2, q=32, factor_std=0.2, seed=158),
+         selection=selection)
 
 
 def test_backward_unused_experts_weights_never_used():
