@@ -73,6 +73,8 @@ __device__ __forceinline__ half8 and8(const half8& v, const unsigned (&m)[4]) {
 // a SIMD do them in opposite order, so that the one fills the gaps of the other.  32768 tokens, two of
 // 8 x 8 experts of rank 16, 8192 units: 1.21-1.27 ms (1.38 with both in the same order; phase 1 alone 0.93), where
 // the kernels it replaces took 3.4; vector ALUs issue in 0.67 of the cycles.
+//   A rank part takes the 32 rank rows of a chunk at once, with zeros where a row is not of the token's expert. Where a
+// panel holds an infinity or a NaN, 0 * Inf would reach the other experts' tokens: it is then taken expert by expert.
 //   U panel [n][kr] and V panel [kr][n], staging [tensor][token][n]: 16-byte chunks at chunk ^ key of the
 // row, keys such that both plain and transposing fragment reads spread over the banks.
 template <int R, int K, int KRP>
@@ -92,6 +94,7 @@ __global__ __launch_bounds__(MD_THREADS) void bw_mid_kernel(bw_mid_args a, int G
   __shared__ __attribute__((aligned(8))) unsigned char sB[3][K][MD_M];   // the experts, 255 for rows past the run
   __shared__ float sD[2][4][MD_M][K];
   __shared__ unsigned sM[2][2][K];   // experts of a 16-token block
+  __shared__ int sApart;             // a panel value is not finite
   char *sU = smem, *sV = smem + U_BYTES, *sS = sV + V_BYTES;
   const int tid = threadIdx.x, lane = tid & 63, t16 = lane & 15, q = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), cg = wave & 3, hi = wave >> 2;
@@ -104,7 +107,10 @@ __global__ __launch_bounds__(MD_THREADS) void bw_mid_kernel(bw_mid_args a, int G
   auto key_u = [](int n) { const int i = (n & 3) | ((n >> 1) & 12); return KRP == 128 ? i : i >> 1; };
 
   // factor panels, zero rows for experts without a token
+  if (tid == 0) sApart = 0;
+  __syncthreads();
   {
+    bool bad = false;
     const int cpr = KRp / 8;
     for (int i = tid; i < nblk * 32 * cpr; i += MD_THREADS) {
       const int n = i / cpr, ch = i % cpr;
@@ -114,14 +120,17 @@ __global__ __launch_bounds__(MD_THREADS) void bw_mid_kernel(bw_mid_args a, int G
         const int e = c * Ke + min((ch * 8 + h) / R, Ke - 1);
         if (a.offe[e + 1] == a.offe[e]) v[h] = v[h + 1] = v[h + 2] = v[h + 3] = (half_t)0.f;
       }
+      bad |= not_finite(v);
       *(half8*)(sU + n * (KRP * 2) + ((ch ^ key_u(n)) << 4)) = v;
     }
     for (int i = tid; i < KRp * nblk * 4; i += MD_THREADS) {
       const int kr = i / (nblk * 4), ch = i % (nblk * 4), e = c * Ke + min(kr / R, Ke - 1);
       half8 v = *(const half8*)(a.v2p + ((size_t)c * KRp + kr) * f + n0 + ch * 8);
       if (a.offe[e + 1] == a.offe[e]) v = half8{0, 0, 0, 0, 0, 0, 0, 0};
+      bad |= not_finite(v);
       *(half8*)(sV + kr * (MD_N * 2) + ((ch ^ (kr & 15)) << 4)) = v;
     }
+    if (bad) sApart = 1;
   }
 
   const size_t block = (size_t)((n0 >> 5) + min(cg, nblk - 1)) * T * 32;   // this wavefront's 32 units in [f / 32][T][32]
@@ -157,7 +166,8 @@ __global__ __launch_bounds__(MD_THREADS) void bw_mid_kernel(bw_mid_args a, int G
   const half8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
 
   // ---------------------------------------------------------------- phase 1
-  auto phase1 = [&](int mt, int buf, int par) __attribute__((always_inline)) {
+  // apart: the experts of a chunk of rank rows one by one
+  auto phase1 = [&](int mt, int buf, int par, auto apart) __attribute__((always_inline)) {
     const half8 h8 = hv, d8 = dv;
     load_tile(mt + MD_M);
     if (cg < nblk) {
@@ -191,19 +201,37 @@ __global__ __launch_bounds__(MD_THREADS) void bw_mid_kernel(bw_mid_args a, int G
           z[0][v] = (float)d8[v];
           z[1][v] = (float)d8[4 + v];
         }
-        for (unsigned m = em; m != 0u;) {
-          const int ch = __builtin_ctz(m) / PER_CHUNK;
-          m &= ~(((1u << PER_CHUNK) - 1u) << (ch * PER_CHUNK));
-          const half8 ft1 = FU::t1_frag(e, ch, q, ft), fu1 = FU::t1_frag(e, ch, q, fu);
+        auto frag_u = [&](int ch, int hh) {
+          const int n = 32 * cg + ((t16 & 12) << 1) + 4 * hh + (t16 & 3);
+          return *(const half8*)(sU + n * (KRP * 2) + (((4 * ch + q) ^ key_u(n)) << 4));
+        };
+        auto frag_v = [&](int ch, int hh) {
+          const int kr = 32 * ch + 8 * q + (t16 >> 2);
+          const char* v0 = sV + kr * (MD_N * 2) + (((4 * cg + (t16 & 3)) ^ (kr & 15)) << 4) + 8 * hh;
+          const char* v1 = sV + (kr + 4) * (MD_N * 2) + (((4 * cg + (t16 & 3)) ^ ((kr + 4) & 15)) << 4) + 8 * hh;
+          return join8(lds_read_tr(v0), lds_read_tr(v1));
+        };
+        if constexpr (!decltype(apart)::value) {
+          for (unsigned m = em; m != 0u;) {
+            const int ch = __builtin_ctz(m) / PER_CHUNK;
+            m &= ~(((1u << PER_CHUNK) - 1u) << (ch * PER_CHUNK));
+            const half8 ft1 = FU::t1_frag(e, ch, q, ft), fu1 = FU::t1_frag(e, ch, q, fu);
 #pragma unroll
-          for (int hh = 0; hh < 2; ++hh) {
-            const int n = 32 * cg + ((t16 & 12) << 1) + 4 * hh + (t16 & 3);
-            const half8 fa = *(const half8*)(sU + n * (KRP * 2) + (((4 * ch + q) ^ key_u(n)) << 4));
-            h[hh] = mfma32(fa, ft1, h[hh]);
-            const int kr = 32 * ch + 8 * q + (t16 >> 2);
-            const char* v0 = sV + kr * (MD_N * 2) + (((4 * cg + (t16 & 3)) ^ (kr & 15)) << 4) + 8 * hh;
-            const char* v1 = sV + (kr + 4) * (MD_N * 2) + (((4 * cg + (t16 & 3)) ^ ((kr + 4) & 15)) << 4) + 8 * hh;
-            z[hh] = mfma32(join8(lds_read_tr(v0), lds_read_tr(v1)), fu1, z[hh]);
+            for (int hh = 0; hh < 2; ++hh) {
+              h[hh] = mfma32(frag_u(ch, hh), ft1, h[hh]);
+              z[hh] = mfma32(frag_v(ch, hh), fu1, z[hh]);
+            }
+          }
+        } else {
+          for (unsigned m = em; m != 0u; m &= m - 1u) {
+            const int x = __builtin_ctz(m), ch = x / PER_CHUNK, kr = 32 * ch + 8 * q;
+            const half8 ft1 = FU::t1_frag(e, ch, q, ft), fu1 = FU::t1_frag(e, ch, q, fu);
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+              const float4v hx = mfma32(rows_of_expert(frag_u(ch, hh), kr, R, x), ft1, h[hh]);
+              const float4v zx = mfma32(rows_of_expert(frag_v(ch, hh), kr, R, x), fu1, z[hh]);
+              if (e == x) h[hh] = hx, z[hh] = zx;
+            }
           }
         }
         float dot = 0.f;
@@ -382,19 +410,22 @@ __global__ __launch_bounds__(MD_THREADS) void bw_mid_kernel(bw_mid_args a, int G
   __syncthreads();
   const int tiles = (m_end - m0 + MD_M - 1) / MD_M;
   // tables: tile i in buffer i % 3
-  auto steps = [&](auto first) __attribute__((always_inline)) {
+  auto steps = [&](auto first, auto apart) __attribute__((always_inline)) {
     for (int i = 0, buf = 0, prev = 0; i < tiles; ++i) {
       const int mt = m0 + i * MD_M, next = buf == 2 ? 0 : buf + 1;
-      if (decltype(first)::value) phase1(mt, buf, i & 1);
+      if (decltype(first)::value) phase1(mt, buf, i & 1, apart);
       if (i > 0) phase2(mt - MD_M, prev, (i - 1) & 1);
-      if (!decltype(first)::value) phase1(mt, buf, i & 1);
+      if (!decltype(first)::value) phase1(mt, buf, i & 1, apart);
       store_table(mt + MD_M, next);
       prev = buf;
       buf = next;
       __syncthreads();
     }
   };
-  if (hi == 0) steps(std::true_type{}); else steps(std::false_type{});
+  // (a branch inside the loop made the kernel 3 % slower)
+  if (__builtin_amdgcn_readfirstlane(sApart)) steps(std::false_type{}, std::true_type{});
+  else if (hi == 0) steps(std::true_type{}, std::false_type{});
+  else steps(std::false_type{}, std::false_type{});
   phase2(m0 + (tiles - 1) * MD_M, (tiles - 1) % 3, (tiles - 1) & 1);
   if (cg >= nblk) return;
   float* out = (hi ? a.dv : a.du) + (size_t)slot * KRp * f + n0 + 32 * cg + 8 * q;

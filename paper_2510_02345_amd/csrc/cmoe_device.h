@@ -106,6 +106,20 @@ __device__ __forceinline__ half4 lds_read_tr(const void* p) {
 __device__ __forceinline__ half8 join8(const half4& a, const half4& b) {
   return half8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
 }
+// Does an element hold an infinity or a NaN?
+__device__ __forceinline__ bool not_finite(const half8& v) {
+  typedef unsigned uint4v __attribute__((ext_vector_type(4)));
+  const uint4v x = __builtin_bit_cast(uint4v, v);
+  unsigned m = 0u;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) m |= (x[i] & 0x7c007c00u) + 0x04000400u;
+  return (m & 0x80008000u) != 0u;
+}
+// Of the rank rows kr .. kr + 7 of a cluster (kr a multiple of 8) those of expert e; zero for the others.
+__device__ __forceinline__ half8 rows_of_expert(const half8& v, int kr, int r, int e) {
+  const half4 z = {0, 0, 0, 0};
+  return join8(kr / r == e ? half4{v[0], v[1], v[2], v[3]} : z, (kr + 4) / r == e ? half4{v[4], v[5], v[6], v[7]} : z);
+}
 // What this wavefront wrote to LDS is read by its own lanes behind this (no barrier needed).
 __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");

@@ -566,7 +566,8 @@ struct EpiStoreBlocked {
 // over the cluster's rank rows, V1cat^T qext (qext[m][e_j r + rho] = q_j[rho], as EpiDownCombine does
 // for the second matrix), and the gate path sum_j dl_j v_{e_j} in FP32, and writes FP32 rows in
 // token order.  The panel V1cat is stored with the contraction index along its rows, so its
-// fragments are transposing LDS reads.  K*r <= 128, k <= 2.
+// fragments are transposing LDS reads.  K*r <= 128, k <= 2.  A panel value that is not finite stays with its expert's
+// tokens as in the middle kernel (cmoe_backward_mid.hip).
 struct EpiInputGrad {
   static constexpr bool SPLITS = false;
   using Quarter = TileQuad;
@@ -583,7 +584,7 @@ struct EpiInputGrad {
   static constexpr int panel_bytes() { return 128 * (TL::BN + 8) * 2; }
   template <class TL>
   static constexpr int smem_bytes() {
-    constexpr int need = panel_bytes<TL>() + TL::BM * (128 + 8) * 2;
+    constexpr int need = panel_bytes<TL>() + TL::BM * (128 + 8) * 2 + 16;
     return need > TL::SMEM_BYTES ? need : TL::SMEM_BYTES;
   }
   template <class TL>
@@ -593,18 +594,23 @@ struct EpiInputGrad {
     const int lds = KRp + 8, n_chunks = KRp / 32;
     half_t* sV = t.smem;                                // [KRp][LDV]
     half_t* sS = t.smem + panel_bytes<TL>() / 2;        // [BM][lds]
+    int* s_apart = (int*)(sS + TL::BM * (128 + 8));     // a panel value is not finite
     const half_t* vc = v1cat + (size_t)t.c * KRp * d;
+    bool bad = false;
     __syncthreads();  // the stage buffers are free
+    if (t.tid == 0) *s_apart = 0;
     constexpr int CPR = TL::BN / 8;
     for (int idx = t.tid; idx < KRp * CPR; idx += TL::NT) {
       const int row = idx / CPR, ch = idx % CPR;
       const int e = t.c * K + min(row / r, K - 1);
       half8 v = *(const half8*)(vc + (size_t)row * d + min(t.n0 + ch * 8, d - 8));
       if (offe[e + 1] == offe[e]) v = half8{0, 0, 0, 0, 0, 0, 0, 0};
+      bad |= not_finite(v);
       *(half8*)(sV + row * LDV + ch * 8) = v;
     }
     for (int i = t.tid; i < TL::BM * lds / 8; i += TL::NT) ((half8*)sS)[i] = half8{0, 0, 0, 0, 0, 0, 0, 0};
     __syncthreads();
+    if (bad) *s_apart = 1;
     const int r4 = r / 4;
     for (int idx = t.tid; idx < TL::BM * k * r4; idx += TL::NT) {
       const int rho = idx % r4 * 4, j = (idx / r4) % k, m = idx / (r4 * k), p = t.m0 + m;
@@ -621,6 +627,7 @@ struct EpiInputGrad {
       *(half4*)(sS + m * lds + ep[j] * r + rho) = v;
     }
     __syncthreads();
+    const bool apart = __builtin_amdgcn_readfirstlane(*s_apart) != 0;
 #pragma unroll
     for (int b = 0; b < TL::MT; ++b) {
       const int m = t.wm * TL::WM + b * 16 + t16, p = t.m0 + m;
@@ -640,15 +647,31 @@ struct EpiInputGrad {
       for (int P = 0; P < TL::NP; ++P) {
         const int nl = t.wn * TL::WN + 32 * P;
         if (t.n0 + nl >= d) continue;
-        for (unsigned mm = cmask; mm != 0u; mm &= mm - 1u) {
-          const int kc = __builtin_ctz(mm);
-          const half8 fb = *(const half8*)(sS + m * lds + kc * 32 + 8 * q4);
-          // rows n = 8 (i / 4) + 4 hh + i % 4 of the pair block, contraction elements 8 q4 ..
-          const half_t* a0 = sV + (kc * 32 + 8 * q4 + (t16 >> 2)) * LDV + nl + 8 * (t16 & 3);
+        // rows n = 8 (i / 4) + 4 hh + i % 4 of the pair block, contraction elements 32 kc + 8 q4 ..
+        auto frag_v = [&](int kc, int hh) {
+          const half_t* a0 = sV + (kc * 32 + 8 * q4 + (t16 >> 2)) * LDV + nl + 8 * (t16 & 3) + 4 * hh;
+          return join8(lds_read_tr(a0), lds_read_tr(a0 + 4 * LDV));
+        };
+        if (__builtin_expect(!apart, 1)) {
+          for (unsigned mm = cmask; mm != 0u; mm &= mm - 1u) {
+            const int kc = __builtin_ctz(mm);
+            const half8 fb = *(const half8*)(sS + m * lds + kc * 32 + 8 * q4);
 #pragma unroll
-          for (int hh = 0; hh < 2; ++hh)
-            acc[2 * P + hh][b] =
-                mfma32(join8(lds_read_tr(a0 + 4 * hh), lds_read_tr(a0 + 4 * LDV + 4 * hh)), fb, acc[2 * P + hh][b]);
+            for (int hh = 0; hh < 2; ++hh) acc[2 * P + hh][b] = mfma32(frag_v(kc, hh), fb, acc[2 * P + hh][b]);
+          }
+        } else {
+          for (int e = 0; e < K; ++e) {
+            bool own = false;
+            for (int j = 0; j < k; ++j) own |= valid && es[pc * k + j] == e;
+            if (__ballot(own) == 0ull) continue;
+            const int kc = (e * r) >> 5;
+            const half8 fb = *(const half8*)(sS + m * lds + kc * 32 + 8 * q4);
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+              const float4v x = mfma32(rows_of_expert(frag_v(kc, hh), kc * 32 + 8 * q4, r, e), fb, acc[2 * P + hh][b]);
+              if (own) acc[2 * P + hh][b] = x;
+            }
+          }
         }
         if (!valid) continue;
         float4v o0 = acc[2 * P][b], o1 = acc[2 * P + 1][b];

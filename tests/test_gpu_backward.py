@@ -129,6 +129,41 @@ def test_backward_of_a_token_that_names_an_expert_twice(r, K):
          selection=selection)
 
 
+@pytest.mark.parametrize("factor", ["v1", "u1", "v2", "u2"])
+@pytest.mark.parametrize("r,K", [(4, 8), (8, 8), (16, 8), (32, 4), (32, 5)])
+def test_backward_factors_that_are_not_finite_stay_with_their_expert(r, K, factor):
+    # one expert's scales hold infinities (0 * inf among its values): the tokens of the other experts, also those that
+    # share its tiles and its block of 32 rank rows, get the gradients they get without it
+    import torch
+    import paper_2510_02345_amd as cm
+    cfg = ci.small_config("bw_inf_factor", T=120, d=128, d_ff=192, G=2, K=K, r=r, k=2, q=32, seed=159)
+    print(f"case {cfg} {factor}", flush=True)
+    w = ci.generate(cfg)
+    dy = np.random.default_rng(3).standard_normal((cfg.T, cfg.d)).astype(np.float16)
+    _, eidx, gate, _, _ = orc.route(w["x"], w["router_cluster"], w["router_expert"], K, cfg.k, w["cluster_bias"])
+    ref = orc.backward_naive(w, w["x"], dy, eidx, gate, K, cfg.q)
+    e = int(eidx[0, 0])
+    w[factor + "_s"] = w[factor + "_s"].copy()
+    w[factor + "_s"][e, r // 2, :] = np.float16(np.inf)
+    layer = cm.Layer(cfg.d, cfg.d_ff, cfg.G, K, r, cfg.k, cfg.q, w, cfg.T)
+    out = layer.backward(_dev(w["x"]), _dev(dy), _dev(eidx.astype(np.int32)), _dev(gate.astype(np.float32)))
+    torch.cuda.synchronize()
+    own = (eidx == e).any(1)
+    assert own.any() and not own.all()
+    dx = out["dx"].cpu().numpy()
+    assert not np.isfinite(dx[own]).all(1).any()
+    m = orc.error_metrics(dx[~own].astype(np.float64), ref["dx"][~own])
+    assert m["max_over_rms"] <= 2e-2 and m["mean_rel"] <= 2e-3, m
+    # the experts that no token shares with this one
+    far = np.setdiff1d(np.unique(eidx[~own]), np.unique(eidx[own]))
+    for n in ("du1", "dv1", "du2", "dv2", "d_router_expert"):
+        assert bool(torch.isfinite(out[n][far]).all()), n
+    other = 1 - e // K
+    for n in ("dw1_base", "dw2_base"):
+        assert bool(torch.isfinite(out[n][other]).all()), n
+    layer.close()
+
+
 def test_backward_unused_experts_weights_never_used():
     # an expert without a token, in a cluster that has some: its stored factors may hold anything
     cfg = ci.small_config("bw_unused", T=40, d=64, d_ff=128, G=2, K=8, r=8, k=2, q=8, seed=157)
