@@ -566,7 +566,7 @@ cmoe_bw_layout cmoe_backward_layout(const cmoe_dims& dm, int T) {
   L.dhst = take(sizeof(half_t) * f * Tp);
   L.agt = take(sizeof(half_t) * f * Tp);
   if (mid) {
-    const size_t chunks = bw_mid_chunks(dm), slots = bw_mid_slots(dm, (int)Tz);
+    const size_t chunks = bw_mid_chunks(dm), slots = bw_mid_slots_room(dm, (int)Tz);
     L.perm2 = take(sizeof(int) * Tz);
     L.rowmap = take(sizeof(int) * Tz);
     L.es = take(sizeof(int) * M);

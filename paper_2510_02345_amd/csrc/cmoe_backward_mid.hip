@@ -537,13 +537,21 @@ void go_mid_r(const cmoe_dims& dm, const bw_mid_args& a, hipStream_t st) {
 
 int bw_mid_chunks(const cmoe_dims& dm) { return (dm.d_ff + MD_N - 1) / MD_N; }
 // Runs such that about 1024 workgroups share the tokens, in whole tiles.
+constexpr int MD_WORKGROUPS = 1024;
 int bw_mid_run(const cmoe_dims& dm, int T) {
-  const long want = (long)T * bw_mid_chunks(dm) / 1024;
+  const long want = (long)T * bw_mid_chunks(dm) / MD_WORKGROUPS;
   return (int)((want < 1 ? 1 : want) + MD_M - 1) / MD_M * MD_M;
 }
 int bw_mid_slots(const cmoe_dims& dm, int T) {
   const int run = bw_mid_run(dm, T);
   return (T + run - 1) / run + dm.G;
+}
+// Runs to reserve space for: no T up to this one has more.  A run of m tiles holds want < 32 m + 1, so T / run is
+// below 33 / 32 of 1024 / chunks, and it is never more than the tiles.
+int bw_mid_slots_room(const cmoe_dims& dm, int T) {
+  const int chunks = bw_mid_chunks(dm), tiles = (T + MD_M - 1) / MD_M;
+  const int most = (MD_WORKGROUPS + MD_WORKGROUPS / MD_M + chunks - 1) / chunks;
+  return (tiles < most ? tiles : most) + dm.G;
 }
 
 hipError_t launch_bw_mid(const cmoe_dims& dm, const bw_mid_args& a, hipStream_t st) {

@@ -232,6 +232,7 @@ inline bool bw_mid_ok(const cmoe_dims& dm) { return dm.k <= 2 && dm.KRp <= 128; 
 int bw_mid_chunks(const cmoe_dims& dm);
 int bw_mid_run(const cmoe_dims& dm, int T);     // tokens of a run
 int bw_mid_slots(const cmoe_dims& dm, int T);   // runs, at most
+int bw_mid_slots_room(const cmoe_dims& dm, int T);   // the same for any number of tokens up to T
 hipError_t launch_bw_mid(const cmoe_dims& dm, const bw_mid_args& a, hipStream_t st);
 hipError_t launch_bw_mid_sums(const cmoe_dims& dm, const bw_mid_args& a, const int* perm2, const int* invm, half_t* q16,
                               half_t* qq, half_t* ss, float* dl, float* du1, float* dv2, hipStream_t st);

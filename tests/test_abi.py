@@ -86,6 +86,28 @@ def test_workspace_for_t_max_serves_every_smaller_t():
         L.cmoe_destroy(h)
 
 
+def test_backward_workspace_for_t_max_serves_every_smaller_t():
+    # the runs that the partial factor gradients come in grow with T and their number falls where they do
+    L = cm.lib()
+    shapes = [dict(d=2048, d_ff=8192, G=8, K=8, r=16, top_k=2, q_group=64),
+              dict(d=1024, d_ff=4096, G=4, K=4, r=16, top_k=2, q_group=64),
+              dict(d=128, d_ff=1984, G=2, K=4, r=4, top_k=1, q_group=32),
+              dict(d=64, d_ff=256 * 1024, G=1, K=4, r=32, top_k=2, q_group=64),
+              dict(d=64, d_ff=64, G=64, K=2, r=4, top_k=2, q_group=8),
+              dict(d=4096, d_ff=14336, G=8, K=8, r=32, top_k=2, q_group=128),
+              dict(d=768, d_ff=3072, G=2, K=8, r=16, top_k=4, q_group=32)]
+    for kw in shapes:
+        rc, h = _create(**kw)
+        assert rc == B.OK
+        prev = (0, 0)
+        ts = [*range(0, 3000), *range(3000, 40000, 7), *range(40000, 1 << 21, 4099)]
+        for t in ts:
+            n = L.cmoe_backward_workspace_bytes(h, t)
+            assert n >= prev[1], (kw, prev, t, n)
+            prev = (t, n)
+        L.cmoe_destroy(h)
+
+
 def test_calls_reject_bad_arguments_without_touching_the_gpu():
     rc, h = _create()
     L = cm.lib()
