@@ -104,7 +104,9 @@ int cmoe_destroy(cmoe_handle *h);
  * cmoe_weights.packed to it and every call reads the bases from it, whatever the token count
  * (cmoe_ffn_forward, cmoe_forward, cmoe_forward_multi, cmoe_backward); the calls that take
  * more than 256 tokens also read the factor panels from it (cmoe_combine too), the calls
- * with fewer tokens decode the INT4 factors on the fly.  With packed == NULL the canonical
+ * with fewer tokens decode the INT4 factors on the fly (cmoe_backward, whatever the token count:
+ * V1, U1 and V2 from the panels where top_k <= 2 and K*r <= 128, U2 and all others from the
+ * codes).  With packed == NULL the canonical
  * arrays are read (and, above 256 tokens, the factors of the clusters that received tokens
  * dequantised per call).  Once packed is set, w1_base and w2_base may be NULL: the packed
  * buffer is then the only resident copy of the bases (the INT4 factor tensors and the
@@ -283,7 +285,8 @@ int cmoe_reconstruction_error(const cmoe_compress_config *cfg, const cmoe_f16 *W
  *   du1 [G*K][r][d_ff], dv1 [G*K][r][d], du2 [G*K][r][d], dv2 [G*K][r][d_ff]
  *                                  with respect to the DEQUANTISED factors, in the stored
  *                                  rank-major orientation: dU = dW V^T, dV = U^T dW
- * Experts that received no token get zero gradients and their stored weights are not read.
+ * Experts that received no token get zero gradients; their codes and scales are not read, and
+ * what a packed copy holds of them enters no result.
  * The shared-base products are computed once per token, the rank-r products once per
  * (token, expert) pair (Sec. 3.2).  Matrix operands are FP16, accumulation, the hidden
  * pre-activations and the gate path are FP32.  T = 0 writes zero

@@ -336,7 +336,7 @@ static int ffn_impl(cmoe_handle* h, const cmoe_weights* w, const cmoe_f16* x, in
   // when the combine is fused into the down-projection its U2 panel joins the same launch
   const bool fuse = y_fused != nullptr && dm.KRp <= 128 && weights_combine_ok(w);
   half_t* u2t = !fuse ? nullptr : pk ? (half_t*)(pkb + PL.u2t) : (half_t*)(ws + L.u2t);
-  if (!pk) CMOE_LAUNCH(TS_DEQUANT, launch_dequant_ffn(dm, *w, offsets, v1cat, u1t, v2p, u2t, st));
+  if (!pk) CMOE_LAUNCH(TS_DEQUANT, launch_dequant_ffn(dm, *w, offsets, nullptr, v1cat, u1t, v2p, u2t, st));
   CMOE_LAUNCH(TS_T1, launch_t1(dm, (const half_t*)x, x_div, T, rperm, offsets, expert_idx, v1cat, t1ext, st));
   CMOE_LAUNCH(TS_GEMM1, launch_gemm1(dm, *w, (const half_t*)x, x_div, T, rperm, offsets, expert_idx, gate, u1t, v2p,
                                      t1ext, a, spart, st));

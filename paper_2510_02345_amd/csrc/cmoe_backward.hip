@@ -681,8 +681,8 @@ hipError_t launch_backward(const cmoe_dims& dm, const cmoe_weights& w, const hal
       const half_t* v1cat = pk ? (const half_t*)(pkb + PL.v1cat) : H(L.v1p);
       const half_t* u1t = pk ? (const half_t*)(pkb + PL.u1t) : H(L.u1p);
       const half_t* v2p = pk ? (const half_t*)(pkb + PL.v2p) : H(L.v2p);
-      if (!pk) BW_CHECK(launch_dequant_ffn(dm, w, offc, H(L.v1p), H(L.u1p), H(L.v2p), nullptr, st));
-      BW_CHECK(launch_dequant_rows(dm, w.u2_q, w.u2_s, offc, d, H(L.u2p), st));
+      if (!pk) BW_CHECK(launch_dequant_ffn(dm, w, offc, offe, H(L.v1p), H(L.u1p), H(L.v2p), nullptr, st));
+      BW_CHECK(launch_dequant_rows(dm, w.u2_q, w.u2_s, offc, offe, d, H(L.u2p), st));
       BW_CHECK(launch_t1_pair(dm, T, permc, offc, expert_idx, x, v1cat, H(L.t1), dy, H(L.u2p), H(L.uy), st));
       BW_CHECK(launch_gemm_blocked(w1b, mat, w1_ld, w1_step, f, x, d, permc, d, offc, G, T, H(L.hb), st));
       BW_CHECK(launch_gemm_blocked(H(L.w2bt), mat, 32, (long)f * 32, f, dy, d, permc, d, offc, G, T, H(L.dab), st));

@@ -2,7 +2,8 @@
 // kernels consume.  value = scale[n / q] * code[n]; code = two's-complement nibble,
 // even n in the low nibble of byte n / 2.  Clusters that received no token are skipped,
 // so their stored factors are never read (offsets == NULL: every cluster, for the one-time
-// packing of the weights).
+// packing of the weights); with the pair offsets offe [G K + 1] of the backward pass neither are those of
+// single experts without a pair, whose part of a panel is left undefined.
 #include "cmoe_internal.h"
 
 namespace {
@@ -14,8 +15,11 @@ __device__ __forceinline__ float nib_hi(unsigned b) { return (float)((int)(b << 
 // Block (bx, kk, c) of a grid ((L / 8 + 255) / 256, KRp, G).
 __device__ __forceinline__ void dequant_rows(int bx, int kk, int c, const uint8_t* __restrict__ qv,
                                              const half_t* __restrict__ sv, int L, int q, int K, int r, int KRp,
-                                             const int* __restrict__ offsets, half_t* __restrict__ out) {
+                                             const int* __restrict__ offsets, const int* __restrict__ offe,
+                                             half_t* __restrict__ out) {
   if (offsets != nullptr && offsets[c + 1] == offsets[c]) return;
+  const int e = c * K + kk / r;
+  if (offe != nullptr && kk < K * r && offe[e + 1] == offe[e]) return;
   const int n8 = (bx * 256 + threadIdx.x) * 8;  // 8 consecutive output positions
   if (n8 >= L) return;
   half8 o = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -42,8 +46,8 @@ __device__ __forceinline__ void dequant_rows(int bx, int kk, int c, const uint8_
 constexpr int DT_N = 64;
 __device__ __forceinline__ void dequant_transpose(int bx, int c, const uint8_t* __restrict__ qv,
                                                   const half_t* __restrict__ sv, int L, int q, int K, int r, int KRp,
-                                                  const int* __restrict__ offsets, half_t* __restrict__ out,
-                                                  half_t* __restrict__ tile) {
+                                                  const int* __restrict__ offsets, const int* __restrict__ offe,
+                                                  half_t* __restrict__ out, half_t* __restrict__ tile) {
   if (offsets != nullptr && offsets[c + 1] == offsets[c]) return;
   const int n0 = bx * DT_N, ld = KRp + 8, KR = K * r;
   // two threads per rank row: 32 n (16 code bytes) each
@@ -51,7 +55,8 @@ __device__ __forceinline__ void dequant_transpose(int bx, int c, const uint8_t* 
     const int kk = idx >> 1, half = idx & 1;
     uint4 w4 = {0u, 0u, 0u, 0u};
     float sc[4] = {0.f, 0.f, 0.f, 0.f};
-    if (kk < KR) {
+    const int e = c * K + kk / r;
+    if (kk < KR && (offe == nullptr || offe[e + 1] != offe[e])) {
       const size_t row = (size_t)(c * K) * r + kk;
       w4 = *(const uint4*)(qv + row * (L / 2) + (n0 + 32 * half) / 2);
 #pragma unroll
@@ -89,7 +94,7 @@ struct DequantJobs {
   int n;
 };
 __global__ __launch_bounds__(256) void dequant_kernel(DequantJobs jobs, int q, int K, int r, int KRp, int G,
-                                                      const int* __restrict__ offsets) {
+                                                      const int* __restrict__ offsets, const int* __restrict__ offe) {
   __shared__ __attribute__((aligned(16))) half_t tile[DT_N * (512 + 8)];
   int ji = 0;
   for (int i = 1; i < jobs.n; ++i)
@@ -97,11 +102,11 @@ __global__ __launch_bounds__(256) void dequant_kernel(DequantJobs jobs, int q, i
   const DequantJob& jb = jobs.j[ji];
   const unsigned local = blockIdx.x - jb.first;
   if (jb.kind == 2) {
-    dequant_transpose((int)(local % jb.nx), (int)(local / jb.nx), jb.qv, jb.sv, jb.L, q, K, r, KRp, offsets, jb.out,
-                      tile);
+    dequant_transpose((int)(local % jb.nx), (int)(local / jb.nx), jb.qv, jb.sv, jb.L, q, K, r, KRp, offsets, offe,
+                      jb.out, tile);
   } else {
     const int bx = (int)(local % jb.nx), kk = (int)((local / jb.nx) % KRp), c = (int)(local / jb.nx / KRp);
-    dequant_rows(bx, kk, c, jb.qv, jb.sv, jb.L, q, K, r, KRp, offsets, jb.out);
+    dequant_rows(bx, kk, c, jb.qv, jb.sv, jb.L, q, K, r, KRp, offsets, offe, jb.out);
   }
 }
 
@@ -125,16 +130,17 @@ void add_job(DequantJobs& js, unsigned& total, const cmoe_dims& dm, const uint8_
 
 }  // namespace
 
-// v1cat, u1t, v2p, and u2t when it is not NULL.
-hipError_t launch_dequant_ffn(const cmoe_dims& dm, const cmoe_weights& w, const int* offsets, half_t* v1cat,
-                              half_t* u1t, half_t* v2p, half_t* u2t, hipStream_t st) {
+// v1cat, u1t, v2p, and u2t when it is not NULL.  offe: NULL, or the pair offsets of the experts.
+hipError_t launch_dequant_ffn(const cmoe_dims& dm, const cmoe_weights& w, const int* offsets, const int* offe,
+                              half_t* v1cat, half_t* u1t, half_t* v2p, half_t* u2t, hipStream_t st) {
   DequantJobs js{};
   unsigned total = 0;
   add_job(js, total, dm, w.u1_q, w.u1_s, u1t, dm.d_ff, 2);
   add_job(js, total, dm, w.v2_q, w.v2_s, v2p, dm.d_ff, 0);
   add_job(js, total, dm, w.v1_q, w.v1_s, v1cat, dm.d, 0);
   if (u2t != nullptr) add_job(js, total, dm, w.u2_q, w.u2_s, u2t, dm.d, 2);
-  hipLaunchKernelGGL(dequant_kernel, dim3(total), dim3(256), 0, st, js, dm.q, dm.K, dm.r, dm.KRp, dm.G, offsets);
+  hipLaunchKernelGGL(dequant_kernel, dim3(total), dim3(256), 0, st, js, dm.q, dm.K, dm.r, dm.KRp, dm.G, offsets,
+                     offe);
   return hipGetLastError();
 }
 
@@ -143,16 +149,18 @@ hipError_t launch_dequant_u2(const cmoe_dims& dm, const cmoe_weights& w, const i
   DequantJobs js{};
   unsigned total = 0;
   add_job(js, total, dm, w.u2_q, w.u2_s, u2t, dm.d, 2);
-  hipLaunchKernelGGL(dequant_kernel, dim3(total), dim3(256), 0, st, js, dm.q, dm.K, dm.r, dm.KRp, dm.G, offsets);
+  hipLaunchKernelGGL(dequant_kernel, dim3(total), dim3(256), 0, st, js, dm.q, dm.K, dm.r, dm.KRp, dm.G, offsets,
+                     (const int*)nullptr);
   return hipGetLastError();
 }
 
-// One factor's row-preserving panel [G][KRp][L].
-hipError_t launch_dequant_rows(const cmoe_dims& dm, const uint8_t* qv, const void* sv, const int* offsets, int L,
-                               half_t* out, hipStream_t st) {
+// One factor's row-preserving panel [G][KRp][L], the rows of experts that have pairs.
+hipError_t launch_dequant_rows(const cmoe_dims& dm, const uint8_t* qv, const void* sv, const int* offsets, const int* offe,
+                               int L, half_t* out, hipStream_t st) {
   DequantJobs js{};
   unsigned total = 0;
   add_job(js, total, dm, qv, sv, out, L, 0);
-  hipLaunchKernelGGL(dequant_kernel, dim3(total), dim3(256), 0, st, js, dm.q, dm.K, dm.r, dm.KRp, dm.G, offsets);
+  hipLaunchKernelGGL(dequant_kernel, dim3(total), dim3(256), 0, st, js, dm.q, dm.K, dm.r, dm.KRp, dm.G, offsets,
+                     offe);
   return hipGetLastError();
 }

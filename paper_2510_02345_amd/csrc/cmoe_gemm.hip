@@ -1296,6 +1296,6 @@ hipError_t launch_pack_bases(const cmoe_dims& dm, const cmoe_weights& w, half_t*
   if (e != hipSuccess) return e;
   // the FP16 panels of all clusters' factors (Sec. 3.4: INT4 is the stored form; the panels are
   // what the matrix cores read)
-  return launch_dequant_ffn(dm, w, nullptr, (half_t*)(pk + PL.v1cat), (half_t*)(pk + PL.u1t), (half_t*)(pk + PL.v2p),
+  return launch_dequant_ffn(dm, w, nullptr, nullptr, (half_t*)(pk + PL.v1cat), (half_t*)(pk + PL.u1t), (half_t*)(pk + PL.v2p),
                             (half_t*)(pk + PL.u2t), st);
 }

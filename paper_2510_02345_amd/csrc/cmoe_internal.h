@@ -127,12 +127,12 @@ hipError_t launch_sort_pairs(const cmoe_dims& dm, const int* ids, int stride, in
                              hipStream_t st);
 hipError_t launch_sort_ids(const int* ids, int stride, int div, int n, int bins, int* perm, int* inv_perm, int* offsets,
                            int* counts, hipStream_t st);
-hipError_t launch_dequant_ffn(const cmoe_dims& dm, const cmoe_weights& w, const int* offsets, half_t* v1cat,
-                              half_t* u1t, half_t* v2p, half_t* u2t, hipStream_t st);
+hipError_t launch_dequant_ffn(const cmoe_dims& dm, const cmoe_weights& w, const int* offsets, const int* offe,
+                              half_t* v1cat, half_t* u1t, half_t* v2p, half_t* u2t, hipStream_t st);
 hipError_t launch_dequant_u2(const cmoe_dims& dm, const cmoe_weights& w, const int* offsets, half_t* u2t,
                              hipStream_t st);
-hipError_t launch_dequant_rows(const cmoe_dims& dm, const uint8_t* qv, const void* sv, const int* offsets, int L,
-                               half_t* out, hipStream_t st);
+hipError_t launch_dequant_rows(const cmoe_dims& dm, const uint8_t* qv, const void* sv, const int* offsets, const int* offe,
+                               int L, half_t* out, hipStream_t st);
 hipError_t launch_t1_pair(const cmoe_dims& dm, int T, const int* perm, const int* offsets, const int* expert_idx,
                           const half_t* x0, const half_t* v0, half_t* t0, const half_t* x1, const half_t* v1, half_t* t1,
                           hipStream_t st);

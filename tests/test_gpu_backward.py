@@ -186,6 +186,37 @@ def test_backward_unused_experts_weights_never_used():
         assert not out[n][unused].any()
 
 
+@pytest.mark.parametrize("r", [4, 8, 32])
+def test_backward_reads_no_codes_of_unused_experts(r):
+    # their rows are in none of the panels that the call unpacks into its workspace, those of the used ones are
+    import torch
+    import paper_2510_02345_amd as cm
+    cfg = ci.small_config("bw_unread", T=12, d=64, d_ff=128, G=2, K=4, r=r, k=2, q=32, seed=160)
+    print(f"case {cfg}", flush=True)
+    w = ci.generate(cfg)
+    rng = np.random.default_rng(4)
+    cid, _, _, _, _ = orc.route(w["x"], w["router_cluster"], w["router_expert"], cfg.K, cfg.k, w["cluster_bias"])
+    eidx = (cid[:, None] * cfg.K + np.array([0, 2])).astype(np.int32)     # experts 1 and 3 of a cluster unused
+    layer = cm.Layer(cfg.d, cfg.d_ff, cfg.G, cfg.K, cfg.r, cfg.k, cfg.q, w, cfg.T, pack=False)
+    x, dy = _dev(w["x"]), _dev(rng.standard_normal((cfg.T, cfg.d)).astype(np.float16))
+    gate = torch.full((cfg.T, 2), 0.5, device="cuda:0")
+    layer.backward(x, dy, _dev(eidx), gate)     # sizes the workspace
+    layer.bw_ws.zero_()
+    layer.backward(x, dy, _dev(eidx), gate)
+    torch.cuda.synchronize()
+    ws = layer.bw_ws.cpu().numpy().tobytes()
+    for n in ("v1", "u2", "v2", "u1"):
+        vals = orc.dequant_int4(w[n + "_q"], w[n + "_s"], cfg.q).astype(np.float16)   # [E][r][L]
+        for e in range(cfg.G * cfg.K):
+            if e // cfg.K not in cid:
+                continue
+            # rank rows as they are, or the rank values of one element side by side
+            row, col = vals[e, 1].tobytes(), np.concatenate([vals[e, :, i] for i in (5,)]).tobytes()
+            found = row in ws or (n == "u1" and col in ws)
+            assert found == (e % cfg.K in (0, 2)), (n, e)
+    layer.close()
+
+
 def test_backward_config1():
     _run(ci.config(1))
 
