@@ -533,7 +533,7 @@ cmoe_bw_layout cmoe_backward_layout(const cmoe_dims& dm, int T) {
   cmoe_bw_layout L{};
   const size_t E = (size_t)dm.G * dm.K, G = dm.G, Tz = (size_t)(T > 0 ? T : 0), M = Tz * dm.k;
   const size_t d = dm.d, f = dm.d_ff, r = dm.r, KRp = dm.KRp;
-  const bool mid = bw_mid_ok(dm);
+  const bool mid = bw_mid_ok(dm, T);
   L.M = (int)M;
   L.Tpad = (int)((Tz + 32 * G + 63) / 64 * 64);
   const size_t Tp = L.Tpad;
@@ -619,7 +619,7 @@ hipError_t launch_backward(const cmoe_dims& dm, const cmoe_weights& w, const hal
   float* dl = out.d_logits ? out.d_logits : F(L.dl);
   float* part = F(L.rgpart);
   const long mat = (long)f * d;
-  const bool mid = bw_mid_ok(dm);
+  const bool mid = bw_mid_ok(dm, T);
   // rows in cluster order; where the middle is one kernel, ordered by expert pair inside a cluster
   int* permc = I(mid ? L.perm2 : L.permc);
   // the bases: from the re-tiled copy when the caller keeps one (the canonical arrays may

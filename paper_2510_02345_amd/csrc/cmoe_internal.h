@@ -213,7 +213,8 @@ hipError_t launch_gemm_blocked(const half_t* W, long w_gstride, int ldw, long ks
 hipError_t launch_gemm_input_grad(const cmoe_dims& dm, const half_t* w1t, const half_t* dhsum, int T, const int* offsets,
                                   const half_t* v1cat, const int* offe, const half_t* q, const int* es, const int* rperm,
                                   const float* dl, const half_t* router_expert, float* dx, hipStream_t st);
-// The middle of the backward pass (cmoe_backward_mid.hip), top_k <= 2 and KRp <= 128 (bw_mid_ok).
+// The middle of the backward pass (cmoe_backward_mid.hip): top_k <= 2, KRp <= 128, and offsets of a row in
+// [T][k][r] and in a block of 32 columns that fit 32 bits, as do the threads that add the partial sums (bw_mid_ok).
 struct bw_mid_args {
   const half_t *hb, *dab;        // [d_ff / 32][T][32] base parts of h and da, rows in tile order
   const half_t *t1, *uy;         // [T][k][r] V1 x and U2^T dy of the pairs, tile order
@@ -228,7 +229,10 @@ struct bw_mid_args {
   float *du, *dv;                // [slots][KRp][d_ff] partial factor gradients
   int T;
 };
-inline bool bw_mid_ok(const cmoe_dims& dm) { return dm.k <= 2 && dm.KRp <= 128; }
+inline bool bw_mid_ok(const cmoe_dims& dm, int T) {
+  const int row = dm.k * dm.r > 32 ? dm.k * dm.r : 32;
+  return dm.k <= 2 && dm.KRp <= 128 && (uint64_t)(T > 0 ? T : 0) * row <= ((uint64_t)1 << 32) - 256;
+}
 int bw_mid_chunks(const cmoe_dims& dm);
 int bw_mid_run(const cmoe_dims& dm, int T);     // tokens of a run
 int bw_mid_slots(const cmoe_dims& dm, int T);   // runs, at most

@@ -108,6 +108,19 @@ def test_backward_workspace_for_t_max_serves_every_smaller_t():
         L.cmoe_destroy(h)
 
 
+def test_backward_takes_the_general_path_beyond_32_bit_offsets():
+    # 2^27 rows of a block of 32 columns, or of two experts' 2 * 32 rank values half as many, are beyond the middle
+    # kernel: from there on the workspace holds the four FP16 activations of the pairs
+    L = cm.lib()
+    for k, r, K, last in ((1, 4, 8, ((1 << 32) - 256) // 32), (2, 32, 4, ((1 << 32) - 256) // 64)):
+        rc, h = _create(d=64, d_ff=64, G=1, K=K, r=r, top_k=k, q_group=32)
+        assert rc == B.OK
+        sizes = [L.cmoe_backward_workspace_bytes(h, t) for t in (last - 1, last, last + 1, last + 2)]
+        assert sizes[1] - sizes[0] < 1 << 16 and sizes[3] - sizes[2] < 1 << 16, sizes
+        assert sizes[2] - sizes[1] > 4 * 2 * 64 * k * last // 2, sizes
+        L.cmoe_destroy(h)
+
+
 def test_calls_reject_bad_arguments_without_touching_the_gpu():
     rc, h = _create()
     L = cm.lib()
