@@ -296,9 +296,10 @@ typedef struct cmoe_grads {
 } cmoe_grads;
 
 /* Workspace of cmoe_backward for up to T_max tokens (0 for a bad handle, T_max < 0 or an
- * unsupported shape): per-token and per-pair activations, about
- * (8 * top_k + 12) * T_max * d_ff bytes, plus the transposed bases, 4 * G * d * d_ff bytes,
- * the rank panels and partial results. */
+ * unsupported shape): FP16 activations per token, about 10 * T_max * d_ff bytes, transposed
+ * copies of x and dy (4 * T_max * d) and of the bases (4 * G * d * d_ff), the rank panels and
+ * partial results; where top_k > 2 or K*r > 128 also FP16 activations per pair, about
+ * (8 * top_k + 2) * T_max * d_ff. */
 size_t cmoe_backward_workspace_bytes(const cmoe_handle *h, int32_t T_max);
 int cmoe_backward(cmoe_handle *h, const cmoe_weights *w, const cmoe_f16 *x, const cmoe_f16 *dy,
                   int32_t T, const int32_t *expert_idx, const float *gate, const cmoe_grads *grads,

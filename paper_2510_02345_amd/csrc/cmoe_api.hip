@@ -520,12 +520,7 @@ extern "C" int cmoe_pack_weights(cmoe_handle* h, const cmoe_weights* w, void* pa
 extern "C" size_t cmoe_backward_workspace_bytes(const cmoe_handle* h, int32_t T_max) {
   if (!handle_ok(h) || T_max < 0) return 0;
   if ((size_t)T_max * h->dm.k > ((size_t)1 << 30)) return 0;
-  // The size that the header states, also where the middle of the pass keeps no activations of the
-  // pairs and needs less (a buffer of the layout's own size is accepted).
-  const cmoe_dims& dm = h->dm;
-  const size_t stated = (size_t)(8 * dm.k + 12) * T_max * dm.d_ff + 4 * (size_t)dm.G * dm.d * dm.d_ff + 256;
-  const size_t need = cmoe_backward_layout(dm, T_max).total;
-  return need > stated ? need : stated;
+  return cmoe_backward_layout(h->dm, T_max).total;
 }
 
 extern "C" int cmoe_backward(cmoe_handle* h, const cmoe_weights* w, const cmoe_f16* x, const cmoe_f16* dy, int32_t T,

@@ -202,8 +202,10 @@ def test_backward_rejects_bad_arguments_without_touching_the_gpu():
     w2 = B.Weights(*([fake] * 13))
     g = B.Grads(*([fake] * 9))
     need = L.cmoe_backward_workspace_bytes(h, 4096)
-    # per-token and per-pair FP16 activations and the transposed bases at least
-    assert need > (8 * 2 + 12) * 4096 * 3072 + 4 * 2 * 768 * 3072
+    # per-token FP16 activations, the transposed copies of x and dy and the transposed bases at least
+    assert need > 10 * 4096 * 3072 + 4 * 4096 * 768 + 4 * 2 * 768 * 3072
+    # and what these and the partial sums take, not the activations of the pairs that this path does not keep
+    assert need < (8 * 2 + 12) * 4096 * 3072 + 4 * 2 * 768 * 3072
     assert L.cmoe_backward_workspace_bytes(h, -1) == 0 and L.cmoe_backward_workspace_bytes(None, 8) == 0
     assert L.cmoe_backward(h, C.byref(w2), fake, fake, 8, fake, fake, None, fake, need, None) == B.ERR_INVALID_ARG
     assert L.cmoe_backward(h, C.byref(w2), None, fake, 8, fake, fake, C.byref(g), fake, need, None) == B.ERR_INVALID_ARG
@@ -213,6 +215,10 @@ def test_backward_rejects_bad_arguments_without_touching_the_gpu():
     assert L.cmoe_backward(h, C.byref(w2), fake, fake, 8, fake, fake, C.byref(g_bad), fake, need, None) == B.ERR_INVALID_ARG
     assert L.cmoe_backward(h, C.byref(w2), fake, fake, 8, fake, fake, C.byref(g), fake, 16, None) == B.ERR_WORKSPACE
     assert L.cmoe_backward(h, C.byref(w2), fake, fake, 8, fake, fake, C.byref(g), None, need, None) == B.ERR_WORKSPACE
+    L.cmoe_destroy(h)
+    # three experts per token: the activations of the pairs too
+    rc, h = _create(d=768, d_ff=3072, G=2, K=4, r=8, top_k=3, q_group=32)
+    assert L.cmoe_backward_workspace_bytes(h, 4096) > (8 * 3 + 12) * 4096 * 3072 + 4 * 2 * 768 * 3072
     L.cmoe_destroy(h)
     # more than 64 experts are supported too (pairs sorted by expert in two passes)
     rc, h = _create(d=64, d_ff=64, G=20, K=8, r=4, top_k=2, q_group=8)

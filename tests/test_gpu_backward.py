@@ -217,6 +217,30 @@ def test_backward_reads_no_codes_of_unused_experts(r):
     layer.close()
 
 
+def test_backward_writes_nothing_behind_its_workspace():
+    # exactly the stated bytes, and behind them what must stay as it is; a call of fewer tokens on the same buffer
+    import torch
+    import paper_2510_02345_amd as cm
+    for K, r, k, T in ((4, 16, 2, 530), (4, 16, 1, 97), (5, 32, 2, 300), (8, 4, 4, 300)):
+        cfg = ci.small_config("bw_guard", T=T, d=128, d_ff=1024, G=3, K=K, r=r, k=k, q=32, seed=161)
+        print(f"case {cfg}", flush=True)
+        w = ci.generate(cfg)
+        layer = cm.Layer(cfg.d, cfg.d_ff, cfg.G, K, r, k, cfg.q, w, T)
+        need = cm.lib().cmoe_backward_workspace_bytes(layer._h, T)
+        buf = torch.full((need + (1 << 20),), 0x5a, dtype=torch.uint8, device="cuda:0")
+        dy = _dev(np.random.default_rng(5).standard_normal((T, cfg.d)).astype(np.float16))
+        x = _dev(w["x"])
+        sel = layer.forward(x)
+        for n in (T, T - 4, T // 2, 1):
+            layer.bw_ws = buf[:need]
+            out = layer.backward(x[:n], dy[:n], sel["expert_idx"][:n], sel["gate"][:n])
+            torch.cuda.synchronize()
+            assert layer.bw_ws.data_ptr() == buf.data_ptr() and layer.bw_ws.numel() == need
+            assert bool((buf[need:] == 0x5a).all())
+            assert all(bool(torch.isfinite(v).all()) for v in out.values())
+        layer.close()
+
+
 def test_backward_config1():
     _run(ci.config(1))
 
