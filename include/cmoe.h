@@ -254,7 +254,9 @@ typedef struct cmoe_compress_config {
   float gate_gamma;
 } cmoe_compress_config;
 
-size_t cmoe_compress_workspace_bytes(const cmoe_compress_config *cfg); /* 0 if unsupported */
+/* Bytes of device workspace (0 if unsupported): one FP16 copy of the residuals, 2 * G * K * out_dim *
+ * in_dim, and the sketches, factors and partial sums. */
+size_t cmoe_compress_workspace_bytes(const cmoe_compress_config *cfg);
 int cmoe_compress(const cmoe_compress_config *cfg, const cmoe_f16 *W, const cmoe_f16 *omega,
                   cmoe_f16 *base, uint8_t *u_q, cmoe_f16 *u_s, uint8_t *v_q, cmoe_f16 *v_s,
                   float *report, void *workspace, size_t workspace_bytes, void *stream);

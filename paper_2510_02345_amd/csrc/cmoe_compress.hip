@@ -1030,11 +1030,7 @@ void orth_rows(const cmoe_compress_config& c, int n, half_t* X, half_t* tmp, cha
 }  // namespace
 
 extern "C" size_t cmoe_compress_workspace_bytes(const cmoe_compress_config* cfg) {
-  if (!compress_cfg_ok(cfg)) return 0;
-  // at least two copies of the residuals, as callers have been told (one is kept)
-  const size_t need = compress_layout(*cfg).total;
-  const size_t stated = 2 * (size_t)cfg->G * cfg->K * cfg->out_dim * cfg->in_dim * sizeof(half_t) + 256;
-  return need > stated ? need : stated;
+  return compress_cfg_ok(cfg) ? compress_layout(*cfg).total : 0;
 }
 
 extern "C" int cmoe_quantize_int4(const float* src, int64_t rows, int32_t L, int32_t q_group, uint8_t* codes,

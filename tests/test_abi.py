@@ -179,7 +179,8 @@ def test_new_entry_points_reject_bad_arguments_without_touching_the_gpu():
     L.cmoe_destroy(h)
     # compression: shapes outside the supported set give no workspace size and are refused
     good = B.CompressConfig(256, 128, 2, 4, 8, 32, 16, 2, 0, 0.0)
-    assert L.cmoe_compress_workspace_bytes(C.byref(good)) > 2 * 8 * 256 * 128 * 2        # Delta and its transpose
+    need = L.cmoe_compress_workspace_bytes(C.byref(good))
+    assert 8 * 256 * 128 * 2 < need < 2 * 8 * 256 * 128 * 2                  # Delta once, and what is small beside it
     for bad in (B.CompressConfig(250, 128, 2, 4, 8, 32, 16, 2, 0, 0.0),      # out_dim not a multiple of 64
                 B.CompressConfig(256, 128, 2, 4, 8, 48, 16, 2, 0, 0.0),      # q_group does not divide
                 B.CompressConfig(256, 128, 2, 4, 8, 32, 4, 2, 0, 0.0),       # sketch narrower than r

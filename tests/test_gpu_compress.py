@@ -166,6 +166,31 @@ WIDE_CASES = [
 ]
 
 
+@pytest.mark.parametrize("G,K,out_d,in_d,r,sketch,q", [(2, 4, 256, 128, 8, 16, 32), (1, 3, 192, 1088, 5, 13, 32),
+                                                       (16, 16, 64, 192, 24, 48, 16)])
+def test_compress_writes_nothing_behind_its_workspace(G, K, out_d, in_d, r, sketch, q):
+    import ctypes as C
+    import torch
+    import paper_2510_02345_amd as cm
+    from paper_2510_02345_amd import binding as B
+    print(f"case {G} {K} {out_d} {in_d} {r} {sketch} {q}", flush=True)
+    W = _dev(ci.generate_dense_experts(G, K, out_d, in_d, rank=6, residual_rel=0.3, noise_rel=0.01, seed=77))
+    omega = _dev(np.random.default_rng(78).standard_normal((sketch, in_d)).astype(np.float16))
+    o = cm.compress(W, omega, G, K, r, q)
+    _sync()
+    want = {n: v.clone() for n, v in o.items() if n != "_workspace"}
+    cfg = B.CompressConfig(out_d, in_d, G, K, r, q, sketch, 2, 0, 0.05)
+    need = cm.lib().cmoe_compress_workspace_bytes(C.byref(cfg))
+    buf = torch.full((need + (1 << 20),), 0x5a, dtype=torch.uint8, device="cuda:0")
+    p = {n: v.zero_().data_ptr() for n, v in o.items() if n != "_workspace"}
+    assert cm.lib().cmoe_compress(C.byref(cfg), W.data_ptr(), omega.data_ptr(), p["base"], p["u_q"], p["u_s"], p["v_q"],
+                                  p["v_s"], p["report"], buf.data_ptr(), need, torch.cuda.current_stream().cuda_stream) == 0
+    _sync()
+    assert bool((buf[need:] == 0x5a).all())
+    for n, v in want.items():
+        assert torch.equal(o[n], v), n
+
+
 @pytest.mark.parametrize("case", WIDE_CASES, ids=[c[0] for c in WIDE_CASES])
 def test_compress_many_experts(case):
     test_compress_against_truncated_svd(case)
