@@ -118,7 +118,9 @@ int cmoe_pack_weights(cmoe_handle *h, const cmoe_weights *w, void *packed, size_
 
 /* Bytes of device workspace that cmoe_permute / cmoe_ffn_forward / cmoe_combine /
  * cmoe_forward need for up to T_max tokens (one buffer serves all of them; contents
- * need not be preserved between calls).  Returns 0 for a NULL handle or T_max < 0. */
+ * need not be preserved between calls).  Returns 0 for a NULL handle or T_max < 0.  Above 256
+ * tokens and with K*r <= 128 the size includes 16.8 MB in which launches of cmoe_forward with
+ * few tiles keep parts of a contraction: a call with that much less is accepted and slower. */
 size_t cmoe_workspace_bytes(const cmoe_handle *h, int32_t T_max);
 
 /* Sec. 3.3, both stages.  x [T][d] f16 ->

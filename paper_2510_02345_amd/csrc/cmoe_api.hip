@@ -86,11 +86,13 @@ extern "C" int cmoe_destroy(cmoe_handle* h) {
 // SKINNY_T tokens, matrix cores above) lay the buffer out differently, so a buffer "for up to
 // T_max tokens" must hold the larger of the two: each layout grows with T inside its own
 // range, hence the largest weight-streaming layout is that of min(T_max, SKINNY_T).
-// Above SKINNY_T the size stated also holds parts of the down-projection's contraction (ffn_impl); a call that
-// brings no more than its layout goes without.
+// Above SKINNY_T the size stated also holds parts of the contraction of the down-projection where that is joined
+// with the combine (ffn_impl); a call that brings no more than its layout goes without.
 constexpr size_t SPLIT_BYTES = sizeof(float) * GEMM_PARTS * GEMM_PART + sizeof(int) * GEMM_PARTS;
+static bool combine_fuses(const cmoe_dims& dm) { return dm.KRp <= 128; }
+static size_t split_bytes(const cmoe_dims& dm, int T) { return T > SKINNY_T && combine_fuses(dm) ? SPLIT_BYTES : 0; }
 static size_t workspace_for_up_to(const cmoe_dims& dm, int T_max) {
-  const size_t big = T_max > SKINNY_T ? align_up(cmoe_layout(dm, T_max).total, 256) + SPLIT_BYTES : 0;
+  const size_t big = T_max > SKINNY_T ? align_up(cmoe_layout(dm, T_max).total, 256) + split_bytes(dm, T_max) : 0;
   const size_t small = cmoe_layout(dm, T_max < SKINNY_T ? T_max : SKINNY_T).total;
   return big > small ? big : small;
 }
@@ -334,7 +336,7 @@ static int ffn_impl(cmoe_handle* h, const cmoe_weights* w, const cmoe_f16* x, in
   const int* rperm = p2;
   const int* rowmap = rm;
   // when the combine is fused into the down-projection its U2 panel joins the same launch
-  const bool fuse = y_fused != nullptr && dm.KRp <= 128 && weights_combine_ok(w);
+  const bool fuse = y_fused != nullptr && combine_fuses(dm) && weights_combine_ok(w);
   half_t* u2t = !fuse ? nullptr : pk ? (half_t*)(pkb + PL.u2t) : (half_t*)(ws + L.u2t);
   if (!pk) CMOE_LAUNCH(TS_DEQUANT, launch_dequant_ffn(dm, *w, offsets, nullptr, v1cat, u1t, v2p, u2t, st));
   CMOE_LAUNCH(TS_T1, launch_t1(dm, (const half_t*)x, x_div, T, rperm, offsets, expert_idx, v1cat, t1ext, st));
@@ -443,7 +445,7 @@ extern "C" int cmoe_forward_multi(cmoe_handle* h, const cmoe_weights* w, const c
   const int g1 = opt->top_g, Tv = T * g1;
   if (workspace == nullptr || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0) return CMOE_ERR_WORKSPACE;
   size_t base_bytes = align_up(cmoe_layout(h->dm, Tv).total, 256);
-  const size_t rb = rep_bytes(h->dm, (size_t)Tv), more = Tv > SKINNY_T ? align_up(SPLIT_BYTES, 256) : 0;
+  const size_t rb = rep_bytes(h->dm, (size_t)Tv), more = align_up(split_bytes(h->dm, Tv), 256);
   if (workspace_bytes < base_bytes + rb) return CMOE_ERR_WORKSPACE;
   if (workspace_bytes >= base_bytes + more + rb) base_bytes += more;
   hipStream_t st = (hipStream_t)stream;

@@ -86,6 +86,18 @@ def test_workspace_for_t_max_serves_every_smaller_t():
         L.cmoe_destroy(h)
 
 
+def test_space_for_parts_of_a_contraction_only_where_there_can_be_any():
+    # the down-projection comes in parts where it is joined with the combine: K * r <= 128, above 256 tokens
+    L = cm.lib()
+    parts = 4 * 256 * 128 * 128 + 4 * 256
+    for r, has in ((8, True), (16, True), (32, False)):
+        rc, h = _create(d=768, d_ff=3072, G=2, K=8, r=r, top_k=2, q_group=32)
+        assert rc == B.OK
+        grown = L.cmoe_workspace_bytes(h, 512) - L.cmoe_workspace_bytes(h, 0)     # what 512 tokens take beside the panels
+        assert (grown > parts) == has and grown - has * parts < 512 * 16384, (r, grown)
+        L.cmoe_destroy(h)
+
+
 def test_backward_workspace_for_t_max_serves_every_smaller_t():
     # the runs that the partial factor gradients come in grow with T and their number falls where they do
     L = cm.lib()
