@@ -669,9 +669,15 @@ __global__ __launch_bounds__(256) void cmp_quantize_kernel(const float* __restri
   uint8_t* dst = codes + row * (L / 2) + (long)g * (q / 2);
   for (int i = 0; i < q; i += 2) dst[i / 2] = (uint8_t)(quant_code(s[i], (float)sc) | quant_code(s[i + 1], (float)sc) << 4);
 }
+}  // namespace
+// The word-wise kernel: its group lengths, and no more words than a launch has threads (a thread per group goes further).
+bool quantize_by_words(long rows, int L, int q) {
+  return q >= 8 && q <= 512 && (q & (q - 1)) == 0 && rows * (L / 8) <= (1L << 32) - 256;
+}
+namespace {
 hipError_t launch_quantize(const float* src, long rows, int L, int q, const int* gate, int rows_per_expert, uint8_t* codes,
                            half_t* scales, hipStream_t st) {
-  if (q >= 8 && q <= 512 && (q & (q - 1)) == 0) {
+  if (quantize_by_words(rows, L, q)) {
     const long words = rows * (L / 8);
     hipLaunchKernelGGL(cmp_quantize8_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, src, words, L, q, gate,
                        rows_per_expert, codes, scales);

@@ -7,10 +7,23 @@ import paper_2510_02345_amd as cm
 HIP_ERROR_INVALID_VALUE = 1
 
 
-def test_grouped_product_takes_no_more_groups_than_lanes():
+def _internal(name):
     names = subprocess.run(["nm", "-D", "--defined-only", cm.binding.lib_path()], check=True, capture_output=True,
                            text=True).stdout.split()
-    f = getattr(cm.lib(), next(n for n in names if "launch_gemm_plain" in n))
+    return getattr(cm.lib(), next(n for n in names if name in n))
+
+
+def test_quantiser_takes_a_thread_per_word_only_while_a_launch_has_as_many():
+    f = _internal("quantize_by_words")
+    f.restype, f.argtypes = C.c_bool, [C.c_long, C.c_int, C.c_int]
+    for q in (8, 64, 512):
+        assert f(1, 512, q) and f((1 << 26) - 4, 512, q)
+        assert not f(1 << 26, 512, q) and not f(1 << 33, 512, q)     # 2^32 words and more
+    assert not f(1, 96, 24) and not f(1, 1024, 1024) and not f(1, 64, 2)
+
+
+def test_grouped_product_takes_no_more_groups_than_lanes():
+    f = _internal("launch_gemm_plain")
     P, I, L = C.c_void_p, C.c_int, C.c_long
     f.restype = I
     # W, w_gstride, ldw, N, X, ldx, gather, x_div, Kc, offsets, n_groups, rows, krange, rowmap, out, ldo, out_f32, stream,
