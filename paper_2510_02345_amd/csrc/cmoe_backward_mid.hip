@@ -21,8 +21,9 @@ constexpr int MD_THREADS = 512;   // eight wavefronts: 4 x 2 of 32 hidden units 
 
 // Phi(u) and exp(-u^2 / 2): the upper tail Phi(-|u|) = exp(-u^2 / 2) P(t), t = 1 / (1 + 0.32 |u|), P of degree 5
 // fitted to 0.5 erfc(x / sqrt 2) exp(x^2 / 2) with weight (1 + x) exp(-x^2 / 2) on 0 <= x <= 7 (least
-// squares, reweighted towards the largest error).  In FP32 |dPhi| < 2.0e-7, and |d GELU| < 3.9e-7 where
-// an erff leaves 4.5e-7 (|u| <= 9); one reciprocal, one exponential and six FMAs serve the function and
+// squares, reweighted towards the largest error).  In FP32, with the reciprocal and the exponential up to an ulp off,
+// |dPhi| < 3.2e-7 (2.2e-7 with both rounded correctly) and |d GELU'| < 3.4e-7; |d GELU| < 3.9e-7 where
+// an erff leaves 4.5e-7 (|u| <= 9).  One reciprocal, one exponential and six FMAs serve the function and
 // its derivative.
 __device__ __forceinline__ void phi_exp(float u, float& phi, float& ex) {
   const float t = __builtin_amdgcn_rcpf(fmaf(0.32f, fabsf(u), 1.f));

@@ -217,6 +217,45 @@ def test_backward_reads_no_codes_of_unused_experts(r):
     layer.close()
 
 
+def test_backward_gelu_in_single_precision():
+    # dL/d(logit) of two experts whose pre-activations are u and 0 at the one hidden unit that dy sees is g_0 g_1 GELU(u) in
+    # FP32, g_0 = g_1 = 1/2 without a further rounding: the function over [-9, 9].  GELU'(u) reaches an output only through
+    # FP16 (dx = g_0 GELU'(u), as the second expert's base and rank parts cancel).
+    import math
+    import torch
+    import paper_2510_02345_amd as cm
+    d, f, r, q = 64, 64, 4, 8
+    u = np.concatenate([np.arange(-9, 9, 1 / 256), np.geomspace(1e-4, 9, 400), -np.geomspace(1e-4, 9, 400)]).astype(np.float16)
+    T = len(u)
+    w = dict(x=np.zeros((T, d), np.float16), router_cluster=np.zeros((1, d), np.float16),
+             router_expert=np.zeros((2, d), np.float16), cluster_bias=None, w1_base=np.zeros((1, f, d), np.float16),
+             w2_base=np.zeros((1, d, f), np.float16))
+    w["x"][:, 0] = u
+    w["w1_base"][0, 0, 0] = w["w2_base"][0, 0, 0] = 1
+    for n, L in (("v1", d), ("u1", f), ("v2", f), ("u2", d)):
+        w[n + "_q"] = np.zeros((2, r, L // 2), np.uint8)
+        w[n + "_s"] = np.zeros((2, r, L // q), np.float16)
+    w["v1_q"][1, 0, 0], w["v1_s"][1, 0, 0] = 1, 1          # t1 = u for the second expert,
+    w["u1_q"][1, 0, 0], w["u1_s"][1, 0, 0] = 15, 1         # h = u - t1 = 0
+    dy = np.zeros((T, d), np.float16)
+    dy[:, 0] = 1
+    layer = cm.Layer(d, f, 1, 2, r, 2, q, w, T)
+    eidx = np.tile(np.array([0, 1], np.int32), (T, 1))
+    out = layer.backward(_dev(w["x"]), _dev(dy), _dev(eidx), torch.full((T, 2), 0.5, device="cuda:0"))
+    torch.cuda.synchronize()
+    x = u.astype(np.float64)
+    phi = np.array([0.5 * math.erfc(-v / math.sqrt(2)) for v in x])
+    err = np.abs(4.0 * out["d_logits"][:, 0].cpu().numpy().astype(np.float64) - x * phi)
+    print(f"  gelu: max error {err.max():.3e}", flush=True)
+    # u Phi(u): Phi to 3.2e-7 and the product's rounding, at most 3.9e-7 together
+    assert (err <= np.minimum(3.9e-7, 3.2e-7 * np.abs(x) + 2.0 ** -24 * np.abs(x * phi))).all()
+    grad = phi + x * np.exp(-x * x / 2) / math.sqrt(2 * math.pi)
+    got = 2.0 * out["dx"][:, 0].cpu().numpy().astype(np.float64)
+    # the sum of dh in FP16, GELU'(u) / 2 + 1 / 4; q = -1 / 4
+    assert (np.abs(got - grad) <= 2 * 2.0 ** -11 * (np.abs(grad) / 2 + 0.25) + 1e-6).all(), np.abs(got - grad).max()
+    layer.close()
+
+
 def test_backward_writes_nothing_behind_its_workspace():
     # exactly the stated bytes, and behind them what must stay as it is; a call of fewer tokens on the same buffer
     import torch
