@@ -56,7 +56,7 @@ def _waits_for_lds(i):
 
 # The loops that refill a stage of LDS behind a bare barrier: the stage was read an iteration ago, and the
 # barrier is passed only with those reads completed, wherever the compiler puts the products.
-@pytest.mark.parametrize("kernel", ["route_rows_lds_kernel", "t1_rows_kernel", "gemm_thin_kernel"])
+@pytest.mark.parametrize("kernel", ["route_rows_lds_kernel", "t1_rows_kernel", "gemm_thin_kernel", "cmp_stream_kernel"])
 def test_lds_reads_are_complete_before_a_stage_is_refilled(kernels, kernel):
     n = 0
     for name, ins in kernels.items():
