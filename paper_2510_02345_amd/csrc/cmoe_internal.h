@@ -52,10 +52,10 @@ struct cmoe_handle {
   cmoe_timing tm;
 };
 
-// Workspace layout for T tokens (byte offsets, all 256-byte aligned).
 // Parts of the contraction of the matrix-core down-projection: at most one per CU, each a tile of FP32 sums.
 constexpr int GEMM_PARTS = 256, GEMM_PART = 128 * 128;
 
+// Workspace layout for T tokens (byte offsets, all 256-byte aligned).
 struct cmoe_ws_layout {
   size_t blk_counts;  // int32 [n_blocks + 1][64 G] permute: per-block counts of (cluster, pair key)
   size_t sort_i32;    // int32 [2][T]          expert-pair order inside clusters: rowmap, perm2
@@ -183,7 +183,7 @@ hipError_t launch_combine(const cmoe_dims& dm, const half_t* u2t, const half_t* 
 // the transposed copies whose groups (clusters) are padded to 32.
 struct cmoe_bw_layout {
   int M, Tpad;
-  size_t counts, permc, invc, offc, permm, invm, offe, krange_c, ssrc_c, dl;
+  size_t counts, permc, invc, offc, permm, invm, offe, krange_c, ssrc_c, dl;   // mid: permc, invc and rowmap are by-products of the sort
   size_t w1bt, w2bt;                          // f16 transposed bases
   size_t hb, dab, dhsum16;                    // f16 [T][d_ff]: token order, or [d_ff/32][T][32] by cluster (mid)
   size_t qq, ss;                              // f16 [M][32] rank-space rows of the pairs, sorted by expert

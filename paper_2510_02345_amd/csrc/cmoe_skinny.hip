@@ -155,47 +155,67 @@ __device__ __forceinline__ bool skinny_tile(const int* offsets, int id, int nx, 
 }
 
 // ---------------------------------------------------------------- t1 = V1_e x
-// t1[tok][j][:] for token tok and its selected expert j, by the calling workgroup: a
-// wavefront takes T1_ROWS rank rows at a time, all loads of a step in flight before the first is used; INT4 codes
-// dequantised on the fly (Sec. 3.4).
-constexpr int T1_ROWS = 4;
-__device__ __forceinline__ void skinny_t1_job(int tok, int j, const half_t* __restrict__ x,
-                                              const int* __restrict__ expert_idx,
-                                              const uint8_t* __restrict__ v1_q, const half_t* __restrict__ v1_s,
-                                              int d, int q, int r, int k, int x_div, int n_exp,
-                                              half_t* __restrict__ t1) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+// t1[tok][j][:] for token tok and its selected expert j, by the calling workgroup of four wavefronts: a wavefront
+// takes ROWS rank rows at a time and U chunks of eight elements a lane, all loads of a step in flight before the first
+// is used; INT4 codes dequantised on the fly (Sec. 3.4).
+template <int ROWS, int U>
+__device__ __forceinline__ void skinny_t1_rows(int tok, int j, const half_t* __restrict__ x,
+                                               const int* __restrict__ expert_idx,
+                                               const uint8_t* __restrict__ v1_q, const half_t* __restrict__ v1_s,
+                                               int d, int q, int r, int k, int x_div, int n_exp,
+                                               half_t* __restrict__ t1) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
   const int e = min(max(expert_idx[(size_t)tok * k + j], 0), n_exp - 1);
   const half_t* xr = x + (size_t)(tok / x_div) * d;
-  for (int rho0 = wave * T1_ROWS; rho0 < r; rho0 += nw * T1_ROWS) {
-    float acc[T1_ROWS] = {};
-    for (int ch0 = lane; ch0 < d / 8; ch0 += 256) {   // 8 elements per chunk: 4 code bytes, one scale
-      unsigned bytes[T1_ROWS][4];
-      half_t sc[T1_ROWS][4];
-      half8 xv[4];
+  for (int rho0 = wave * ROWS; rho0 < r; rho0 += nw * ROWS) {   // r is a multiple of ROWS
+    float acc[ROWS] = {};
+    for (int ch0 = lane; ch0 < d / 8; ch0 += 64 * U) {   // 8 elements per chunk: 4 code bytes, one scale
+      unsigned bytes[ROWS][U];
+      half_t sc[ROWS][U];
+      half8 xv[U];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < U; ++u) {
         const int ch = ch0 + 64 * u;
         const bool in = ch < d / 8;
         xv[u] = in ? *(const half8*)(xr + ch * 8) : half8{0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-        for (int i = 0; i < T1_ROWS; ++i) {
-          const size_t row = (size_t)e * r + min(rho0 + i, r - 1);
+        for (int i = 0; i < ROWS; ++i) {
+          const size_t row = (size_t)e * r + rho0 + i;
           bytes[i][u] = in ? *(const unsigned*)(v1_q + row * (d / 2) + ch * 4) : 0u;
           sc[i][u] = in ? v1_s[row * (d / q) + (ch * 8) / q] : (half_t)0.f;
         }
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int i = 0; i < T1_ROWS; ++i) acc[i] = fmaf((float)sc[i][u], code_dot8(bytes[i][u], xv[u]), acc[i]);
+        for (int i = 0; i < ROWS; ++i) acc[i] = fmaf((float)sc[i][u], code_dot8(bytes[i][u], xv[u]), acc[i]);
     }
 #pragma unroll
-    for (int i = 0; i < T1_ROWS; ++i) {
+    for (int i = 0; i < ROWS; ++i) {
       const float sum = wave_sum(acc[i]);
-      if (lane == 0 && rho0 + i < r) t1[((size_t)tok * k + j) * r + rho0 + i] = (half_t)sum;
+      if (lane == 0) t1[((size_t)tok * k + j) * r + rho0 + i] = (half_t)sum;
     }
   }
+}
+// Four rows a wavefront from rank 16 on, as many as give all four wavefronts work below, and no more chunks in flight
+// than a row of up to 1024 elements has: with four rows and chunks always, half the wavefronts idled at rank 8 and half
+// the products were of zeros at width 1024 (expert computation of 256 tokens, four experts of rank 8 each, 4 clusters
+// of 1024 x 4096: 49.8 -> 47.0 us, a wavefront per rank row 47.4).
+__device__ __forceinline__ void skinny_t1_job(int tok, int j, const half_t* __restrict__ x,
+                                              const int* __restrict__ expert_idx,
+                                              const uint8_t* __restrict__ v1_q, const half_t* __restrict__ v1_s,
+                                              int d, int q, int r, int k, int x_div, int n_exp,
+                                              half_t* __restrict__ t1) {
+  auto go = [&](auto rows, auto u) {
+    skinny_t1_rows<decltype(rows)::value, decltype(u)::value>(tok, j, x, expert_idx, v1_q, v1_s, d, q, r, k, x_div, n_exp,
+                                                              t1);
+  };
+  auto pick = [&](auto u) {
+    if (r == 4) go(std::integral_constant<int, 1>{}, u);
+    else if (r == 8) go(std::integral_constant<int, 2>{}, u);
+    else go(std::integral_constant<int, 4>{}, u);
+  };
+  if (d <= 1024) pick(std::integral_constant<int, 2>{}); else pick(std::integral_constant<int, 4>{});
 }
 
 // ---------------------------------------------------------------- residual-down

@@ -46,6 +46,14 @@ def test_groups_of_experts(G, K, r, k):
     _check(ci.small_config("groups", T=5, d=128, d_ff=2112, G=G, K=K, r=r, k=k, q=32, seed=r + k), 0.0)
 
 
+# V1 x beside the stream: one, two and four rank rows a wavefront, once and twice around, widths of part of a
+# wavefront's chunks, of all of them and of one step more, for both numbers of chunks; factors that make up much of y
+@pytest.mark.parametrize("r", [4, 8, 16, 32])
+@pytest.mark.parametrize("d", [64, 1024, 1088, 2112])
+def test_rank_rows_of_few_tokens(r, d):
+    _check(ci.small_config("t1few", T=21, d=d, d_ff=64, G=2, K=4, r=r, k=2, q=32, factor_std=0.1, seed=r + d), 0.0)
+
+
 def _check(cfg, skew):
     import torch
 
