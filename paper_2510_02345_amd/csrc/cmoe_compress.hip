@@ -622,8 +622,8 @@ __global__ __launch_bounds__(256) void cmp_apply_kernel(const float* __restrict_
 // 0 when the scale rounds to 0 or the row's expert is gated off (gate != NULL and
 // gate[row / rows_per_expert] != 0).
 __device__ __forceinline__ half_t quant_scale(float absmax, bool off) { return off ? (half_t)0.f : (half_t)(absmax / 7.0f); }
-__device__ __forceinline__ unsigned quant_code(float w, float sc) {
-  return sc > 0.f ? (unsigned)(int)fminf(fmaxf(rintf(w / sc), -7.f), 7.f) & 0xFu : 0u;
+__device__ __forceinline__ unsigned quant_code(float w, float sc) {   // sc > 0
+  return (unsigned)(int)fminf(fmaxf(rintf(w / sc), -7.f), 7.f) & 0xFu;
 }
 // q = 8, 16, .. 512: a thread takes eight elements (32 contiguous bytes, one code word), q / 8 lanes a group.
 // 33 MB of factors (64 experts, rank 16, 8192): 74 us with a thread per group of 64.
@@ -648,7 +648,7 @@ __global__ __launch_bounds__(256) void cmp_quantize8_kernel(const float* __restr
   if (i * 8 % q == 0) scales[i * 8 / q] = sc;
   unsigned w = 0;
 #pragma unroll
-  for (int u = 0; u < 8; ++u) w |= quant_code(v[u], (float)sc) << (4 * u);
+  for (int u = 0; u < 8; ++u) w |= sc > (half_t)0.f ? quant_code(v[u], (float)sc) << (4 * u) : 0u;
   *(unsigned*)(codes + i * 4) = w;
 }
 // Any even q: one thread per group.
@@ -665,9 +665,14 @@ __global__ __launch_bounds__(256) void cmp_quantize_kernel(const float* __restri
   float absmax = 0.f;
   for (int i = 0; i < q; ++i) absmax = fmaxf(absmax, fabsf(s[i]));
   const half_t sc = quant_scale(absmax, off);
+  const float scf = (float)sc;
   scales[row * gpr + g] = sc;
   uint8_t* dst = codes + row * (L / 2) + (long)g * (q / 2);
-  for (int i = 0; i < q; i += 2) dst[i / 2] = (uint8_t)(quant_code(s[i], (float)sc) | quant_code(s[i + 1], (float)sc) << 4);
+  for (int i = 0; i < q; i += 2) {
+    unsigned c = 0u;
+    if (scf > 0.f) c = quant_code(s[i], scf) | quant_code(s[i + 1], scf) << 4;
+    dst[i / 2] = (uint8_t)c;
+  }
 }
 }  // namespace
 // The word-wise kernel: its group lengths, and no more words than a launch has threads (a thread per group goes further).
