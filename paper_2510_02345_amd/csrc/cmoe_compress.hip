@@ -728,9 +728,10 @@ __device__ __forceinline__ float cmp_nib(const uint8_t* row, int n) {
 // Columns are its rows (A = V), rows its columns (B = U); a wavefront owns 16 rows, and tile row
 // 4 q + i of block a holds column 8 q + 4 a + i of 32, so that blocks 0 and 1 give lane (t, q) the
 // eight consecutive columns 8 q .. 8 q + 7 of row t, as it loads them from W and base.
-constexpr int CE_CT = 4, CE_COLS = 64 * CE_CT;
+// CE_CT = 4, or as many as a narrower matrix has: 15 experts of 2112 x 64 28.5 us on the FP32 instruction, 29.9 with four
+// tiles loaded of which one exists, 25.9 with one (each with its launches and the wait of the caller).
 // A panel row (one column of V, one row of U): the upper parts of RB rank values, then the lower ones.
-template <int RB>
+template <int RB, int CE_CT>
 __global__ __launch_bounds__(256) void cmp_error_kernel(const half_t* __restrict__ W, const half_t* __restrict__ base,
                                                         const uint8_t* __restrict__ u_q,
                                                         const half_t* __restrict__ u_s,
@@ -738,7 +739,7 @@ __global__ __launch_bounds__(256) void cmp_error_kernel(const half_t* __restrict
                                                         const half_t* __restrict__ v_s, int G, int K, int out_d, int in_d,
                                                         int r, int q, int tiles_x, int tiles_y,
                                                         float* __restrict__ epart) {
-  constexpr int LD = 2 * RB + 8;
+  constexpr int LD = 2 * RB + 8, CE_COLS = 64 * CE_CT;
   __shared__ __attribute__((aligned(16))) half_t us[64][LD], vs[CE_COLS][LD];
   __shared__ float red[4][2];
   // Workgroups are dealt round-robin to the 8 XCDs; the K experts of one (cluster, tile) take
@@ -916,12 +917,17 @@ __global__ __launch_bounds__(64) void cmp_error_finish_kernel(const float* __res
 // epart and then err[e * stride] of the stored form.
 void launch_error(const cmoe_compress_config& c, const half_t* W, const half_t* base, const uint8_t* u_q, const half_t* u_s,
                   const uint8_t* v_q, const half_t* v_s, float* epart, int stride, float* err, hipStream_t st) {
-  const int tx = (c.in_dim / 64 + CE_CT - 1) / CE_CT, ty = c.out_dim / 64;
+  const int ct = c.in_dim <= 64 ? 1 : c.in_dim <= 128 ? 2 : 4;
+  const int tx = (c.in_dim / 64 + ct - 1) / ct, ty = c.out_dim / 64;
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3((unsigned)((c.G * tx * ty + 7) / 8 * 8 * c.K)), dim3(256), 0, st, W, base, u_q, u_s, v_q, v_s,
                        c.G, c.K, c.out_dim, c.in_dim, c.r, c.q_group, tx, ty, epart);
   };
-  if (c.r <= 16) go(cmp_error_kernel<16>); else go(cmp_error_kernel<32>);
+  auto pick = [&](auto rb) {
+    constexpr int RB = decltype(rb)::value;
+    if (ct == 1) go(cmp_error_kernel<RB, 1>); else if (ct == 2) go(cmp_error_kernel<RB, 2>); else go(cmp_error_kernel<RB, 4>);
+  };
+  if (c.r <= 16) pick(std::integral_constant<int, 16>{}); else pick(std::integral_constant<int, 32>{});
   hipLaunchKernelGGL(cmp_error_finish_kernel, dim3(c.G * c.K), dim3(64), 0, st, (const float*)epart, tx * ty, stride, err);
 }
 

@@ -102,7 +102,7 @@ def test_reconstruction_error_of_a_given_stored_form():
 # ranks off the matrix instruction's four rows, one and several column tiles per workgroup, a
 # ragged last one, group lengths with and without whole code words
 @pytest.mark.parametrize("r,q,out_d,in_d", [(1, 32, 64, 64), (3, 2, 128, 320), (7, 4, 64, 576), (13, 64, 192, 256),
-                                            (30, 32, 64, 128), (32, 64, 128, 640)])
+                                            (30, 32, 64, 128), (32, 64, 128, 640), (32, 16, 128, 64), (5, 32, 192, 128)])
 def test_reconstruction_error_at_odd_ranks_and_widths(r, q, out_d, in_d):
     import paper_2510_02345_amd as cm
     G, K = 3, 2
