@@ -133,14 +133,14 @@ __device__ __forceinline__ void skinny_reduce(float* red, int wave, int lane, co
 struct SkinnyTile {
   int c, n0, m0, m_end, s;
 };
-// Stream workgroup `id` of a launch of nx row blocks x `split` parts of the contraction (t.s) x slots (row
+// Stream workgroup `id` of a launch of nx row blocks x 2^split parts of the contraction (t.s) x slots (row
 // block fastest).  A slot is a pass over `cols` tokens of a cluster, m_end the end of the pass; the slots
 // are the passes that exist, found from the offsets.
 __device__ __forceinline__ bool skinny_tile(const int* offsets, int id, int nx, int split, int G, int cols,
                                             SkinnyTile& t) {
   int xb = id % nx;
-  const int slot = id / nx / split;
-  t.s = id / nx % split;
+  const int slot = id / nx >> split;
+  t.s = id / nx & ((1 << split) - 1);
   // Workgroups are dealt round-robin to the 8 XCDs.  The INT4 factor rows are 128-byte
   // lines shared by 8 neighbouring row blocks, so inside every run of 64 blocks the 8
   // workgroups that land on one XCD take 8 neighbouring row blocks: each line is then
@@ -424,9 +424,10 @@ __global__ __launch_bounds__(256, (SkRing<COLS>::OCC)) void skinny_base_kernel(
   for (int rb = 0; rb < SK_RB; ++rb)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[rb][v] = 0.f;
-  const int iters = Kc / 64, shares = SK_WAVES * split, share = t.s * SK_WAVES + wv;
+  static_assert(SK_WAVES == 4, "shares of the contraction");
+  const int iters = Kc / 64, share = t.s * SK_WAVES + wv;
   skinny_stream<COLS, NT>(wrow, 8 * w_ld, w_blk ? (size_t)w_blk : 32, brow, smem + wv * RG::RING,
-                          smem_lds + wv * RG::RING, lane, share * iters / shares, (share + 1) * iters / shares, acc);
+                          smem_lds + wv * RG::RING, lane, share * iters >> (2 + split), (share + 1) * iters >> (2 + split), acc);
   __syncthreads();  // every ring has been consumed: its space becomes red
   float16v hb;
   skinny_reduce(red, wave, lane, acc, hb);
@@ -733,7 +734,7 @@ hipError_t launch_stream(const cmoe_dims& dm, int cols, const half_t* X, const i
                          const SideArgs& sa, const FewSortArgs& fs, hipStream_t st) {
   const int nx = N / SK_ROWS;
   const int slots = T < dm.G + T / cols ? T : dm.G + T / cols;   // at most: a slot holds a token, all but G of them `cols`
-  const dim3 grid((unsigned)nx * slots * split + sa.n_side), block(256);
+  const dim3 grid(((unsigned)nx * slots << split) + sa.n_side), block(256);
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, grid, block, 0, st, X, gather, W, offsets, N, Kc, out, parts, split, T, nx, dm.G, w_blk, sa, fs);
   };
@@ -760,8 +761,8 @@ hipError_t launch_skinny_hb(const cmoe_dims& dm, const cmoe_weights& w, const ha
   auto go = [&](auto side) {
     constexpr int SIDE = decltype(side)::value;
     if (cluster_id != nullptr)
-      return launch_stream<SIDE, true>(dm, cols, x, perm, w1, offsets, dm.d_ff, dm.d, hb, nullptr, 1, T, w_blk, sa, fs, st);
-    return launch_stream<SIDE, false>(dm, cols, x, perm, w1, offsets, dm.d_ff, dm.d, hb, nullptr, 1, T, w_blk, sa, fs, st);
+      return launch_stream<SIDE, true>(dm, cols, x, perm, w1, offsets, dm.d_ff, dm.d, hb, nullptr, 0, T, w_blk, sa, fs, st);
+    return launch_stream<SIDE, false>(dm, cols, x, perm, w1, offsets, dm.d_ff, dm.d, hb, nullptr, 0, T, w_blk, sa, fs, st);
   };
   if (t1 == nullptr) return go(std::integral_constant<int, SIDE_NONE>{});
   sa.x = x;
@@ -804,7 +805,7 @@ hipError_t launch_skinny_resid_up(const cmoe_dims& dm, const cmoe_weights& w, in
   return hipGetLastError();
 }
 
-// Parts of the contraction of the down-projection.  A launch that leaves CUs idle lasts as long as a wavefront's
+// Parts of the contraction of the down-projection, as a power of two.  A launch that leaves CUs idle lasts as long as a wavefront's
 // chain of steps; parts shorten the chain, until the launch has 192 workgroups (256 where the base comes from HBM
 // and the loads take longer), two steps a wavefront are left or the parts no longer fit the space of the factor
 // panels, which this path does not use.  Down-projection of 1, 2 and 4 parts, one token: 768 x 3072 6.7, 5.8 and
@@ -813,10 +814,10 @@ hipError_t launch_skinny_resid_up(const cmoe_dims& dm, const cmoe_weights& w, in
 inline int down_split(const cmoe_dims& dm, int T, int cols) {
   const int slots = T < dm.G + T / cols ? T : dm.G + T / cols, most = stream_once(dm) ? 256 : 192;
   const size_t room = sizeof(half_t) * 2 * dm.G * dm.KRp * ((size_t)dm.d + dm.d_ff);
-  int split = 4;
-  while (split > 1 && (dm.d / SK_ROWS * slots * split > most || dm.d_ff / 64 < 2 * SK_WAVES * split ||
-                       sizeof(float) * split * T * dm.d > room))
-    split /= 2;
+  int split = 2;
+  while (split > 0 && ((dm.d / SK_ROWS * slots << split) > most || dm.d_ff / 64 < 2 * SK_WAVES << split ||
+                       sizeof(float) * (T * (size_t)dm.d << split) > room))
+    --split;
   return split;
 }
 
@@ -832,7 +833,7 @@ hipError_t launch_skinny_down(const cmoe_dims& dm, const cmoe_weights& w, const 
   const long w_blk = w.packed ? (long)dm.d * 32 : 0;
   const int cols = stream_cols(dm, T, true);
   if (ures == nullptr)
-    return launch_stream<SIDE_NONE, false>(dm, cols, a, nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted, nullptr, 1, T,
+    return launch_stream<SIDE_NONE, false>(dm, cols, a, nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted, nullptr, 0, T,
                                            w_blk, sa, FewSortArgs{}, st);
   sa.expert_idx = expert_idx;
   sa.gate = gate;
@@ -851,7 +852,7 @@ hipError_t launch_skinny_down(const cmoe_dims& dm, const cmoe_weights& w, const 
   sa.n_jobs = T * ((dm.d + 2047) / 2048);
   sa.n_side = (sa.n_jobs + 7) & ~7;
   return launch_stream<SIDE_URES, false>(dm, cols, a, nullptr, w2, offsets, dm.d, dm.d_ff, y_base_sorted,
-                                         split > 1 ? parts : nullptr, split, T, w_blk, sa,
+                                         split > 0 ? parts : nullptr, split, T, w_blk, sa,
                                          FewSortArgs{}, st);
 }
 
@@ -862,8 +863,8 @@ hipError_t launch_skinny_add(const cmoe_dims& dm, const half_t* y_base_sorted, c
                        dm.d, y);
   };
   switch (down_split(dm, T, stream_cols(dm, T, true))) {
-    case 1: go(skinny_add_kernel<1>); break;
-    case 2: go(skinny_add_kernel<2>); break;
+    case 0: go(skinny_add_kernel<1>); break;
+    case 1: go(skinny_add_kernel<2>); break;
     default: go(skinny_add_kernel<4>); break;
   }
   return hipGetLastError();
