@@ -374,16 +374,18 @@ __device__ __forceinline__ void tile_small(const GemmArgs& g, const Epi& epi, ch
 // Where the quarters of the leftover still leave CUs idle, the down-projection also cuts their contraction, into as many
 // parts as there are CUs (and 10 blocks of it in a part): one more exchange of the sums, through memory,
 // costs about 8 us (with ordinary stores and a device fence in each workgroup 30), a step of 64 elements takes 0.42.
-// So a contraction below 56 blocks stays whole.  Whole forward with parts and without, 777 tokens of 4 clusters of width
-// 1024 and contraction 1024 63.4 and 59.4, 1536 63.8 and 64.0, 1792 65.1 and 66.8, 2560 67.1 and 72.1; of 2 of width 128
-// and 512 45.2 and 42.8, 1024 47.8 and 46.3, 1792 49.8 and 52.0.  Of 4 of width 512 and 2048 in four parts 57.4, in eight of 8
-// blocks 60.7, whole 60.8.
+// So a contraction below 50 blocks stays whole.  Whole forward with parts and without, 777 tokens of 4 clusters of width 1024
+// and contraction 1024 63.4 and 59.4, 1536 63.7 and 64.0, 1728 64.8 and 66.0, 2560 67.1 and 72.1; of 2 of width 768 and 1408
+// 60.2 and 58.7, 1600 60.2 and 60.5.  Of 4 of width 512 and 2048 in four parts 57.4, in eight of 8 blocks 60.7, whole 60.8.
+// Groups of at most a quarter's tokens are bound by their weights where there are several of them on an XCD: four
+// tiles (300 tokens of 16 of width 512) 1728 60.2 and 58.7, 2048 60.3 and 60.4, eight (width 1024) 1728 69.8 and 67.2,
+// 3072 81.1 and 80.5, 777 tokens 89.2 and 91.8; so they are cut from 64 blocks on with four tiles, from 96 with eight.
 // 4 clusters of 1024 x 4096: 777 tokens (2 tiles per XCD) 41 -> 29 us, 1200 (3) 43 -> 35; 2 of 768 x 3072,
 // 300 tokens 30 -> 23; 8 of 2048 x 8192, 300 tokens (8, upper quarters only) 73 -> 63; 16384 Zipf tokens, whole
 // forward 429 -> 422.
 constexpr int XSM = 4, XSN = 8, XCD_CUS = 32;
 constexpr int MAX_SPLIT = 3;   // log2 of the parts of the contraction of a quarter, at most
-constexpr int SPLIT_BLOCKS = 56, PART_BLOCKS = 10;   // 32-element blocks of a contraction that is split, and of a part
+constexpr int SPLIT_BLOCKS = 50, PART_BLOCKS = 10;   // 32-element blocks of a contraction that is cut and of a part, at least
 static_assert(8 * XCD_CUS == GEMM_PARTS, "a part per CU");
 template <class Epi>
 __global__ __launch_bounds__(512, 1) void gemm_kernel(GemmArgs g, Epi epi) {
@@ -401,10 +403,12 @@ __global__ __launch_bounds__(512, 1) void gemm_kernel(GemmArgs g, Epi epi) {
   int pieces = cut, split = 0;   // log2 of a leftover tile's pieces and of the parts of the contraction of each
   if constexpr (Epi::SPLITS) {
     const int left = mine - full;
-    if (g.parts != nullptr && cut == 2 && left > 0) {   // only with SPLIT_BLOCKS and more
+    if (g.parts != nullptr && cut == 2 && left > 0) {
       // no group with more tokens than a quarter: its lower quarters are empty
       if (__ballot(rt.hi - rt.lo > Quarter::BM) == 0ull) pieces = TileBig::BN / Quarter::BN == 2 ? 1 : 0;
-      while (split < MAX_SPLIT && left << (pieces + split + 1) <= XCD_CUS && g.Kc / 32 >= PART_BLOCKS << (split + 1)) ++split;
+      const int blocks = g.Kc / 32, least = pieces == cut ? SPLIT_BLOCKS : max(SPLIT_BLOCKS, 32 + 8 * left);
+      if (blocks >= least)
+        while (split < MAX_SPLIT && left << (pieces + split + 1) <= XCD_CUS && blocks >= PART_BLOCKS << (split + 1)) ++split;
     }
   }
   const bool big = local < full;

@@ -23,11 +23,11 @@ def test_down_projection_tiles(T):
     _check(ci.small_config("tiles2", T=T, d=1088, d_ff=192, G=2, K=4, r=8, k=2, q=32, seed=T))
 
 
-# parts of its contraction: one or two tiles per XCD in quarters of two, four and eight parts (56 to 96 blocks of it, parts
-# of equal and of unequal length), groups that fill only the upper quarters, up to four and more tiles per XCD, one
+# parts of its contraction: one or two tiles per XCD in quarters of two, four and eight parts (50 to 96 blocks of it, parts
+# of equal and of unequal length; small groups with four tiles on an XCD from 64 on), groups that fill only the upper quarters, up to four and more tiles per XCD, one
 # after a full round; contractions that stay whole; and the same calls with a workspace that holds no parts
 @pytest.mark.parametrize("T,G,d_ff", [(300, 2, 2112), (400, 4, 1024), (500, 4, 2112), (1000, 8, 1088), (1400, 2, 2112),
-                                      (2000, 3, 1024), (13000, 1, 512), (400, 4, 1792), (400, 4, 1728), (1000, 8, 1856),
+                                      (2000, 3, 1024), (13000, 1, 512), (400, 4, 1600), (400, 4, 1536), (300, 6, 1984), (300, 6, 2048), (1000, 8, 1856),
                                       (2000, 3, 1792), (13000, 1, 1792), (300, 2, 2560), (300, 1, 2496), (600, 2, 3072)])
 def test_down_projection_parts(T, G, d_ff):
     cfg = ci.small_config("parts", T=T, d=1088, d_ff=d_ff, G=G, K=4, r=8, k=2, q=32, seed=T)
