@@ -95,7 +95,7 @@ __global__ __launch_bounds__(MD_THREADS) void bw_mid_kernel(bw_mid_args a, int G
   __shared__ __attribute__((aligned(8))) unsigned char sB[3][K][MD_M];   // the experts, 255 for rows past the run
   __shared__ float sD[2][4][MD_M][K];
   __shared__ unsigned sM[2][2][K];   // experts of a 16-token block
-  __shared__ int sApart;             // a panel value is not finite
+  __shared__ int sApart[MD_THREADS / 64];   // a panel value that the wavefront loaded is not finite
   char *sU = smem, *sV = smem + U_BYTES, *sS = sV + V_BYTES;
   const int tid = threadIdx.x, lane = tid & 63, t16 = lane & 15, q = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), cg = wave & 3, hi = wave >> 2;
@@ -108,8 +108,6 @@ __global__ __launch_bounds__(MD_THREADS) void bw_mid_kernel(bw_mid_args a, int G
   auto key_u = [](int n) { const int i = (n & 3) | ((n >> 1) & 12); return KRP == 128 ? i : i >> 1; };
 
   // factor panels, zero rows for experts without a token
-  if (tid == 0) sApart = 0;
-  __syncthreads();
   {
     bool bad = false;
     const int cpr = KRp / 8;
@@ -131,7 +129,8 @@ __global__ __launch_bounds__(MD_THREADS) void bw_mid_kernel(bw_mid_args a, int G
       bad |= not_finite(v);
       *(half8*)(sV + kr * (MD_N * 2) + ((ch ^ (kr & 15)) << 4)) = v;
     }
-    if (bad) sApart = 1;
+    const bool any = __ballot(bad) != 0ull;
+    if (lane == 0) sApart[wave] = any;
   }
 
   const size_t block = (size_t)((n0 >> 5) + min(cg, nblk - 1)) * T * 32;   // this wavefront's 32 units in [f / 32][T][32]
@@ -424,7 +423,7 @@ __global__ __launch_bounds__(MD_THREADS) void bw_mid_kernel(bw_mid_args a, int G
     }
   };
   // (a branch inside the loop made the kernel 3 % slower)
-  if (__builtin_amdgcn_readfirstlane(sApart)) steps(std::false_type{}, std::true_type{});
+  if (__ballot(lane < MD_THREADS / 64 && sApart[lane % (MD_THREADS / 64)] != 0) != 0ull) steps(std::false_type{}, std::true_type{});
   else if (hi == 0) steps(std::true_type{}, std::false_type{});
   else steps(std::false_type{}, std::false_type{});
   phase2(m0 + (tiles - 1) * MD_M, (tiles - 1) % 3, (tiles - 1) & 1);
