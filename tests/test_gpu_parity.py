@@ -4,6 +4,8 @@ Bars: routing indices, permutation and offsets bit-exact; gates to 1e-5; layer o
 max|y - y_ref| <= 1e-2 * RMS(y_ref) and sum|y - y_ref| / sum|y_ref| <= 2e-3.
 Intermediates (y_base_sorted, s_down) use the same max/RMS bar.
 """
+import math
+
 import numpy as np
 import pytest
 
@@ -143,6 +145,51 @@ def test_pre_activations_far_outside_the_gelu_polynomial_range(cfg):
     h = w["w1_base"][0].astype(np.float64) @ w["x"][: min(cfg.T, 64)].astype(np.float64).T
     assert np.mean(np.abs(h) > 3.75) > 0.4
     _stepwise(cfg, w=w)
+
+
+def _one_hidden_unit(x, w1):
+    """y of a layer in which hidden unit 0 = w1 x and y = its GELU, all else zero; weight-streaming and matrix-core path."""
+    import paper_2510_02345_amd as cm
+    d, f, r, q, T = 64, 64, 4, 8, len(x)
+    w = dict(router_cluster=np.zeros((1, d), np.float16), router_expert=np.zeros((1, d), np.float16), cluster_bias=None,
+             w1_base=np.zeros((1, f, d), np.float16), w2_base=np.zeros((1, d, f), np.float16))
+    w["w1_base"][0, 0, 0], w["w2_base"][0, 0, 0] = w1, 1
+    for n, L in (("v1", d), ("u1", f), ("v2", f), ("u2", d)):
+        w[n + "_q"], w[n + "_s"] = np.zeros((1, r, L // 2), np.uint8), np.zeros((1, r, L // q), np.float16)
+    xs = np.zeros((T, d), np.float16)
+    xs[:, 0] = x
+    layer = cm.Layer(d, f, 1, 1, r, 1, q, w, T)
+    big = layer.forward(_dev(xs))["y"][:, 0].cpu().numpy().astype(np.float64)
+    few = np.concatenate([layer.forward(_dev(xs[i:i + 256]))["y"][:, 0].cpu().numpy() for i in range(0, T, 256)])
+    layer.close()
+    return few.astype(np.float64), big
+
+
+def test_gelu_point_by_point():
+    u = np.concatenate([np.arange(-9, 9, 1 / 256), np.geomspace(1e-4, 9, 400), -np.geomspace(1e-4, 9, 400)]).astype(np.float16)
+    x = u.astype(np.float64)
+    exact = np.array([v * 0.5 * math.erfc(-v / math.sqrt(2)) for v in x])
+    # the polynomial's error in FP32 (largest 1.93e-5, 5.19e-5, 8.59e-5 up to 1, 2 and 3, 1.317e-4 beyond) and the rounding of
+    # the result to FP16
+    a = np.abs(x)
+    bound = np.select([a <= 1, a <= 2, a <= 3], [1.95e-5, 5.2e-5, 8.65e-5], 1.33e-4)
+    for y in _one_hidden_unit(u, 1):
+        err = np.abs(y - exact)
+        print(f"gelu: max error below zero {err[x < 0].max():.3e} at {x[x < 0][err[x < 0].argmax()]}", flush=True)
+        assert (err <= bound + 2.0 ** -11 * (np.abs(exact) + bound) + 2.0 ** -25).all()
+        assert (y[x <= -4] == 0).all() and (y[x >= 4] == x[x >= 4]).all()
+
+
+def test_gelu_far_out():
+    # pre-activations of +-3.6e9: the weight-streaming path holds them in FP16, as infinities; the positive ones leave FP16
+    x = np.tile(np.array([6e4, -6e4], np.float16), 150)
+    few, big = _one_hidden_unit(x, 6e4)
+    for y in (few, big):
+        assert not np.isfinite(y[x > 0]).any() and (y[x < 0] == 0).all()
+    x = np.tile(np.array([6e4, -6e4, 17, -17], np.float16), 75)
+    few, big = _one_hidden_unit(x, 1)
+    for y in (few, big):
+        assert np.array_equal(y, np.maximum(x.astype(np.float64), 0))
 
 
 @pytest.mark.parametrize("cfg", [SMALL[0], SMALL[7]], ids=lambda c: c.name)
