@@ -1,5 +1,6 @@
 """Hazards of the built device code that no output shows reliably, looked for in its disassembly
-(the library of this repository, built from csrc): direct-to-LDS loads and their wait states."""
+(the library of this repository, built from csrc): direct-to-LDS loads and their wait states; and registers that a kernel
+spills, from its metadata."""
 import os
 import re
 import shutil
@@ -10,21 +11,24 @@ import pytest
 import paper_2510_02345_amd as cm
 
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+READELF = "/opt/rocm/llvm/bin/llvm-readelf"
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """{kernel symbol: its instructions in order}"""
+def code_objects(tmp_path_factory):
     cm.lib()
     d = tmp_path_factory.mktemp("device_code")
     lib = shutil.copy(cm.binding.lib_path(), d)
     subprocess.run([OBJDUMP, "--offloading", lib], cwd=d, check=True, capture_output=True)
+    return [os.path.join(d, f) for f in sorted(os.listdir(d)) if "gfx950" in f]
+
+
+@pytest.fixture(scope="module")
+def kernels(code_objects):
+    """{kernel symbol: its instructions in order}"""
     out = {}
-    for f in sorted(os.listdir(d)):
-        if "gfx950" not in f:
-            continue
-        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", os.path.join(d, f)], check=True, capture_output=True,
-                              text=True).stdout
+    for f in code_objects:
+        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", f], check=True, capture_output=True, text=True).stdout
         ins = None
         for line in text.splitlines():
             m = re.match(r"[0-9a-f]+ <(.+)>:$", line)
@@ -83,3 +87,17 @@ def test_t1_rows_shares_its_expert_table_behind_a_barrier(kernels):
         shuffles = [at for at, i in enumerate(ins) if at > written and i.startswith("ds_bpermute")]
         # the six shuffles that join the tile's needs come right behind the table
         assert "s_barrier" in ins[written:shuffles[5]]
+
+
+def test_up_projection_with_its_panels_in_memory_spills_nothing(code_objects):
+    # K*r > 128: operands fetched ahead would wait in registers, of which the 256 x 256 tile has none to spare
+    found = {}
+    for f in code_objects:
+        notes = subprocess.run([READELF, "--notes", f], check=True, capture_output=True, text=True).stdout
+        for kernel in notes.split("- .agpr_count")[1:]:
+            name = re.search(r"\.name:\s+(\S+)", kernel).group(1)
+            m = re.search(r"gemm_kernel.*EpiFusedUpILi(\d+)ELi([12])ELb0E", name)
+            if m:
+                found[m.groups()] = int(re.search(r"\.vgpr_spill_count:\s+(\d+)", kernel).group(1))
+    assert set(found) == {(r, k) for r in ("4", "8", "16", "32") for k in "12"}
+    assert not any(found.values()), found

@@ -26,6 +26,14 @@ def test_up_projection_panels(T, d, K, r, k):
     _check(ci.small_config("panels", T=T, d=d, d_ff=1344, G=3, K=K, r=r, k=k, q=32, factor_std=0.2, seed=T + K))
 
 
+# the same with panels too large for LDS, and one to three experts a token: whole tiles with and without groups of 16 rows that no token
+# fills, halves, slabs, a ragged last column tile
+@pytest.mark.parametrize("T", [301, 2999, 5801, 13301])
+@pytest.mark.parametrize("d,K,r,k", [(64, 8, 32, 2), (128, 16, 16, 1), (64, 9, 16, 2), (64, 32, 8, 3)])
+def test_up_projection_panels_in_memory(T, d, K, r, k):
+    _check(ci.small_config("panels", T=T, d=d, d_ff=1344, G=3, K=K, r=r, k=k, q=32, factor_std=0.2, seed=T + K))
+
+
 # the same for the down-projection: d = 1088 is four column tiles and a quarter of one
 @pytest.mark.parametrize("T", [700, 2000, 4700, 9000, 14000])
 def test_down_projection_tiles(T):
