@@ -185,33 +185,40 @@ __device__ __forceinline__ void skinny_wide(const half_t* const (&wrow)[2], size
     for (int i = 0; i < SW_CH; ++i) load_w(w[h][i], h, i);
   put_x(0);
   const int frag = t16 * 64 + ((q ^ swz(t16)) << 4), nb = (n_tok + 15) / 16;
-  for (int c0 = 0; c0 < chunks; c0 += 2) {
+  // Chunk c, from half h of the registers; more: chunk c + 2 follows and takes their place.  (Loads under a condition in one loop
+  // for all chunks make the compiler wait for every load before each use: three to four times as slow.)
+  auto chunk = [&](int c, auto h_, auto more) {
+    constexpr int h = decltype(h_)::value;
+    // the chunk's tokens are there; the other buffer has been read
+    wait_lds();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (more || c + 1 < chunks) load_x(c + 1);
+    const char* sx = smem + h * SW_CHUNK + frag;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int c = c0 + h;
-      if (c >= chunks) break;
-      // the chunk's tokens are there; the other buffer has been read
-      wait_lds();
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      if (c + 1 < chunks) load_x(c + 1);
-      const char* sx = smem + h * SW_CHUNK + frag;
+    for (int i = 0; i < SW_CH; ++i) {
+      if (more || b0 + c * SW_CH + i < b1) {
 #pragma unroll
-      for (int i = 0; i < SW_CH; ++i) {
-        if (b0 + c * SW_CH + i < b1) {
+        for (int b = 0; b < 4; ++b)
+          if (b < nb) {
+            const half8 fb = *(const half8*)(sx + i * 4096 + b * 1024);
 #pragma unroll
-          for (int b = 0; b < 4; ++b)
-            if (b < nb) {
-              const half8 fb = *(const half8*)(sx + i * 4096 + b * 1024);
-#pragma unroll
-              for (int a = 0; a < 2; ++a) acc[a][b] = mfma32(w[h][i][a], fb, acc[a][b]);
-            }
-        }
-        load_w(w[h][i], c + 2, i);
+            for (int a = 0; a < 2; ++a) acc[a][b] = mfma32(w[h][i][a], fb, acc[a][b]);
+          }
       }
-      if (c + 1 < chunks) put_x(h ^ 1);
+      if (more) load_w(w[h][i], c + 2, i);
     }
+    if (more || c + 1 < chunks) put_x(h ^ 1);
+  };
+  constexpr std::integral_constant<int, 0> H0{};
+  constexpr std::integral_constant<int, 1> H1{};
+  int c = 0;
+  for (; c + 2 < chunks; c += 2) {   // of an odd number the second loads nothing new, once
+    chunk(c, H0, std::true_type{});
+    chunk(c + 1, H1, std::true_type{});
   }
+  chunk(c, H0, std::false_type{});
+  if (c + 1 < chunks) chunk(c + 1, H1, std::false_type{});
 }
 
 struct SkinnyTile {

@@ -78,6 +78,21 @@ def test_lds_reads_are_complete_before_a_stage_is_refilled(kernels, kernel):
     assert n
 
 
+# The same of the weight stream of 64 tokens a pass, whose weights go to registers: a chunk's tokens are written by all four
+# wavefronts ahead of the barrier, and the other buffer has been read there.  And behind the last two barriers, those of the last
+# chunks, no more weights are loaded (non-temporal), which nothing would use.
+def test_wide_weight_stream(kernels):
+    found = [ins for name, ins in kernels.items() if re.search("skinny_base_kernelILi[0-9]ELi64E", name)]
+    assert found
+    for ins in found:
+        mfma = [at for at, i in enumerate(ins) if i.startswith("v_mfma")]
+        loads = [at for at, i in enumerate(ins) if i.startswith("global_load") and i.endswith(" nt")]
+        chunks = [at for at, i in enumerate(ins) if i == "s_barrier" and loads[0] < at < mfma[-1]]
+        assert len(chunks) == 4 and loads[-1] < chunks[-2]
+        for at in chunks:
+            assert any(_waits_for_lds(w) for w in ins[at - 6:at]), ins[at - 6:at]
+
+
 def test_t1_rows_shares_its_expert_table_behind_a_barrier(kernels):
     # wavefront 0 writes the table that all four read: a barrier of its own before the first stage's loads
     found = [ins for name, ins in kernels.items() if "t1_rows_kernel" in name]
