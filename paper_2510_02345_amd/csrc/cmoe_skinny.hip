@@ -5,6 +5,7 @@
 // contraction dimension, and both operands travel global -> LDS by DMA into per-wavefront
 // rings.  The per-expert rank-r terms (INT4 factors dequantised on the fly, Sec. 3.4) are
 // small kernels of their own or ride along in the stream launches.
+#include <algorithm>
 #include <type_traits>
 
 #include "cmoe_device.h"
@@ -137,7 +138,9 @@ __device__ __forceinline__ void skinny_reduce(float* red, int wave, int lane, co
 // of the contraction, so that a cluster of up to 64 tokens reads its weights once.  A weight row is read by one
 // wavefront only: it goes straight to registers as the matrix-core operand (16 rows x 64 bytes of the re-tiled base are
 // 1 KiB of contiguous memory), 16 blocks ahead; the tokens come through LDS, once for the four wavefronts' 128 rows, 256
-// elements at a time.  row_of(i): row of X of token i of the pass; n_tok: tokens of the pass.
+// elements at a time.  A row's products are one chain of FP32 sums (four shorter ones in skinny_stream): y of 256 tokens of 8
+// clusters of 2048 x 8192 against 64 bits 3.8e-4 (4.4e-4 there, whose second stream is not in parts and rounds to FP16 first).
+// row_of(i): row of X of token i of the pass; n_tok: tokens of the pass.
 constexpr int SW_CH = 8;   // blocks of a chunk of tokens; two chunks of weights in flight
 constexpr int SW_CHUNK = SW_CH * 64 * 64, SW_LDS = 2 * SW_CHUNK;
 template <bool NT, class RowOf>
@@ -834,6 +837,25 @@ static bool stream_once(const cmoe_dims& dm) {
   return (size_t)dm.G * dm.d * dm.d_ff * sizeof(half_t) > ((size_t)96 << 20);
 }
 
+// Parts of the contraction of the down-projection, as a power of two.  A launch that leaves CUs idle lasts as long as a wavefront's
+// chain of steps; parts shorten the chain, until the launch has 192 workgroups (256 where the base comes from HBM
+// and the loads take longer), two steps a wavefront are left or the parts no longer fit the space of the factor
+// panels, which this path does not use.  Down-projection of 1, 2 and 4 parts, one token: 768 x 3072 6.7, 5.8 and
+// 4.6 us, of 8 clusters of 2048 x 8192 16.9, 11.6 and 9.2 us; one part and two: two tokens there (128 workgroups) 18.9
+// and 14.7 us, one of 4096 x 14336 30 and 21 us, but 8 tokens of 4 clusters of 1024 x 4096 (128) 9.5 and 10.7 us.
+// The form of 64 tokens has a quarter of the row blocks and is cut up to 1024 workgroups: 256 tokens of 8 clusters of 4096 x 14336
+// whole and in two parts (704) 163 and 161 us, of 2048 x 8192 in two and in four (768) 57.8 and 58.2.
+inline int down_split(const cmoe_dims& dm, int T, int cols) {
+  const int slots = T < dm.G + T / cols ? T : dm.G + T / cols, most = cols == 64 ? 1024 : stream_once(dm) ? 256 : 192;
+  const int nx = (dm.d + stream_rows(cols) - 1) / stream_rows(cols);
+  const size_t room = sizeof(half_t) * 2 * dm.G * dm.KRp * ((size_t)dm.d + dm.d_ff);
+  int split = 2;
+  while (split > 0 && ((nx * slots << split) > most || dm.d_ff / 64 < 2 * SK_WAVES << split ||
+                       sizeof(float) * (T * (size_t)dm.d << split) > room))
+    --split;
+  return split;
+}
+
 // Tokens of a cluster that a workgroup of a weight stream takes: 16, 32 or 64; 32 (two workgroups per CU
 // instead of three) where the second reading of a matrix by the passes of a cluster costs more.
 //   - Up to 16 tokens no cluster has a second pass.
@@ -846,15 +868,33 @@ static bool stream_once(const cmoe_dims& dm) {
 //     for the up-projection, whose launch also holds a workgroup per token and expert: 8 clusters of
 //     4096 x 14336, 104 tokens: both 32-token 345 us, the down-projection alone 338, neither 339;
 //     112 tokens: 352, 381, 410; of 2048 x 8192, 97 tokens: 126.7, 126.1, 134.
-// And 64 (skinny_wide) for a matrix that the caches do not keep, once some cluster is likely to hold more than 32: then its
-// second pass reads it from memory again.  32- and 64-token form, up- and down-projection of 8 clusters of 2048 x 8192:
-// 130 tokens 54.7 and 52.0, 52.2 and 58.6 us; 165 56.9 and 52.2, 54.4 and 57.5; 203 65.4 and 55.0, 64.3 and 58.2; 256 77.5
-// and 58.1, 71.9 and 60.5; of 4096 x 14336: 110 156 and 162, 148 and 162; 150 166 and 159, 157 and 163; 203 183 and 178,
-// 163 and 171; 256 246 and 191, 219 and 171 (whole forward 519 and 417).  (Where the 203 had a cluster of more than 32;
-// where they had none the down-projection lost 5 us.)
-inline int stream_cols(const cmoe_dims& dm, int T, bool down) {
+// And 64 (skinny_wide) for a matrix that the caches do not keep:
+//   - Where some cluster is likely to hold more than 32 tokens, so that its second pass would read the matrix again: above 28
+//     tokens a cluster on average (a single cluster: above 32), while the launch keeps most CUs busy.  32- and 64-token form,
+//     down-projection of 8 clusters of 2048 x 8192: 256 tokens 81.9 and 57.0 us, 203 with a cluster of 37 64.3 and 57.1, with
+//     none above 32 54.7 and 57.1; of 4096 x 14336: 230 186 and 159, 130 (at most 27) 145 and 155; one of 4096 x 14336: 70
+//     69.8 and 46.4, 64 (128 workgroups) 40.3 and 42.6, 20 23.5 and 29.5; one of 2048 x 32768: 100 (128) 84.1 and 84.1, 150
+//     (192) 145 and 86.  Up-projection: one of 8192 x 8192, 60 (64 workgroups) 52.7 and 84.9, 100 (128) 95.6 and 85.6; of
+//     4096 x 14336, 64 (112) 50.0 and 47.7.
+//   - In the up-projection from 18 tokens a cluster on: in the form of 32 rows the tokens that a workgroup reads from the caches are
+//     as many bytes as its weights, here a quarter.  8 clusters of 2048 x 8192: 140 tokens 55.3 and 51.1 us, 165 54.7 and 50.9;
+//     of 12: 256 80.5 and 72.6; 4 of 4096 x 14336: 64 79.7 and 77.3; 2: 30 43.4 and 40.5; 3 of 3072 x 8192 (192 workgroups) 58 33.2
+//     and 30.5.  Not where that leaves CUs idle, in the first round of workgroups or in the second: 1 of 4096 x 14336 (112), 20 25.9
+//     and 32.4; 2 of 4096 x 8192 (128), 40 31.1 and 32.8; 3 of 4096 x 14336 (336) 58 63.8 and 69.4; 5 of 2048 x 8192 (320) 95
+//     37.3 and 39.5; but 6 (384) 115 42.6 and 39.9.
+static bool stream_wide(const cmoe_dims& dm, int T, bool down) {
+  if (!stream_once(dm)) return false;
+  const int N = down ? dm.d : dm.d_ff;
+  const long row_blocks = (N + stream_rows(64) - 1) / stream_rows(64), once = row_blocks * dm.G;   // workgroups of a pass per cluster
+  if (T > 28 * dm.G && T > 32) {
+    const long least = row_blocks * std::max(dm.G, (T + 63) / 64);
+    return down ? least << down_split(dm, T, 64) >= 192 : least >= 112;
+  }
+  return !down && T > 18 * dm.G && ((once >= 192 && once <= 256) || once >= 384);
+}
+int stream_cols(const cmoe_dims& dm, int T, bool down) {
   if (T <= 16 || T <= (down ? 12 : 13) * dm.G) return 16;
-  if (stream_once(dm) && T > (down ? 28 : 18) * dm.G) return 64;
+  if (stream_wide(dm, T, down)) return 64;
   const long narrow = (long)(dm.d_ff / SK_ROWS) * (dm.G + T / 16);   // workgroups, at most
   return !stream_once(dm) && narrow <= 1024 ? 16 : 32;
 }
@@ -937,23 +977,6 @@ hipError_t launch_skinny_resid_up(const cmoe_dims& dm, const cmoe_weights& w, in
     default: pick(std::integral_constant<int, 32>{}); break;
   }
   return hipGetLastError();
-}
-
-// Parts of the contraction of the down-projection, as a power of two.  A launch that leaves CUs idle lasts as long as a wavefront's
-// chain of steps; parts shorten the chain, until the launch has 192 workgroups (256 where the base comes from HBM
-// and the loads take longer), two steps a wavefront are left or the parts no longer fit the space of the factor
-// panels, which this path does not use.  Down-projection of 1, 2 and 4 parts, one token: 768 x 3072 6.7, 5.8 and
-// 4.6 us, of 8 clusters of 2048 x 8192 16.9, 11.6 and 9.2 us; one part and two: two tokens there (128 workgroups) 18.9
-// and 14.7 us, one of 4096 x 14336 30 and 21 us, but 8 tokens of 4 clusters of 1024 x 4096 (128) 9.5 and 10.7 us.
-inline int down_split(const cmoe_dims& dm, int T, int cols) {
-  const int slots = T < dm.G + T / cols ? T : dm.G + T / cols, most = cols == 64 ? 1024 : stream_once(dm) ? 256 : 192;
-  const int nx = (dm.d + stream_rows(cols) - 1) / stream_rows(cols);
-  const size_t room = sizeof(half_t) * 2 * dm.G * dm.KRp * ((size_t)dm.d + dm.d_ff);
-  int split = 2;
-  while (split > 0 && ((nx * slots << split) > most || dm.d_ff / 64 < 2 * SK_WAVES << split ||
-                       sizeof(float) * (T * (size_t)dm.d << split) > room))
-    --split;
-  return split;
 }
 
 // y_base_sorted = W2_base(c) A.  With ures != NULL the residual-down jobs ride along (ures[tok] = sum_j g_j U2

@@ -81,7 +81,7 @@ def _check(cfg, skew):
 # The form of 64 tokens a pass (bases beyond the caches): a pass of up to 16, 32, 48 and 64 tokens, a second pass of a
 # cluster, rows and blocks of the contraction that do not divide into workgroups and chunks; whole step and single calls,
 # re-tiled and canonical bases.
-@pytest.mark.parametrize("T,pack", [(58, True), (200, True), (256, False)])
+@pytest.mark.parametrize("T,pack", [(58, True), (100, True), (200, True), (256, False)])
 def test_sixty_four_token_passes(T, pack):
     import torch
 

@@ -32,3 +32,28 @@ def test_grouped_product_takes_no_more_groups_than_lanes():
     for N in (32, 256):   # the thin and the tiled product
         for out_f32 in (False, True):
             assert f(None, 0, 64, N, None, 64, None, 1, 64, None, 65, 0, None, None, None, N, out_f32, None, 0, 0) == HIP_ERROR_INVALID_VALUE
+
+
+class _Dims(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("d", "d_ff", "G", "K", "r", "k", "q", "KR", "KRp")]
+
+
+def test_weight_streams_take_passes_of_64_tokens_where_they_save_a_reading_and_fill_the_chip():
+    f = _internal("stream_cols")
+    f.restype, f.argtypes = C.c_int, [C.POINTER(_Dims), C.c_int, C.c_bool]
+
+    def cols(d, d_ff, G, T, down):
+        return f(_Dims(d, d_ff, G, 8, 16, 2, 64, 128, 128), T, down)
+
+    for T in range(17, 33):                       # one cluster: 32 tokens are one pass in either form
+        assert cols(4096, 14336, 1, T, False) == 32 and cols(4096, 14336, 1, T, True) == 32
+    assert cols(4096, 14336, 1, 65, False) == 64 and cols(4096, 14336, 1, 65, True) == 64
+    assert cols(4096, 14336, 1, 64, True) == 32   # 32 row blocks in four parts: 128 workgroups
+    assert cols(8192, 8192, 1, 64, False) == 32   # 64 workgroups
+    assert cols(4096, 14336, 3, 60, False) == 32 and cols(2048, 8192, 5, 100, False) == 32   # 336 and 320 for 256 CUs
+    assert cols(4096, 14336, 3, 96, False) == 64
+    for G in (2, 4, 8):
+        for T in range(18 * G + 1, 257):
+            assert cols(4096, 14336, G, T, False) == 64
+            assert cols(4096, 14336, G, T, True) == (64 if T > 28 * G else 32)
+    assert cols(1024, 4096, 4, 256, False) == 32  # a base that the caches keep
