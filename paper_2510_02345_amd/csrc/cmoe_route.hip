@@ -596,7 +596,7 @@ constexpr int ST_NA = 4, ST_PAIRS = 16;   // blocks of 16 rank rows at a time; (
 __device__ __forceinline__ void t1_tokens_block(const T1Tokens& a, int blk, char* smem) {
   __shared__ int es[RW_M][ST_PAIRS];      // first rank row of the pair's expert in its cluster; -1: another cluster's
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (wave >= RW_WAVES) return;
+  if (wave >= RW_WAVES) return;   // the barriers below wait for the wavefronts that have not ended (s_barrier)
   const int c = blk % a.G, row0 = blk / a.G * RW_M, t16 = lane & 15, q = lane >> 4;
   const int row = row0 + (lane & (RW_M - 1));
   unsigned need = 0u;
@@ -647,6 +647,7 @@ __device__ __forceinline__ void t1_tokens_block(const T1Tokens& a, int blk, char
     if (n <= 2) pass(std::integral_constant<int, 2>{}); else pass(std::integral_constant<int, ST_NA>{});
   }
 }
+// 1024 threads leave 128 registers a thread, and the product of t1 spills 18; the times at sort_takes_t1 are with them.
 constexpr int ST_LDS = RowsRing<2>::SMEM > RowsRing<ST_NA>::SMEM ? RowsRing<2>::SMEM : RowsRing<ST_NA>::SMEM;
 __global__ __launch_bounds__(SORT_BLOCK) void sort_rank_t1_kernel(SortArgs a, int mode, const int* __restrict__ counts,
                                                                   int* __restrict__ perm, int* __restrict__ inv_perm,
@@ -777,19 +778,25 @@ __global__ __launch_bounds__(SORT_BLOCK) void pair_sort_kernel(const int* __rest
 
 inline int two_keys_of(const cmoe_dims& dm) { return (dm.k >= 2 && dm.K * dm.K <= 64) ? 1 : 0; }
 
+// LDS of sort_rank_block; n_ids: 0 without PAIR
+constexpr size_t sort_lds(int bins, int n_ids) {
+  return 4 * (2 * (size_t)bins + n_ids) + SORT_WAVES * (size_t)(((bins + 3) & ~3) + ((n_ids + 3) & ~3));
+}
+static_assert(sort_lds(SORT_BINS, 64) <= ST_LDS, "a permutation whose launch takes t1 along");
+
 template <bool PAIR>
 hipError_t go_sort(SortArgs a, int* perm, int* inv_perm, int* offsets, int* rowmap, int* perm2, int* counts,
                    hipStream_t st, const T1Tokens* t1 = nullptr) {
   a.n_blocks = (a.n + SORT_BLOCK - 1) / SORT_BLOCK;
   a.bins = PAIR ? a.n_ids * a.nk : a.n_ids;
+  const size_t lds = sort_lds(a.bins, PAIR ? a.n_ids : 0);
+  if (t1 != nullptr && lds > ST_LDS) return hipErrorInvalidValue;
   const bool sum = a.n_blocks <= SORT_SUM_BLOCKS && a.n_blocks * a.bins <= SORT_SUM_COUNTS;
   const int mode = a.n <= SORT_SELF ? SORT_FROM_IDS : sum ? SORT_FROM_HIST : SORT_FROM_SCAN;
   const dim3 grid(a.n_blocks), block(SORT_BLOCK);
   if (mode != SORT_FROM_IDS) hipLaunchKernelGGL((sort_hist_kernel<PAIR>), grid, block, 0, st, a, counts);
   if (mode == SORT_FROM_SCAN) hipLaunchKernelGGL(sort_scan_kernel, dim3((a.bins + 63) / 64), dim3(64), 0, st, a, counts);
-  const size_t lds = 4 * (2 * (size_t)a.bins + (PAIR ? a.n_ids : 0)) +
-                     SORT_WAVES * (size_t)(((a.bins + 3) & ~3) + (PAIR ? ((a.n_ids + 3) & ~3) : 0));
-  if (PAIR && t1 != nullptr && lds <= ST_LDS) {
+  if (PAIR && t1 != nullptr) {
     hipLaunchKernelGGL(sort_rank_t1_kernel, dim3(a.n_blocks + (t1->rows + RW_M - 1) / RW_M * t1->G), block, 0, st, a, mode,
                        (const int*)counts, perm, inv_perm, offsets, rowmap, perm2, *t1);
     return hipGetLastError();

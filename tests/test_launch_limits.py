@@ -57,3 +57,12 @@ def test_weight_streams_take_passes_of_64_tokens_where_they_save_a_reading_and_f
             assert cols(4096, 14336, G, T, False) == 64
             assert cols(4096, 14336, G, T, True) == (64 if T > 28 * G else 32)
     assert cols(1024, 4096, 4, 256, False) == 32  # a base that the caches keep
+
+
+def test_permutation_that_cannot_take_t1_along_is_refused():
+    f = _internal("launch_sort_pairs_t1")
+    P, I = C.c_void_p, C.c_int
+    # dims, cluster_id, expert_idx, T, x, x_div, v1cat, t1, perm, inv_perm, offsets, counts, rowmap, perm2, stream
+    f.restype, f.argtypes = I, [C.POINTER(_Dims), P, P, I, P, I, P, P, P, P, P, P, P, P, P]
+    dims = _Dims(64, 64, 64, 100, 4, 2, 64, 400, 416)   # 6400 bins, more than a layer has and than fit its LDS
+    assert f(dims, None, None, 300, None, 1, *[None] * 9) == HIP_ERROR_INVALID_VALUE
