@@ -1018,8 +1018,8 @@ struct EpiFusedUp {
   // LDS while the tile's first blocks are under way: behind the main loop the chain of loads rows, experts and gates
   // costs 3 to 5 us of a tile.
   static constexpr bool TOK = STAGE && KMAX <= 2, TOK_T1 = TOK && KMAX * R <= 32;
-  template <class TL>
-  static constexpr int tok_bytes() { return TOK ? TL::BM * (KMAX * 8 + (TOK_T1 ? KMAX * R * 2 : 0)) : 0; }
+  template <class TL>   // experts and gates, then t1 in whole KiBs as the loads bring it (64 rows of 8 bytes are half of one)
+  static constexpr int tok_bytes() { return TOK ? TL::BM * KMAX * 8 + (TOK_T1 ? (TL::BM * KMAX * R * 2 + 1023) / 1024 * 1024 : 0) : 0; }
   // The last BM threads take a token each: their wavefronts wait for rows of perm anyway.
   template <class TL>
   __device__ __forceinline__ int token(int tid, int m0, int m_end) const {
@@ -1028,6 +1028,7 @@ struct EpiFusedUp {
   template <class TL>
   __device__ __forceinline__ void put_tokens(int tok, int tid, int m0, unsigned smem_base) const {
     if constexpr (TOK) {
+      static_assert(!TOK_T1 || (tok_bytes<TL>() - TL::BM * KMAX * 8) % 1024 == 0, "a piece of t1 is a KiB");
       const int kr = k * R, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
       const unsigned at = smem_base + panel_bytes<TL>();
       constexpr int FIRST = (TL::NT - TL::BM) / 64;
