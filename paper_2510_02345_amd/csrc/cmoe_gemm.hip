@@ -1130,10 +1130,9 @@ struct EpiFusedUp {
     // at the end in one go; otherwise block by block
     constexpr int NSB = BATCH ? TL::MT : 1;
     float4v sacc[NSB][KMAX][FU::NSP];
-    // partials of wavefront column wn >= 1 of token column wm
+    // block by block: partials of wavefront column wn >= 1 of token column wm
     auto xs = [&](int wn) {
-      return (BATCH ? (float*)t.smem : (float*)((char*)t.smem + panel_bytes<TL>())) +
-             ((wn - 1) * TL::WAVES_M + t.wm) * xs_floats<TL>() + t.lane;
+      return (float*)((char*)t.smem + panel_bytes<TL>()) + ((wn - 1) * TL::WAVES_M + t.wm) * xs_floats<TL>() + t.lane;
     };
 #pragma unroll
     for (int b = 0; b < TL::MT; ++b) {

@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256) void stats_partial_kernel(const half_t* __rest
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc[i] = 0.f;
   if (grp < groups)
-    for (int i0 = grp * U; i0 < n; i0 += groups * U) {   // added in row order
+    for (int i0 = grp * U; i0 < n; i0 += groups * U) {   // a group's rows in their order, the groups in theirs below
       half8 v[U];
 #pragma unroll
       for (int u = 0; u < U; ++u)
