@@ -967,15 +967,23 @@ __global__ __launch_bounds__(64) void cmp_error_finish_kernel(const float* __res
 }
 
 // epart and then err[e * stride] of the stored form.
+}  // namespace
+// Row tiles of a workgroup of cmp_error_kernel: four share the panel of V and load the next tile's elements during the work on one,
+// where that leaves four workgroups a CU and the last of a column has not too few of its four, on average 3.5 (3 at rank 17 on,
+// where the panel is twice the work).  One and four: 64 experts of 8192 x 2048 644 -> 593 us at r = 16 and 923 -> 736 at r = 32,
+// 16 of 4096 x 1024 63.9 -> 59.3 and 79.4 -> 65.7 (at r = 24 and groups of 2 codes 174 -> 108); of 64 experts, r = 16, 1472 x 1024
+// (3.83) 78.3 -> 73.7, 1344 x 1024 (3.5) 74.2 -> 73.5, 832 x 2048 (3.25) 84.9 -> 87.0, 576 x 2048 (3) 67.3 -> 71.9, 320 x 2048
+// (2.5) 49.6 -> 54.0; r = 32, 832 x 2048 109.3 -> 101.4, 576 x 2048 84.2 -> 81.0, 320 x 2048 59.4 -> 60.9.
+int error_row_tiles(const cmoe_compress_config& c) {
+  const int tiles = c.out_dim / 64, groups = (tiles + 3) / 4;
+  const bool full = 2 * tiles >= (c.r > 16 ? 6 : 7) * groups;
+  return c.in_dim > 128 && full && (long)c.G * c.K * ((c.in_dim / 64 + 3) / 4) * (c.out_dim / 256) >= 1024 ? 4 : 1;
+}
+namespace {
 void launch_error(const cmoe_compress_config& c, const half_t* W, const half_t* base, const uint8_t* u_q, const half_t* u_s,
                   const uint8_t* v_q, const half_t* v_s, float* epart, int stride, float* err, hipStream_t st) {
   const int ct = c.in_dim <= 64 ? 1 : c.in_dim <= 128 ? 2 : 4;
-  // Four row tiles a workgroup share the panel of V and load the next tile's elements during the work on one, where that
-  // leaves four workgroups a CU: 64 experts of 8192 x 2048 644 -> 593 us at r = 16 and 923 -> 736 at r = 32, 16 of
-  // 4096 x 1024 63.9 -> 59.8 and 79.4 -> 65.9 (at r = 24 and groups of 2 codes 174 -> 108); 16 of 4160 x 1088, whose last
-  // workgroups have one tile of four, 72.4 and 73.2, 88.9 -> 83.0.
-  const int tx = (c.in_dim / 64 + ct - 1) / ct;
-  const int rt = (long)c.G * c.K * tx * (c.out_dim / 256) >= 1024 && ct == 4 ? 4 : 1, ty = (c.out_dim / 64 + rt - 1) / rt;
+  const int tx = (c.in_dim / 64 + ct - 1) / ct, rt = error_row_tiles(c), ty = (c.out_dim / 64 + rt - 1) / rt;
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3((unsigned)((c.G * tx * ty + 7) / 8 * 8 * c.K)), dim3(256), 0, st, W, base, u_q, u_s, v_q, v_s,
                        c.G, c.K, c.out_dim, c.in_dim, c.r, c.q_group, tx, ty, epart);

@@ -124,7 +124,7 @@ def test_reconstruction_error_at_odd_ranks_and_widths(r, q, out_d, in_d):
 
 # four row tiles a workgroup: 1024 workgroups or more; one row tile in the last one of four, a ragged column
 # tile, both panel widths, both ways to read the codes
-@pytest.mark.parametrize("r,q,G,K,out_d,in_d", [(5, 32, 64, 16, 320, 192), (24, 2, 32, 16, 256, 320), (32, 64, 16, 8, 1088, 512)])
+@pytest.mark.parametrize("r,q,G,K,out_d,in_d", [(5, 32, 64, 16, 320, 192), (5, 32, 64, 16, 448, 192), (24, 2, 32, 16, 256, 320), (32, 64, 16, 8, 1088, 512)])
 def test_reconstruction_error_of_many_row_tiles(r, q, G, K, out_d, in_d):
     import paper_2510_02345_amd as cm
     print(f"case r={r} q={q} {G}x{K} {out_d}x{in_d}", flush=True)

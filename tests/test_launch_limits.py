@@ -66,3 +66,23 @@ def test_permutation_that_cannot_take_t1_along_is_refused():
     f.restype, f.argtypes = I, [C.POINTER(_Dims), P, P, I, P, I, P, P, P, P, P, P, P, P, P]
     dims = _Dims(64, 64, 64, 100, 4, 2, 64, 400, 416)   # 6400 bins, more than a layer has and than fit its LDS
     assert f(dims, None, None, 300, None, 1, *[None] * 9) == HIP_ERROR_INVALID_VALUE
+
+
+class _Compress(C.Structure):
+    _fields_ = [(n, C.c_int32) for n in ("out_dim", "in_dim", "G", "K", "r", "q_group", "sketch", "n_iter", "use_gate")] + [("gate_gamma", C.c_float)]
+
+
+def test_error_pass_takes_four_row_tiles_a_workgroup_where_the_last_has_enough_of_them():
+    f = _internal("error_row_tiles")
+    f.restype, f.argtypes = C.c_int, [C.POINTER(_Compress)]
+
+    def tiles(out_dim, in_dim, experts, r):
+        return f(_Compress(out_dim, in_dim, experts // 8, 8, r, 32, r + 8, 2, 0, 0.0))
+
+    assert tiles(8192, 2048, 64, 16) == 4 and tiles(8192 + 64, 2048, 64, 16) == 4
+    assert tiles(512, 2048, 64, 16) == 4 and tiles(448, 2048, 128, 16) == 4
+    for out_dim in (320, 384, 576, 832, 1088):
+        assert tiles(out_dim, 2048, 128, 16) == 1, out_dim
+    assert tiles(384, 2048, 128, 32) == 4 and tiles(1088, 2048, 64, 32) == 4 and tiles(320, 2048, 128, 32) == 1
+    assert tiles(4096, 1024, 8, 16) == 1     # two workgroups a CU
+    assert tiles(8192, 128, 64, 16) == 1     # narrower than four column tiles
