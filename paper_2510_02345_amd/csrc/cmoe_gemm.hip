@@ -981,8 +981,8 @@ struct EpiDownCombine {
 // With STAGE the U1 / V2 panels of the tile are staged through LDS (K*r <= 128), in portions of 32 rank rows that the
 // tile has under way while it works on its last blocks (PANELS); otherwise they are read from global memory.  Panels and
 // token state loaded behind the main loop, through registers, cost 4 us of a 256 x 256 tile for 32 rank rows and 9 for
-// 128, now 0.6 and 1.5; with the GELU of ten operations the whole kernel, 4096 tokens of 2 clusters of 768 x 3072 46.6 ->
-// 42.7 us, 16384 Zipf tokens of 4 of 1024 x 4096 246 -> 222, 32768 of 8 of 2048 x 8192 1450 -> 1390.
+// 128, now 0.6 and 1.5; whole kernel, with a GELU of ten operations (of eleven, as it is now, 1 to 3 % more), 4096 tokens of 2
+// clusters of 768 x 3072 46.6 -> 42.7 us, 16384 Zipf tokens of 4 of 1024 x 4096 246 -> 222, 32768 of 8 of 2048 x 8192 1450 -> 1390.
 template <int R, int KMAX, bool STAGE>
 struct EpiFusedUp {
   static constexpr bool SPLITS = false, EXTENDS = false, PANELS = STAGE;
